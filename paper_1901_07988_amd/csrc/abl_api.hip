@@ -342,6 +342,13 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
     return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta,
                          dwsum.copies > 0 ? &dwsum : nullptr);
   }
+  // Channel counts that are not multiples of 16: the weight gradient goes first, while the workspace of dA3
+  // is free to hold its copies.
+  if (!channels_in_tiles(g)) {
+    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, da3, dW, K == 32, nullptr, act)) return e;
+    if (int e = launch_conv_dgrad(st, *s, bf16, dy, W, da3)) return e;
+    return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta);
+  }
   if (int e = launch_conv_dgrad(st, *s, bf16, dy, W, da3)) return e;
   // exact storage keeps the pre-ReLU A2: the weight gradient applies Eq. 3 on the way in
   DwSum dwsum;

@@ -133,9 +133,20 @@ int launch_conv_fwd_fused(hipStream_t st, const abl_shape& s, int K, bool bf16, 
 // K = 32: `packed` is an fp32 tensor, used as it is or (relu32) as the pre-ReLU activation A2.
 // defer (nullable): where the kernel leaves split partial copies, describe them there instead of
 // summing them (copies = 0 when dw is already complete) - for launch_bn_bwd_finish.
+// room: bytes at `scratch` where channel counts are not multiples of 16 (wgrad_partial_bytes covers the others).
 int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf16, const void* packed,
                              const void* stats, const float* dy, void* scratch, float* dw, bool relu32 = false,
-                             DwSum* defer = nullptr);
+                             DwSum* defer = nullptr, size_t room = 0);
+
+// ---- channel counts that are not multiples of 16 (conv_ragged.hip), fp32 ----
+inline bool channels_in_tiles(const ConvGeom& g) { return g.Cin % 16 == 0 && g.Cout % 16 == 0; }
+int launch_ragged_conv(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
+                       float* out);
+// Copies of dW ([copies][R][S][Cin][Cout] floats, 1 = dW itself) that launch_ragged_wgrad writes with `room` bytes
+// for them; 0: too few to keep the GPU busy.
+int ragged_wgrad_copies(const ConvGeom& g, size_t room);
+int launch_ragged_wgrad(hipStream_t st, const ConvGeom& g, int K, const void* packed, const float* stats,
+                        const float* dy, int copies, float* dst, bool relu32);
 
 // ---- ABL_MATH_BF16 contractions on the 32-deep bf16 matrix instruction (conv_bf16.hip) ----
 // Forward (mode 0) / gradient to the input (mode 1) of any stride, filter and padding whose

@@ -745,64 +745,9 @@ __global__ __launch_bounds__(kThreads) void wgrad_reduce_kernel(const float* __r
 }
 
 // ------------------------------------------------------------------------------------------
-// Fallbacks for channel counts that are not multiples of 16: one thread per output element.
-__global__ __launch_bounds__(kThreads) void naive_fwd_kernel(const float* __restrict__ a3,
-                                                             const float* __restrict__ w, const float* skip,
-                                                             float* out, ConvGeom g) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int64_t total = (int64_t)g.N * g.Ho * g.Wo * g.Cout;
-  if (i >= total) return;
-  const int co = (int)(i % g.Cout);
-  int64_t p = i / g.Cout;
-  const int wo = (int)(p % g.Wo); p /= g.Wo;
-  const int ho = (int)(p % g.Ho);
-  const int n = (int)(p / g.Ho);
-  float acc = 0.f;
-  for (int r = 0; r < g.R; ++r) {
-    const int h = ho * g.stride + r - g.pad;
-    if (h < 0 || h >= g.H) continue;
-    for (int s = 0; s < g.S; ++s) {
-      const int x = wo * g.stride + s - g.pad;
-      if (x < 0 || x >= g.W) continue;
-      const float* ap = a3 + (((int64_t)n * g.H + h) * g.W + x) * g.Cin;
-      const float* wp = w + ((int64_t)(r * g.S + s) * g.Cin) * g.Cout + co;
-      for (int ci = 0; ci < g.Cin; ++ci) acc += ap[ci] * wp[(int64_t)ci * g.Cout];
-    }
-  }
-  if (skip != nullptr) acc += skip[i];
-  out[i] = acc;
-}
-
-__global__ __launch_bounds__(kThreads) void naive_dgrad_kernel(const float* __restrict__ dy,
-                                                               const float* __restrict__ w,
-                                                               float* __restrict__ da3, ConvGeom g) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int64_t total = (int64_t)g.N * g.H * g.W * g.Cin;
-  if (i >= total) return;
-  const int ci = (int)(i % g.Cin);
-  int64_t p = i / g.Cin;
-  const int x = (int)(p % g.W); p /= g.W;
-  const int h = (int)(p % g.H);
-  const int n = (int)(p / g.H);
-  float acc = 0.f;
-  for (int r = 0; r < g.R; ++r) {
-    const int hh = h + g.pad - r;
-    if (hh < 0 || hh % g.stride) continue;
-    const int ho = hh / g.stride;
-    if (ho >= g.Ho) continue;
-    for (int s = 0; s < g.S; ++s) {
-      const int ww = x + g.pad - s;
-      if (ww < 0 || ww % g.stride) continue;
-      const int wo = ww / g.stride;
-      if (wo >= g.Wo) continue;
-      const float* gp = dy + (((int64_t)n * g.Ho + ho) * g.Wo + wo) * g.Cout;
-      const float* wp = w + ((int64_t)(r * g.S + s) * g.Cin + ci) * g.Cout;
-      for (int co = 0; co < g.Cout; ++co) acc += gp[co] * wp[co];
-    }
-  }
-  da3[i] = acc;
-}
-
+// Weight gradient for channel counts that are not multiples of 16 where the caller has no room for
+// copies of dW (the stage call on its own; with room, ragged_wgrad_kernel: 456 -> 36 us on a
+// 50 x 27 x 21 layer of 20 -> 36 channels).
 // One block per dW element; the 256 threads stride over the output pixels, fixed-order tree.
 template <int K>
 __global__ __launch_bounds__(kThreads) void naive_wgrad_kernel(const uint8_t* __restrict__ packed,
@@ -846,7 +791,7 @@ __global__ __launch_bounds__(kThreads) void naive_wgrad_kernel(const uint8_t* __
   if (threadIdx.x == 0) dw[blockIdx.x] = red[0];
 }
 
-inline bool mfma_ok(const ConvGeom& g) { return g.Cin % 16 == 0 && g.Cout % 16 == 0; }
+inline bool mfma_ok(const ConvGeom& g) { return channels_in_tiles(g); }
 
 // Tile choice, from timing the candidates on 1x1 and 3x3 layers at 56x56 and 14x14.  Blocks
 // of one wave per SIMD spend much of their time at the two barriers of a chunk, so the tile
@@ -970,11 +915,7 @@ int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* 
                     const float* skip, float* y, double* sums, int* rows) {
   const ConvGeom g = geom_of(s);
   if (rows != nullptr) *rows = 0;
-  if (!mfma_ok(g)) {
-    const int64_t total = (int64_t)g.N * g.Ho * g.Wo * g.Cout;
-    naive_fwd_kernel<<<(unsigned)((total + kThreads - 1) / kThreads), kThreads, 0, st>>>(a3, w, skip, y, g);
-    return hip_status();
-  }
+  if (!mfma_ok(g)) return launch_ragged_conv(st, g, 0, a3, w, skip, y);
   // bf16 operands: the 32-deep bf16 matrix instruction with bf16 tiles in LDS
   if (bf16 && image_bf16_supported(g, 0)) {
     const bool want = sums != nullptr && rows != nullptr && g.N <= kMaxPartialBlocks;
@@ -1028,11 +969,7 @@ int launch_conv_fwd_fused(hipStream_t st, const abl_shape& s, int K, bool bf16, 
 int launch_conv_dgrad(hipStream_t st, const abl_shape& s, bool bf16, const float* dy, const float* w,
                       float* da3) {
   const ConvGeom g = geom_of(s);
-  if (!mfma_ok(g)) {
-    const int64_t total = (int64_t)g.N * g.H * g.W * g.Cin;
-    naive_dgrad_kernel<<<(unsigned)((total + kThreads - 1) / kThreads), kThreads, 0, st>>>(dy, w, da3, g);
-    return hip_status();
-  }
+  if (!mfma_ok(g)) return launch_ragged_conv(st, g, 1, dy, w, nullptr, da3);
   if (bf16 && image_bf16_supported(g, 1)) return launch_image_bf16(st, g, 1, dy, w, nullptr, da3, nullptr);
   if (bf16 && bf16_gemm_supported(g, 1)) return launch_bf16_gemm(st, g, 1, dy, w, nullptr, da3);
   if (!bf16 && image_f32_supported(g, 1)) return launch_image_f32(st, g, 1, dy, w, nullptr, da3, nullptr);
@@ -1056,12 +993,19 @@ static void launch_wgrad_tile(hipStream_t st, const ConvGeom& g, const WgradPlan
 
 int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf16, const void* packed,
                              const void* stats, const float* dy, void* scratch, float* dw, bool relu32,
-                             DwSum* defer) {
+                             DwSum* defer, size_t room) {
   const int r32 = relu32 ? 1 : 0;
   if (defer != nullptr) defer->copies = 0;
   const ConvGeom g = geom_of(s);
   const float* sp = static_cast<const float*>(stats);
   if (!mfma_ok(g)) {
+    if (const int copies = ragged_wgrad_copies(g, room)) {
+      float* dst = copies == 1 ? dw : static_cast<float*>(scratch);
+      if (int e = launch_ragged_wgrad(st, g, K, packed, sp, dy, copies, dst, relu32)) return e;
+      const int64_t n = (int64_t)g.R * g.S * g.Cin * g.Cout;
+      if (copies > 1) wgrad_reduce_kernel<<<(unsigned)((n + 63) / 64), kThreads, 0, st>>>(dst, copies, n, dw);
+      return hip_status();
+    }
     const unsigned blocks = (unsigned)(g.R * g.S * g.Cin * g.Cout);
     const uint8_t* pk = static_cast<const uint8_t*>(packed);
     if (K == 4) naive_wgrad_kernel<4><<<blocks, kThreads, 0, st>>>(pk, sp, dy, dw, g, 0);

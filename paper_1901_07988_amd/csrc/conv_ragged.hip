@@ -1,0 +1,323 @@
+// Convolutions whose channel counts are not multiples of 16 (narrowed layers, image inputs): Eq. 4, both
+// halves of Eq. 5, any filter, stride and padding, fp32.
+//
+// The matrix instructions want operands in tiles of 16, and a row of 20 channels cannot be read 16 bytes at
+// a time by every lane.  So the contraction is flattened - (tap, channel) is one index - and both operands
+// are gathered element by element into LDS tiles whose ends are filled with zeros; from there on it is a
+// plain GEMM on the fp32 matrix cores.  A block is 64 rows x up to 64 columns with the four waves on 16
+// rows each, and a 32-deep chunk of the contraction per barrier, the next chunk's elements in flight in
+// registers meanwhile.  What bounds it is the gather (one address and one 4-byte load per element of the
+// unfolded operand), which the small tiles keep on many blocks: 50 x 27 x 21, 3x3, 20 -> 36 channels takes
+// 18 us forward, 24 us for the input's gradient and 36 us for the weights', where one thread per output
+// element took 75, 246 and 456 us.
+
+#include "abl_internal.h"
+
+namespace abl {
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int RB_M = 64;    // rows of the output tile per block (16 per wave)
+constexpr int RB_K = 32;    // contraction elements per chunk
+constexpr int RB_LD = 36;   // floats per LDS row of a chunk: 16-byte fragments of 16 rows on different banks
+
+// MODE 0: out[p][co] = sum_{tap, ci} a3[p at tap][ci] W[tap][ci][co] (+ skip)
+// MODE 1: out[p][ci] = sum_{tap, co} dy[p at tap][co] W[tap][ci][co]
+// STRIDED: stride other than 1 (in mode 1 a tap then reaches only every stride-th pixel).
+template <int MODE, int NT, bool STRIDED>
+__global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __restrict__ in,
+                                                               const float* __restrict__ wgt, const float* skip,
+                                                               float* out, ConvGeom g) {
+  constexpr int BN = 16 * NT;
+  constexpr int A_N = RB_M * RB_K / kThreads;   // elements of the A chunk per thread: 8
+  constexpr int B_N = BN * RB_K / kThreads;     // ... of the B chunk: 2 NT
+  __shared__ __attribute__((aligned(16))) float As[2][RB_M * RB_LD];
+  __shared__ __attribute__((aligned(16))) float Bs[2][BN * RB_LD];
+  const int Hi = MODE == 0 ? g.H : g.Ho, Wi = MODE == 0 ? g.W : g.Wo;
+  const int Hq = MODE == 0 ? g.Ho : g.H, Wq = MODE == 0 ? g.Wo : g.W;
+  const int Cg = MODE == 0 ? g.Cin : g.Cout;
+  const int Ng = MODE == 0 ? g.Cout : g.Cin;
+  const int64_t Mg = (int64_t)g.N * Hq * Wq;
+  const int KK = g.R * g.S * Cg;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int ncol = (Ng + BN - 1) / BN;
+  const int64_t m0 = (int64_t)(blockIdx.x / ncol) * RB_M;
+  const int n0 = (int)(blockIdx.x % ncol) * BN;
+
+  // A: the thread's column of the chunk is fixed (tid % 32), its rows are tid / 32 + 8 i
+  const int a_k = tid & (RB_K - 1), a_row = tid >> 5;
+  int a_base[A_N], a_h[A_N], a_w[A_N];   // offset of the row's image, position of tap (0, 0); a_h: far outside = no row
+#pragma unroll
+  for (int i = 0; i < A_N; ++i) {
+    const int64_t p = m0 + a_row + 8 * i;
+    const bool ok = p < Mg;
+    const int pp = ok ? (int)p : 0;
+    const int t = pp / Wq, n = t / Hq;
+    const int wq = pp - t * Wq, hq = t - n * Hq;
+    a_base[i] = n * Hi * Wi;
+    a_h[i] = ok ? (MODE == 0 ? hq * g.stride - g.pad : hq + g.pad) : -(1 << 28);
+    a_w[i] = MODE == 0 ? wq * g.stride - g.pad : wq + g.pad;
+  }
+  float ra[A_N], rb[B_N];
+  auto fetch = [&](int k0) __attribute__((always_inline)) {
+    const int kk = k0 + a_k;
+    const int tap = kk / Cg, c = kk - tap * Cg;
+    const int r = tap / g.S, s = tap - r * g.S;
+#pragma unroll
+    for (int i = 0; i < A_N; ++i) {
+      int hi, wi;
+      bool ok = kk < KK;
+      if (MODE == 0) {
+        hi = a_h[i] + r;
+        wi = a_w[i] + s;
+      } else {
+        const int hh = a_h[i] - r, ww = a_w[i] - s;
+        hi = STRIDED ? hh / g.stride : hh;
+        wi = STRIDED ? ww / g.stride : ww;
+        if (STRIDED) ok = ok && hh >= 0 && ww >= 0 && hi * g.stride == hh && wi * g.stride == ww;
+      }
+      ok = ok && hi >= 0 && hi < Hi && wi >= 0 && wi < Wi;
+      const uint32_t o = (uint32_t)((a_base[i] + hi * Wi + wi) * Cg + c);   // (tensors have fewer than 2^31 elements)
+      const float v = in[ok ? o : 0u];
+      ra[i] = ok ? v : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < B_N; ++j) {
+      // forward: lanes along the output channel (contiguous in W); gradient: along the contraction
+      const int idx = tid + kThreads * j;
+      const int n = MODE == 0 ? idx % BN : idx / RB_K;
+      const int kb = MODE == 0 ? k0 + idx / BN : kk;   // (idx % RB_K is the thread's own column)
+      const bool ok = kb < KK && n0 + n < Ng;
+      const uint32_t o = (uint32_t)(MODE == 0 ? kb * g.Cout + n0 + n : (tap * g.Cin + n0 + n) * g.Cout + c);
+      const float v = wgt[ok ? o : 0u];
+      rb[j] = ok ? v : 0.f;
+    }
+  };
+  auto stage = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < A_N; ++i) As[buf][(a_row + 8 * i) * RB_LD + a_k] = ra[i];
+#pragma unroll
+    for (int j = 0; j < B_N; ++j) {
+      const int idx = tid + kThreads * j;
+      const int n = MODE == 0 ? idx % BN : idx / RB_K;
+      const int kb = MODE == 0 ? idx / BN : idx % RB_K;
+      Bs[buf][n * RB_LD + kb] = rb[j];
+    }
+  };
+  // transposed product (first operand = weights): a lane ends up with four consecutive channels of a pixel.
+  // Two sums per output, of the two halves of every chunk: chains half as long round half as often.
+  floatx4 acc[2][NT][1];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[0][j][0] = acc[1][j][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int chunks = (KK + RB_K - 1) / RB_K;
+  fetch(0);
+  stage(0);
+  __syncthreads();
+  for (int it = 0; it < chunks; ++it) {
+    const int cur = it & 1;
+    if (it + 1 < chunks) fetch((it + 1) * RB_K);
+#pragma unroll
+    for (int h = 0; h < RB_K; h += 16) {
+      float4 bf[NT], af[1];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) bf[j] = *reinterpret_cast<const float4*>(&Bs[cur][(16 * j + li) * RB_LD + h + 4 * lk]);
+      af[0] = *reinterpret_cast<const float4*>(&As[cur][(16 * wave + li) * RB_LD + h + 4 * lk]);
+      mma_k4<false, NT, 1>(bf, af, acc[h / 16]);
+    }
+    if (it + 1 < chunks) stage(cur ^ 1);   // (the other buffer: its readers passed the barrier of the last chunk)
+    __syncthreads();
+  }
+  const int64_t p = m0 + 16 * wave + li;
+  if (p >= Mg) return;
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int n = n0 + 16 * j + 4 * lk + r;
+      if (n >= Ng) continue;
+      const int64_t o = p * Ng + n;
+      const float v = acc[0][j][0][r] + acc[1][j][0][r];
+      out[o] = skip != nullptr ? v + skip[o] : v;
+    }
+}
+
+// p / d for p < 2^31 with m = floor(2^32 / d) + 1 (d > 1): the high product is the quotient or one more.
+__device__ inline int div_magic(int p, int d, uint32_t m) {
+  if (d == 1) return p;
+  const int q = (int)__umulhi((uint32_t)p, m);
+  return (int64_t)q * d > p ? q - 1 : q;
+}
+inline uint32_t magic_of(int d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint32_t)d + 1) : 0u; }
+
+// dW[(tap, ci)][co] = sum over output pixels of A3~[p at tap][ci] dy[p][co].  Rows of the tile = flattened
+// (tap, ci), contraction = the pixels of this block's share, 32 per chunk; the shares' copies of dW are
+// summed by the caller.  Both tiles lie in LDS with the pixel outermost, which is how they are read from
+// memory and how the 4-deep fp32 MFMA wants its operands (one 4-byte read per lane, the four pixels of a
+// step on different quarters of the banks).
+template <int K, int NT>
+__global__ __launch_bounds__(kThreads) void ragged_wgrad_kernel(const uint8_t* __restrict__ packed,
+                                                                const float* __restrict__ stats,
+                                                                const float* __restrict__ dy,
+                                                                float* __restrict__ dst, ConvGeom g, int relu32,
+                                                                int chunks, int split, uint32_t wo_magic,
+                                                                uint32_t ho_magic) {
+  constexpr int BN = 16 * NT;
+  constexpr int LDA = RB_M + 16, LDB = (BN % 64 == 16 || BN % 64 == 48) ? BN : BN + 16;   // 16 or 48 words past a multiple of 64
+  constexpr int A_N = RB_M * RB_K / kThreads, B_N = BN * RB_K / kThreads;
+  __shared__ float As[2][RB_K * LDA];
+  __shared__ float Bs[2][RB_K * LDB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const int MR = g.R * g.S * g.Cin;
+  const int ncol = (g.Cout + BN - 1) / BN, nrow = (MR + RB_M - 1) / RB_M;
+  const int part = blockIdx.x / (ncol * nrow), tile = blockIdx.x - part * (ncol * nrow);
+  const int m0 = (tile / ncol) * RB_M, n0 = (tile % ncol) * BN;
+  const int c_begin = (int)((int64_t)part * chunks / split), c_end = (int)((int64_t)(part + 1) * chunks / split);
+  const int Mg = g.N * g.Ho * g.Wo;   // at most 2^31 - 1; pixel numbers past it wrap to negative ones
+
+  // the thread's row (tap, ci) is fixed: lane of the block's 64 rows; its pixels are wave + 4 i
+  const int row = m0 + lane;
+  const bool row_ok = row < MR;
+  const int rr = row_ok ? row : 0;
+  const int tap = rr / g.Cin, ci = rr - tap * g.Cin;
+  const int tr = tap / g.S, ts = tap - tr * g.S;
+  const float step = K == 32 ? 0.f : stats[P_STEP * g.Cin + ci];
+  const int32_t fb = K == 32 ? 0 : reinterpret_cast<const int32_t*>(stats)[P_FB * g.Cin + ci];
+
+  float ra[A_N], rb[B_N];
+  auto fetch = [&](int chunk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < A_N; ++i) {
+      const int p = (int)((unsigned)chunk * RB_K + wave + 4 * i);   // the same for the whole wave
+      const bool in_p = (unsigned)p < (unsigned)Mg;
+      const int pc = in_p ? p : 0;
+      const int t = div_magic(pc, g.Wo, wo_magic), n = div_magic(t, g.Ho, ho_magic);
+      const int wi = (pc - t * g.Wo) * g.stride - g.pad + ts, hi = (t - n * g.Ho) * g.stride - g.pad + tr;
+      const bool ok = row_ok && in_p && hi >= 0 && hi < g.H && wi >= 0 && wi < g.W;
+      const uint32_t e = ok ? (uint32_t)(((n * g.H + hi) * g.W + wi) * g.Cin + ci) : 0u;
+      float v;
+      if constexpr (K == 32) {
+        v = reinterpret_cast<const float*>(packed)[e];
+        ra[i] = ok && !(relu32 != 0 && v < 0.f) ? v : 0.f;
+      } else {
+        const uint32_t code = K == 4 ? (packed[e >> 1] >> ((e & 1) * 4)) & 15u : packed[e];
+        v = dequant<K>(code, step, fb);                  // Eq. 10
+        ra[i] = ok && v > 0.f ? v : 0.f;                 // Eq. 3
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < B_N; ++j) {
+      const int idx = tid + kThreads * j;
+      const int p = (int)((unsigned)chunk * RB_K + idx / BN), n = n0 + idx % BN;
+      const bool ok = (unsigned)p < (unsigned)Mg && n < g.Cout;
+      const float v = dy[ok ? (uint32_t)p * (uint32_t)g.Cout + n : 0u];
+      rb[j] = ok ? v : 0.f;
+    }
+  };
+  auto stage = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < A_N; ++i) As[buf][(wave + 4 * i) * LDA + lane] = ra[i];
+#pragma unroll
+    for (int j = 0; j < B_N; ++j) {
+      const int idx = tid + kThreads * j;
+      Bs[buf][(idx / BN) * LDB + idx % BN] = rb[j];
+    }
+  };
+  floatx4 acc[2][NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) acc[0][j] = acc[1][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (c_begin < c_end) {
+    fetch(c_begin);
+    stage(0);
+  }
+  __syncthreads();
+  for (int it = c_begin; it < c_end; ++it) {
+    const int cur = (it - c_begin) & 1;
+    if (it + 1 < c_end) fetch(it + 1);
+#pragma unroll
+    for (int q = 0; q < RB_K / 4; ++q) {
+      const float a = As[cur][(4 * q + lk) * LDA + 16 * wave + li];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[q & 1][j] = mfma16(a, Bs[cur][(4 * q + lk) * LDB + 16 * j + li], acc[q & 1][j]);
+    }
+    if (it + 1 < c_end) stage(cur ^ 1);
+    __syncthreads();
+  }
+  float* d = dst + (size_t)part * MR * g.Cout;
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + 16 * wave + 4 * lk + r, n = n0 + 16 * j + li;
+      if (m < MR && n < g.Cout) d[(size_t)m * g.Cout + n] = acc[0][j][r] + acc[1][j][r];
+    }
+}
+
+// column tiles per block: no more than the channels fill
+inline int ragged_nt(int channels) { return channels > 32 ? (channels > 48 ? 4 : 3) : (channels > 16 ? 2 : 1); }
+
+template <int MODE>
+int launch_ragged(hipStream_t st, const ConvGeom& g, const float* in, const float* w, const float* skip, float* out) {
+  const int Ng = MODE == 0 ? g.Cout : g.Cin;
+  const int64_t Mg = MODE == 0 ? (int64_t)g.N * g.Ho * g.Wo : (int64_t)g.N * g.H * g.W;
+  const int nt = ragged_nt(Ng);
+  const unsigned grid = (unsigned)(((Mg + RB_M - 1) / RB_M) * ((Ng + 16 * nt - 1) / (16 * nt)));
+  constexpr bool ST = MODE == 1;   // (the forward only multiplies by the stride)
+  const bool st1 = !ST || g.stride == 1;
+  auto kern = nt == 1 ? (st1 ? ragged_conv_kernel<MODE, 1, false> : ragged_conv_kernel<MODE, 1, ST>)
+            : nt == 2 ? (st1 ? ragged_conv_kernel<MODE, 2, false> : ragged_conv_kernel<MODE, 2, ST>)
+            : nt == 3 ? (st1 ? ragged_conv_kernel<MODE, 3, false> : ragged_conv_kernel<MODE, 3, ST>)
+                      : (st1 ? ragged_conv_kernel<MODE, 4, false> : ragged_conv_kernel<MODE, 4, ST>);
+  kern<<<grid, kThreads, 0, st>>>(in, w, skip, out, g);
+  return hip_status();
+}
+
+template <int K>
+void run_ragged_wgrad(hipStream_t st, const ConvGeom& g, const void* packed, const float* stats, const float* dy,
+                      float* dst, int relu32, int chunks, int split, unsigned tiles, int nt) {
+  auto kern = nt == 1 ? ragged_wgrad_kernel<K, 1> : nt == 2 ? ragged_wgrad_kernel<K, 2>
+            : nt == 3 ? ragged_wgrad_kernel<K, 3> : ragged_wgrad_kernel<K, 4>;
+  kern<<<tiles * (unsigned)split, kThreads, 0, st>>>(static_cast<const uint8_t*>(packed), stats, dy, dst, g, relu32,
+                                                     chunks, split, magic_of(g.Wo), magic_of(g.Ho));
+}
+
+}  // namespace
+
+int launch_ragged_conv(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
+                       float* out) {
+  return mode == 0 ? launch_ragged<0>(st, g, in, w, skip, out) : launch_ragged<1>(st, g, in, w, skip, out);
+}
+
+int ragged_wgrad_copies(const ConvGeom& g, size_t room) {
+  const int nt = ragged_nt(g.Cout);
+  const int64_t MR = (int64_t)g.R * g.S * g.Cin;
+  const int64_t tiles = ((MR + RB_M - 1) / RB_M) * ((g.Cout + 16 * nt - 1) / (16 * nt));
+  const int64_t chunks = ((int64_t)g.N * g.Ho * g.Wo + RB_K - 1) / RB_K;
+  // about four blocks per compute unit, at least four chunks each (a chunk is a round trip to memory)
+  int64_t split = 1024 / tiles;
+  if (split > chunks / 4) split = chunks / 4;
+  if (split < 1) split = 1;
+  const int64_t fit = (int64_t)(room / ((size_t)MR * g.Cout * sizeof(float)));
+  // one copy needs no room: it is dW itself
+  if (split > fit) split = fit > 1 ? fit : 1;
+  // A block walks its share one chunk after the other, about a microsecond each; with shares of more than
+  // 64 chunks the kernel with a block per element of dW is the faster one.
+  return chunks / split > 64 ? 0 : (int)split;
+}
+
+int launch_ragged_wgrad(hipStream_t st, const ConvGeom& g, int K, const void* packed, const float* stats,
+                        const float* dy, int copies, float* dst, bool relu32) {
+  const int nt = ragged_nt(g.Cout);
+  const int MR = g.R * g.S * g.Cin;
+  const unsigned tiles = (unsigned)(((MR + RB_M - 1) / RB_M) * ((g.Cout + 16 * nt - 1) / (16 * nt)));
+  const int chunks = (int)(((int64_t)g.N * g.Ho * g.Wo + RB_K - 1) / RB_K);
+  const int r32 = relu32 ? 1 : 0;
+  if (K == 4) run_ragged_wgrad<4>(st, g, packed, stats, dy, dst, r32, chunks, copies, tiles, nt);
+  else if (K == 8) run_ragged_wgrad<8>(st, g, packed, stats, dy, dst, r32, chunks, copies, tiles, nt);
+  else run_ragged_wgrad<32>(st, g, packed, stats, dy, dst, r32, chunks, copies, tiles, nt);
+  return hip_status();
+}
+
+}  // namespace abl
