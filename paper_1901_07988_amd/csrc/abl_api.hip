@@ -174,14 +174,17 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   // once in the fused kernel wins)
   const bool bf16_gemm = bf16 && bf16_gemm_supported(g, 0) && 2 * g.Cout * g.R * g.S >= 512;
   if (K == 32 || naive || bf16_gemm) return 0;
+  // The split-operand kernels have no prologue either: 3x3 layers are faster with the pack pass in front (56x56
+  // 64 -> 64: 118 us against 173; 14x14 256 -> 256: 87 against 135), 1x1 layers from 128 channels on both sides on
+  // (28x28 128 -> 256: 51 against 53.5; 14x14 256 -> 256: 33 against 37; but 56x56 64 -> 256 103 against 96 and
+  // 256 -> 64 185 against 129: there reading x once wins).
+  if (!bf16 && split_conv_blocks(g, 0) > 0 && (g.R > 1 || (s.Cin >= 128 && s.Cout >= 128))) return 0;
   // (Not for the small images of the image-resident kernel: the pack pass plus that kernel is
-  // faster than the fused one - 14x14 256->256: 7 + 120 us against 146.)
+  // faster than the fused one.)
   if (halo_fused_supported(g) && !(!bf16 && image_f32_supported(g, 0))) return 1;
   // With the prologue every block along the output channels repeats the normalization of its
   // input rows; measured against the separate pack kernel this pays up to 256 output channels.
-  // (Not for the long contractions that the register-resident 1x1 kernel takes: the pack pass plus
-  // that kernel is faster - 1024 -> 256 at 14x14: 17.6 + 55 us against 81.)
-  if (igemm_fused_supported(s) && s.Cout <= 256 && !(!bf16 && rows_f32_blocks(g, 0) > 0)) return 2;
+  if (igemm_fused_supported(s) && s.Cout <= 256) return 2;
   return 0;
 }
 
@@ -290,6 +293,14 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
     const DwSum dwsum{static_cast<const float*>(wpart), t16, (int64_t)9 * 16 * 16, dW};
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, t16, dx, dgamma, dbeta, &dwsum);
   }
+  // the split-operand kernels, with the Eq. 6-7 sums in their epilogue
+  if (const int nb = K != 32 && !bf16 ? split_conv_blocks(g, 1) : 0) {
+    if (int e = launch_split_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
+    DwSum dwsum;
+    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
+    return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nb, dx, dgamma, dbeta,
+                                dwsum.copies > 0 ? &dwsum : nullptr);
+  }
   // small images (3x3 'same' stride 1): the image-resident kernel, one row of sums per image
   if (K != 32 && !bf16 && image_f32_supported(g, 1)) {
     if (int e = launch_image_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
@@ -314,14 +325,6 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
     DwSum dwsum;
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, tiles, dx, dgamma, dbeta,
-                                dwsum.copies > 0 ? &dwsum : nullptr);
-  }
-  // 1x1 layers with a long contraction: the register-resident kernel, one row of sums per row block
-  if (const int nrb = (K != 32 && !bf16) ? rows_f32_blocks(g, 1) : 0) {
-    if (int e = launch_rows_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
-    DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
-    return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nrb, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr);
   }
   // 1x1 stride-1 layers: the same sums in the epilogue of the pointwise dgrad kernel
@@ -441,10 +444,10 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
     return ABL_ERR_ARG;
   const ConvGeom g = geom_of(*s);
   if (scratch_bytes < bn_partial_bytes(rows_of(*s), s->Cin)) return ABL_ERR_SCRATCH;
-  if (const int nrb = !(flags & ABL_MATH_BF16) ? rows_f32_blocks(g, 1) : 0) {   // 1x1, long contraction
-    *rows = nrb;
-    return launch_rows_dgrad_reduce((hipStream_t)stream, g, K, dy, W, packed, stats, da3,
-                                    static_cast<double*>(scratch));
+  if (const int nb = !(flags & ABL_MATH_BF16) ? split_conv_blocks(g, 1) : 0) {
+    *rows = nb;
+    return launch_split_dgrad_reduce((hipStream_t)stream, g, K, dy, W, packed, stats, da3,
+                                     static_cast<double*>(scratch));
   }
   if (!halo_conv_supported(g) && pointwise_supported(g, 1)) {  // 1x1 stride 1: the pointwise kernel's epilogue
     int r = 0;

@@ -168,6 +168,16 @@ bool image_bf16_supported(const ConvGeom& g, int mode);
 int launch_image_bf16(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w,
                       const float* skip, float* out, double* sums);
 
+// ---- fp32 contractions on the bf16 matrix cores, operands split into three bf16 parts (conv_split.hip) ----
+// 'same' stride-1 3x3 and 1x1 layers with contraction channels in multiples of 32 (1x1: 64) and output channels
+// in multiples of 64, unless too small.  split_conv_blocks: rows of the sums ([rows][2][C] doubles: of y in mode
+// 0, Eq. 6-7 in launch_split_dgrad_reduce), 0 = not supported.
+int split_conv_blocks(const ConvGeom& g, int mode);
+int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
+                      float* out, double* sums);
+int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
+                              const void* packed, const void* stats, float* da3, double* partial);
+
 // ---- fp32 3x3 'same' stride-1 convolutions with the whole image resident in LDS (conv_image.hip) ----
 // Images of up to 208 pixels (14x14, 7x7 ...), 16, 32 or a multiple of 64 contraction channels,
 // output channels a multiple of 64, at most kMaxPartialBlocks images and at least 224 blocks: one
@@ -198,16 +208,6 @@ int launch_image_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, cons
 int rows_wgrad_copies(const ConvGeom& g, int K, bool bf16);
 int launch_rows_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, const void* packed, const float* stats,
                       const float* dy, float* copies);
-
-// 1x1 stride-1 convolutions (channel counts in multiples of 64) with the block's whole output tile in
-// accumulator registers and the operands loaded straight from global memory, for shapes that give
-// about one block per compute unit.  rows_f32_blocks: number of row blocks = rows of the sums
-// ([blocks][2][C] doubles: of y in mode 0, Eq. 6-7 in launch_rows_dgrad_reduce), 0 = not supported.
-int rows_f32_blocks(const ConvGeom& g, int mode);
-int launch_rows_f32(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
-                    float* out, double* sums);
-int launch_rows_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
-                             const void* packed, const void* stats, float* da3, double* partial);
 
 // ---- Eq. 9 / Eq. 10 for one value.  Callers must be compiled with floating-point contraction
 // off: the codes are compared bit for bit with an IEEE fp32 evaluation.

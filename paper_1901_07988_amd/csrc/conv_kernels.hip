@@ -923,6 +923,11 @@ int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* 
     return launch_image_bf16(st, g, 0, a3, w, skip, y, want ? sums : nullptr);
   }
   if (bf16 && bf16_gemm_supported(g, 0)) return launch_bf16_gemm(st, g, 0, a3, w, skip, y, sums, rows);
+  if (const int nb = !bf16 ? split_conv_blocks(g, 0) : 0) {
+    const bool want = sums != nullptr && rows != nullptr;
+    if (want) *rows = nb;
+    return launch_split_conv(st, g, 0, a3, w, skip, y, want ? sums : nullptr);
+  }
   // small images: the whole image resident in LDS, one row of sums per image
   if (!bf16 && image_f32_supported(g, 0)) {
     const bool want = sums != nullptr && rows != nullptr;
@@ -934,13 +939,6 @@ int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* 
     const bool want = tiles > 0 && tiles <= kMaxPartialBlocks;
     if (want) *rows = tiles;
     return launch_halo_conv(st, g, 0, bf16, a3, w, skip, y, want ? sums : nullptr);
-  }
-  // 1x1 layers that give about one block per compute unit: the output tile in registers, one row of sums
-  // per row block
-  if (const int nrb = !bf16 ? rows_f32_blocks(g, 0) : 0) {
-    const bool want = sums != nullptr && rows != nullptr;
-    if (want) *rows = nrb;
-    return launch_rows_f32(st, g, 0, a3, w, skip, y, want ? sums : nullptr);
   }
   if (pointwise_supported(g, 0))
     return launch_pointwise_conv(st, g, 0, bf16, a3, w, skip, y, rows != nullptr ? sums : nullptr, rows);
@@ -972,9 +970,9 @@ int launch_conv_dgrad(hipStream_t st, const abl_shape& s, bool bf16, const float
   if (!mfma_ok(g)) return launch_ragged_conv(st, g, 1, dy, w, nullptr, da3);
   if (bf16 && image_bf16_supported(g, 1)) return launch_image_bf16(st, g, 1, dy, w, nullptr, da3, nullptr);
   if (bf16 && bf16_gemm_supported(g, 1)) return launch_bf16_gemm(st, g, 1, dy, w, nullptr, da3);
+  if (!bf16 && split_conv_blocks(g, 1) > 0) return launch_split_conv(st, g, 1, dy, w, nullptr, da3, nullptr);
   if (!bf16 && image_f32_supported(g, 1)) return launch_image_f32(st, g, 1, dy, w, nullptr, da3, nullptr);
   if (halo_conv_supported(g)) return launch_halo_conv(st, g, 1, bf16, dy, w, nullptr, da3);
-  if (!bf16 && rows_f32_blocks(g, 1) > 0) return launch_rows_f32(st, g, 1, dy, w, nullptr, da3, nullptr);
   if (pointwise_supported(g, 1)) return launch_pointwise_conv(st, g, 1, bf16, dy, w, nullptr, da3);
   return launch_igemm<1, 0>(st, g, bf16, dy, w, nullptr, da3, nullptr, nullptr);
 }

@@ -1,0 +1,592 @@
+// fp32 contractions on the bf16 matrix cores: Eq. 4 (forward, mode 0) and the second half of Eq. 5 (gradient
+// to the conv input, mode 1) of 'same' stride-1 3x3 and 1x1 layers.
+//
+// An fp32 value is the exact sum of three bf16 values (8 + 8 + 8 significant bits: x = h + m + l, each the
+// rounded remainder of the ones before), so a product of two is nine bf16 products, each exact in fp32.  Six
+// of them are taken - hh, hm, mh, mm, hl, lh; the dropped ones (ml, lm, ll) are below 2^-26 of the product,
+// a quarter of an fp32 rounding.  v_mfma_f32_16x16x32_bf16 does 32 of the contraction in the time in which
+// v_mfma_f32_16x16x4_f32 does about three (measured 1600 against 154 TFLOP/s), so six of them are 1.7 times
+// faster; and the sum is rounded once per 32 terms and product instead of once per 4 terms.  The five small
+// products have an accumulator of their own: added to the large one they would each round at its magnitude
+// (relative error of a 2304-term contraction against 64 bits: fp32 matrix cores 8.6e-7, one accumulator
+// 7.4e-7, two 2.9e-7).  What the split cannot carry: an infinity becomes a NaN (inf - inf), so an output that
+// is not finite is computed again from the fp32 operands by exact_output(); below 2^-110 the lowest bits of a
+// value fall under the smallest bf16.
+//
+// One block = a run of up to 112 consecutive pixels (of one image, or across images where that makes fewer
+// tiles) x 16 NT WN output channels.  Its input patch (the rows of those pixels and the filter's border) is
+// split once, on the way into LDS, CHUNKS 32-channel chunks at a time; a position holds the three
+// parts of a chunk side by side (192 bytes) and positions are padded by 16 bytes, so that the 16-byte
+// fragment reads of 16 neighbouring positions fall into different banks.  Weights go from the L2 straight
+// into registers, one k-step (32 contraction channels of one tap) ahead, and are split there: every wave has
+// output channels of its own, so a block splits nothing twice.  A wave computes 112 pixels x 16 NT channels: 7 NT tiles, 12 NT reads and 42 NT MFMAs per k-step.
+// KS = 2: the chunks of a phase go to two groups of waves whose sums meet in LDS at the end - two waves per
+// SIMD also where a layer gives only one block per compute unit - and the patch has two buffers.
+// KS = 1: one buffer, two blocks per compute unit cover each other's staging.
+#include <mutex>
+#include <set>
+#include <utility>
+
+#include "abl_internal.h"
+
+namespace abl {
+namespace {
+
+constexpr int MT = 7;   // 16-pixel tiles per wave and block
+constexpr int WN = 4;   // waves along the output channels
+
+int allow_full_lds(const void* kern) {
+  static std::mutex mu;
+  static std::set<std::pair<int, const void*>> done;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return ABL_ERR_HIP;
+  }
+  const std::pair<int, const void*> key(dev, kern);
+  std::lock_guard<std::mutex> lock(mu);
+  if (done.find(key) == done.end()) {
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+      (void)hipGetLastError();
+      return ABL_ERR_HIP;
+    }
+    done.insert(key);
+  }
+  return ABL_OK;
+}
+
+struct Tiling {
+  int run;           // pixels per tile
+  int unit, ntr;     // a tile never crosses a multiple of `unit` pixels (an image, or the whole batch): ntr tiles each
+  int tiles, per;    // tiles in all, tiles per block (consecutive)
+  int gm;            // blocks along the pixels
+  int npos;          // positions of a patch
+};
+
+// x = h + m + l, eight values at a time (the parts of two values share a 32-bit word)
+__device__ inline void split3(const float (&x)[8], bf16x8_t& h, bf16x8_t& m, bf16x8_t& l) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  uint4 hw, mw, lw;
+  auto two = [](float a, float b, uint32_t& u, uint32_t& v, uint32_t& w) __attribute__((always_inline)) {
+    u = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+    const float ra = a - __uint_as_float(u << 16), rb = b - __uint_as_float(u & 0xFFFF0000u);
+    v = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
+    w = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)(ra - __uint_as_float(v << 16)),
+                                            (__bf16)(rb - __uint_as_float(v & 0xFFFF0000u))});
+  };
+  two(x[0], x[1], hw.x, mw.x, lw.x);
+  two(x[2], x[3], hw.y, mw.y, lw.y);
+  two(x[4], x[5], hw.z, mw.z, lw.z);
+  two(x[6], x[7], hw.w, mw.w, lw.w);
+  h = __builtin_bit_cast(bf16x8_t, hw);
+  m = __builtin_bit_cast(bf16x8_t, mw);
+  l = __builtin_bit_cast(bf16x8_t, lw);
+}
+
+// One output in fp32 from the operands themselves, for values that are not finite.
+template <int MODE, int TAPS>
+__device__ inline float exact_output(const float* in, const float* wgt, int H, int W, int Cin, int Cout, int p,
+                                            int n) {
+  const int Cg = MODE == 0 ? Cin : Cout;
+  const int HW = H * W;
+  const int img = p / HW, h = (p - img * HW) / W, w = p - img * HW - h * W;
+  float s = 0.0f;
+  for (int tap = 0; tap < TAPS; ++tap) {
+    const int hi = h + (TAPS == 9 ? tap / 3 - 1 : 0), wi = w + (TAPS == 9 ? tap % 3 - 1 : 0);
+    if (hi < 0 || hi >= H || wi < 0 || wi >= W) continue;
+    const float* a = in + ((size_t)(img * H + hi) * W + wi) * Cg;
+    const float* b = MODE == 0 ? wgt + (size_t)tap * Cin * Cout + n : wgt + ((size_t)(TAPS - 1 - tap) * Cin + n) * Cout;
+    for (int c = 0; c < Cg; ++c) {
+      s = fmaf(a[c], MODE == 0 ? b[(size_t)c * Cout] : b[c], s);
+      if (s != s) return s;
+    }
+  }
+  return s;
+}
+
+// EPI: 0 none; 1 = sums of y and y^2 per channel (first pass of the next layer's Eq. 1); 4 / 8 = the Eq. 6-7
+// sums from the layer's K-bit codes.  Row blockIdx of sums: [gm][2][Ng] doubles.
+template <int MODE, int TAPS, int NT, int KS, int CPP, int SU, int EPI>
+__global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float* __restrict__ in,
+                                                                          const float* __restrict__ wgt,
+                                                                          const float* skip, float* out,
+                                                                          double* __restrict__ sums,
+                                                                          const uint8_t* __restrict__ codes,
+                                                                          const float* __restrict__ stats, ConvGeom g,
+                                                                          Tiling tl, int bufsz) {
+  constexpr int THREADS = 64 * WN * KS;
+  constexpr int CHUNKS = KS * CPP, CH = 32 * CHUNKS;   // per phase
+  constexpr int PITCH = 192 * CHUNKS + 16;             // bytes per patch position
+  constexpr int BN = 16 * NT * WN;
+  constexpr bool DB = KS > 1;
+  constexpr int C8 = CH / 8;                           // staging items per position
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  double* const sum_lds = reinterpret_cast<double*>(smem + (DB ? 2 : 1) * bufsz);   // [KS][2][BN]
+
+  const int Cg = MODE == 0 ? g.Cin : g.Cout;
+  const int Ng = MODE == 0 ? g.Cout : g.Cin;
+  const int H = g.H, W = g.W, PW = W + 2;
+  const int Mg = g.N * H * W;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = wave % WN, kg = wave / WN;
+  const int li = lane & 15, lk = lane >> 4;
+  // ids 8 apart share an XCD and its L2: the blocks that read the same pixels for different output channels
+  // run there back to back
+  const int nblk = Ng / BN;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int mb = (slot / nblk) * 8 + xcd;
+  const int n0 = (slot % nblk) * BN + 16 * NT * wn;
+  if (mb >= tl.gm) return;
+  const int t_end = min((mb + 1) * tl.per, tl.tiles);
+  const int nph = Cg / CH;
+
+  // weights of a k-step: forward: the lane's column in eight rows; gradient: 32 contiguous bytes
+  uint32_t w_lane = 4u * (MODE == 0 ? (uint32_t)(8 * lk * g.Cout + li) : (uint32_t)(li * g.Cout + 8 * lk));
+  auto load_w = [&](float (&raw)[NT][8], int tap, int c0) __attribute__((always_inline)) {
+    // (opaque: the lane's 32-bit offset stays a register beside the scalar base instead of a 64-bit address)
+    asm volatile("" : "+v"(w_lane));
+    if constexpr (MODE == 0) {
+      const char* wb = reinterpret_cast<const char*>(wgt + ((size_t)(tap * g.Cin + c0) * g.Cout + n0));
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          raw[j][e] = *reinterpret_cast<const float*>(wb + (size_t)(4 * e) * g.Cout + 64 * j + w_lane);
+    } else {
+      const char* wb = reinterpret_cast<const char*>(wgt + ((size_t)((TAPS - 1 - tap) * g.Cin + n0) * g.Cout + c0));
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const floatx4 v = *reinterpret_cast<const floatx4*>(wb + (size_t)(64 * j) * g.Cout + 16 * q + w_lane);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) raw[j][4 * q + e] = v[e];
+        }
+    }
+  };
+
+  if (EPI != 0)
+    for (int i = tid; i < KS * 2 * BN; i += THREADS) sum_lds[i] = 0.0;
+
+  for (int t = mb * tl.per; t < t_end; ++t) {
+    // ---- the tile: pixels p0 .. p_end - 1; its patch starts a row above the first of them, in rows of images
+    // padded to H + 2
+    const int p0 = (t / tl.ntr) * tl.unit + (t % tl.ntr) * tl.run;
+    const int p_end = min(min(p0 + tl.run, (t / tl.ntr + 1) * tl.unit), Mg);
+    const int row0 = p0 / W + 2 * (p0 / (H * W));
+    int s_off[SU], l_off[SU];   // staging items: element offset of the item's channels (phase 0), -1 = zeros; LDS offset
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      int it = tid + THREADS * u;
+      const int last = tl.npos * C8 - 1;
+      it = it < last ? it : last;   // (a thread past the end repeats the last item)
+      const int pos = it / C8, c8 = it % C8;
+      l_off[u] = pos * PITCH + (c8 >> 2) * 192 + (c8 & 3) * 16;
+      if (TAPS == 9) {
+        const int prow = pos / PW, w = pos - prow * PW - 1;
+        const int n = (row0 + prow) / (H + 2), h = row0 + prow - n * (H + 2) - 1;
+        s_off[u] = n < g.N && h >= 0 && h < H && w >= 0 && w < W ? ((n * H + h) * W + w) * Cg + 8 * c8 : -1;
+      } else {
+        s_off[u] = p0 + pos < p_end ? (p0 + pos) * Cg + 8 * c8 : -1;
+      }
+    }
+    float sv[SU][8];
+    auto stage_load = [&](int ph) __attribute__((always_inline)) {
+      const float* src = in + ph * CH;
+#pragma unroll
+      for (int u = 0; u < SU; ++u) {
+        const int o = s_off[u] < 0 ? 0 : s_off[u];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const floatx4 v = *reinterpret_cast<const floatx4*>(src + o + 4 * q);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sv[u][4 * q + e] = v[e];
+        }
+      }
+    };
+    auto stage_store = [&](unsigned char* buf) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < SU; ++u) {
+        bf16x8_t h, m, l;
+        if (TAPS == 9 || s_off[u] < 0)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) sv[u][e] = s_off[u] < 0 ? 0.0f : sv[u][e];
+        split3(sv[u], h, m, l);
+        *reinterpret_cast<bf16x8_t*>(buf + l_off[u]) = h;
+        *reinterpret_cast<bf16x8_t*>(buf + l_off[u] + 64) = m;
+        *reinterpret_cast<bf16x8_t*>(buf + l_off[u] + 128) = l;
+      }
+    };
+    int a_base[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      int m = 16 * i + li;
+      if (TAPS == 9) {
+        const int p = p0 + m < p_end ? p0 + m : p_end - 1;   // slots past the tile: any position of it, never stored
+        const int row = p / W;
+        m = (row + 2 * (row / H) - row0) * PW + p - row * W;
+      }
+      a_base[i] = m * PITCH + kg * CPP * 192 + lk * 16;
+    }
+
+    floatx4 hi[NT][MT], lo[NT][MT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) hi[j][i] = lo[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    float raw[NT][8];
+    stage_load(0);
+    load_w(raw, 0, kg * CPP * 32);
+    for (int ph = 0; ph < nph; ++ph) {
+      unsigned char* cur = smem + (DB ? (ph & 1) * bufsz : 0);
+      // (two buffers: this one was last read a phase ago, before the barrier that followed)
+      if (!DB || ph == 0) __syncthreads();
+      stage_store(cur);
+      __syncthreads();
+      if (ph + 1 < nph) stage_load(ph + 1);
+#pragma unroll 1
+      for (int ks = 0; ks < TAPS * CPP; ++ks) {
+        const int cc = ks / TAPS, tap = ks - cc * TAPS;
+        bf16x8_t bh[NT], bm[NT], bl[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) split3(raw[j], bh[j], bm[j], bl[j]);
+        // the next k-step's weights (the very last step asks for its own again: no branch)
+        {
+          const bool wrap = ks + 1 == TAPS * CPP;
+          const bool end = wrap && ph + 1 == nph;
+          const int nks = end ? ks : wrap ? 0 : ks + 1;
+          const int ncc = nks / TAPS, ntap = nks - ncc * TAPS;
+          load_w(raw, ntap, (wrap && !end ? ph + 1 : ph) * CH + (kg * CPP + ncc) * 32);
+        }
+        const int off = (TAPS == 9 ? (tap / 3) * PW + tap % 3 : 0) * PITCH + cc * 192;
+        const unsigned char* ab = cur + off;
+        bf16x8_t ah[2], am[2], al[2];
+        auto read_a = [&](int set, int i) __attribute__((always_inline)) {
+          ah[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i]);
+          am[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + 64);
+          al[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + 128);
+        };
+        read_a(0, 0);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          const int c = i & 1;
+          if (i + 1 < MT) read_a(c ^ 1, i + 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[j], ah[c], lo[j][i], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) hi[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], ah[c], hi[j][i], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], al[c], lo[j][i], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[j], am[c], lo[j][i], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[j], ah[c], lo[j][i], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], am[c], lo[j][i], 0, 0, 0);
+        }
+      }
+    }
+
+    // ---- the lane holds channels n0 + 16 j + 4 lk .. +3 of pixel slot 16 (MT wm + i) + li
+    floatx4 v[NT][MT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) v[j][i] = hi[j][i] + lo[j][i];
+    constexpr int I0 = 4;   // KS = 2: group 0 finishes the first four pixel tiles, group 1 the others
+    if constexpr (KS == 2) {
+      __syncthreads();      // every wave has finished reading the patch
+      unsigned char* dst = smem + (size_t)((wave ^ WN) * I0 * NT) * 1024 + lane * 16;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          if ((i < I0) == (kg == 1)) *reinterpret_cast<floatx4*>(dst + (j * I0 + (i < I0 ? i : i - I0)) * 1024) = v[j][i];
+      __syncthreads();
+      const unsigned char* srcp = smem + (size_t)(wave * I0 * NT) * 1024 + lane * 16;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          if ((i < I0) == (kg == 0)) v[j][i] += *reinterpret_cast<const floatx4*>(srcp + (j * I0 + (i < I0 ? i : i - I0)) * 1024);
+    }
+    int px[MT];   // the lane's pixels, -1 = none
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      px[i] = p0 + 16 * i + li;
+      if (px[i] >= p_end) px[i] = -1;
+    }
+    // outputs that are not finite: again from the fp32 operands, one after the other
+    {
+      float bad = 0.0f;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) bad = fmaf(v[j][i][r], 0.0f, bad);
+      if (__builtin_expect(bad != 0.0f, 0)) {   // (a NaN)
+        for (int e = 0; e < NT * MT * 4; ++e) {
+          float x = 0.0f;
+          int p = -1;
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if (e == (j * MT + i) * 4 + r && (KS == 1 || (i < I0) == (kg == 0))) x = v[j][i][r], p = px[i];
+          if (fabsf(x) < INFINITY || p < 0) continue;
+          x = exact_output<MODE, TAPS>(in, wgt, H, W, g.Cin, g.Cout, p, n0 + 16 * (e / (4 * MT)) + 4 * lk + (e & 3));
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) v[j][i][r] = e == (j * MT + i) * 4 + r ? x : v[j][i][r];
+        }
+      }
+    }
+    // (before the stores: loads and stores retire in order)
+    uint32_t cw[NT][MT];
+    if constexpr (EPI > 1) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        if (KS == 2 && (i < I0) != (kg == 0)) continue;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          const size_t o = (size_t)(px[i] < 0 ? 0 : px[i]) * Ng + n0 + 16 * j + 4 * lk;
+          if constexpr (EPI == 4) cw[j][i] = *reinterpret_cast<const uint16_t*>(codes + (o >> 1));
+          else cw[j][i] = *reinterpret_cast<const uint32_t*>(codes + o);
+        }
+      }
+    }
+    // a pixel's channels one after the other: the two halves of a 128-byte line leave together (64 -> 256
+    // channels at 56x56: 60 us, channel tile by channel tile 89 us)
+    if (MODE == 0 && skip != nullptr) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        if (KS == 2 && (i < I0) != (kg == 0)) continue;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          v[j][i] += *reinterpret_cast<const floatx4*>(skip + (size_t)(px[i] < 0 ? 0 : px[i]) * Ng + n0 + 16 * j + 4 * lk);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      if (KS == 2 && (i < I0) != (kg == 0)) continue;
+      if (px[i] < 0) continue;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        *reinterpret_cast<floatx4*>(out + (size_t)px[i] * Ng + n0 + 16 * j + 4 * lk) = v[j][i];
+    }
+    // the sums, a channel tile at a time: one tile's sums and constants only are live
+    if constexpr (EPI != 0)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int nch = n0 + 16 * j + 4 * lk;
+      double s1[4] = {0.0, 0.0, 0.0, 0.0}, s2[4] = {0.0, 0.0, 0.0, 0.0};
+      floatx4 st4;
+      float offh[4];   // code + offh = Eq. 10 over its step (exact: both are below 2^24)
+      if constexpr (EPI > 1) {
+        st4 = *reinterpret_cast<const floatx4*>(stats + P_STEP * Ng + nch);
+        const int4 fb4 = *reinterpret_cast<const int4*>(stats + P_FB * Ng + nch);
+        const int32_t fbv[4] = {fb4.x, fb4.y, fb4.z, fb4.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) offh[r] = (float)(fbv[r] - (1 << (EPI - 1))) + 0.5f;
+      }
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        if (KS == 2 && (i < I0) != (kg == 0)) continue;
+        const bool ok = px[i] >= 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if constexpr (EPI == 1) {
+            const double y = ok ? v[j][i][r] : 0.0f;
+            s1[r] += y;
+            s2[r] = __builtin_fma(y, y, s2[r]);
+          } else if constexpr (EPI > 1) {
+            const float q = (float)((cw[j][i] >> (EPI * r)) & ((1u << EPI) - 1u)) + offh[r];
+            const float da2 = ok && st4[r] * q > 0.0f ? v[j][i][r] : 0.0f;   // Eq. 10, Eq. 6
+            s1[r] += (double)da2;
+            s2[r] = __builtin_fma((double)q, (double)da2, s2[r]);
+          }
+        }
+      }
+      if constexpr (EPI != 0) {
+        // over the 16 pixel lanes, then onto the wave's own row of sums
+        double* row = sum_lds + (size_t)kg * 2 * BN + 16 * NT * wn;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double t1 = row16_sum(s1[r]), t2 = row16_sum(s2[r]);
+          if (li == 0) {
+            row[16 * j + 4 * lk + r] += t1;
+            row[BN + 16 * j + 4 * lk + r] += t2;
+          }
+        }
+      }
+    }
+    if (DB) __syncthreads();   // the exchange area is the next tile's patch
+  }
+  if constexpr (EPI != 0) {
+    __syncthreads();
+    const int nb = (slot % nblk) * BN;
+    for (int c = tid; c < BN; c += THREADS) {
+      double t1 = 0.0, t2 = 0.0;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        t1 += sum_lds[(size_t)k * 2 * BN + c];
+        t2 += sum_lds[(size_t)k * 2 * BN + BN + c];
+      }
+      // Eq. 7 by linearity: with A~2 = step q, sum A~1 dA2 = (step sum q dA2 - beta sum dA2) / gamma
+      if (EPI > 1)
+        t2 = ((double)stats[P_STEP * Ng + nb + c] * t2 - (double)stats[P_BETA * Ng + nb + c] * t1) /
+             (double)stats[P_GAMMA * Ng + nb + c];
+      sums[((size_t)mb * 2) * Ng + nb + c] = t1;
+      sums[((size_t)mb * 2 + 1) * Ng + nb + c] = t2;
+    }
+  }
+}
+
+// ---- which configuration a layer takes ---------------------------------------------------------------
+struct Plan {
+  int nt, ks, cpp, su;   // the kernel's parameters
+  Tiling tl;
+  size_t lds;
+  int bufsz, bn;
+};
+
+// The configuration with nt, ks for this layer; false where its sizes do not fit.
+bool fit_plan(const ConvGeom& g, int mode, int nt, int ks, Plan& p) {
+  const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
+  const bool k3 = g.R == 3;
+  p.nt = nt;
+  p.ks = ks;
+  p.cpp = !k3 && ks == 1 ? 2 : 1;                                // 1x1: two k-steps between barriers
+  p.su = k3 ? (ks == 2 ? (nt == 2 ? 3 : 4) : nt == 2 ? 4 : 7) : ks == 2 ? 2 : 4;   // staging items per thread, at most
+  p.bn = 16 * nt * WN;
+  if (Ng % p.bn != 0 || Cg % (32 * ks * p.cpp) != 0) return false;
+  const int threads = 64 * WN * ks, c8 = 4 * ks * p.cpp, pitch = 192 * ks * p.cpp + 16, bm = 16 * MT;
+  const int M = g.N * g.H * g.W, HW = g.H * g.W, W = g.W;
+  Tiling& t = p.tl;
+  if (!k3) {
+    t.run = bm;
+    t.unit = M;
+    t.ntr = t.tiles = (M + bm - 1) / bm;
+    t.npos = bm;
+  } else {
+    // image by image, the tiles of an image of equal lengths
+    t.unit = HW;
+    t.ntr = (HW + bm - 1) / bm;
+    t.run = (HW + t.ntr - 1) / t.ntr;
+    t.tiles = g.N * t.ntr;
+    int rows = t.run % W == 0 ? t.run / W : (t.run + W - 2) / W + 1;   // that a run touches
+    if (rows > g.H) rows = g.H;
+    t.npos = (rows + 2) * (W + 2);
+    // across images, where the patch has room for the two rows of border that each of them brings: runs of
+    // any pixels, or of whole images
+    const int room = p.su * threads / c8;
+    int xrows = bm % W == 0 ? bm / W : (bm + W - 2) / W + 1;
+    xrows += 2 + 2 * ((xrows + g.H - 2) / g.H);
+    int imgs = bm / HW;
+    if (imgs > room / ((g.H + 2) * (W + 2))) imgs = room / ((g.H + 2) * (W + 2));
+    if ((M + bm - 1) / bm < t.tiles && xrows * (W + 2) <= room) {
+      t.run = bm;
+      t.npos = xrows * (W + 2);
+      t.unit = M;
+    } else if (imgs > 1) {
+      t.run = imgs * HW;
+      t.npos = imgs * (g.H + 2) * (W + 2);
+      t.unit = M;
+    }
+    if (t.unit == M) t.ntr = t.tiles = (M + t.run - 1) / t.run;
+  }
+  if (t.npos * c8 > p.su * threads) return false;
+  if (p.su == 7 && t.npos * c8 <= 4 * threads) p.su = 4;
+  t.per = (t.tiles + kMaxPartialBlocks - 1) / kMaxPartialBlocks;   // one row of sums per block
+  t.gm = (t.tiles + t.per - 1) / t.per;
+  p.bufsz = t.npos * pitch;
+  if (ks == 2 && p.bufsz < 2 * nt * WN * 1024 * 4) p.bufsz = 2 * nt * WN * 1024 * 4;   // the exchange of the partial sums
+  p.lds = (size_t)p.bufsz * ks + (size_t)ks * 2 * p.bn * sizeof(double);
+  return p.lds <= (size_t)160 * 1024;
+}
+
+// 128 output channels per block where that fills the chip, else 64.  About one block per compute unit: the
+// contraction in two groups of waves; more: four-wave blocks, two per unit.  (us, blocks of 8 / 4 waves: 3x3
+// 256 -> 256 @14x14, 256 blocks 79 / 89; 1x1 1024 -> 256 @14x14, 224 blocks 45 / 55; 3x3 128 -> 128 @28x28,
+// 448 blocks 79 / 74; 1x1 256 -> 1024 @14x14, 896 blocks 54 / 45; with 64 channels per block 3x3 512 -> 512 @7x7
+// 88 / 105 instead of 125 / 160 with 128 channels on 112 blocks.)  Small grids stay on the other kernels, which
+// need no pass of their own for Eq. 1-3 and 9 (3x3 64 -> 64 on 128 images of 8x8, 74 blocks: layer step 69 us
+// against 65).
+bool make_plan(const ConvGeom& g, int mode, Plan& p) {
+  const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
+  const bool k3 = g.R == 3 && g.S == 3 && g.pad == 1, k1 = g.R == 1 && g.S == 1 && g.pad == 0;
+  if (g.stride != 1 || !(k3 || k1) || Cg % 32 != 0 || Ng % 64 != 0) return false;
+  const int64_t M = (int64_t)g.N * g.H * g.W;
+  if (M * g.Cin >= ((int64_t)1 << 31) || M * g.Cout >= ((int64_t)1 << 31)) return false;
+  for (int nt = 2; nt >= 1; --nt)
+    for (int ks = 2; ks >= 1; --ks) {
+      if (!fit_plan(g, mode, nt, ks, p)) continue;
+      const int64_t blocks = (int64_t)p.tl.gm * (Ng / p.bn);
+      if (blocks >= (nt == 2 ? 200 : 96) && (ks == 1 || blocks <= 256)) return true;
+    }
+  return false;
+}
+
+template <int MODE, int TAPS, int NT, int KS, int CPP, int SU>
+int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const float* skip,
+               float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
+  const int Ng = MODE == 0 ? g.Cout : g.Cin;
+  const unsigned grid = (unsigned)((p.tl.gm + 7) / 8 * 8 * (Ng / p.bn));
+  auto kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 0>;
+  if constexpr (MODE == 0) {
+    if (epi == 1) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 1>;
+  } else {
+    if (epi == 4) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 4>;
+    if (epi == 8) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8>;
+  }
+  if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
+  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, skip, out, sums, codes, stats, g, p.tl, p.bufsz);
+  return hip_status();
+}
+
+template <int MODE>
+int launch(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const float* skip,
+           float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
+  auto run = [&](auto f) { return f(st, g, p, in, w, skip, out, sums, codes, stats, epi); };
+  if (g.R == 3) {
+    if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, 9, 2, 2, 1, 3> : launch_cfg<MODE, 9, 1, 2, 1, 4>);
+    if (p.nt == 2) return run(launch_cfg<MODE, 9, 2, 1, 1, 4>);
+    return run(p.su == 4 ? launch_cfg<MODE, 9, 1, 1, 1, 4> : launch_cfg<MODE, 9, 1, 1, 1, 7>);
+  }
+  if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, 1, 2, 2, 1, 2> : launch_cfg<MODE, 1, 1, 2, 1, 2>);
+  return run(p.nt == 2 ? launch_cfg<MODE, 1, 2, 1, 2, 4> : launch_cfg<MODE, 1, 1, 1, 2, 4>);
+}
+
+}  // namespace
+
+int split_conv_blocks(const ConvGeom& g, int mode) {
+  Plan p;
+  return make_plan(g, mode, p) ? p.tl.gm : 0;
+}
+
+int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
+                      float* out, double* sums) {
+  Plan p;
+  if (!make_plan(g, mode, p)) return ABL_ERR_SHAPE;
+  if (mode == 0) return launch<0>(st, g, p, in, w, skip, out, sums, nullptr, nullptr, sums != nullptr ? 1 : 0);
+  return launch<1>(st, g, p, in, w, nullptr, out, nullptr, nullptr, nullptr, 0);
+}
+
+int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
+                              const void* packed, const void* stats, float* da3, double* partial) {
+  Plan p;
+  if (!make_plan(g, 1, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
+  return launch<1>(st, g, p, dy, w, nullptr, da3, partial, static_cast<const uint8_t*>(packed),
+                   static_cast<const float*>(stats), K);
+}
+
+}  // namespace abl

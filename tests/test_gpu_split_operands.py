@@ -1,0 +1,158 @@
+"""fp32 contractions whose operands are split into three bf16 parts, against 64-bit values, at the edges of their
+tiles (runs of 112 pixels within an image, across images or of whole images; 64 or 128 output channels per block;
+32-channel phases) and for values that the split cannot carry."""
+import pytest
+import torch
+
+from paper_1901_07988_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+# N, H, W, Cin, Cout, R
+SHAPES = [
+    (2100, 1, 1, 64, 64, 3),     # images of one pixel: 21 of them to a patch
+    (220, 7, 7, 64, 64, 3),      # runs of whole images; two groups of waves
+    (120, 14, 14, 64, 128, 3),   # runs across images; 128 channels per block forward, 64 backward
+    (100, 12, 11, 32, 64, 3),    # one 32-channel phase; two images' borders in a patch
+    (12, 57, 57, 64, 64, 3),     # a run of 112 pixels touches three rows
+    (29, 28, 28, 64, 128, 3),    # seven runs of four rows to an image
+    (40, 56, 56, 64, 64, 3),     # several tiles to a block
+    (11, 13, 60, 128, 192, 3),
+    (1, 110, 101, 64, 64, 1),    # 112 pixels to a tile, the last one short; two groups of waves
+    (1, 150, 150, 64, 128, 1),
+    (2, 150, 151, 128, 256, 1),  # more blocks than compute units
+    (3, 141, 143, 192, 64, 1),   # several tiles to a block
+]
+IDS = ["x".join(map(str, s)) for s in SHAPES]
+
+
+def shape9(s):
+    return s[:5] + (s[5], s[5], 1, (s[5] - 1) // 2)
+
+
+def conv64(a, w):
+    """'Same' stride-1 convolution in 64 bits, a NHWC, w RSCK."""
+    R, pad = w.shape[0], (w.shape[0] - 1) // 2
+    N, H, W, c = a.shape
+    p, wd = torch.nn.functional.pad(a.double(), (0, 0, pad, pad, pad, pad)), w.double()
+    y = torch.zeros(N * H * W, w.shape[3], dtype=torch.float64, device=a.device)
+    for r in range(R):
+        for q in range(R):
+            y += p[:, r:r + H, q:q + W].reshape(-1, c) @ wd[r, q].contiguous()
+    return y.view(N, H, W, -1)
+
+
+def grad_weights(w):
+    return w.flip(0, 1).transpose(2, 3).contiguous()
+
+
+def tolerance(terms):
+    # the large products are rounded once per 32 terms at the magnitude of the running sum, which is a random walk
+    # for these inputs: sqrt(terms / 32) roundings of 2^-24, and two for the small products and the final sum
+    return 2.0 ** -24 * ((terms / 32) ** 0.5 + 2)
+
+
+def rel(a, b):
+    return float((a.double() - b).norm() / b.norm())
+
+
+def draw(s, seed=3):
+    N, H, W, ci, co, R = s
+    g = torch.Generator(device="cuda").manual_seed(seed)
+
+    def normal(*size):
+        return torch.randn(*size, device="cuda", generator=g)
+
+    return normal(N, H, W, ci), normal(R, R, ci, co) * (2.0 / (ci * R * R)) ** 0.5, normal(N, H, W, co)
+
+
+@pytest.mark.parametrize("s", SHAPES, ids=IDS)
+def test_forward_and_gradient(s):
+    print("case split operands", s, flush=True)
+    x, w, dy = draw(s)
+    R, ci, co = s[5], s[3], s[4]
+    y, da3, y2 = torch.full_like(dy, float("nan")), torch.full_like(x, float("nan")), torch.empty_like(dy)
+    B.abl_conv_fwd(shape9(s), x, w, None, y)
+    B.abl_conv_dgrad(shape9(s), dy, w, da3)
+    B.abl_conv_fwd(shape9(s), x, w, dy, y2)
+    assert rel(y, conv64(x, w)) < tolerance(R * R * ci)
+    if ci % 64 == 0:   # (other kernels compute gradients of 32 channels)
+        assert rel(da3, conv64(dy, grad_weights(w))) < tolerance(R * R * co)
+    assert torch.equal(y2, y + dy)   # the shortcut is one fp32 addition
+
+
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("s", [s for s in SHAPES if s[3] % 64 == 0], ids=lambda s: "x".join(map(str, s)))
+def test_sums_of_the_gradient(s, K):
+    print("case split operands, sums", s, K, flush=True)
+    x, w, dy = draw(s)
+    N, H, W, ci, co, R = s
+    M, s9 = N * H * W, shape9(s)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    gamma, beta = torch.rand(ci, device="cuda", generator=g) + 0.5, torch.randn(ci, device="cuda", generator=g) * 0.1
+    stats = torch.empty(32 * ci, dtype=torch.uint8, device="cuda")
+    packed = torch.empty(B.abl_packed_bytes(s9, K), dtype=torch.uint8, device="cuda")
+    scratch = torch.empty(B.abl_scratch_bytes(s9, K), dtype=torch.uint8, device="cuda")
+    a3, a2t, da3, plain = (torch.empty_like(x) for _ in range(4))
+    B.abl_bn_stats(x, M, ci, gamma, beta, K, scratch, stats)
+    B.abl_bn_relu_pack(x, M, ci, K, stats, a3, packed)
+    B.abl_unpack(packed, M, ci, K, stats, a2t)
+    B.abl_conv_dgrad(s9, dy, w, plain)
+    rows = B.abl_conv_dgrad_bn_reduce(s9, K, dy, w, packed, stats, scratch, da3)
+    assert torch.equal(da3, plain)
+    sums = scratch[: rows * 2 * ci * 8].view(torch.float64).view(rows, 2, ci).sum(0)
+    da2 = torch.where(a2t > 0, da3, torch.zeros_like(da3)).double().view(M, ci)
+    a1 = (a2t.double().view(M, ci) - beta.double()) / gamma.double()
+    for got, terms in ((sums[0], da2), (sums[1], da2 * a1)):
+        # sums in 64 bits; a2t is rounded to 32 bits here and not there
+        assert float((got - terms.sum(0)).abs().max()) <= 2.0 ** -23 * float(terms.abs().sum(0).max())
+
+
+@pytest.mark.parametrize("s", [SHAPES[2], SHAPES[5], SHAPES[9], SHAPES[10]], ids=lambda s: "x".join(map(str, s)))
+def test_statistics_of_the_output(s):
+    """The next layer's statistics from the sums that the convolution leaves."""
+    print("case split operands, statistics", s, flush=True)
+    x, w, _ = draw(s)
+    N, H, W, ci, co, R = s
+    first, second = shape9(s), (N, H, W, co, 64, 1, 1, 1, 0)
+    w2 = torch.randn(1, 1, co, 64, device="cuda") * 0.1
+    descs = []
+    for sh, wt in ((first, w), (second, w2)):
+        c = sh[3]
+        f = torch.zeros
+        descs.append(dict(shape=sh, W=wt, gamma=torch.ones(c, device="cuda"), beta=f(c, device="cuda"),
+                          packed=torch.empty(B.abl_packed_bytes(sh, 4), dtype=torch.uint8, device="cuda"),
+                          stats=torch.empty(32 * c, dtype=torch.uint8, device="cuda"), dW=f(wt.numel(), device="cuda"),
+                          dgamma=f(c, device="cuda"), dbeta=f(c, device="cuda")))
+    layers = B.make_layers(descs)
+    nb = B.abl_stack_buffer_bytes(layers) // 4
+    bs, bt = torch.zeros(nb, device="cuda"), torch.zeros(nb, device="cuda")
+    bs[: x.numel()].copy_(x.view(-1))
+    B.abl_stack_forward(layers, 4, 0, bs, bt, torch.empty(B.abl_stack_scratch_bytes(layers, 4), dtype=torch.uint8, device="cuda"))
+    y = bt[: N * H * W * co].view(-1, co).double()   # the first layer writes the second buffer
+    planes = descs[1]["stats"][: 28 * co].view(torch.float32).view(7, co).double()
+    var = y.var(0, unbiased=False)
+    assert float((planes[0] - y.mean(0)).abs().max()) <= 2.0 ** -23 * float(y.abs().mean(0).max())
+    assert float(((planes[1] - var) / var).abs().max()) <= 2.0 ** -22
+
+
+@pytest.mark.parametrize("s", [SHAPES[1], SHAPES[5], SHAPES[8], SHAPES[10]], ids=lambda s: "x".join(map(str, s)))
+def test_values_the_split_cannot_carry(s):
+    """Infinities, NaN and values that round to an infinite bf16 give what fp32 products and sums give."""
+    print("case split operands, not finite", s, flush=True)
+    x, w, _ = draw(s)
+    x, w = x.abs() + 0.5, w.abs() + 0.01
+    big = 3.4e38
+    w[..., 1] = 2.0 ** -20          # keeps the largest values finite
+    w[..., 2] = 0.0                 # infinity times zero
+    x[0, 0, 0, 5] = float("inf")
+    x[-1, -1, -1, 7] = float("nan")
+    x[x.shape[0] // 2, x.shape[1] // 2, x.shape[2] // 2, 9] = big
+    x[0, -1, 0, 11] = -float("inf")
+    y = torch.empty(*x.shape[:3], s[4], device="cuda")
+    B.abl_conv_fwd(shape9(s), x, w, None, y)
+    ref = conv64(x, w).float()
+    assert torch.equal(torch.isnan(y), torch.isnan(ref))
+    assert torch.equal(torch.isinf(y), torch.isinf(ref))
+    ok = torch.isfinite(ref)
+    assert float(((y - ref)[ok].abs() / ref[ok].abs().clamp(min=1e-30)).max()) < 1e-5   # (positive terms: no cancellation)
