@@ -15,9 +15,11 @@
 //
 // One block = a run of up to 112 consecutive pixels (of one image, or across images where that makes fewer
 // tiles) x 16 NT WN output channels.  Its input patch (the rows of those pixels and the filter's border) is
-// split once, on the way into LDS, CHUNKS 32-channel chunks at a time; a position holds the three
-// parts of a chunk side by side (192 bytes) and positions are padded by 16 bytes, so that the 16-byte
-// fragment reads of 16 neighbouring positions fall into different banks.  Weights go from the L2 straight
+// split once, on the way into LDS, CHUNKS 32-channel chunks at a time.  3x3: every eight channels of a part are a
+// plane of 16 bytes per position, planes multiples of 256 bytes apart: the 16-byte reads of a fragment - 16
+// positions, four planes - then touch every bank once, whichever lanes the LDS serves together (with a position's
+// channels side by side they took twice the cycles; 64 -> 64 @56x56 95 -> 87 us).  1x1: a position's channels side
+// by side, which loads whole lines of the input (1024 -> 256 @14x14 45 us, in planes 48).  Weights go from the L2 straight
 // into registers, one k-step (32 contraction channels of one tap) ahead, and are split there: every wave has
 // output channels of its own, so a block splits nothing twice.  A wave computes 112 pixels x 16 NT channels: 7 NT tiles, 12 NT reads and 42 NT MFMAs per k-step.
 // KS = 2: the chunks of a phase go to two groups of waves whose sums meet in LDS at the end - two waves per
@@ -93,11 +95,11 @@ __device__ inline float exact_output(const float* in, const float* wgt, int H, i
   float s = 0.0f;
   for (int tap = 0; tap < TAPS; ++tap) {
     const int hi = h + (TAPS == 9 ? tap / 3 - 1 : 0), wi = w + (TAPS == 9 ? tap % 3 - 1 : 0);
-    if (hi < 0 || hi >= H || wi < 0 || wi >= W) continue;
-    const float* a = in + ((size_t)(img * H + hi) * W + wi) * Cg;
+    const bool in_image = hi >= 0 && hi < H && wi >= 0 && wi < W;   // (the border's zeros take part)
+    const float* a = in + (in_image ? ((size_t)(img * H + hi) * W + wi) * Cg : 0);
     const float* b = MODE == 0 ? wgt + (size_t)tap * Cin * Cout + n : wgt + ((size_t)(TAPS - 1 - tap) * Cin + n) * Cout;
     for (int c = 0; c < Cg; ++c) {
-      s = fmaf(a[c], MODE == 0 ? b[(size_t)c * Cout] : b[c], s);
+      s = fmaf(in_image ? a[c] : 0.0f, MODE == 0 ? b[(size_t)c * Cout] : b[c], s);
       if (s != s) return s;
     }
   }
@@ -113,13 +115,18 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
                                                                           double* __restrict__ sums,
                                                                           const uint8_t* __restrict__ codes,
                                                                           const float* __restrict__ stats, ConvGeom g,
-                                                                          Tiling tl, int bufsz) {
+                                                                          Tiling tl) {
   constexpr int THREADS = 64 * WN * KS;
   constexpr int CHUNKS = KS * CPP, CH = 32 * CHUNKS;   // per phase
-  constexpr int PITCH = 192 * CHUNKS + 16;             // bytes per patch position
   constexpr int BN = 16 * NT * WN;
   constexpr bool DB = KS > 1;
   constexpr int C8 = CH / 8;                           // staging items per position
+  // the patch: bytes from a position, eight channels, a part and a chunk to the next
+  constexpr int NPOS = SU * THREADS / C8;
+  constexpr int POS_B = TAPS == 9 ? 16 : 192 * CHUNKS + 16, C8_B = TAPS == 9 ? 16 * NPOS : 16;
+  constexpr int PART_B = 4 * C8_B, CHUNK_B = 12 * C8_B;
+  constexpr int bufsz = TAPS == 9 ? CHUNKS * CHUNK_B : NPOS * POS_B;
+  static_assert(TAPS == 1 || C8_B % 256 == 0, "planes on the same banks");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   double* const sum_lds = reinterpret_cast<double*>(smem + (DB ? 2 : 1) * bufsz);   // [KS][2][BN]
 
@@ -136,7 +143,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   const int nblk = Ng / BN;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int mb = (slot / nblk) * 8 + xcd;
-  const int n0 = (slot % nblk) * BN + 16 * NT * wn;
+  const int nb = (slot % nblk) * BN, n0 = nb + 16 * NT * wn;
   if (mb >= tl.gm) return;
   const int t_end = min((mb + 1) * tl.per, tl.tiles);
   const int nph = Cg / CH;
@@ -169,42 +176,49 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   if (EPI != 0)
     for (int i = tid; i < KS * 2 * BN; i += THREADS) sum_lds[i] = 0.0;
 
-  for (int t = mb * tl.per; t < t_end; ++t) {
-    // ---- the tile: pixels p0 .. p_end - 1; its patch starts a row above the first of them, in rows of images
-    // padded to H + 2
-    const int p0 = (t / tl.ntr) * tl.unit + (t % tl.ntr) * tl.run;
-    const int p_end = min(min(p0 + tl.run, (t / tl.ntr + 1) * tl.unit), Mg);
-    const int row0 = p0 / W + 2 * (p0 / (H * W));
-    int s_off[SU], l_off[SU];   // staging items: element offset of the item's channels (phase 0), -1 = zeros; LDS offset
+  // ---- staging: per thread SU items of eight channels of a position; the first phase of the next tile is requested
+  // before the epilogue of this one
+  int s_off[SU];   // element offset of the item's channels (phase 0), -1 = zeros
+  float sv[SU][8];
+  auto stage_load = [&](int ph) __attribute__((always_inline)) {
+    const float* src = in + ph * CH;
 #pragma unroll
     for (int u = 0; u < SU; ++u) {
-      int it = tid + THREADS * u;
-      const int last = tl.npos * C8 - 1;
-      it = it < last ? it : last;   // (a thread past the end repeats the last item)
-      const int pos = it / C8, c8 = it % C8;
-      l_off[u] = pos * PITCH + (c8 >> 2) * 192 + (c8 & 3) * 16;
+      const int o = s_off[u] < 0 ? 0 : s_off[u];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const floatx4 v = *reinterpret_cast<const floatx4*>(src + o + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sv[u][4 * q + e] = v[e];
+      }
+    }
+  };
+  // a tile: pixels p0 .. p_end - 1; its patch starts a row above the first of them, in rows of images padded to H + 2
+  auto first_pixel = [&](int t) __attribute__((always_inline)) { return (t / tl.ntr) * tl.unit + (t % tl.ntr) * tl.run; };
+  auto last_pixel = [&](int t) __attribute__((always_inline)) {
+    return min(min(first_pixel(t) + tl.run, (t / tl.ntr + 1) * tl.unit), Mg);
+  };
+  auto first_row = [&](int p0) __attribute__((always_inline)) { return p0 / W + 2 * (p0 / (H * W)); };
+  auto begin_tile = [&](int t) __attribute__((always_inline)) {
+    const int p0 = first_pixel(t), p_end = last_pixel(t), row0 = first_row(p0);
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      const int it = tid + THREADS * u;
+      const int pos = TAPS == 9 ? (it & 15) + 16 * (it / (16 * C8)) : it / C8;
+      const int c8 = TAPS == 9 ? (it >> 4) % C8 : it % C8;
       if (TAPS == 9) {
         const int prow = pos / PW, w = pos - prow * PW - 1;
         const int n = (row0 + prow) / (H + 2), h = row0 + prow - n * (H + 2) - 1;
-        s_off[u] = n < g.N && h >= 0 && h < H && w >= 0 && w < W ? ((n * H + h) * W + w) * Cg + 8 * c8 : -1;
+        s_off[u] = pos < tl.npos && n < g.N && h >= 0 && h < H && w >= 0 && w < W ? ((n * H + h) * W + w) * Cg + 8 * c8 : -1;
       } else {
         s_off[u] = p0 + pos < p_end ? (p0 + pos) * Cg + 8 * c8 : -1;
       }
     }
-    float sv[SU][8];
-    auto stage_load = [&](int ph) __attribute__((always_inline)) {
-      const float* src = in + ph * CH;
-#pragma unroll
-      for (int u = 0; u < SU; ++u) {
-        const int o = s_off[u] < 0 ? 0 : s_off[u];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const floatx4 v = *reinterpret_cast<const floatx4*>(src + o + 4 * q);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) sv[u][4 * q + e] = v[e];
-        }
-      }
-    };
+    stage_load(0);
+  };
+  begin_tile(mb * tl.per);
+  for (int t = mb * tl.per; t < t_end; ++t) {
+    const int p0 = first_pixel(t), p_end = last_pixel(t), row0 = first_row(p0);
     auto stage_store = [&](unsigned char* buf) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < SU; ++u) {
@@ -213,9 +227,13 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
 #pragma unroll
           for (int e = 0; e < 8; ++e) sv[u][e] = s_off[u] < 0 ? 0.0f : sv[u][e];
         split3(sv[u], h, m, l);
-        *reinterpret_cast<bf16x8_t*>(buf + l_off[u]) = h;
-        *reinterpret_cast<bf16x8_t*>(buf + l_off[u] + 64) = m;
-        *reinterpret_cast<bf16x8_t*>(buf + l_off[u] + 128) = l;
+        const int it = tid + THREADS * u;
+        const int pos = TAPS == 9 ? (it & 15) + 16 * (it / (16 * C8)) : it / C8;
+        const int c8 = TAPS == 9 ? (it >> 4) % C8 : it % C8;
+        unsigned char* to = buf + (c8 >> 2) * CHUNK_B + (c8 & 3) * C8_B + pos * POS_B;
+        *reinterpret_cast<bf16x8_t*>(to) = h;
+        *reinterpret_cast<bf16x8_t*>(to + PART_B) = m;
+        *reinterpret_cast<bf16x8_t*>(to + 2 * PART_B) = l;
       }
     };
     int a_base[MT];
@@ -227,7 +245,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         const int row = p / W;
         m = (row + 2 * (row / H) - row0) * PW + p - row * W;
       }
-      a_base[i] = m * PITCH + kg * CPP * 192 + lk * 16;
+      a_base[i] = m * POS_B + kg * CPP * CHUNK_B + lk * C8_B;
     }
 
     floatx4 hi[NT][MT], lo[NT][MT];
@@ -236,8 +254,14 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
 #pragma unroll
       for (int i = 0; i < MT; ++i) hi[j][i] = lo[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+    constexpr int I0 = 4;   // KS = 2: group 0 finishes the first four pixel tiles, group 1 the others
+    // Eq. 6-7: the tile's codes go through LDS in whole 16-byte pieces (loaded where they are used, two bytes per
+    // lane and channel tile, they took half as long as the contraction: 1x1 256 -> 64 @56x56 122 us, without them 88)
+    constexpr int CPR = EPI > 1 ? BN * EPI / 128 : 1;                        // pieces per pixel
+    constexpr int CU = (16 * MT * CPR + THREADS - 1) / THREADS;              // ... per thread
+    constexpr int CPITCH = 16 * CPR + 16;
+    uint4 cq[CU];
     float raw[NT][8];
-    stage_load(0);
     load_w(raw, 0, kg * CPP * 32);
     for (int ph = 0; ph < nph; ++ph) {
       unsigned char* cur = smem + (DB ? (ph & 1) * bufsz : 0);
@@ -245,7 +269,17 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       if (!DB || ph == 0) __syncthreads();
       stage_store(cur);
       __syncthreads();
-      if (ph + 1 < nph) stage_load(ph + 1);
+      if (ph + 1 < nph) {
+        stage_load(ph + 1);
+      } else if constexpr (EPI > 1) {
+        // the epilogue's codes, behind the last k-steps
+        const uint8_t* cs = codes + ((size_t)p0 * Ng + nb) * EPI / 8;
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+          const int it = min(tid + THREADS * u, (p_end - p0) * CPR - 1);
+          cq[u] = *reinterpret_cast<const uint4*>(cs + (uint32_t)(it / CPR * (Ng * EPI / 8) + it % CPR * 16));
+        }
+      }
 #pragma unroll 1
       for (int ks = 0; ks < TAPS * CPP; ++ks) {
         const int cc = ks / TAPS, tap = ks - cc * TAPS;
@@ -260,13 +294,13 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
           const int ncc = nks / TAPS, ntap = nks - ncc * TAPS;
           load_w(raw, ntap, (wrap && !end ? ph + 1 : ph) * CH + (kg * CPP + ncc) * 32);
         }
-        const int off = (TAPS == 9 ? (tap / 3) * PW + tap % 3 : 0) * PITCH + cc * 192;
+        const int off = (TAPS == 9 ? (tap / 3) * PW + tap % 3 : 0) * POS_B + cc * CHUNK_B;
         const unsigned char* ab = cur + off;
         bf16x8_t ah[2], am[2], al[2];
         auto read_a = [&](int set, int i) __attribute__((always_inline)) {
           ah[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i]);
-          am[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + 64);
-          al[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + 128);
+          am[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + PART_B);
+          al[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + 2 * PART_B);
         };
         read_a(0, 0);
 #pragma unroll
@@ -290,15 +324,26 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       }
     }
 
+    if (t + 1 < t_end) begin_tile(t + 1);
     // ---- the lane holds channels n0 + 16 j + 4 lk .. +3 of pixel slot 16 (MT wm + i) + li
     floatx4 v[NT][MT];
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int i = 0; i < MT; ++i) v[j][i] = hi[j][i] + lo[j][i];
-    constexpr int I0 = 4;   // KS = 2: group 0 finishes the first four pixel tiles, group 1 the others
+    static_assert(KS == 1 || 2 * bufsz >= 4 * NT * 1024 * WN * KS, "room for the exchange");
+    unsigned char* const cbuf = smem + (KS == 2 ? 4 * NT * 1024 * WN * KS : 0);
+    static_assert((KS == 2 ? 4 * NT * 1024 * WN * KS : 0) + (EPI > 1 ? 16 * MT * CPITCH : 0) <= (DB ? 2 : 1) * bufsz, "room for the codes");
+    if (KS == 2 || EPI > 1) __syncthreads();      // every wave has finished reading the patch
+    if constexpr (EPI > 1) {
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int it = tid + THREADS * u;
+        if (it < 16 * MT * CPR) *reinterpret_cast<uint4*>(cbuf + it / CPR * CPITCH + it % CPR * 16) = cq[u];
+      }
+      if (KS == 1) __syncthreads();
+    }
     if constexpr (KS == 2) {
-      __syncthreads();      // every wave has finished reading the patch
       unsigned char* dst = smem + (size_t)((wave ^ WN) * I0 * NT) * 1024 + lane * 16;
 #pragma unroll
       for (int j = 0; j < NT; ++j)
@@ -350,20 +395,6 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         }
       }
     }
-    // (before the stores: loads and stores retire in order)
-    uint32_t cw[NT][MT];
-    if constexpr (EPI > 1) {
-#pragma unroll
-      for (int i = 0; i < MT; ++i) {
-        if (KS == 2 && (i < I0) != (kg == 0)) continue;
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          const size_t o = (size_t)(px[i] < 0 ? 0 : px[i]) * Ng + n0 + 16 * j + 4 * lk;
-          if constexpr (EPI == 4) cw[j][i] = *reinterpret_cast<const uint16_t*>(codes + (o >> 1));
-          else cw[j][i] = *reinterpret_cast<const uint32_t*>(codes + o);
-        }
-      }
-    }
     // a pixel's channels one after the other: the two halves of a 128-byte line leave together (64 -> 256
     // channels at 56x56: 60 us, channel tile by channel tile 89 us)
     if (MODE == 0 && skip != nullptr) {
@@ -402,6 +433,11 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       for (int i = 0; i < MT; ++i) {
         if (KS == 2 && (i < I0) != (kg == 0)) continue;
         const bool ok = px[i] >= 0;
+        uint32_t cw = 0;
+        if constexpr (EPI > 1) {
+          const unsigned char* ca = cbuf + (16 * i + li) * CPITCH + (16 * (NT * wn + j) + 4 * lk) * EPI / 8;
+          cw = EPI == 4 ? (uint32_t) * reinterpret_cast<const uint16_t*>(ca) : *reinterpret_cast<const uint32_t*>(ca);
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           if constexpr (EPI == 1) {
@@ -409,7 +445,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
             s1[r] += y;
             s2[r] = __builtin_fma(y, y, s2[r]);
           } else if constexpr (EPI > 1) {
-            const float q = (float)((cw[j][i] >> (EPI * r)) & ((1u << EPI) - 1u)) + offh[r];
+            const float q = (float)((cw >> (EPI * r)) & ((1u << EPI) - 1u)) + offh[r];
             const float da2 = ok && st4[r] * q > 0.0f ? v[j][i][r] : 0.0f;   // Eq. 10, Eq. 6
             s1[r] += (double)da2;
             s2[r] = __builtin_fma((double)q, (double)da2, s2[r]);
@@ -433,7 +469,6 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   }
   if constexpr (EPI != 0) {
     __syncthreads();
-    const int nb = (slot % nblk) * BN;
     for (int c = tid; c < BN; c += THREADS) {
       double t1 = 0.0, t2 = 0.0;
 #pragma unroll
@@ -456,7 +491,7 @@ struct Plan {
   int nt, ks, cpp, su;   // the kernel's parameters
   Tiling tl;
   size_t lds;
-  int bufsz, bn;
+  int bn;
 };
 
 // The configuration with nt, ks for this layer; false where its sizes do not fit.
@@ -466,10 +501,10 @@ bool fit_plan(const ConvGeom& g, int mode, int nt, int ks, Plan& p) {
   p.nt = nt;
   p.ks = ks;
   p.cpp = !k3 && ks == 1 ? 2 : 1;                                // 1x1: two k-steps between barriers
-  p.su = k3 ? (ks == 2 ? (nt == 2 ? 3 : 4) : nt == 2 ? 4 : 7) : ks == 2 ? 2 : 4;   // staging items per thread, at most
+  p.su = k3 ? (ks == 2 ? 3 : nt == 2 ? 4 : 7) : ks == 2 ? 2 : 4;   // staging items per thread, at most
   p.bn = 16 * nt * WN;
   if (Ng % p.bn != 0 || Cg % (32 * ks * p.cpp) != 0) return false;
-  const int threads = 64 * WN * ks, c8 = 4 * ks * p.cpp, pitch = 192 * ks * p.cpp + 16, bm = 16 * MT;
+  const int threads = 64 * WN * ks, c8 = 4 * ks * p.cpp, bm = 16 * MT;
   const int M = g.N * g.H * g.W, HW = g.H * g.W, W = g.W;
   Tiling& t = p.tl;
   if (!k3) {
@@ -508,9 +543,7 @@ bool fit_plan(const ConvGeom& g, int mode, int nt, int ks, Plan& p) {
   if (p.su == 7 && t.npos * c8 <= 4 * threads) p.su = 4;
   t.per = (t.tiles + kMaxPartialBlocks - 1) / kMaxPartialBlocks;   // one row of sums per block
   t.gm = (t.tiles + t.per - 1) / t.per;
-  p.bufsz = t.npos * pitch;
-  if (ks == 2 && p.bufsz < 2 * nt * WN * 1024 * 4) p.bufsz = 2 * nt * WN * 1024 * 4;   // the exchange of the partial sums
-  p.lds = (size_t)p.bufsz * ks + (size_t)ks * 2 * p.bn * sizeof(double);
+  p.lds = (size_t)(k3 ? 48 * p.su * threads : p.su * threads / c8 * (48 * c8 + 16)) * ks + (size_t)ks * 2 * p.bn * sizeof(double);
   return p.lds <= (size_t)160 * 1024;
 }
 
@@ -549,7 +582,7 @@ int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in
     if (epi == 8) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8>;
   }
   if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
-  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, skip, out, sums, codes, stats, g, p.tl, p.bufsz);
+  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, skip, out, sums, codes, stats, g, p.tl);
   return hip_status();
 }
 
@@ -558,7 +591,7 @@ int launch(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, co
            float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
   auto run = [&](auto f) { return f(st, g, p, in, w, skip, out, sums, codes, stats, epi); };
   if (g.R == 3) {
-    if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, 9, 2, 2, 1, 3> : launch_cfg<MODE, 9, 1, 2, 1, 4>);
+    if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, 9, 2, 2, 1, 3> : launch_cfg<MODE, 9, 1, 2, 1, 3>);
     if (p.nt == 2) return run(launch_cfg<MODE, 9, 2, 1, 1, 4>);
     return run(p.su == 4 ? launch_cfg<MODE, 9, 1, 1, 1, 4> : launch_cfg<MODE, 9, 1, 1, 1, 7>);
   }
