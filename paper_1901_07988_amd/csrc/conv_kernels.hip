@@ -853,6 +853,15 @@ int launch_igemm(hipStream_t st, const ConvGeom& g, bool bf16, const float* in, 
     } else {
       ABL_IGEMM(128, 64, 64, 32, 32);
     }
+  } else if (blocks(256, 32) < 512) {  // small grids: a quarter of the pixels per block (3x3 stride 2 16 -> 32 @32x32 N=128,
+    // 128 blocks: layer step 80 us; 512 blocks 74)
+    if (Cg % 32 == 0) {
+      if (Ng > 16) ABL_IGEMM(64, 32, 32, 16, 32);
+      else ABL_IGEMM(64, 16, 16, 16, 32);
+    } else {
+      if (Ng > 16) ABL_IGEMM(64, 32, 32, 16, 16);
+      else ABL_IGEMM(64, 16, 16, 16, 16);
+    }
   } else if (Cg % 32 == 0) {  // 32-channel chunks: whole 128-byte lines per pixel row
     if (Ng > 16) ABL_IGEMM(256, 32, 64, 32, 32);
     else ABL_IGEMM(256, 16, 64, 16, 32);
