@@ -178,6 +178,14 @@ int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, const float* 
 int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
                               const void* packed, const void* stats, float* da3, double* partial);
 
+// Weight gradient of 'same' stride-1 3x3 and 1x1 layers from the codes, dy split into three bf16 parts
+// (wgrad_split.hip; Cin a multiple of 32 - 1x1: 64 - and Cout of 64).  split_wgrad_copies: copies of dW that launch_split_wgrad leaves in dst, at most
+// `room` bytes of them ([copies][R][S][Cin][Cout] floats); 0 = not supported or too small.  bf16: both operands rounded
+// to bf16 instead.
+int split_wgrad_copies(const ConvGeom& g, int K, size_t room);
+int launch_split_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, const void* packed, const float* stats,
+                       const float* dy, float* dst, size_t room);
+
 // ---- fp32 3x3 'same' stride-1 convolutions with the whole image resident in LDS (conv_image.hip) ----
 // Images of up to 208 pixels (14x14, 7x7 ...), 16, 32 or a multiple of 64 contraction channels,
 // output channels a multiple of 64, at most kMaxPartialBlocks images and at least 224 blocks: one
@@ -191,22 +199,15 @@ int launch_image_f32(hipStream_t st, const ConvGeom& g, int mode, const float* i
 int launch_image_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
                               const void* packed, const void* stats, float* da3, double* partial);
 
-// Weight gradient of the same layers (14-pixel-wide images) from the K-bit codes (K = 4 / 8): one
-// block per 32 x 64 tile of (input, output) channels and share of the images, each share leaving
-// its own copy of dW in `copies` ([image_wgrad_copies][R][S][Cin][Cout] floats) for the caller to
-// sum.  image_wgrad_copies returns 0 when the shape is not supported.  bf16: operands rounded to bf16,
-// 16 pixels per MFMA.
+// Copies of dW that the workspace of a 3x3 layer on 14-pixel-wide images has room for (0: the tiled kernel's).
 int image_wgrad_copies(const ConvGeom& g, int K);
-int launch_image_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, const void* packed, const float* stats,
-                       const float* dy, float* copies);
 
-// Weight gradient of a 1x1 stride-1 layer from its K-bit codes with the block's 64 x 256 tile of dW in
-// registers (fp32; Cin a multiple of 64, Cout of 256, N H W of 16).  Each share of the pixels
-// writes its own copy of dW in `copies` ([rows_wgrad_copies][Cin][Cout] floats) for the caller to sum.
-// rows_wgrad_copies returns 0 when the shape is not supported.
-// bf16: operands rounded to bf16 and contracted 32 pixels per MFMA (N H W a multiple of 32).
+// Weight gradient of a 1x1 stride-1 layer from its K-bit codes with operands rounded to bf16 and the block's 64 x 256
+// tile of dW in registers (Cin a multiple of 64, Cout of 256, N H W of 32).  Each share of the pixels writes its own
+// copy of dW in `copies` ([rows_wgrad_copies][Cin][Cout] floats) for the caller to sum.  rows_wgrad_copies returns 0
+// when the shape is not supported; with bf16 = false it counts N H W in multiples of 16 (the workspace's size).
 int rows_wgrad_copies(const ConvGeom& g, int K, bool bf16);
-int launch_rows_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, const void* packed, const float* stats,
+int launch_rows_wgrad(hipStream_t st, const ConvGeom& g, int K, const void* packed, const float* stats,
                       const float* dy, float* copies);
 
 // ---- Eq. 9 / Eq. 10 for one value.  Callers must be compiled with floating-point contraction

@@ -20,10 +20,8 @@
 // and takes the per-channel sums (of y for the next layer's Eq. 1, or Eq. 6-7 from the layer's
 // codes).
 //
-// The file also holds the other kernels built for one block per compute unit with their results in
-// accumulator registers, each described where it is defined: the weight gradient of the same 3x3 layers
-// from the packed codes (image_wgrad_kernel, fp32 or bf16 operands) and the weight gradient of 1x1 layers
-// (rows_wgrad_kernel, rows_wgrad_bf16_kernel).
+// The file also holds another kernel built for one block per compute unit with its results in accumulator
+// registers: the weight gradient of 1x1 layers from the packed codes with bf16 operands (rows_wgrad_bf16_kernel).
 //
 // The MFMAs are written as inline assembly with the accumulator tied to the result: left to the
 // register allocator, some tiles get a result register of their own and are copied back every
@@ -362,318 +360,8 @@ __global__ __launch_bounds__(kThreads, 1) void image_f32_kernel(const float* __r
 }
 
 
-// ---- weight gradient (first half of Eq. 5) of the same layers from the packed codes ----------------
-// dW[tap][ci][co] = sum over images and pixels of A3~[pixel + tap][ci] * dy[pixel][co], A3~ = ReLU of Eq. 10.
-// One block owns a 32 (ci) x 64 (co) tile of all nine taps and a share of the images; per image it
-// dequantizes the tile's 32 channels of the image once into an LDS patch with its zero border (the nine
-// taps are nine offsets into it) and stages the tile's 64 channels of dy beside it.  The contraction
-// index of the MFMAs is the pixel (four per MFMA), the wave owns one 16-channel tile of ci and two of co for all 9
-// taps (18 accumulator tiles), and per 4-pixel step it reads 2 fragments of dy and 9 of the patch
-// - all at one address plus a constant (the image width is a template parameter) - for 18 MFMAs; the
-// fragments of the next step are read while this step's MFMAs run.  The next image's dy and codes are
-// requested at the start of an image's 49 steps and go to LDS after them.  Each share of the images
-// leaves its own copy of dW, summed in a fixed order by the caller's launch.
+// Copies of dW that a layer's workspace has had room for on 14-pixel-wide images (tiles of 32 x 64 channels).
 constexpr int WG_CI = 32, WG_CO = 64;
-constexpr int WG_AP = 4 * WG_CI + 64;   // bytes per patch position: the four pixel groups of a read hit
-constexpr int WG_DP = 4 * WG_CO + 64;   // ... different quarters of the banks (48 resp. 80 words apart)
-
-// BF16: operands rounded to bf16 on their way from LDS to the registers and contracted 16 at a time
-// (v_mfma_f32_16x16x16_bf16); the tiles and the copies are the same.  Here the contraction runs over the
-// positions of the PADDED rows (image width + 2 = 16 = one MFMA step per image row): dy is staged in the
-// same 16-wide rows with zeros in the two border columns, so the patch address of every tap is the
-// step's base plus a constant (no row wrap to track, 0 address instructions per read) and the two
-// products with the border columns vanish.  The patch has one position of margin before and after it
-// for the corner taps of the border columns.
-template <int K, int IW, bool BF16 = false>
-__global__ __launch_bounds__(kThreads, 1) void image_wgrad_kernel(const uint8_t* __restrict__ codes,
-                                                                  const float* __restrict__ stats,
-                                                                  const float* __restrict__ dy,
-                                                                  float* __restrict__ dst, ConvGeom g, int splits) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int PW = IW + 2;
-  const int H = g.H, HW = H * IW;             // HW a multiple of 4
-  unsigned char* const AL = smem + (BF16 ? WG_AP : 0);            // [(H+2) * PW][WG_AP] (BF16: a position of margin on either side)
-  unsigned char* const DL = AL + ((H + 2) * PW + (BF16 ? 1 : 0)) * WG_AP;   // [HW][WG_DP]; BF16: [H * PW][WG_DP]
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int li = lane & 15, lk = lane >> 4;
-  // ids 8 apart share an XCD and its L2: the blocks that stage the same dy (same co tile and share
-  // of the images, different ci tiles) run there
-  const int n_ci = g.Cin / WG_CI, n_co = g.Cout / WG_CO;
-  int ci_blk, pair;
-  if ((n_co * splits) % 8 == 0) {
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    pair = (slot / n_ci) * 8 + xcd;
-    ci_blk = slot % n_ci;
-  } else {
-    pair = blockIdx.x / n_ci;
-    ci_blk = blockIdx.x % n_ci;
-  }
-  const int co_blk = pair % n_co, split = pair / n_co;
-  const int ci0 = ci_blk * WG_CI, co0 = co_blk * WG_CO;
-  const int img_begin = split * g.N / splits, img_end = (split + 1) * g.N / splits;
-
-  // ---- zero border of the patch, once
-  {
-    constexpr int per = WG_AP / 16;
-    const int nz = (2 * PW + 2 * H) * per;
-    for (int i0 = 0; i0 < nz; i0 += kThreads) {
-      const int it = i0 + tid < nz ? i0 + tid : nz - 1;
-      const int bp = it / per, piece = it - bp * per;
-      int pos;
-      if (bp < PW) pos = bp;
-      else if (bp < 2 * PW) pos = (H + 1) * PW + (bp - PW);
-      else pos = (((bp - 2 * PW) >> 1) + 1) * PW + (((bp - 2 * PW) & 1) ? PW - 1 : 0);
-      *reinterpret_cast<uint4*>(AL + pos * WG_AP + piece * 16) = make_uint4(0u, 0u, 0u, 0u);
-    }
-    if constexpr (BF16) {
-      // the two margin positions of the patch and the border columns of dy
-      if (tid < 2 * per)
-        *reinterpret_cast<uint4*>(AL + (tid < per ? -1 : (H + 2) * PW) * WG_AP + (tid % per) * 16) = make_uint4(0u, 0u, 0u, 0u);
-      constexpr int perd = WG_DP / 16;
-      for (int it = tid; it < 2 * H * perd; it += kThreads) {
-        const int bp = it / perd, piece = it - bp * perd;
-        *reinterpret_cast<uint4*>(DL + ((bp >> 1) * PW + ((bp & 1) ? PW - 1 : 0)) * WG_DP + piece * 16) = make_uint4(0u, 0u, 0u, 0u);
-      }
-    }
-  }
-
-  // ---- staging roles.  Codes: the thread dequantizes 8 channels (one 32- or 64-bit word) of pixels
-  // tid/4 + 64 q.  Eq. 10 as one multiply per element: step * ((code - 2^(K-1) + fb) + 0.5) =
-  // step * (code + offh), offh = fb - 2^(K-1) + 0.5 (exact in fp32 while |fb| < 2^22).
-  const int cg = tid & 3, cpix = tid >> 2;
-  constexpr int CQ = 4;                          // pixel rounds: 4 x 64 >= 196
-  float stp[8], offh[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int c = ci0 + 8 * cg + e;
-    stp[e] = stats[P_STEP * g.Cin + c];
-    offh[e] = (float)(reinterpret_cast<const int32_t*>(stats)[P_FB * g.Cin + c] - (1 << (K - 1))) + 0.5f;
-  }
-  constexpr int DU = 13;                         // float4 of dy per thread: 13 x 256 >= 196 x 16
-  floatx4 dyv[DU];
-  uint32_t cw[CQ][K / 4];
-  const int ndy = HW * (WG_CO / 4);
-  auto stage_load = [&](int img) __attribute__((always_inline)) {
-    const float* src = dy + ((size_t)img * HW) * g.Cout + co0;
-#pragma unroll
-    for (int u = 0; u < DU; ++u) {
-      const int f = tid + kThreads * u;
-      const int fi = f < ndy ? f : ndy - 1;   // (a lane past the end repeats the last item)
-      dyv[u] = *reinterpret_cast<const floatx4*>(src + (size_t)(fi >> 4) * g.Cout + 4 * (fi & 15));
-    }
-    const uint8_t* cs = codes + (((size_t)img * HW) * g.Cin + ci0 + 8 * cg) * K / 8;
-#pragma unroll
-    for (int q = 0; q < CQ; ++q) {
-      const int px = cpix + 64 * q;
-      const int pc = px < HW ? px : HW - 1;
-      const uint8_t* a = cs + (size_t)pc * g.Cin * K / 8;
-      if (K == 4) cw[q][0] = *reinterpret_cast<const uint32_t*>(a);
-      else {
-        const uint2 t = *reinterpret_cast<const uint2*>(a);
-        cw[q][0] = t.x;
-        cw[q][K / 4 - 1] = t.y;
-      }
-    }
-  };
-  auto stage_store = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < DU; ++u) {
-      const int f = tid + kThreads * u;
-      const int fi = f < ndy ? f : ndy - 1;
-      int row = fi >> 4;                       // pixel h * IW + w
-      if constexpr (BF16) {                    // ... to position h * PW + w + 1 of the padded rows
-        const int h = (row * (65536 / IW + 1)) >> 16;   // row / IW for row < 4096
-        row += h * (PW - IW) + 1;
-      }
-      *reinterpret_cast<floatx4*>(DL + row * WG_DP + (fi & 15) * 16) = dyv[u];
-    }
-#pragma unroll
-    for (int q = 0; q < CQ; ++q) {
-      const int px = cpix + 64 * q;
-      const int pc = px < HW ? px : HW - 1;
-      const int h = pc / IW, w = pc - h * IW;
-      float v[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t word = cw[q][(e * K) / 32];
-        const uint32_t code = (word >> ((e * K) % 32)) & ((1u << K) - 1u);
-        v[e] = fmaxf(stp[e] * ((float)code + offh[e]), 0.0f);   // Eq. 10, then the ReLU
-      }
-      unsigned char* d = AL + ((h + 1) * PW + w + 1) * WG_AP + cg * 32;
-      *reinterpret_cast<floatx4*>(d) = floatx4{v[0], v[1], v[2], v[3]};
-      *reinterpret_cast<floatx4*>(d + 16) = floatx4{v[4], v[5], v[6], v[7]};
-    }
-  };
-
-  // the wave's tiles: ci tile wc, co tiles 2 wo and 2 wo + 1, all nine taps - 18 MFMAs per step
-  // from 9 + 2 fragments
-  const int wc = wave & 1, wo = wave >> 1;
-  floatx4 acc[9][2];
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int o = 0; o < 2; ++o) acc[t][o] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  // fragments of one 4-pixel step: the lane's pixel is 4 j + lk
-  struct Frag {
-    float d[2];   // dy[pixel][co0 + 16 (2 wo + o) + li]
-    float a[9];   // patch[pixel + tap][ci0 + 16 wc + li]
-  };
-  auto read_a = [&](Frag& f, int t, int abase) __attribute__((always_inline)) {
-    f.a[t] = *reinterpret_cast<const float*>(AL + abase + ((t / 3) * PW + (t % 3)) * WG_AP);
-  };
-  auto read_d = [&](Frag& f, int o, int dbase) __attribute__((always_inline)) {
-    f.d[o] = *reinterpret_cast<const float*>(DL + dbase + o * 64);
-  };
-  // One step: the 18 MFMAs on `cur` with the 11 reads of the next step's fragments spread between
-  // them, one behind every pair of MFMAs.  Measured on 64 x 14 x 14 x 256 -> 256: all reads in a burst
-  // between two steps 143 us, spread like this 136 us, the same reads as six two-address
-  // instructions behind the first six pairs 141 us, no reads at all 120 us - every vector-memory or
-  // vector-ALU instruction between two MFMAs costs the matrix pipe some 9 cycles, so what counts is
-  // their number and an even spread.  The order below is the schedule.
-  auto step = [&](const Frag& cur, Frag& nxt, int abase, int dbase) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-#pragma unroll
-      for (int o = 0; o < 2; ++o)
-        asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(acc[t][o]) : "v"(cur.d[o]), "v"(cur.a[t]));
-      read_a(nxt, t, abase);
-      if (t < 2) read_d(nxt, t, dbase);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  auto mma = [&](const Frag& f) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-      for (int o = 0; o < 2; ++o)
-        asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(acc[t][o]) : "v"(f.d[o]), "v"(f.a[t]));
-  };
-
-  if (img_begin < img_end) stage_load(img_begin);
-  for (int img = img_begin; img < img_end; ++img) {
-    __syncthreads();   // every wave is done with the previous image's patch and dy
-    stage_store();
-    __syncthreads();
-    if (img + 1 < img_end) stage_load(img + 1);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (BF16) {
-      // step j = image row j; the lane's positions are 4 i + lk of the padded row (element i of its operand:
-      // any assignment of the step's 16 positions to the MFMA's 16 k will do, and with this one the four lane
-      // groups of a read are at neighbouring positions - different banks, as in the fp32 loop).  Output
-      // position P of row j reads the patch at P + (tap row) * PW + (tap column) - 1.
-      static_assert(!BF16 || IW + 2 == 16, "one padded row per 16-deep MFMA");
-      struct FragB {
-        shortx4 d[2];   // four positions of dy[.][co0 + 16 (2 wo + o) + li]
-        shortx4 a[9];   // four positions of patch[. + tap][ci0 + 16 wc + li]
-      };
-      auto pack4 = [](float x0, float x1, float x2, float x3) __attribute__((always_inline)) {
-        typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-        const bf16x2_t lo = {(__bf16)x0, (__bf16)x1}, hi = {(__bf16)x2, (__bf16)x3};
-        const uint2 u = make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
-        return __builtin_bit_cast(shortx4, u);
-      };
-      auto read_frag = [&](FragB& f, int abase, int dbase) __attribute__((always_inline)) {
-#pragma unroll
-        for (int o = 0; o < 2; ++o)
-          f.d[o] = pack4(*reinterpret_cast<const float*>(DL + dbase + o * 64),
-                         *reinterpret_cast<const float*>(DL + dbase + 4 * WG_DP + o * 64),
-                         *reinterpret_cast<const float*>(DL + dbase + 8 * WG_DP + o * 64),
-                         *reinterpret_cast<const float*>(DL + dbase + 12 * WG_DP + o * 64));
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-          const int off = ((t / 3) * PW + (t % 3)) * WG_AP;
-          f.a[t] = pack4(*reinterpret_cast<const float*>(AL + abase + off),
-                         *reinterpret_cast<const float*>(AL + abase + 4 * WG_AP + off),
-                         *reinterpret_cast<const float*>(AL + abase + 8 * WG_AP + off),
-                         *reinterpret_cast<const float*>(AL + abase + 12 * WG_AP + off));
-        }
-      };
-      auto mma16 = [&](const FragB& f) __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-          for (int o = 0; o < 2; ++o)
-            acc[t][o] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(f.d[o], f.a[t], acc[t][o], 0, 0, 0);
-      };
-      int abase = (lk - 1) * WG_AP + (16 * wc + li) * 4;
-      int dbase = lk * WG_DP + (32 * wo + li) * 4;
-      FragB f0, f1;
-      read_frag(f0, abase, dbase);
-      for (int j = 0; j + 1 < H; j += 2) {
-        abase += PW * WG_AP;
-        dbase += PW * WG_DP;
-        read_frag(f1, abase, dbase);
-        mma16(f0);
-        // (the last pair of an even count asks for one row past the image: the first row again, never used)
-        const bool more = j + 2 < H;
-        abase = more ? abase + PW * WG_AP : (lk - 1) * WG_AP + (16 * wc + li) * 4;
-        dbase = more ? dbase + PW * WG_DP : lk * WG_DP + (32 * wo + li) * 4;
-        read_frag(f0, abase, dbase);
-        mma16(f1);
-      }
-      if (H & 1) mma16(f0);
-      continue;
-    }
-    // The lane's pixel of step j is 4 j + lk.  Seven steps are 28 pixels = two image rows, so within such a
-    // group the lane's patch positions are seven constants (the row wrap included) and from group to
-    // group everything moves by two rows: one address add per step instead of tracking the column (six
-    // vector instructions per step, each as dear as a third of an MFMA here).  H is even: H / 2 groups.
-    static_assert(BF16 || (2 * IW) % 4 == 0, "two rows are a whole number of steps");
-    constexpr int GS = 2 * IW / 4;   // steps per group: 7
-    int off7[GS];
-#pragma unroll
-    for (int j = 0; j < GS; ++j) {
-      const int p = lk + 4 * j, hh = p >= IW ? 1 : 0;
-      off7[j] = (hh * PW + p - hh * IW) * WG_AP + (16 * wc + li) * 4;
-    }
-    int ag = 0;                                        // the group's first patch row, in bytes
-    int dg = lk * WG_DP + (32 * wo + li) * 4;          // the lane's dy of the group's step 0
-    Frag f0, f1;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) read_a(f0, t, off7[0]);
-#pragma unroll
-    for (int o = 0; o < 2; ++o) read_d(f0, o, dg);
-    // one group: fa holds the fragments of its step 0, the steps take fa, fb, fa, ... and leave the next
-    // group's first fragments in fb (the image's last step asks for address 0 - never used)
-    auto group = [&](Frag& fa, Frag& fb, bool last) __attribute__((always_inline)) {
-#pragma unroll
-      for (int j = 0; j < GS; ++j) {
-        int an, dn;
-        if (j + 1 < GS) {
-          an = ag + off7[j + 1];
-          dn = dg + (j + 1) * 4 * WG_DP;
-        } else {
-          an = last ? 0 : ag + 2 * PW * WG_AP + off7[0];
-          dn = last ? 0 : dg + 2 * IW * WG_DP;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (j & 1) step(fb, fa, an, dn);
-        else step(fa, fb, an, dn);
-      }
-      ag += 2 * PW * WG_AP;
-      dg += 2 * IW * WG_DP;
-    };
-    static_assert(BF16 || GS % 2 == 1, "an odd number of steps: the two fragment sets swap roles from group to group");
-    const int groups = H / 2;
-    for (int grp = 0; grp + 1 < groups; grp += 2) {
-      group(f0, f1, false);
-      group(f1, f0, grp + 2 >= groups);
-    }
-    if (groups & 1) group(f0, f1, true);
-  }
-  // the MFMAs' results are read below by instructions the compiler does not know to depend on a
-  // matrix-core result: more wait states than the longest such hazard
-  asm volatile("s_nop 15\n\ts_nop 15");
-  float* out = dst + (size_t)split * 9 * g.Cin * g.Cout;
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int o = 0; o < 2; ++o)
-      *reinterpret_cast<floatx4*>(out + ((size_t)(t * g.Cin + ci0 + 16 * wc + li)) * g.Cout + co0 + 16 * (2 * wo + o) +
-                                  4 * lk) = acc[t][o];
-}
 
 int image_wgrad_splits(const ConvGeom& g) {
   const int tiles = (g.Cin / WG_CI) * (g.Cout / WG_CO);
@@ -683,194 +371,22 @@ int image_wgrad_splits(const ConvGeom& g) {
   return s < 1 ? 1 : s;
 }
 
-// ---- weight gradient (first half of Eq. 5) of 1x1 stride-1 layers from the packed codes ------------
+// ---- weight gradient (first half of Eq. 5) of 1x1 stride-1 layers from the packed codes, bf16 operands ----
 // dW[ci][co] = sum over the N H W pixels of A3~[pixel][ci] * dy[pixel][co], A3~ = ReLU of Eq. 10: one matrix
-// product whose contraction index is the pixel (four per MFMA).  One block owns a 64 (ci) x 256 (co) tile
-// and a share of the pixels; each wave keeps 64 x 64 of it (16 accumulator tiles) in registers.
-// The rows and columns of an MFMA tile need not be neighbouring channels: lane li supplies, for its pixel,
-// FOUR input channels (4 li .. 4 li + 3: one 16-byte LDS read) and FOUR output channels (4 li .. 4 li + 3
-// of the wave's 64: one 16-byte load of dy straight from global memory, no LDS), and the 4 x 4 register
-// pairs are the 16 MFMAs of a 4-pixel step - 2 operand instructions for 16 MFMAs instead of one 4-byte
-// read per operand register.  Only the dequantized activation goes through LDS (shared by the four waves,
-// dequantized once per block): 16 pixels at a time in two buffers, one 16- or 32-bit code word per thread
-// and chunk, dequantized between the MFMAs of the chunk before.  The step of Eq. 10 is a factor per input
-// channel and is applied to the sums at the end (max(step * x, 0) = step * max(x, 0), step > 0), so a
-// dequantized element costs a convert, an add and a max.  Each share of the pixels leaves its own copy of
-// dW, summed in a fixed order by the caller's launch: the chip's accumulators are 16 copies of a 1024 x 256
-// dW.  (A 128 x 256 tile per block - eight input channels per lane, 32 MFMAs from 3 operand instructions,
-// twice the accumulators and copies - measured 2-5 us slower on every shape tried.)
+// product whose contraction index is the pixel (v_mfma_f32_16x16x32_bf16: 32 pixels per MFMA, a lane supplies eight
+// of them per operand register set).  One block owns a 64 (ci) x 256 (co) tile and a share of the pixels; each wave
+// keeps 64 x 64 of it (16 accumulator tiles) in registers.  The rows and columns of an MFMA tile need not be
+// neighbouring channels: lane li supplies FOUR input channels (4 li .. 4 li + 3) and FOUR output channels (4 li ..
+// 4 li + 3 of the wave's 64), and the 4 x 4 register sets are the 16 MFMAs of a chunk.  Only the dequantized
+// activation goes through LDS, shared by the four waves.  Each share of the pixels leaves its own copy of dW,
+// summed in a fixed order by the caller's launch.  Both operands are rounded to bf16 by the hardware's packed
+// convert, which takes its two inputs from any two registers - so the regrouping from "four channels of one pixel"
+// (what a 16-byte load delivers) to "eight pixels of one channel" (what the MFMA wants) costs nothing beyond the
+// conversion itself: dy goes from eight 16-byte global loads (the lane's eight pixels) through 16 converts into the
+// four operand sets; the activation is dequantized (Eq. 10 with its step, ReLU: the rounded value is that of the
+// tiled bf16 kernel), converted in pairs of neighbouring pixels and written to LDS as [pixel group][e][li][8
+// pixels], from where a lane's operand set e is one 16-byte read.  dy runs four chunks ahead in a ring of 128 registers.
 constexpr int PW_CI = 64, PW_CO = 256, PW_PX = 16;
-
-template <int K>
-__global__ __launch_bounds__(kThreads, 1) void rows_wgrad_kernel(const uint8_t* __restrict__ codes,
-                                                                 const float* __restrict__ stats,
-                                                                 const float* __restrict__ dy,
-                                                                 float* __restrict__ dst, ConvGeom g, int splits) {
-  __shared__ __attribute__((aligned(16))) float AL[2][PW_PX][PW_CI];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int li = lane & 15, lk = lane >> 4;
-  // ids 8 apart share an XCD and its L2: the blocks that read the same dy (same co tile and share of
-  // the pixels, different ci tiles) run there
-  const int n_ci = g.Cin / PW_CI, n_co = g.Cout / PW_CO;
-  int ci_blk, pair;
-  if ((n_co * splits) % 8 == 0) {
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    pair = (slot / n_ci) * 8 + xcd;
-    ci_blk = slot % n_ci;
-  } else {
-    pair = blockIdx.x / n_ci;
-    ci_blk = blockIdx.x % n_ci;
-  }
-  const int co_blk = pair % n_co, split = pair / n_co;
-  const int ci0 = ci_blk * PW_CI, co0 = co_blk * PW_CO + 64 * wave;
-  const int chunks = (int)(((int64_t)g.N * g.H * g.W) / PW_PX);   // N H W is a multiple of 16
-  const int c_begin = (int)((int64_t)split * chunks / splits), c_end = (int)((int64_t)(split + 1) * chunks / splits);
-
-  // ---- staging role: the four channels ci0 + 4 cg .. of pixel px of a chunk.  Eq. 10 without its step:
-  // (code - 2^(K-1) + fb) + 0.5 = code + offh, exact in fp32 while |fb| < 2^22.
-  const int cg = tid & 15, px = tid >> 4;
-  float offh[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    offh[e] = (float)(reinterpret_cast<const int32_t*>(stats)[P_FB * g.Cin + ci0 + 4 * cg + e] - (1 << (K - 1))) + 0.5f;
-  uint32_t c_lane = (uint32_t)((px * g.Cin + ci0 + 4 * cg) * K / 8);
-  const size_t c_chunk = (size_t)PW_PX * g.Cin * K / 8;          // bytes of codes per chunk
-  uint32_t cw[2];                                                 // code words of the chunks of either parity
-  // (a chunk index past the tensor's last one asks for the last one again: never used)
-  auto load_codes = [&](uint32_t& w, int c) __attribute__((always_inline)) {
-    const uint8_t* cb = codes + (size_t)(c < chunks ? c : chunks - 1) * c_chunk;
-    asm volatile("" : "+v"(c_lane));
-    if constexpr (K == 4) w = *reinterpret_cast<const uint16_t*>(cb + c_lane);
-    else w = *reinterpret_cast<const uint32_t*>(cb + c_lane);
-  };
-  float vals[4];
-  uint32_t by[2];   // K = 4: the even and the odd codes of the word, one per byte (a byte converts in one instruction)
-  auto dequant = [&](uint32_t w, int e) __attribute__((always_inline)) {
-    uint32_t code;
-    if constexpr (K == 4) {
-      if (e == 0) {
-        by[0] = w & 0x0F0Fu;
-        by[1] = (w >> 4) & 0x0F0Fu;
-        asm volatile("" : "+v"(by[0]), "+v"(by[1]));   // (kept as they are: not folded back into a field extract per code)
-      }
-      code = (by[e & 1] >> (8 * (e >> 1))) & 0xFFu;
-    } else {
-      code = (w >> (8 * e)) & 0xFFu;
-    }
-    vals[e] = fmaxf((float)code + offh[e], 0.0f);   // Eq. 10 over its step, then the ReLU
-  };
-  auto store_vals = [&](int buf) __attribute__((always_inline)) {
-    *reinterpret_cast<floatx4*>(&AL[buf][px][4 * cg]) = floatx4{vals[0], vals[1], vals[2], vals[3]};
-  };
-
-  // ---- operands of the MFMAs.  dy: the lane's pixel of step s is 4 s + lk, its channels co0 + 4 li ..
-  uint32_t d_lane[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) d_lane[s] = 4u * (uint32_t)((4 * s + lk) * g.Cout + co0 + 4 * li);
-  const size_t d_chunk = (size_t)PW_PX * g.Cout;                 // floats of dy per chunk
-  floatx4 dyr[8];                                                // ring: slot 4 (chunk parity) + s, two chunks ahead
-  auto load_dy = [&](int slot, int c, int s) __attribute__((always_inline)) {
-    const char* db = reinterpret_cast<const char*>(dy + (size_t)(c < chunks ? c : chunks - 1) * d_chunk);
-    asm volatile("" : "+v"(d_lane[s]));
-    dyr[slot] = *reinterpret_cast<const floatx4*>(db + d_lane[s]);
-  };
-  floatx4 af[2];                                                 // two sets taking turns: channels 4 li .. + 3
-  auto read_a = [&](int set, int buf, int s) __attribute__((always_inline)) {
-    af[set] = *reinterpret_cast<const floatx4*>(&AL[buf][4 * s + lk][4 * li]);
-  };
-
-  floatx4 acc[4][4];   // [e][j]: rows = input channels 4 (4 lk + r) + e, column = output channel 4 li + j
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[e][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  // One chunk (four steps of 16 MFMAs) of parity PAR.  Between the MFMAs, one piece behind every group of
-  // four: the reads of the next step's activation fragments, the dequantization of the next chunk (code
-  // words in cw[PAR ^ 1], to buffer PAR ^ 1), the request for the code word of the chunk after that and,
-  // behind a step's last MFMA, the request for dy of the same step two chunks ahead into the slot just
-  // used.  The barrier sits behind step 2: the buffer written here was last read before the previous
-  // chunk's barrier, and step 3 already reads the next chunk's first fragments from it.
-  auto chunk = [&](auto par, int c) __attribute__((always_inline)) {
-    constexpr int PAR = decltype(par)::value;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int cur = s & 1, slot = 4 * PAR + s;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0"
-                       : "+a"(acc[e][j])
-                       : "v"(af[cur][e]), "v"(dyr[slot][j]));
-        if (e == 0) {
-          if (s < 3) read_a(cur ^ 1, PAR, s + 1);
-          else read_a(cur ^ 1, PAR ^ 1, 0);
-        } else if (s == 0) {
-          if (e == 1) load_codes(cw[PAR], c + 2);
-          else dequant(cw[PAR ^ 1], e - 2);           // values 0, 1
-        } else if (s == 1) {
-          if (e >= 2) dequant(cw[PAR ^ 1], e);        // values 2, 3
-        } else if (s == 2) {
-          if (e == 1) store_vals(PAR ^ 1);
-        }
-        if (e == 3) load_dy(slot, c + 2, s);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (s == 2) __syncthreads();
-    }
-  };
-
-  if (c_begin < c_end) {
-    load_codes(cw[0], c_begin);
-    load_codes(cw[1], c_begin + 1);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) load_dy(s, c_begin, s);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) load_dy(4 + s, c_begin + 1, s);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) dequant(cw[0], e);
-    store_vals(0);
-    __syncthreads();
-    read_a(0, 0, 0);
-    const int n = c_end - c_begin;
-    for (int i = 0; i + 1 < n; i += 2) {
-      chunk(std::integral_constant<int, 0>{}, c_begin + i);
-      chunk(std::integral_constant<int, 1>{}, c_begin + i + 1);
-    }
-    // The MFMAs' results are read by instructions the compiler does not know to depend on a matrix-core
-    // result - here already where it copies the accumulators around the conditional last chunk: more wait
-    // states than the longest such hazard, tied to the accumulator written last (every other one is at
-    // least one MFMA, 32 cycles, older), so that no read of it is placed above the wait.
-    asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[3][3]));
-    if (n & 1) chunk(std::integral_constant<int, 0>{}, c_end - 1);
-  }
-  asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[3][3]));
-  float* out = dst + (size_t)split * g.Cin * g.Cout;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int ci = ci0 + 4 * (4 * lk + r);
-    const floatx4 st4 = *reinterpret_cast<const floatx4*>(stats + P_STEP * g.Cin + ci);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float st = st4[e];
-      *reinterpret_cast<floatx4*>(out + (size_t)(ci + e) * g.Cout + co0 + 4 * li) =
-          floatx4{st * acc[e][0][r], st * acc[e][1][r], st * acc[e][2][r], st * acc[e][3][r]};
-    }
-  }
-}
-
-// The same weight gradient with bf16 operands (v_mfma_f32_16x16x32_bf16: 32 pixels per MFMA, a lane
-// supplies eight of them per operand register set).  The tile, the shares and the copies are those of the
-// fp32 kernel; a chunk is 32 pixels = one step of 16 MFMAs.  Both operands are rounded to bf16 by the
-// hardware's packed convert, which takes its two inputs from any two registers - so the regrouping from
-// "four channels of one pixel" (what a 16-byte load delivers) to "eight pixels of one channel" (what
-// the MFMA wants) costs nothing beyond the conversion itself: dy goes from eight 16-byte global loads
-// (the lane's eight pixels) through 16 converts into the four operand sets; the activation is
-// dequantized (Eq. 10 with its step, ReLU: the rounded value is that of the tiled bf16 kernel),
-// converted in pairs of neighbouring pixels and written to LDS as [pixel group][e][li][8 pixels], from
-// where a lane's operand set e is one 16-byte read.  dy runs four chunks ahead in a ring of 128 registers.
 constexpr int PB_PX = 32;
 
 template <int K>
@@ -1110,20 +626,6 @@ int image_wgrad_copies(const ConvGeom& g, int K) {
   return s;
 }
 
-int launch_image_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, const void* packed, const float* stats,
-                       const float* dy, float* copies) {
-  const int s = image_wgrad_copies(g, K);
-  if (s == 0) return ABL_ERR_SHAPE;
-  const size_t lds = bf16 ? (size_t)((g.H + 2) * (g.W + 2) + 2) * WG_AP + (size_t)g.H * (g.W + 2) * WG_DP
-                          : (size_t)(g.H + 2) * (g.W + 2) * WG_AP + (size_t)g.H * g.W * WG_DP;
-  const unsigned grid = (unsigned)(s * (g.Cin / WG_CI) * (g.Cout / WG_CO));
-  auto kern = bf16 ? (K == 4 ? image_wgrad_kernel<4, 14, true> : image_wgrad_kernel<8, 14, true>)
-                   : (K == 4 ? image_wgrad_kernel<4, 14> : image_wgrad_kernel<8, 14>);
-  if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
-  kern<<<grid, kThreads, lds, st>>>(static_cast<const uint8_t*>(packed), stats, dy, copies, g, s);
-  return hip_status();
-}
-
 int rows_wgrad_copies(const ConvGeom& g, int K, bool bf16) {
   if (g.R != 1 || g.S != 1 || g.stride != 1 || g.pad != 0 || (K != 4 && K != 8)) return 0;
   if (g.Cin % PW_CI != 0 || g.Cout % PW_CO != 0) return 0;
@@ -1136,13 +638,12 @@ int rows_wgrad_copies(const ConvGeom& g, int K, bool bf16) {
   return s;
 }
 
-int launch_rows_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, const void* packed, const float* stats,
+int launch_rows_wgrad(hipStream_t st, const ConvGeom& g, int K, const void* packed, const float* stats,
                       const float* dy, float* copies) {
-  const int s = rows_wgrad_copies(g, K, bf16);
+  const int s = rows_wgrad_copies(g, K, true);
   if (s == 0) return ABL_ERR_SHAPE;
   const unsigned grid = (unsigned)(s * (g.Cin / PW_CI) * (g.Cout / PW_CO));
-  auto kern = bf16 ? (K == 4 ? rows_wgrad_bf16_kernel<4> : rows_wgrad_bf16_kernel<8>)
-                   : (K == 4 ? rows_wgrad_kernel<4> : rows_wgrad_kernel<8>);
+  auto kern = K == 4 ? rows_wgrad_bf16_kernel<4> : rows_wgrad_bf16_kernel<8>;
   kern<<<grid, kThreads, 0, st>>>(static_cast<const uint8_t*>(packed), stats, dy, copies, g, s);
   return hip_status();
 }

@@ -1020,23 +1020,11 @@ int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf1
     else naive_wgrad_kernel<32><<<blocks, kThreads, 0, st>>>(pk, sp, dy, dw, g, r32);
     return hip_status();
   }
-  if (K != 32 && use_halo_wgrad(g)) return launch_halo_wgrad(st, g, K, bf16, packed, sp, dy, scratch, dw);
-  // 3x3 layers on 14-pixel-wide images: the image-resident kernel, one copy of dW per share of the images
-  if (const int copies = !relu32 ? image_wgrad_copies(g, K) : 0) {
+  // bf16 operands, 1x1 layers with 64 x 256 channels and more: the kernel that keeps its tile of dW in registers (1024 ->
+  // 256 @14x14 25-28 us, the split kernels' bf16 form 28-29)
+  if (const int copies = bf16 && !relu32 ? rows_wgrad_copies(g, K, bf16) : 0) {
     float* dst = copies == 1 ? dw : static_cast<float*>(scratch);
-    if (int e = launch_image_wgrad(st, g, K, bf16, packed, sp, dy, dst)) return e;
-    const int64_t n = (int64_t)g.R * g.S * g.Cin * g.Cout;
-    if (copies > 1 && defer != nullptr) {
-      *defer = DwSum{dst, copies, n, dw};
-    } else if (copies > 1) {
-      wgrad_reduce_kernel<<<(unsigned)((n + 63) / 64), kThreads, 0, st>>>(dst, copies, n, dw);
-    }
-    return hip_status();
-  }
-  // 1x1 layers with 64 x 256 channels and more: the kernel that keeps its tile of dW in registers
-  if (const int copies = !relu32 ? rows_wgrad_copies(g, K, bf16) : 0) {
-    float* dst = copies == 1 ? dw : static_cast<float*>(scratch);
-    if (int e = launch_rows_wgrad(st, g, K, bf16, packed, sp, dy, dst)) return e;
+    if (int e = launch_rows_wgrad(st, g, K, packed, sp, dy, dst)) return e;
     const int64_t n = (int64_t)g.Cin * g.Cout;
     if (copies > 1 && defer != nullptr) {
       *defer = DwSum{dst, copies, n, dw};
@@ -1045,6 +1033,20 @@ int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf1
     }
     return hip_status();
   }
+  // other 'same' stride-1 3x3 and 1x1 layers (3x3 64 -> 64 @56x56: fp32 177 -> 86 us, bf16 102 -> 55)
+  const size_t part = wgrad_partial_bytes(s);
+  if (const int copies = !relu32 ? split_wgrad_copies(g, K, part) : 0) {
+    float* dst = copies == 1 ? dw : static_cast<float*>(scratch);
+    if (int e = launch_split_wgrad(st, g, K, bf16, packed, sp, dy, dst, part)) return e;
+    const int64_t n = (int64_t)g.R * g.S * g.Cin * g.Cout;
+    if (copies > 1 && defer != nullptr) {
+      *defer = DwSum{dst, copies, n, dw};
+    } else if (copies > 1) {
+      wgrad_reduce_kernel<<<(unsigned)((n + 63) / 64), kThreads, 0, st>>>(dst, copies, n, dw);
+    }
+    return hip_status();
+  }
+  if (K != 32 && use_halo_wgrad(g)) return launch_halo_wgrad(st, g, K, bf16, packed, sp, dy, scratch, dw);
   const WgradPlan p = wgrad_plan(g);
   float* dst = p.split == 1 ? dw : static_cast<float*>(scratch);
   if (p.tm == 64 && p.tn == 128) launch_wgrad_tile<64, 128>(st, g, p, K, bf16, packed, sp, dy, dst, r32);

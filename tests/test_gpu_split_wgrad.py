@@ -1,0 +1,119 @@
+"""Weight gradients from the codes with dy split into three bf16 parts, against 64-bit values: at the edges of their
+tiles and chunks, for codes that reach beyond what one bf16 holds, and for values that the split cannot carry."""
+import pytest
+import torch
+
+from paper_1901_07988_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+# N, H, W, Cin, Cout, R
+SHAPES = [
+    (16, 14, 14, 256, 256, 3),    # chunks of eight and of six rows
+    (9, 7, 7, 512, 512, 3),       # two images to a chunk, the last one of one; one copy per two tiles
+    (40, 8, 8, 64, 192, 3),       # rows of eight: the column of zeros is a group of its own
+    (10, 20, 57, 96, 128, 3),     # an odd width beyond 56
+    (6, 5, 113, 160, 192, 3),     # a row is nearly a chunk
+    (20, 3, 3, 320, 320, 3),      # three images to a chunk
+    (64, 14, 14, 256, 128, 1),    # tiles of 128 x 128
+    (33, 13, 15, 64, 128, 1),     # ... 64 x 128; 6435 pixels: the last chunk is short
+    (33, 13, 15, 128, 64, 1),
+    (57, 11, 13, 192, 64, 1),     # ... 64 x 64
+]
+IDS = ["x".join(map(str, s)) for s in SHAPES]
+
+
+def shape9(s):
+    return s[:5] + (s[5], s[5], 1, (s[5] - 1) // 2)
+
+
+class Layer:
+    """Inputs, codes and 64-bit values of one layer.  beta decides how far the codes reach."""
+
+    def __init__(self, s, K, beta, sign=1.0):
+        N, H, W, ci, co, R = s
+        g = torch.Generator(device="cuda").manual_seed(7)
+        self.s, self.K = s, K
+        x = torch.randn(N, H, W, ci, device="cuda", generator=g)
+        self.dy = torch.randn(N, H, W, co, device="cuda", generator=g)
+        gamma = (torch.rand(ci, device="cuda", generator=g) + 0.5) * sign
+        beta = torch.rand(ci, device="cuda", generator=g) * beta
+        s9, M = shape9(s), N * H * W
+        self.stats = torch.empty(32 * ci, dtype=torch.uint8, device="cuda")
+        self.packed = torch.empty(B.abl_packed_bytes(s9, K), dtype=torch.uint8, device="cuda")
+        scratch = torch.empty(B.abl_bn_scratch_bytes(M, ci), dtype=torch.uint8, device="cuda")
+        a3, self.a2t = torch.empty_like(x), torch.empty_like(x)
+        B.abl_bn_stats(x, M, ci, gamma, beta, K, scratch, self.stats)
+        B.abl_bn_relu_pack(x, M, ci, K, self.stats, a3, self.packed)
+        B.abl_unpack(self.packed, M, ci, K, self.stats, self.a2t)
+
+    def run(self):
+        ci, co, R = self.s[3:]
+        ws = torch.empty(B.abl_wgrad_scratch_bytes(shape9(self.s)), dtype=torch.uint8, device="cuda")
+        dW = torch.full((R, R, ci, co), float("nan"), device="cuda")
+        B.abl_conv_wgrad_packed(shape9(self.s), self.K, self.packed, self.stats, self.dy, ws, dW)
+        return dW
+
+    def ref(self):
+        N, H, W, ci, co, R = self.s
+        pad = (R - 1) // 2
+        p = torch.nn.functional.pad(self.a2t.clamp(min=0).double(), (0, 0, pad, pad, pad, pad))
+        g, dW = self.dy.double().view(-1, co), torch.empty(R, R, ci, co, dtype=torch.float64, device="cuda")
+        for r in range(R):
+            for q in range(R):
+                dW[r, q] = p[:, r:r + H, q:q + W].reshape(-1, ci).t().contiguous() @ g
+        return dW
+
+    def tolerance(self):
+        # exact products; three roundings of 2^-24 per 32 pixels at the magnitude of the running sum, a random walk,
+        # and those of a2t, the copies' sum and the step
+        return 2.0 ** -24 * ((3 * self.s[0] * self.s[1] * self.s[2] / 32) ** 0.5 + 4)
+
+
+def rel(a, b):
+    return float((a.double() - b).norm() / b.norm())
+
+
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("s", SHAPES, ids=IDS)
+def test_weight_gradient(s, K):
+    print("case split weight gradient", s, K, flush=True)
+    layer = Layer(s, K, 0.0)
+    assert rel(layer.run(), layer.ref()) < layer.tolerance()
+
+
+# beta: largest v = 2^K + 2 fb beyond 256 / 511 / 65535 (the last for 8-bit codes only); a negative gamma turns the
+# codes' order round
+@pytest.mark.parametrize("K,beta,sign", [(4, 300.0, 1), (8, 0.5, 1), (8, 30.0, 1), (8, 5000.0, 1), (8, 1.0, -1), (4, 0.5, -1)])
+@pytest.mark.parametrize("s", [SHAPES[0], SHAPES[2], SHAPES[6], SHAPES[7], SHAPES[8]], ids=lambda s: "x".join(map(str, s)))
+def test_codes_beyond_one_part(s, K, beta, sign):
+    print("case split weight gradient, wide codes", s, K, beta, sign, flush=True)
+    layer = Layer(s, K, beta, float(sign))
+    # (a large beta makes the activations nearly constant: their products with dy cancel, by up to beta in the sums)
+    ref, got = layer.ref(), layer.run()
+    scale = float(layer.a2t.clamp(min=0).double().norm()) * float(layer.dy.double().norm())
+    n = layer.s[0] * layer.s[1] * layer.s[2]
+    bound = layer.tolerance() * scale * (ref.numel() / (layer.a2t.shape[-1] * layer.dy.shape[-1]) / n) ** 0.5
+    assert float((got.double() - ref).norm()) < bound * (1 if beta <= 1 else 2)
+
+
+@pytest.mark.parametrize("s", [SHAPES[0], SHAPES[5], SHAPES[6], SHAPES[7]], ids=lambda s: "x".join(map(str, s)))
+def test_values_the_split_cannot_carry(s):
+    """Infinities, NaN and values that round to an infinite bf16 give what fp32 products and sums give."""
+    print("case split weight gradient, not finite", s, flush=True)
+    layer = Layer(s, 4, 0.1)
+    dy = layer.dy
+    dy.abs_()
+    dy[0, 0, 0, 1] = float("inf")
+    dy[-1, -1, -1, 3] = float("nan")
+    dy[0, 1, 1, 5] = -float("inf")
+    dy[..., 6] = 0.0
+    dy[s[0] // 2, 1, 1, 6] = 3.4e38      # alone in its channel: times an activation of less than 1, finite
+    got, ref = layer.run(), layer.ref()
+    big = ref.abs() > 3.3e38             # (within a rounding of the largest value either way)
+    ref = ref.float()
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    fin = ~big & torch.isfinite(ref)
+    assert bool(torch.isinf(got)[torch.isinf(ref)].all()) and bool(torch.isfinite(got)[fin].all())
+    ok = torch.isfinite(ref) & torch.isfinite(got)
+    assert float(((got - ref)[ok].abs() / ref[ok].abs().clamp(min=1e-30)).max()) < 2e-5   # (positive terms)
