@@ -753,7 +753,7 @@ bool make_chunking(const ConvGeom& g, int K, size_t room, Chunking& c) {
   const size_t n = (size_t)9 * g.Cin * g.Cout * sizeof(float);
   int64_t s = 256 / tiles;
   if (s > (int64_t)(room / n)) s = (int64_t)(room / n);
-  if (s > c.chunks / 2) s = c.chunks / 2;
+  if (s > c.chunks) s = c.chunks;
   if (s < 1) s = 1;
   c.splits = (int)s;
   return s * tiles >= 96;
