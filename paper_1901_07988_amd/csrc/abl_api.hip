@@ -174,11 +174,10 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   // once in the fused kernel wins)
   const bool bf16_gemm = bf16 && bf16_gemm_supported(g, 0) && 2 * g.Cout * g.R * g.S >= 512;
   if (K == 32 || naive || bf16_gemm) return 0;
-  // The split-operand kernels have no prologue either: 3x3 layers are faster with the pack pass in front (56x56
-  // 64 -> 64: 118 us against 173; 14x14 256 -> 256: 87 against 135), 1x1 layers from 128 channels on both sides on
-  // (28x28 128 -> 256: 51 against 53.5; 14x14 256 -> 256: 33 against 37; but 56x56 64 -> 256 103 against 96 and
-  // 256 -> 64 185 against 129: there reading x once wins).
-  if (!bf16 && split_conv_blocks(g, 0) > 0 && (g.R > 1 || (s.Cin >= 128 && s.Cout >= 128))) return 0;
+  // Split operands: 1x1 layers from 128 channels on both sides on are faster with the pack pass in front (28x28 128 ->
+  // 256: 51 us against 53.5; 14x14 256 -> 256: 33 against 37; but 56x56 64 -> 256 103 against 96 and 256 -> 64 185
+  // against 129: there reading x once wins).
+  if (!bf16 && g.R == 1 && s.Cin >= 128 && s.Cout >= 128 && split_conv_blocks(g, 0) > 0) return 0;
   // (Not for the small images of the image-resident kernel: the pack pass plus that kernel is
   // faster than the fused one.)
   if (halo_fused_supported(g) && !(!bf16 && image_f32_supported(g, 0))) return 1;
@@ -216,6 +215,11 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
   // 'same' stride-1 convolutions normalise, quantize and pack while they stage their input
   // patch: x is read once and A3 never reaches memory.  (Not when y aliases x: a block would
   // overwrite input pixels that a neighbouring block has not staged yet.)
+  if (const int nb = path == 1 && !bf16 ? split_fused_blocks(g) : 0) {
+    if (int e = launch_split_fwd_fused(st, g, K, x, stats, W, skip, y, packed, out_partial)) return e;
+    if (out_partial != nullptr && out_nb != nullptr) *out_nb = nb;
+    return ABL_OK;
+  }
   if (path == 1) {
     const int tiles = halo_tile_count(g, 0);
     const bool want = out_partial != nullptr && tiles > 0 && tiles <= kMaxPartialBlocks;
@@ -295,7 +299,7 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
   }
   // the split-operand kernels, with the Eq. 6-7 sums in their epilogue
   if (const int nb = K != 32 && !bf16 ? split_conv_blocks(g, 1) : 0) {
-    if (int e = launch_split_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
+    if (int e = launch_split_dgrad_reduce(st, g, K, false, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
     DwSum dwsum;
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nb, dx, dgamma, dbeta,
@@ -446,7 +450,7 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
   if (scratch_bytes < bn_partial_bytes(rows_of(*s), s->Cin)) return ABL_ERR_SCRATCH;
   if (const int nb = !(flags & ABL_MATH_BF16) ? split_conv_blocks(g, 1) : 0) {
     *rows = nb;
-    return launch_split_dgrad_reduce((hipStream_t)stream, g, K, dy, W, packed, stats, da3,
+    return launch_split_dgrad_reduce((hipStream_t)stream, g, K, false, dy, W, packed, stats, da3,
                                      static_cast<double*>(scratch));
   }
   if (!halo_conv_supported(g) && pointwise_supported(g, 1)) {  // 1x1 stride 1: the pointwise kernel's epilogue

@@ -172,10 +172,15 @@ int launch_image_bf16(hipStream_t st, const ConvGeom& g, int mode, const float* 
 // 'same' stride-1 3x3 and 1x1 layers with contraction channels in multiples of 32 (1x1: 64) and output channels
 // in multiples of 64, unless too small.  split_conv_blocks: rows of the sums ([rows][2][C] doubles: of y in mode
 // 0, Eq. 6-7 in launch_split_dgrad_reduce), 0 = not supported.
-int split_conv_blocks(const ConvGeom& g, int mode);
-int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
-                      float* out, double* sums);
-int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
+// bf16: operands rounded to bf16 instead.
+int split_conv_blocks(const ConvGeom& g, int mode, bool bf16 = false);
+int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
+                      const float* skip, float* out, double* sums);
+// The 3x3 forward with Eq. 1-3 and Eq. 9 applied while the patch is staged (fp32 operands, y not x).
+int split_fused_blocks(const ConvGeom& g);
+int launch_split_fwd_fused(hipStream_t st, const ConvGeom& g, int K, const float* x, const void* stats, const float* w,
+                           const float* skip, float* y, void* packed, double* sums);
+int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* dy, const float* w,
                               const void* packed, const void* stats, float* da3, double* partial);
 
 // Weight gradient of 'same' stride-1 3x3 and 1x1 layers from the codes, dy split into three bf16 parts

@@ -931,11 +931,18 @@ int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* 
     if (want) *rows = g.N;
     return launch_image_bf16(st, g, 0, a3, w, skip, y, want ? sums : nullptr);
   }
+  // (3x3 64 -> 64 @56x56 61 -> 53 us, 128 -> 128 @28x28 60 -> 30; 1x1 1024 -> 256 @14x14 31 -> 25, 2048 -> 512 @7x7 53 -> 35;
+  // with 64 output channels per block not faster: 256 -> 64 @56x56 43 against 45)
+  if (const int nb = bf16 && (g.R == 3 || g.Cout % 128 == 0) ? split_conv_blocks(g, 0, true) : 0) {
+    const bool want = sums != nullptr && rows != nullptr;
+    if (want) *rows = nb;
+    return launch_split_conv(st, g, 0, true, a3, w, skip, y, want ? sums : nullptr);
+  }
   if (bf16 && bf16_gemm_supported(g, 0)) return launch_bf16_gemm(st, g, 0, a3, w, skip, y, sums, rows);
   if (const int nb = !bf16 ? split_conv_blocks(g, 0) : 0) {
     const bool want = sums != nullptr && rows != nullptr;
     if (want) *rows = nb;
-    return launch_split_conv(st, g, 0, a3, w, skip, y, want ? sums : nullptr);
+    return launch_split_conv(st, g, 0, false, a3, w, skip, y, want ? sums : nullptr);
   }
   // small images: the whole image resident in LDS, one row of sums per image
   if (!bf16 && image_f32_supported(g, 0)) {
@@ -978,8 +985,13 @@ int launch_conv_dgrad(hipStream_t st, const abl_shape& s, bool bf16, const float
   const ConvGeom g = geom_of(s);
   if (!mfma_ok(g)) return launch_ragged_conv(st, g, 1, dy, w, nullptr, da3);
   if (bf16 && image_bf16_supported(g, 1)) return launch_image_bf16(st, g, 1, dy, w, nullptr, da3, nullptr);
+  // (1x1: from contractions of 1024 channels on, 512 -> 2048 @7x7 44 -> 35 us, 256 -> 1024 @14x14 28 -> 26; shorter ones
+  // write more than they contract, 1024 -> 256 @14x14 27 against 31.  With the Eq. 6-7 sums the split kernels are the
+  // faster ones throughout)
+  if (bf16 && (g.R == 3 || g.Cout >= 1024) && split_conv_blocks(g, 1, true) > 0)
+    return launch_split_conv(st, g, 1, true, dy, w, nullptr, da3, nullptr);
   if (bf16 && bf16_gemm_supported(g, 1)) return launch_bf16_gemm(st, g, 1, dy, w, nullptr, da3);
-  if (!bf16 && split_conv_blocks(g, 1) > 0) return launch_split_conv(st, g, 1, dy, w, nullptr, da3, nullptr);
+  if (!bf16 && split_conv_blocks(g, 1) > 0) return launch_split_conv(st, g, 1, false, dy, w, nullptr, da3, nullptr);
   if (!bf16 && image_f32_supported(g, 1)) return launch_image_f32(st, g, 1, dy, w, nullptr, da3, nullptr);
   if (halo_conv_supported(g)) return launch_halo_conv(st, g, 1, bf16, dy, w, nullptr, da3);
   if (pointwise_supported(g, 1)) return launch_pointwise_conv(st, g, 1, bf16, dy, w, nullptr, da3);

@@ -25,6 +25,7 @@
 // KS = 2: the chunks of a phase go to two groups of waves whose sums meet in LDS at the end - two waves per
 // SIMD also where a layer gives only one block per compute unit - and the patch has two buffers.
 // KS = 1: one buffer, two blocks per compute unit cover each other's staging.
+// With bf16 operands (ABL_MATH_BF16) the same kernel runs with one part per operand: rounded once, one product.
 #include <mutex>
 #include <set>
 #include <utility>
@@ -86,9 +87,9 @@ __device__ inline void split3(const float (&x)[8], bf16x8_t& h, bf16x8_t& m, bf1
 }
 
 // One output in fp32 from the operands themselves, for values that are not finite.
-template <int MODE, int TAPS>
-__device__ inline float exact_output(const float* in, const float* wgt, int H, int W, int Cin, int Cout, int p,
-                                            int n) {
+template <int MODE, int TAPS, int FUSE>
+__device__ inline float exact_output(const float* in, const float* wgt, const float* stats, int H, int W, int Cin, int Cout,
+                                     int p, int n) {
   const int Cg = MODE == 0 ? Cin : Cout;
   const int HW = H * W;
   const int img = p / HW, h = (p - img * HW) / W, w = p - img * HW - h * W;
@@ -99,7 +100,13 @@ __device__ inline float exact_output(const float* in, const float* wgt, int H, i
     const float* a = in + (in_image ? ((size_t)(img * H + hi) * W + wi) * Cg : 0);
     const float* b = MODE == 0 ? wgt + (size_t)tap * Cin * Cout + n : wgt + ((size_t)(TAPS - 1 - tap) * Cin + n) * Cout;
     for (int c = 0; c < Cg; ++c) {
-      s = fmaf(in_image ? a[c] : 0.0f, MODE == 0 ? b[(size_t)c * Cout] : b[c], s);
+      float x = in_image ? a[c] : 0.0f;
+      if (FUSE != 0 && in_image) {   // Eq. 1-3
+        const float a1 = (x - stats[P_MEAN * Cin + c]) * stats[P_RSTD * Cin + c];
+        const float a2 = stats[P_GAMMA * Cin + c] * a1 + stats[P_BETA * Cin + c];
+        x = a2 > 0.0f ? a2 : 0.0f;
+      }
+      s = fmaf(x, MODE == 0 ? b[(size_t)c * Cout] : b[c], s);
       if (s != s) return s;
     }
   }
@@ -108,14 +115,29 @@ __device__ inline float exact_output(const float* in, const float* wgt, int H, i
 
 // EPI: 0 none; 1 = sums of y and y^2 per channel (first pass of the next layer's Eq. 1); 4 / 8 = the Eq. 6-7
 // sums from the layer's K-bit codes.  Row blockIdx of sums: [gm][2][Ng] doubles.
-template <int MODE, int TAPS, int NT, int KS, int CPP, int SU, int EPI>
+// Bytes of LDS of a block besides its sums: the patch (KS of them), later the exchange of the groups' sums and the codes.
+__host__ __device__ constexpr int patch_bytes(int taps, int ks, int cpp, int su, int np) {
+  const int c8 = 4 * ks * cpp, npos = su * 64 * WN * ks / c8;
+  return taps == 9 ? 16 * np * c8 * npos : npos * (16 * np * c8 + 16);
+}
+__host__ __device__ constexpr int exchange_bytes(int nt, int ks) { return ks == 2 ? 4 * nt * 1024 * WN * ks : 0; }
+__host__ __device__ constexpr int area_bytes(int taps, int nt, int ks, int cpp, int su, int np) {
+  const int a = ks * patch_bytes(taps, ks, cpp, su, np);
+  const int b = exchange_bytes(nt, ks) + 16 * MT * (16 * nt * WN + 16);   // (8-bit codes: a byte per channel)
+  return a > b ? a : b;
+}
+
+// NP = 3: operands in three parts, as above; NP = 1: rounded to bf16.
+// FUSE = K (4 or 8, 3x3 forward): `in` is the layer input x; Eq. 1-3 are applied on the way into LDS and the K-bit codes of
+// the block's own pixels written to `packed` (the blocks along the output channels take turns over the phases).
+template <int MODE, int TAPS, int NT, int KS, int CPP, int SU, int EPI, int NP, int FUSE = 0>
 __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float* __restrict__ in,
                                                                           const float* __restrict__ wgt,
                                                                           const float* skip, float* out,
                                                                           double* __restrict__ sums,
                                                                           const uint8_t* __restrict__ codes,
                                                                           const float* __restrict__ stats, ConvGeom g,
-                                                                          Tiling tl) {
+                                                                          Tiling tl, uint8_t* packed, int pack_pad) {
   constexpr int THREADS = 64 * WN * KS;
   constexpr int CHUNKS = KS * CPP, CH = 32 * CHUNKS;   // per phase
   constexpr int BN = 16 * NT * WN;
@@ -123,12 +145,12 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   constexpr int C8 = CH / 8;                           // staging items per position
   // the patch: bytes from a position, eight channels, a part and a chunk to the next
   constexpr int NPOS = SU * THREADS / C8;
-  constexpr int POS_B = TAPS == 9 ? 16 : 192 * CHUNKS + 16, C8_B = TAPS == 9 ? 16 * NPOS : 16;
-  constexpr int PART_B = 4 * C8_B, CHUNK_B = 12 * C8_B;
-  constexpr int bufsz = TAPS == 9 ? CHUNKS * CHUNK_B : NPOS * POS_B;
+  constexpr int POS_B = TAPS == 9 ? 16 : 64 * NP * CHUNKS + 16, C8_B = TAPS == 9 ? 16 * NPOS : 16;
+  constexpr int PART_B = 4 * C8_B, CHUNK_B = 4 * NP * C8_B;
+  constexpr int bufsz = patch_bytes(TAPS, KS, CPP, SU, NP);
   static_assert(TAPS == 1 || C8_B % 256 == 0, "planes on the same banks");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  double* const sum_lds = reinterpret_cast<double*>(smem + (DB ? 2 : 1) * bufsz);   // [KS][2][BN]
+  double* const sum_lds = reinterpret_cast<double*>(smem + area_bytes(TAPS, NT, KS, CPP, SU, NP));   // [KS][2][BN]
 
   const int Cg = MODE == 0 ? g.Cin : g.Cout;
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
@@ -173,12 +195,15 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     }
   };
 
+  if (FUSE != 0 && blockIdx.x == 0 && tid < pack_pad)   // the tail of the store's last 128-byte row
+    packed[((int64_t)Mg * Cg * FUSE) / 8 + tid] = 0;
   if (EPI != 0)
     for (int i = tid; i < KS * 2 * BN; i += THREADS) sum_lds[i] = 0.0;
 
   // ---- staging: per thread SU items of eight channels of a position; the first phase of the next tile is requested
   // before the epilogue of this one
   int s_off[SU];   // element offset of the item's channels (phase 0), -1 = zeros
+  uint32_t own = 0;   // (FUSE) items whose position is a pixel of the tile
   float sv[SU][8];
   auto stage_load = [&](int ph) __attribute__((always_inline)) {
     const float* src = in + ph * CH;
@@ -201,6 +226,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   auto first_row = [&](int p0) __attribute__((always_inline)) { return p0 / W + 2 * (p0 / (H * W)); };
   auto begin_tile = [&](int t) __attribute__((always_inline)) {
     const int p0 = first_pixel(t), p_end = last_pixel(t), row0 = first_row(p0);
+    own = 0;
 #pragma unroll
     for (int u = 0; u < SU; ++u) {
       const int it = tid + THREADS * u;
@@ -210,6 +236,10 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         const int prow = pos / PW, w = pos - prow * PW - 1;
         const int n = (row0 + prow) / (H + 2), h = row0 + prow - n * (H + 2) - 1;
         s_off[u] = pos < tl.npos && n < g.N && h >= 0 && h < H && w >= 0 && w < W ? ((n * H + h) * W + w) * Cg + 8 * c8 : -1;
+        if constexpr (FUSE != 0) {
+          const int p = (n * H + h) * W + w;
+          own |= s_off[u] >= 0 && p >= p0 && p < p_end ? 1u << u : 0u;
+        }
       } else {
         s_off[u] = p0 + pos < p_end ? (p0 + pos) * Cg + 8 * c8 : -1;
       }
@@ -219,21 +249,67 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   begin_tile(mb * tl.per);
   for (int t = mb * tl.per; t < t_end; ++t) {
     const int p0 = first_pixel(t), p_end = last_pixel(t), row0 = first_row(p0);
-    auto stage_store = [&](unsigned char* buf) __attribute__((always_inline)) {
+    auto stage_store = [&](unsigned char* buf, int ph) __attribute__((always_inline)) {
+      if constexpr (FUSE != 0) {
+        // (a thread's items are the same eight channels of different positions)
+        static_assert(THREADS % (16 * C8) == 0, "one channel group per thread");
+        const int c = ph * CH + 8 * ((tid >> 4) % C8);
+        const bool packs = ph % nblk == slot % nblk;   // block-uniform
+        float mean[8], rstd[8], gm[8], bt[8], cq[8];
+        int32_t fb[8];
+#pragma unroll
+        for (int q = 0; q < 8; q += 4) {
+          const floatx4 m4 = *reinterpret_cast<const floatx4*>(stats + P_MEAN * Cg + c + q);
+          const floatx4 r4 = *reinterpret_cast<const floatx4*>(stats + P_RSTD * Cg + c + q);
+          const floatx4 g4 = *reinterpret_cast<const floatx4*>(stats + P_GAMMA * Cg + c + q);
+          const floatx4 b4 = *reinterpret_cast<const floatx4*>(stats + P_BETA * Cg + c + q);
+          const floatx4 c4 = *reinterpret_cast<const floatx4*>(stats + P_CQ * Cg + c + q);
+          const int4 f4 = *reinterpret_cast<const int4*>(stats + P_FB * Cg + c + q);
+          const int32_t f[4] = {f4.x, f4.y, f4.z, f4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            mean[q + e] = m4[e]; rstd[q + e] = r4[e]; gm[q + e] = g4[e]; bt[q + e] = b4[e]; cq[q + e] = c4[e]; fb[q + e] = f[e];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < SU; ++u) {
+          float a2[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float d = sv[u][e] - mean[e];
+            const float a1 = d * rstd[e];                    // Eq. 1
+            const float t2 = gm[e] * a1;
+            a2[e] = t2 + bt[e];                              // Eq. 2
+            sv[u][e] = a2[e] > 0.0f ? a2[e] : 0.0f;          // Eq. 3 (the border is zeroed below)
+          }
+          if (packs && ((own >> u) & 1u)) {
+            uint32_t word[2] = {0, 0};
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              word[e * FUSE / 32] |= quant_code<FUSE>(a2[e], cq[e], fb[e]) << ((e * FUSE) % 32);   // Eq. 9
+            uint8_t* to = packed + (size_t)(s_off[u] + ph * CH) * FUSE / 8;
+            if (FUSE == 4) *reinterpret_cast<uint32_t*>(to) = word[0];
+            else *reinterpret_cast<uint2*>(to) = make_uint2(word[0], word[1]);
+          }
+        }
+      }
 #pragma unroll
       for (int u = 0; u < SU; ++u) {
-        bf16x8_t h, m, l;
+        bf16x8_t h, m, l;   // (NP = 1: the first only)
         if (TAPS == 9 || s_off[u] < 0)
 #pragma unroll
           for (int e = 0; e < 8; ++e) sv[u][e] = s_off[u] < 0 ? 0.0f : sv[u][e];
-        split3(sv[u], h, m, l);
+        if constexpr (NP == 3) split3(sv[u], h, m, l);
+        else h = to_bf16x8(sv[u]);
         const int it = tid + THREADS * u;
         const int pos = TAPS == 9 ? (it & 15) + 16 * (it / (16 * C8)) : it / C8;
         const int c8 = TAPS == 9 ? (it >> 4) % C8 : it % C8;
         unsigned char* to = buf + (c8 >> 2) * CHUNK_B + (c8 & 3) * C8_B + pos * POS_B;
         *reinterpret_cast<bf16x8_t*>(to) = h;
-        *reinterpret_cast<bf16x8_t*>(to + PART_B) = m;
-        *reinterpret_cast<bf16x8_t*>(to + 2 * PART_B) = l;
+        if constexpr (NP == 3) {
+          *reinterpret_cast<bf16x8_t*>(to + PART_B) = m;
+          *reinterpret_cast<bf16x8_t*>(to + 2 * PART_B) = l;
+        }
       }
     };
     int a_base[MT];
@@ -267,7 +343,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       unsigned char* cur = smem + (DB ? (ph & 1) * bufsz : 0);
       // (two buffers: this one was last read a phase ago, before the barrier that followed)
       if (!DB || ph == 0) __syncthreads();
-      stage_store(cur);
+      stage_store(cur, ph);
       __syncthreads();
       if (ph + 1 < nph) {
         stage_load(ph + 1);
@@ -285,7 +361,10 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         const int cc = ks / TAPS, tap = ks - cc * TAPS;
         bf16x8_t bh[NT], bm[NT], bl[NT];
 #pragma unroll
-        for (int j = 0; j < NT; ++j) split3(raw[j], bh[j], bm[j], bl[j]);
+        for (int j = 0; j < NT; ++j) {
+          if constexpr (NP == 3) split3(raw[j], bh[j], bm[j], bl[j]);
+          else bh[j] = to_bf16x8(raw[j]);
+        }
         // the next k-step's weights (the very last step asks for its own again: no branch)
         {
           const bool wrap = ks + 1 == TAPS * CPP;
@@ -299,8 +378,10 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         bf16x8_t ah[2], am[2], al[2];
         auto read_a = [&](int set, int i) __attribute__((always_inline)) {
           ah[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i]);
-          am[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + PART_B);
-          al[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + 2 * PART_B);
+          if constexpr (NP == 3) {
+            am[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + PART_B);
+            al[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + 2 * PART_B);
+          }
         };
         read_a(0, 0);
 #pragma unroll
@@ -308,10 +389,13 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
           const int c = i & 1;
           if (i + 1 < MT) read_a(c ^ 1, i + 1);
           __builtin_amdgcn_sched_barrier(0);
+          if constexpr (NP == 3) {
 #pragma unroll
           for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[j], ah[c], lo[j][i], 0, 0, 0);
+          }
 #pragma unroll
           for (int j = 0; j < NT; ++j) hi[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], ah[c], hi[j][i], 0, 0, 0);
+          if constexpr (NP == 3) {
 #pragma unroll
           for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], al[c], lo[j][i], 0, 0, 0);
 #pragma unroll
@@ -320,6 +404,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
           for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[j], ah[c], lo[j][i], 0, 0, 0);
 #pragma unroll
           for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], am[c], lo[j][i], 0, 0, 0);
+          }
         }
       }
     }
@@ -330,10 +415,8 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
-      for (int i = 0; i < MT; ++i) v[j][i] = hi[j][i] + lo[j][i];
-    static_assert(KS == 1 || 2 * bufsz >= 4 * NT * 1024 * WN * KS, "room for the exchange");
-    unsigned char* const cbuf = smem + (KS == 2 ? 4 * NT * 1024 * WN * KS : 0);
-    static_assert((KS == 2 ? 4 * NT * 1024 * WN * KS : 0) + (EPI > 1 ? 16 * MT * CPITCH : 0) <= (DB ? 2 : 1) * bufsz, "room for the codes");
+      for (int i = 0; i < MT; ++i) v[j][i] = NP == 3 ? hi[j][i] + lo[j][i] : hi[j][i];
+      unsigned char* const cbuf = smem + exchange_bytes(NT, KS);
     if (KS == 2 || EPI > 1) __syncthreads();      // every wave has finished reading the patch
     if constexpr (EPI > 1) {
 #pragma unroll
@@ -365,7 +448,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       if (px[i] >= p_end) px[i] = -1;
     }
     // outputs that are not finite: again from the fp32 operands, one after the other
-    {
+    if constexpr (NP == 3) {
       float bad = 0.0f;
 #pragma unroll
       for (int j = 0; j < NT; ++j)
@@ -385,7 +468,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
               for (int r = 0; r < 4; ++r)
                 if (e == (j * MT + i) * 4 + r && (KS == 1 || (i < I0) == (kg == 0))) x = v[j][i][r], p = px[i];
           if (fabsf(x) < INFINITY || p < 0) continue;
-          x = exact_output<MODE, TAPS>(in, wgt, H, W, g.Cin, g.Cout, p, n0 + 16 * (e / (4 * MT)) + 4 * lk + (e & 3));
+          x = exact_output<MODE, TAPS, FUSE>(in, wgt, stats, H, W, g.Cin, g.Cout, p, n0 + 16 * (e / (4 * MT)) + 4 * lk + (e & 3));
 #pragma unroll
           for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -495,7 +578,7 @@ struct Plan {
 };
 
 // The configuration with nt, ks for this layer; false where its sizes do not fit.
-bool fit_plan(const ConvGeom& g, int mode, int nt, int ks, Plan& p) {
+bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
   const bool k3 = g.R == 3;
   p.nt = nt;
@@ -543,7 +626,7 @@ bool fit_plan(const ConvGeom& g, int mode, int nt, int ks, Plan& p) {
   if (p.su == 7 && t.npos * c8 <= 4 * threads) p.su = 4;
   t.per = (t.tiles + kMaxPartialBlocks - 1) / kMaxPartialBlocks;   // one row of sums per block
   t.gm = (t.tiles + t.per - 1) / t.per;
-  p.lds = (size_t)(k3 ? 48 * p.su * threads : p.su * threads / c8 * (48 * c8 + 16)) * ks + (size_t)ks * 2 * p.bn * sizeof(double);
+  p.lds = (size_t)area_bytes(k3 ? 9 : 1, nt, ks, p.cpp, p.su, np) + (size_t)ks * 2 * p.bn * sizeof(double);
   return p.lds <= (size_t)160 * 1024;
 }
 
@@ -554,7 +637,7 @@ bool fit_plan(const ConvGeom& g, int mode, int nt, int ks, Plan& p) {
 // 88 / 105 instead of 125 / 160 with 128 channels on 112 blocks.)  Small grids stay on the other kernels, which
 // need no pass of their own for Eq. 1-3 and 9 (3x3 64 -> 64 on 128 images of 8x8, 74 blocks: layer step 69 us
 // against 65).
-bool make_plan(const ConvGeom& g, int mode, Plan& p) {
+bool make_plan(const ConvGeom& g, int mode, int np, Plan& p) {
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
   const bool k3 = g.R == 3 && g.S == 3 && g.pad == 1, k1 = g.R == 1 && g.S == 1 && g.pad == 0;
   if (g.stride != 1 || !(k3 || k1) || Cg % 32 != 0 || Ng % 64 != 0) return false;
@@ -562,64 +645,103 @@ bool make_plan(const ConvGeom& g, int mode, Plan& p) {
   if (M * g.Cin >= ((int64_t)1 << 31) || M * g.Cout >= ((int64_t)1 << 31)) return false;
   for (int nt = 2; nt >= 1; --nt)
     for (int ks = 2; ks >= 1; --ks) {
-      if (!fit_plan(g, mode, nt, ks, p)) continue;
+      if (!fit_plan(g, mode, np, nt, ks, p)) continue;
       const int64_t blocks = (int64_t)p.tl.gm * (Ng / p.bn);
       if (blocks >= (nt == 2 ? 200 : 96) && (ks == 1 || blocks <= 256)) return true;
     }
   return false;
 }
 
-template <int MODE, int TAPS, int NT, int KS, int CPP, int SU>
+template <int MODE, int NP, int TAPS, int NT, int KS, int CPP, int SU>
 int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const float* skip,
                float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
   const unsigned grid = (unsigned)((p.tl.gm + 7) / 8 * 8 * (Ng / p.bn));
-  auto kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 0>;
+  auto kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 0, NP>;
   if constexpr (MODE == 0) {
-    if (epi == 1) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 1>;
+    if (epi == 1) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 1, NP>;
   } else {
-    if (epi == 4) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 4>;
-    if (epi == 8) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8>;
+    if (epi == 4) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 4, NP>;
+    if (epi == 8) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8, NP>;
   }
   if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
-  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, skip, out, sums, codes, stats, g, p.tl);
+  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, skip, out, sums, codes, stats, g, p.tl, nullptr, 0);
   return hip_status();
 }
 
-template <int MODE>
+template <int MODE, int NP>
 int launch(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const float* skip,
            float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
   auto run = [&](auto f) { return f(st, g, p, in, w, skip, out, sums, codes, stats, epi); };
   if (g.R == 3) {
-    if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, 9, 2, 2, 1, 3> : launch_cfg<MODE, 9, 1, 2, 1, 3>);
-    if (p.nt == 2) return run(launch_cfg<MODE, 9, 2, 1, 1, 4>);
-    return run(p.su == 4 ? launch_cfg<MODE, 9, 1, 1, 1, 4> : launch_cfg<MODE, 9, 1, 1, 1, 7>);
+    if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, NP, 9, 2, 2, 1, 3> : launch_cfg<MODE, NP, 9, 1, 2, 1, 3>);
+    if (p.nt == 2) return run(launch_cfg<MODE, NP, 9, 2, 1, 1, 4>);
+    return run(p.su == 4 ? launch_cfg<MODE, NP, 9, 1, 1, 1, 4> : launch_cfg<MODE, NP, 9, 1, 1, 1, 7>);
   }
-  if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, 1, 2, 2, 1, 2> : launch_cfg<MODE, 1, 1, 2, 1, 2>);
-  return run(p.nt == 2 ? launch_cfg<MODE, 1, 2, 1, 2, 4> : launch_cfg<MODE, 1, 1, 1, 2, 4>);
+  if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, NP, 1, 2, 2, 1, 2> : launch_cfg<MODE, NP, 1, 1, 2, 1, 2>);
+  return run(p.nt == 2 ? launch_cfg<MODE, NP, 1, 2, 1, 2, 4> : launch_cfg<MODE, NP, 1, 1, 1, 2, 4>);
+}
+
+template <int FUSE, int KS, int SU>
+int launch_fused(hipStream_t st, const ConvGeom& g, const Plan& p, const float* x, const float* stats, const float* w,
+                 const float* skip, float* y, uint8_t* packed, double* sums) {
+  const unsigned grid = (unsigned)((p.tl.gm + 7) / 8 * 8 * (g.Cout / p.bn));
+  const int64_t raw = (int64_t)g.N * g.H * g.W * g.Cin * FUSE / 8;
+  auto kern = sums != nullptr ? split_conv_kernel<0, 9, 1, KS, 1, SU, 1, 3, FUSE> : split_conv_kernel<0, 9, 1, KS, 1, SU, 0, 3, FUSE>;
+  if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
+  kern<<<grid, 64 * WN * KS, p.lds, st>>>(x, w, skip, y, sums, nullptr, stats, g, p.tl, packed, (int)((raw + 127) / 128 * 128 - raw));
+  return hip_status();
+}
+
+// The fused forward: 64 output channels per block (the constants of Eq. 1-3 take the registers of the second tile).
+bool make_fused_plan(const ConvGeom& g, Plan& p) {
+  return g.R == 3 && make_plan(g, 0, 3, p) && fit_plan(g, 0, 3, 1, 1, p);
 }
 
 }  // namespace
 
-int split_conv_blocks(const ConvGeom& g, int mode) {
+int split_conv_blocks(const ConvGeom& g, int mode, bool bf16) {
   Plan p;
-  return make_plan(g, mode, p) ? p.tl.gm : 0;
+  return make_plan(g, mode, bf16 ? 1 : 3, p) ? p.tl.gm : 0;
 }
 
-int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
-                      float* out, double* sums) {
+int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
+                      const float* skip, float* out, double* sums) {
   Plan p;
-  if (!make_plan(g, mode, p)) return ABL_ERR_SHAPE;
-  if (mode == 0) return launch<0>(st, g, p, in, w, skip, out, sums, nullptr, nullptr, sums != nullptr ? 1 : 0);
-  return launch<1>(st, g, p, in, w, nullptr, out, nullptr, nullptr, nullptr, 0);
+  if (!make_plan(g, mode, bf16 ? 1 : 3, p)) return ABL_ERR_SHAPE;
+  const int epi = sums != nullptr ? 1 : 0;
+  if (mode == 0)
+    return bf16 ? launch<0, 1>(st, g, p, in, w, skip, out, sums, nullptr, nullptr, epi)
+                : launch<0, 3>(st, g, p, in, w, skip, out, sums, nullptr, nullptr, epi);
+  return bf16 ? launch<1, 1>(st, g, p, in, w, nullptr, out, nullptr, nullptr, nullptr, 0)
+              : launch<1, 3>(st, g, p, in, w, nullptr, out, nullptr, nullptr, nullptr, 0);
 }
 
-int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
+int split_fused_blocks(const ConvGeom& g) {
+  Plan p;
+  return make_fused_plan(g, p) ? p.tl.gm : 0;
+}
+
+int launch_split_fwd_fused(hipStream_t st, const ConvGeom& g, int K, const float* x, const void* stats, const float* w,
+                           const float* skip, float* y, void* packed, double* sums) {
+  Plan p;
+  if (!make_fused_plan(g, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
+  const float* sp = static_cast<const float*>(stats);
+  uint8_t* pk = static_cast<uint8_t*>(packed);
+  if (p.su == 4) return K == 4 ? launch_fused<4, 1, 4>(st, g, p, x, sp, w, skip, y, pk, sums)
+                               : launch_fused<8, 1, 4>(st, g, p, x, sp, w, skip, y, pk, sums);
+  return K == 4 ? launch_fused<4, 1, 7>(st, g, p, x, sp, w, skip, y, pk, sums)
+                : launch_fused<8, 1, 7>(st, g, p, x, sp, w, skip, y, pk, sums);
+}
+
+int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* dy, const float* w,
                               const void* packed, const void* stats, float* da3, double* partial) {
   Plan p;
-  if (!make_plan(g, 1, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
-  return launch<1>(st, g, p, dy, w, nullptr, da3, partial, static_cast<const uint8_t*>(packed),
-                   static_cast<const float*>(stats), K);
+  if (!make_plan(g, 1, bf16 ? 1 : 3, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
+  const uint8_t* codes = static_cast<const uint8_t*>(packed);
+  const float* sp = static_cast<const float*>(stats);
+  return bf16 ? launch<1, 1>(st, g, p, dy, w, nullptr, da3, partial, codes, sp, K)
+              : launch<1, 3>(st, g, p, dy, w, nullptr, da3, partial, codes, sp, K);
 }
 
 }  // namespace abl

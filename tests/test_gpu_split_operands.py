@@ -81,6 +81,21 @@ def test_forward_and_gradient(s):
     assert torch.equal(y2, y + dy)   # the shortcut is one fp32 addition
 
 
+@pytest.mark.parametrize("s", SHAPES, ids=IDS)
+def test_bf16_operands(s):
+    """ABL_MATH_BF16: each operand rounded to bf16 once, sums in fp32."""
+    print("case bf16 operands", s, flush=True)
+    x, w, dy = draw(s)
+    R, ci, co = s[5], s[3], s[4]
+    y, da3 = torch.full_like(dy, float("nan")), torch.full_like(x, float("nan"))
+    B.abl_conv_fwd(shape9(s), x, w, None, y, flags=B.ABL_MATH_BF16)
+    B.abl_conv_dgrad(shape9(s), dy, w, da3, flags=B.ABL_MATH_BF16)
+    xr, wr, dr = (t.bfloat16().float() for t in (x, w, dy))
+    # (the other bf16 kernels and the fp32 ones round per 4 to 32 terms)
+    assert rel(y, conv64(xr, wr)) < 3 * tolerance(R * R * ci)
+    assert rel(da3, conv64(dr, grad_weights(wr))) < 3 * tolerance(R * R * co)
+
+
 @pytest.mark.parametrize("K", [4, 8])
 @pytest.mark.parametrize("s", [s for s in SHAPES if s[3] % 64 == 0], ids=lambda s: "x".join(map(str, s)))
 def test_sums_of_the_gradient(s, K):
@@ -156,3 +171,29 @@ def test_values_the_split_cannot_carry(s):
     assert torch.equal(torch.isinf(y), torch.isinf(ref))
     ok = torch.isfinite(ref)
     assert float(((y - ref)[ok].abs() / ref[ok].abs().clamp(min=1e-30)).max()) < 1e-5   # (positive terms: no cancellation)
+
+
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("s", [SHAPES[3], SHAPES[4], SHAPES[5], SHAPES[7], SHAPES[6]], ids=lambda s: "x".join(map(str, s)))
+def test_forward_with_prologue(s, K):
+    """abl_forward where the kernel normalises and packs while it stages: the codes are those of the separate pass bit
+    for bit, the output is the separate pass's convolution up to the order of the sums."""
+    print("case split operands, fused forward", s, K, flush=True)
+    x, w, skip = draw(s)
+    N, H, W, ci, co, R = s
+    s9, M = shape9(s), N * H * W
+    assert B.abl_forward_is_fused(s9, K)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    gamma, beta = torch.rand(ci, device="cuda", generator=g) + 0.5, torch.randn(ci, device="cuda", generator=g) * 0.1
+
+    def raw(n):
+        return torch.full((n,), 0xA5, dtype=torch.uint8, device="cuda")
+
+    scratch = raw(B.abl_scratch_bytes(s9, K))
+    y, packed, stats = torch.full_like(skip, float("nan")), raw(B.abl_packed_bytes(s9, K)), raw(32 * ci)
+    B.abl_forward(s9, K, x, w, gamma, beta, skip, scratch, y, packed, stats)
+    a3, packed2, stats2 = torch.empty_like(x), raw(B.abl_packed_bytes(s9, K)), raw(32 * ci)
+    B.abl_bn_stats(x, M, ci, gamma, beta, K, scratch, stats2)
+    B.abl_bn_relu_pack(x, M, ci, K, stats2, a3, packed2)
+    assert torch.equal(stats, stats2) and torch.equal(packed, packed2)
+    assert rel(y, conv64(a3, w) + skip.double()) < tolerance(R * R * ci)
