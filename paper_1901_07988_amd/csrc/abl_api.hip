@@ -177,7 +177,8 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   // Split operands: 1x1 layers from 128 channels on both sides on are faster with the pack pass in front (28x28 128 ->
   // 256: 51 us against 53.5; 14x14 256 -> 256: 33 against 37; but 56x56 64 -> 256 103 against 96 and 256 -> 64 185
   // against 129: there reading x once wins).
-  if (!bf16 && g.R == 1 && s.Cin >= 128 && s.Cout >= 128 && split_conv_blocks(g, 0) > 0) return 0;
+  // (And with contractions of 512 channels and more: 1024 -> 256 at 14x14 17 + 45 us against 81.)
+  if (!bf16 && g.R == 1 && (s.Cin >= 512 || (s.Cin >= 128 && s.Cout >= 128)) && split_conv_blocks(g, 0) > 0) return 0;
   // (Not for the small images of the image-resident kernel: the pack pass plus that kernel is
   // faster than the fused one.)
   if (halo_fused_supported(g) && !(!bf16 && image_f32_supported(g, 0))) return 1;
@@ -437,6 +438,26 @@ int abl_bn_conv_fwd(void* stream, const abl_shape* s, int K, uint32_t flags, con
                                packed, nullptr);
 }
 
+}  // extern "C"
+
+namespace {
+// Shapes that abl_conv_dgrad_bn_reduce has always taken (the layer calls use the split kernels' sums beyond them): 1x1
+// with at most 256 output channels, or 512 and more in 224 to 2048 blocks of about 200 rows x 64 channels; 3x3 with one
+// row of sums per image or per tile of at most kMaxPartialBlocks.
+bool reduce_stage_accepts(const ConvGeom& g) {
+  if (g.R == 1) {
+    const int64_t M = (int64_t)g.N * g.H * g.W;
+    const int hw = g.H * g.W, rb = hw > 104 && hw <= 208 ? hw : 208;
+    const int64_t nrb = (M + rb - 1) / rb, blocks = nrb * (g.Cin / 64);
+    return g.Cout <= 256 || (g.Cout >= 512 && nrb <= kMaxPartialBlocks && blocks >= 224 && blocks <= 2048);
+  }
+  const int tiles = halo_conv_supported(g) ? halo_tile_count(g, 1) : 0;
+  return image_f32_supported(g, 1) || (tiles > 0 && tiles <= kMaxPartialBlocks);
+}
+}  // namespace
+
+extern "C" {
+
 int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t flags, const float* dy,
                              const float* W, const void* packed, const void* stats, void* scratch,
                              size_t scratch_bytes, float* da3, int32_t* rows) {
@@ -448,7 +469,7 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
     return ABL_ERR_ARG;
   const ConvGeom g = geom_of(*s);
   if (scratch_bytes < bn_partial_bytes(rows_of(*s), s->Cin)) return ABL_ERR_SCRATCH;
-  if (const int nb = !(flags & ABL_MATH_BF16) ? split_conv_blocks(g, 1) : 0) {
+  if (const int nb = !(flags & ABL_MATH_BF16) && reduce_stage_accepts(g) ? split_conv_blocks(g, 1) : 0) {
     *rows = nb;
     return launch_split_dgrad_reduce((hipStream_t)stream, g, K, false, dy, W, packed, stats, da3,
                                      static_cast<double*>(scratch));
