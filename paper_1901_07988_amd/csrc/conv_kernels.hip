@@ -755,7 +755,9 @@ __global__ __launch_bounds__(kThreads) void naive_wgrad_kernel(const uint8_t* __
                                                                const float* __restrict__ dy,
                                                                float* __restrict__ dw, ConvGeom g, int relu32) {
   __shared__ float red[kThreads];
-  int t = blockIdx.x;
+  const int64_t el = block_of_grid();
+  if (el >= (int64_t)g.R * g.S * g.Cin * g.Cout) return;
+  int t = (int)el;
   const int co = t % g.Cout; t /= g.Cout;
   const int ci = t % g.Cin; t /= g.Cin;
   const int s = t % g.S, r = t / g.S;
@@ -788,7 +790,7 @@ __global__ __launch_bounds__(kThreads) void naive_wgrad_kernel(const uint8_t* __
     if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
     __syncthreads();
   }
-  if (threadIdx.x == 0) dw[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) dw[el] = red[0];
 }
 
 inline bool mfma_ok(const ConvGeom& g) { return channels_in_tiles(g); }
@@ -1025,7 +1027,7 @@ int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf1
       if (copies > 1) wgrad_reduce_kernel<<<(unsigned)((n + 63) / 64), kThreads, 0, st>>>(dst, copies, n, dw);
       return hip_status();
     }
-    const unsigned blocks = (unsigned)(g.R * g.S * g.Cin * g.Cout);
+    const dim3 blocks = grid_of((int64_t)g.R * g.S * g.Cin * g.Cout);
     const uint8_t* pk = static_cast<const uint8_t*>(packed);
     if (K == 4) naive_wgrad_kernel<4><<<blocks, kThreads, 0, st>>>(pk, sp, dy, dw, g, 0);
     else if (K == 8) naive_wgrad_kernel<8><<<blocks, kThreads, 0, st>>>(pk, sp, dy, dw, g, 0);

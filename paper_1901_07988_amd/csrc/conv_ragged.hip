@@ -38,12 +38,14 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
   const int Cg = MODE == 0 ? g.Cin : g.Cout;
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
   const int64_t Mg = (int64_t)g.N * Hq * Wq;
-  const int KK = g.R * g.S * Cg;
+  const uint32_t KK = (uint32_t)(g.R * g.S * Cg);   // (at most 2^31 - 1: indexes past it stay unsigned)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int ncol = (Ng + BN - 1) / BN;
-  const int64_t m0 = (int64_t)(blockIdx.x / ncol) * RB_M;
-  const int n0 = (int)(blockIdx.x % ncol) * BN;
+  const int64_t blk = block_of_grid();
+  const int64_t m0 = blk / ncol * RB_M;
+  const int n0 = (int)(blk % ncol) * BN;
+  if (m0 >= Mg) return;
 
   // A: the thread's column of the chunk is fixed (tid % 32), its rows are tid / 32 + 8 i
   const int a_k = tid & (RB_K - 1), a_row = tid >> 5;
@@ -60,9 +62,9 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
     a_w[i] = MODE == 0 ? wq * g.stride - g.pad : wq + g.pad;
   }
   float ra[A_N], rb[B_N];
-  auto fetch = [&](int k0) __attribute__((always_inline)) {
-    const int kk = k0 + a_k;
-    const int tap = kk / Cg, c = kk - tap * Cg;
+  auto fetch = [&](uint32_t k0) __attribute__((always_inline)) {
+    const uint32_t kk = k0 + a_k;
+    const int tap = (int)(kk / (uint32_t)Cg), c = (int)(kk - (uint32_t)tap * Cg);
     const int r = tap / g.S, s = tap - r * g.S;
 #pragma unroll
     for (int i = 0; i < A_N; ++i) {
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
         if (STRIDED) ok = ok && hh >= 0 && ww >= 0 && hi * g.stride == hh && wi * g.stride == ww;
       }
       ok = ok && hi >= 0 && hi < Hi && wi >= 0 && wi < Wi;
-      const uint32_t o = (uint32_t)((a_base[i] + hi * Wi + wi) * Cg + c);   // (tensors have fewer than 2^31 elements)
+      const uint32_t o = ((uint32_t)a_base[i] + (uint32_t)hi * Wi + wi) * Cg + c;   // (tensors have fewer than 2^31 elements)
       const float v = in[ok ? o : 0u];
       ra[i] = ok ? v : 0.f;
     }
@@ -87,9 +89,9 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
       // forward: lanes along the output channel (contiguous in W); gradient: along the contraction
       const int idx = tid + kThreads * j;
       const int n = MODE == 0 ? idx % BN : idx / RB_K;
-      const int kb = MODE == 0 ? k0 + idx / BN : kk;   // (idx % RB_K is the thread's own column)
+      const uint32_t kb = MODE == 0 ? k0 + idx / BN : kk;   // (idx % RB_K is the thread's own column)
       const bool ok = kb < KK && n0 + n < Ng;
-      const uint32_t o = (uint32_t)(MODE == 0 ? kb * g.Cout + n0 + n : (tap * g.Cin + n0 + n) * g.Cout + c);
+      const uint32_t o = MODE == 0 ? kb * g.Cout + n0 + n : ((uint32_t)tap * g.Cin + n0 + n) * g.Cout + c;
       const float v = wgt[ok ? o : 0u];
       rb[j] = ok ? v : 0.f;
     }
@@ -110,11 +112,11 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
   floatx4 acc[2][NT][1];
 #pragma unroll
   for (int j = 0; j < NT; ++j) acc[0][j][0] = acc[1][j][0] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int chunks = (KK + RB_K - 1) / RB_K;
+  const uint32_t chunks = (KK + RB_K - 1) / RB_K;
   fetch(0);
   stage(0);
   __syncthreads();
-  for (int it = 0; it < chunks; ++it) {
+  for (uint32_t it = 0; it < chunks; ++it) {
     const int cur = it & 1;
     if (it + 1 < chunks) fetch((it + 1) * RB_K);
 #pragma unroll
@@ -171,16 +173,19 @@ __global__ __launch_bounds__(kThreads) void ragged_wgrad_kernel(const uint8_t* _
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   const int MR = g.R * g.S * g.Cin;
-  const int ncol = (g.Cout + BN - 1) / BN, nrow = (MR + RB_M - 1) / RB_M;
-  const int part = blockIdx.x / (ncol * nrow), tile = blockIdx.x - part * (ncol * nrow);
-  const int m0 = (tile / ncol) * RB_M, n0 = (tile % ncol) * BN;
+  const int ncol = (g.Cout + BN - 1) / BN, nrow = (int)(((uint32_t)MR + RB_M - 1) / RB_M);
+  const int64_t blk = block_of_grid();
+  const int part = (int)(blk / (ncol * nrow)), tile = (int)(blk - (int64_t)part * (ncol * nrow));
+  if (part >= split) return;
+  const uint32_t m0 = (uint32_t)(tile / ncol) * RB_M;
+  const int n0 = (tile % ncol) * BN;
   const int c_begin = (int)((int64_t)part * chunks / split), c_end = (int)((int64_t)(part + 1) * chunks / split);
   const int Mg = g.N * g.Ho * g.Wo;   // at most 2^31 - 1; pixel numbers past it wrap to negative ones
 
   // the thread's row (tap, ci) is fixed: lane of the block's 64 rows; its pixels are wave + 4 i
-  const int row = m0 + lane;
-  const bool row_ok = row < MR;
-  const int rr = row_ok ? row : 0;
+  const uint32_t row = m0 + lane;
+  const bool row_ok = row < (uint32_t)MR;
+  const int rr = row_ok ? (int)row : 0;
   const int tap = rr / g.Cin, ci = rr - tap * g.Cin;
   const int tr = tap / g.S, ts = tap - tr * g.S;
   const float step = K == 32 ? 0.f : stats[P_STEP * g.Cin + ci];
@@ -250,8 +255,9 @@ __global__ __launch_bounds__(kThreads) void ragged_wgrad_kernel(const uint8_t* _
   for (int j = 0; j < NT; ++j)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int m = m0 + 16 * wave + 4 * lk + r, n = n0 + 16 * j + li;
-      if (m < MR && n < g.Cout) d[(size_t)m * g.Cout + n] = acc[0][j][r] + acc[1][j][r];
+      const uint32_t m = m0 + 16 * wave + 4 * lk + r;
+      const int n = n0 + 16 * j + li;
+      if (m < (uint32_t)MR && n < g.Cout) d[(size_t)m * g.Cout + n] = acc[0][j][r] + acc[1][j][r];
     }
 }
 
@@ -263,7 +269,7 @@ int launch_ragged(hipStream_t st, const ConvGeom& g, const float* in, const floa
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
   const int64_t Mg = MODE == 0 ? (int64_t)g.N * g.Ho * g.Wo : (int64_t)g.N * g.H * g.W;
   const int nt = ragged_nt(Ng);
-  const unsigned grid = (unsigned)(((Mg + RB_M - 1) / RB_M) * ((Ng + 16 * nt - 1) / (16 * nt)));
+  const dim3 grid = grid_of(((Mg + RB_M - 1) / RB_M) * ((Ng + 16 * nt - 1) / (16 * nt)));
   constexpr bool ST = MODE == 1;   // (the forward only multiplies by the stride)
   const bool st1 = !ST || g.stride == 1;
   auto kern = nt == 1 ? (st1 ? ragged_conv_kernel<MODE, 1, false> : ragged_conv_kernel<MODE, 1, ST>)
@@ -276,10 +282,10 @@ int launch_ragged(hipStream_t st, const ConvGeom& g, const float* in, const floa
 
 template <int K>
 void run_ragged_wgrad(hipStream_t st, const ConvGeom& g, const void* packed, const float* stats, const float* dy,
-                      float* dst, int relu32, int chunks, int split, unsigned tiles, int nt) {
+                      float* dst, int relu32, int chunks, int split, int64_t tiles, int nt) {
   auto kern = nt == 1 ? ragged_wgrad_kernel<K, 1> : nt == 2 ? ragged_wgrad_kernel<K, 2>
             : nt == 3 ? ragged_wgrad_kernel<K, 3> : ragged_wgrad_kernel<K, 4>;
-  kern<<<tiles * (unsigned)split, kThreads, 0, st>>>(static_cast<const uint8_t*>(packed), stats, dy, dst, g, relu32,
+  kern<<<grid_of(tiles * split), kThreads, 0, st>>>(static_cast<const uint8_t*>(packed), stats, dy, dst, g, relu32,
                                                      chunks, split, magic_of(g.Wo), magic_of(g.Ho));
 }
 
@@ -310,8 +316,8 @@ int ragged_wgrad_copies(const ConvGeom& g, size_t room) {
 int launch_ragged_wgrad(hipStream_t st, const ConvGeom& g, int K, const void* packed, const float* stats,
                         const float* dy, int copies, float* dst, bool relu32) {
   const int nt = ragged_nt(g.Cout);
-  const int MR = g.R * g.S * g.Cin;
-  const unsigned tiles = (unsigned)(((MR + RB_M - 1) / RB_M) * ((g.Cout + 16 * nt - 1) / (16 * nt)));
+  const int64_t MR = (int64_t)g.R * g.S * g.Cin;
+  const int64_t tiles = ((MR + RB_M - 1) / RB_M) * ((g.Cout + 16 * nt - 1) / (16 * nt));
   const int chunks = (int)(((int64_t)g.N * g.Ho * g.Wo + RB_K - 1) / RB_K);
   const int r32 = relu32 ? 1 : 0;
   if (K == 4) run_ragged_wgrad<4>(st, g, packed, stats, dy, dst, r32, chunks, copies, tiles, nt);

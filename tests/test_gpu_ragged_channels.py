@@ -2,7 +2,9 @@
 edges of their tiles: 64 rows, 16 to 64 columns, 32-deep chunks of the flattened (tap, channel) index, 32-pixel
 chunks and their shares in the weight gradient.  TOL: fp32 products, sums of at most N Ho Wo terms."""
 import pytest
+import torch
 
+from paper_1901_07988_amd import binding as B
 from paper_1901_07988_amd import synth
 from paper_1901_07988_amd.synth import LayerShape
 
@@ -41,3 +43,35 @@ def test_layer_with_any_channel_count(G, oracle, s, K):
     if s.M > 1:   # (one row: the normalized input and its gradient are zero up to rounding)
         for a, b in zip(got, ref):
             assert rel(a, b) < TOL
+
+
+def test_one_channel_with_more_than_2_to_the_30_pixels():
+    """The largest grids: 64 pixels to a block of 256 threads, 2^24 blocks and more."""
+    s = (1, 32768, 32784, 1, 1, 1, 1, 1, 0)
+    print("case ragged layer, one channel", s, flush=True)
+    n = s[1] * s[2]
+    x = torch.arange(n, dtype=torch.int32, device="cuda").bitwise_and_(0xFFFF).to(torch.float32)
+    w, y = torch.full((1,), 3.0, device="cuda"), torch.zeros(n, device="cuda")
+    for call in (lambda: B.abl_conv_fwd(s, x, w, None, y), lambda: B.abl_conv_dgrad(s, x, w, y)):
+        y.zero_()
+        call()
+        for i in range(0, n, 1 << 28):
+            assert torch.equal(y[i:i + (1 << 28)], 3.0 * x[i:i + (1 << 28)])
+
+
+def test_more_than_2_to_the_24_weights():
+    """One block of 256 threads per weight, on the weight gradient without room for copies."""
+    s, K = (1, 4, 520, 4099, 4103, 1, 1, 1, 0), 4
+    print("case ragged layer, many weights", s, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    M, ci, co = s[1] * s[2], s[3], s[4]
+    x, dy = torch.randn(M, ci, device="cuda", generator=g), torch.randn(M, co, device="cuda", generator=g)
+    raw = lambda n: torch.zeros(int(n), dtype=torch.uint8, device="cuda")
+    packed, stats, scratch = raw(B.abl_packed_bytes(s, K)), raw(B.abl_stats_bytes(s)), raw(B.abl_bn_scratch_bytes(M, ci))
+    one, a, dW = torch.ones(ci, device="cuda"), torch.empty_like(x), torch.full((ci, co), float("nan"), device="cuda")
+    B.abl_bn_stats(x, M, ci, one, 0 * one, K, scratch, stats)
+    B.abl_bn_relu_pack(x, M, ci, K, stats, a, packed)
+    B.abl_unpack(packed, M, ci, K, stats, a)
+    B.abl_conv_wgrad_packed(s, K, packed, stats, dy, scratch, dW)
+    ref = a.clamp(min=0).double().t().contiguous() @ dy.double()
+    assert float((dW - ref).abs().max()) <= TOL * float(ref.abs().max())
