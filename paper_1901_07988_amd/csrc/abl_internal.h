@@ -372,12 +372,12 @@ __device__ inline float4 keep_if(bool ok, const float4& v) {
 }
 
 // Grids of one dimension: more than 2^22 blocks go on in y, since a dimension holds fewer than 2^32 work-items (a larger
-// one is cut off without an error).  The last row of blocks may go past the end.
+// one is cut off without an error).  The last row of blocks may go past the end; up to 2^31 blocks in all.
 inline dim3 grid_of(int64_t blocks) {
   const int64_t x = (int64_t)1 << 22;
   return blocks <= x ? dim3((unsigned)blocks) : dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
 }
-__device__ inline int64_t block_of_grid() { return blockIdx.x + (int64_t)gridDim.x * blockIdx.y; }
+__device__ inline uint32_t block_of_grid() { return blockIdx.x + gridDim.x * blockIdx.y; }
 
 inline int hip_status() { return hipGetLastError() == hipSuccess ? ABL_OK : ABL_ERR_HIP; }
 

@@ -755,8 +755,8 @@ __global__ __launch_bounds__(kThreads) void naive_wgrad_kernel(const uint8_t* __
                                                                const float* __restrict__ dy,
                                                                float* __restrict__ dw, ConvGeom g, int relu32) {
   __shared__ float red[kThreads];
-  const int64_t el = block_of_grid();
-  if (el >= (int64_t)g.R * g.S * g.Cin * g.Cout) return;
+  const uint32_t el = block_of_grid();
+  if (el >= (uint32_t)(g.R * g.S * g.Cin * g.Cout)) return;
   int t = (int)el;
   const int co = t % g.Cout; t /= g.Cout;
   const int ci = t % g.Cin; t /= g.Cin;

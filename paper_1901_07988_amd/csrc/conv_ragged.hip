@@ -21,11 +21,43 @@ constexpr int RB_M = 64;    // rows of the output tile per block (16 per wave)
 constexpr int RB_K = 32;    // contraction elements per chunk
 constexpr int RB_LD = 36;   // floats per LDS row of a chunk: 16-byte fragments of 16 rows on different banks
 
+// One output from the positions inside the image alone, for values that are not finite: in the tiles a position outside
+// is a zero, which an infinite weight would turn into a NaN.
+template <int MODE>
+__device__ inline float output_inside(const float* in, const float* wgt, const ConvGeom& g, int p, int n) {
+  const int Hi = MODE == 0 ? g.H : g.Ho, Wi = MODE == 0 ? g.W : g.Wo;
+  const int Hq = MODE == 0 ? g.Ho : g.H, Wq = MODE == 0 ? g.Wo : g.W;
+  const int Cg = MODE == 0 ? g.Cin : g.Cout;
+  const int t = p / Wq, img = t / Hq, wq = p - t * Wq, hq = t - img * Hq;
+  double sum = 0.0;
+  for (int r = 0; r < g.R; ++r)
+    for (int s = 0; s < g.S; ++s) {
+      int hi, wi;
+      if (MODE == 0) {
+        hi = hq * g.stride + r - g.pad;
+        wi = wq * g.stride + s - g.pad;
+      } else {
+        const int hh = hq + g.pad - r, ww = wq + g.pad - s;
+        if (hh < 0 || ww < 0 || hh % g.stride != 0 || ww % g.stride != 0) continue;
+        hi = hh / g.stride;
+        wi = ww / g.stride;
+      }
+      if (hi < 0 || hi >= Hi || wi < 0 || wi >= Wi) continue;
+      const float* a = in + (int64_t)((img * Hi + hi) * Wi + wi) * Cg;
+      const float* b = wgt + (int64_t)(r * g.S + s) * g.Cin * g.Cout + (MODE == 0 ? n : (int64_t)n * g.Cout);
+      for (int c = 0; c < Cg; ++c) {
+        sum += (double)a[c] * (double)b[MODE == 0 ? (int64_t)c * g.Cout : c];
+        if (sum != sum) return (float)sum;
+      }
+    }
+  return (float)sum;
+}
+
 // MODE 0: out[p][co] = sum_{tap, ci} a3[p at tap][ci] W[tap][ci][co] (+ skip)
 // MODE 1: out[p][ci] = sum_{tap, co} dy[p at tap][co] W[tap][ci][co]
 // STRIDED: stride other than 1 (in mode 1 a tap then reaches only every stride-th pixel).
 template <int MODE, int NT, bool STRIDED>
-__global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __restrict__ in,
+__global__ __launch_bounds__(kThreads, NT == 4 || (NT == 3 && MODE == 0) ? 4 : 1) void ragged_conv_kernel(const float* __restrict__ in,
                                                                const float* __restrict__ wgt, const float* skip,
                                                                float* out, ConvGeom g) {
   constexpr int BN = 16 * NT;
@@ -37,13 +69,13 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
   const int Hq = MODE == 0 ? g.Ho : g.H, Wq = MODE == 0 ? g.Wo : g.W;
   const int Cg = MODE == 0 ? g.Cin : g.Cout;
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
-  const int64_t Mg = (int64_t)g.N * Hq * Wq;
+  const uint32_t Mg = (uint32_t)(g.N * Hq * Wq);
   const uint32_t KK = (uint32_t)(g.R * g.S * Cg);   // (at most 2^31 - 1: indexes past it stay unsigned)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int ncol = (Ng + BN - 1) / BN;
-  const int64_t blk = block_of_grid();
-  const int64_t m0 = blk / ncol * RB_M;
+  const uint32_t blk = block_of_grid();
+  const uint32_t m0 = blk / ncol * RB_M;
   const int n0 = (int)(blk % ncol) * BN;
   if (m0 >= Mg) return;
 
@@ -52,7 +84,7 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
   int a_base[A_N], a_h[A_N], a_w[A_N];   // offset of the row's image, position of tap (0, 0); a_h: far outside = no row
 #pragma unroll
   for (int i = 0; i < A_N; ++i) {
-    const int64_t p = m0 + a_row + 8 * i;
+    const uint32_t p = m0 + a_row + 8 * i;
     const bool ok = p < Mg;
     const int pp = ok ? (int)p : 0;
     const int t = pp / Wq, n = t / Hq;
@@ -64,7 +96,7 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
   float ra[A_N], rb[B_N];
   auto fetch = [&](uint32_t k0) __attribute__((always_inline)) {
     const uint32_t kk = k0 + a_k;
-    const int tap = (int)(kk / (uint32_t)Cg), c = (int)(kk - (uint32_t)tap * Cg);
+    const int tap = (int)kk / Cg, c = (int)kk - tap * Cg;   // (not used where kk >= KK)
     const int r = tap / g.S, s = tap - r * g.S;
 #pragma unroll
     for (int i = 0; i < A_N; ++i) {
@@ -130,18 +162,27 @@ __global__ __launch_bounds__(kThreads) void ragged_conv_kernel(const float* __re
     if (it + 1 < chunks) stage(cur ^ 1);   // (the other buffer: its readers passed the barrier of the last chunk)
     __syncthreads();
   }
-  const int64_t p = m0 + 16 * wave + li;
+  const uint32_t p = m0 + 16 * wave + li;
   if (p >= Mg) return;
+  uint32_t odd = 0;   // outputs that are not finite
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int n = n0 + 16 * j + 4 * lk + r;
       if (n >= Ng) continue;
-      const int64_t o = p * Ng + n;
+      const size_t o = (size_t)p * Ng + n;
       const float v = acc[0][j][0][r] + acc[1][j][0][r];
-      out[o] = skip != nullptr ? v + skip[o] : v;
+      const bool fin = fabsf(v) < INFINITY;
+      odd |= fin ? 0u : 1u << (4 * j + r);
+      if (fin) out[o] = skip != nullptr ? v + skip[o] : v;
     }
+  for (; __builtin_expect(odd != 0, 0); odd &= odd - 1) {
+    const int e = __builtin_ctz(odd), n = n0 + 16 * (e >> 2) + 4 * lk + (e & 3);
+    const size_t o = (size_t)p * Ng + n;
+    const float v = output_inside<MODE>(in, wgt, g, (int)p, n);
+    out[o] = skip != nullptr ? v + skip[o] : v;
+  }
 }
 
 // p / d for p < 2^31 with m = floor(2^32 / d) + 1 (d > 1): the high product is the quotient or one more.
@@ -151,6 +192,34 @@ __device__ inline int div_magic(int p, int d, uint32_t m) {
   return (int64_t)q * d > p ? q - 1 : q;
 }
 inline uint32_t magic_of(int d) { return d > 1 ? (uint32_t)((1ull << 32) / (uint32_t)d + 1) : 0u; }
+
+// One sum of the weight gradient over the pixels p_begin .. p_end - 1 that the tap reaches inside the image with an
+// activation that is not zero, for values that are not finite (an infinite dy times a zero of the tile is a NaN).
+template <int K>
+__device__ inline float sum_inside(const uint8_t* packed, const float* stats, const float* dy, const ConvGeom& g,
+                                   int relu32, int tap, int ci, int co, int64_t p_begin, int64_t p_end) {
+  const float step = K == 32 ? 0.f : stats[P_STEP * g.Cin + ci];
+  const int32_t fb = K == 32 ? 0 : reinterpret_cast<const int32_t*>(stats)[P_FB * g.Cin + ci];
+  const int tr = tap / g.S, ts = tap - tr * g.S;
+  double sum = 0.0;
+  for (int64_t p = p_begin; p < p_end; ++p) {
+    const int t = (int)p / g.Wo, n = t / g.Ho;
+    const int wi = ((int)p - t * g.Wo) * g.stride - g.pad + ts, hi = (t - n * g.Ho) * g.stride - g.pad + tr;
+    if (hi < 0 || hi >= g.H || wi < 0 || wi >= g.W) continue;
+    const int64_t e = (int64_t)((n * g.H + hi) * g.W + wi) * g.Cin + ci;
+    float v;
+    if constexpr (K == 32) {
+      v = reinterpret_cast<const float*>(packed)[e];
+      if (relu32 != 0 && v < 0.f) continue;
+    } else {
+      v = dequant<K>(K == 4 ? (packed[e >> 1] >> ((e & 1) * 4)) & 15u : packed[e], step, fb);
+      if (!(v > 0.f)) continue;
+    }
+    sum += (double)v * (double)dy[p * g.Cout + co];
+    if (sum != sum) return (float)sum;
+  }
+  return (float)sum;
+}
 
 // dW[(tap, ci)][co] = sum over output pixels of A3~[p at tap][ci] dy[p][co].  Rows of the tile = flattened
 // (tap, ci), contraction = the pixels of this block's share, 32 per chunk; the shares' copies of dW are
@@ -174,8 +243,8 @@ __global__ __launch_bounds__(kThreads) void ragged_wgrad_kernel(const uint8_t* _
   const int li = lane & 15, lk = lane >> 4;
   const int MR = g.R * g.S * g.Cin;
   const int ncol = (g.Cout + BN - 1) / BN, nrow = (int)(((uint32_t)MR + RB_M - 1) / RB_M);
-  const int64_t blk = block_of_grid();
-  const int part = (int)(blk / (ncol * nrow)), tile = (int)(blk - (int64_t)part * (ncol * nrow));
+  const uint32_t blk = block_of_grid();
+  const int part = (int)(blk / (uint32_t)(ncol * nrow)), tile = (int)(blk - (uint32_t)part * (ncol * nrow));
   if (part >= split) return;
   const uint32_t m0 = (uint32_t)(tile / ncol) * RB_M;
   const int n0 = (tile % ncol) * BN;
@@ -251,14 +320,26 @@ __global__ __launch_bounds__(kThreads) void ragged_wgrad_kernel(const uint8_t* _
     __syncthreads();
   }
   float* d = dst + (size_t)part * MR * g.Cout;
+  uint32_t odd = 0;   // sums that are not finite
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const uint32_t m = m0 + 16 * wave + 4 * lk + r;
       const int n = n0 + 16 * j + li;
-      if (m < (uint32_t)MR && n < g.Cout) d[(size_t)m * g.Cout + n] = acc[0][j][r] + acc[1][j][r];
+      const float v = acc[0][j][r] + acc[1][j][r];
+      if (m < (uint32_t)MR && n < g.Cout) {
+        odd |= fabsf(v) < INFINITY ? 0u : 1u << (4 * j + r);
+        d[(size_t)m * g.Cout + n] = v;
+      }
     }
+  for (; __builtin_expect(odd != 0, 0); odd &= odd - 1) {
+    const int e = __builtin_ctz(odd), n = n0 + 16 * (e >> 2) + li;
+    const uint32_t m = m0 + 16 * wave + 4 * lk + (e & 3);
+    const int64_t p_end = (int64_t)c_end * RB_K;
+    d[(size_t)m * g.Cout + n] = sum_inside<K>(packed, stats, dy, g, relu32, (int)(m / (uint32_t)g.Cin),
+                                              (int)(m % (uint32_t)g.Cin), n, (int64_t)c_begin * RB_K, p_end < Mg ? p_end : Mg);
+  }
 }
 
 // column tiles per block: no more than the channels fill

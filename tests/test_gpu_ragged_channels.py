@@ -45,6 +45,82 @@ def test_layer_with_any_channel_count(G, oracle, s, K):
             assert rel(a, b) < TOL
 
 
+def valid(o, n, k, stride, pad):
+    """Outputs along one axis that tap k reaches inside the image, and the positions it reaches there."""
+    i = [(p, p * stride + k - pad) for p in range(o) if 0 <= p * stride + k - pad < n]
+    return torch.tensor([p for p, _ in i], device="cuda", dtype=torch.long), torch.tensor([q for _, q in i], device="cuda", dtype=torch.long)
+
+
+def taps(s):
+    for r in range(s.R):
+        for q in range(s.S):
+            (ho, hi), (wo, wi) = valid(s.Ho, s.H, r, s.stride, s.pad), valid(s.Wo, s.W, q, s.stride, s.pad)
+            yield r, q, ho[:, None], wo[None, :], hi[:, None], wi[None, :]
+
+
+def same_kind(got, ref):
+    ref32 = ref.float()
+    assert torch.equal(torch.isnan(got), torch.isnan(ref32))
+    assert torch.equal(torch.isinf(got), torch.isinf(ref32)) and torch.equal(got[torch.isinf(got)], ref32[torch.isinf(ref32)])
+    ok = torch.isfinite(ref32)
+    assert bool(ok.any()) and bool((~ok).any())
+    assert float((got - ref)[ok].abs().max()) <= TOL * float(ref[ok].abs().max())
+
+
+@pytest.mark.parametrize("K", [4, 8, 32])
+@pytest.mark.parametrize("s", [LayerShape(2, 8, 4, 3, 17), LayerShape(3, 10, 11, 12, 50, 3, 3, 2, 1),
+                               LayerShape(2, 9, 10, 9, 36, 5, 5, 1, 2), LayerShape(30, 21, 27, 20, 36)],
+                         ids=lambda s: "x".join(map(str, s.as_tuple())))
+def test_taps_outside_the_image_are_skipped(s, K):
+    """Positions outside the image take no part, also where they would meet an infinity."""
+    print("case ragged layer, not finite", s.as_tuple(), K, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    t = s.as_tuple()
+
+    def normal(*size):
+        return torch.randn(*size, device="cuda", generator=g)
+
+    a, w, dy = normal(s.N, s.H, s.W, s.Cin), normal(s.R, s.S, s.Cin, s.Cout), normal(s.N, s.Ho, s.Wo, s.Cout)
+    a[0, 0, 0, 1] = float("inf")
+    a[-1, -1, -1, 2] = float("nan")
+    w[0, 0, 1, 2] = float("inf")
+    w[-1, -1, 0, 4] = -float("inf")
+    y, da = torch.empty_like(dy), torch.empty_like(a)
+    B.abl_conv_fwd(t, a, w, None, y)
+    B.abl_conv_dgrad(t, dy, w, da)
+    y64, da64 = torch.zeros_like(y, dtype=torch.float64), torch.zeros_like(a, dtype=torch.float64)
+    for r, q, ho, wo, hi, wi in taps(s):
+        y64[:, ho, wo] += a[:, hi, wi].double() @ w[r, q].double()
+        da64[:, hi, wi] += dy[:, ho, wo].double() @ w[r, q].double().t().contiguous()
+    same_kind(y, y64)
+    same_kind(da, da64)
+
+    # the weight gradient, on its own and (with room for shares of the pixels) in the layer's backward pass
+    x = normal(s.N, s.H, s.W, s.Cin)
+    dy[0, 0, 0, 3] = float("inf")
+    dy[-1, -1, -1, 5] = float("nan")
+    raw = lambda n: torch.zeros(int(n), dtype=torch.uint8, device="cuda")
+    packed, stats, scratch = raw(B.abl_packed_bytes(t, K)), raw(B.abl_stats_bytes(t)), raw(B.abl_scratch_bytes(t, K))
+    a2t, dW, dW2, dx = torch.empty_like(x), torch.empty_like(w), torch.empty_like(w), torch.empty_like(x)
+    one, zero = torch.ones(s.Cin, device="cuda"), torch.zeros(s.Cin, device="cuda")
+    dg, db = torch.empty_like(one), torch.empty_like(one)
+    B.abl_forward(t, K, x, w, one, zero, None, scratch, y, packed, stats)
+    B.abl_unpack(packed, s.N * s.H * s.W, s.Cin, K, stats, a2t)
+    B.abl_conv_wgrad_packed(t, K, packed, stats, dy, scratch, dW)
+    B.abl_backward(t, K, packed, stats, dy, w, scratch, dx, dW2, dg, db)
+    ref = torch.zeros_like(w, dtype=torch.float64)
+    for r, q, ho, wo, hi, wi in taps(s):
+        p, d = a2t[:, hi, wi].reshape(-1, s.Cin).double(), dy[:, ho, wo].reshape(-1, s.Cout).double()
+        fin = torch.isfinite(d).all(1)
+        ref[r, q] += p[fin].clamp(min=0).t().contiguous() @ d[fin]
+        for i in (~fin).nonzero().view(-1).tolist():   # (the few others: an activation of zero takes no part either)
+            prod = p[i].clamp(min=0)[:, None] * d[i][None, :]
+            ref[r, q] += torch.where((p[i] > 0)[:, None] | (torch.tensor(K == 32, device="cuda") & ~(p[i] < 0))[:, None],
+                                     prod, torch.zeros_like(prod))
+    same_kind(dW, ref)
+    same_kind(dW2, ref)
+
+
 def test_one_channel_with_more_than_2_to_the_30_pixels():
     """The largest grids: 64 pixels to a block of 256 threads, 2^24 blocks and more."""
     s = (1, 32768, 32784, 1, 1, 1, 1, 1, 0)
