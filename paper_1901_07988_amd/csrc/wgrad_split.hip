@@ -242,11 +242,12 @@ __global__ __launch_bounds__(THREADS, 2) void split_wgrad_kernel(const uint8_t* 
   // bytes from the chunk's first pixel (v: from the row above it) to the item's columns, the last one again past
   // the row; items outside the image load the chunk's first pixel
   uint32_t d_off[8], a_off[8];
-  const uint32_t a_row = (uint32_t)(W * Cin * K / 8);
+  // (elements first, then bytes: a chunk of many channels has up to 2^31 of them, and their bits do not fit 32)
+  const uint32_t a_row = (uint32_t)(W * Cin) / (8 / K);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     d_off[i] = (uint32_t)(((dti * H + dh) * W + min(dw0 + i, W - 1)) * Cout + 2 * dcp) * 4u;
-    a_off[i] = (uint32_t)((((ati * H + ah + 1) * W + min(aw0 + i, W - 1)) * Cin + 4 * ac4) * K / 8);
+    a_off[i] = ((uint32_t)((ati * H + ah + 1) * W + min(aw0 + i, W - 1)) * Cin + 4 * ac4) / (8 / K);
   }
   float2 dv[8];
   uint32_t cw[8];

@@ -117,3 +117,27 @@ def test_values_the_split_cannot_carry(s):
     assert bool(torch.isinf(got)[torch.isinf(ref)].all()) and bool(torch.isfinite(got)[fin].all())
     ok = torch.isfinite(ref) & torch.isfinite(got)
     assert float(((got - ref)[ok].abs() / ref[ok].abs().clamp(min=1e-30)).max()) < 2e-5   # (positive terms)
+
+
+def test_more_channels_than_32_bits_of_code_bits():
+    """A chunk's codes, counted in bits, pass 2^31: 700928 channels of one row of 128 pixels and its two neighbours."""
+    s, K = (1, 2, 128, 700928, 64, 3, 3, 1, 1), 8
+    print("case split weight gradient, many channels", s, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    M, ci, co = s[1] * s[2], s[3], s[4]
+    x, dy = torch.randn(M, ci, device="cuda", generator=g), torch.randn(1, s[1], s[2], co, device="cuda", generator=g)
+    raw = lambda n: torch.empty(int(n), dtype=torch.uint8, device="cuda")
+    packed, stats, scratch = raw(B.abl_packed_bytes(s, K)), raw(B.abl_stats_bytes(s)), raw(B.abl_bn_scratch_bytes(M, ci))
+    one, a2t = torch.ones(ci, device="cuda"), torch.empty_like(x)
+    B.abl_bn_stats(x, M, ci, one, 0 * one, K, scratch, stats)
+    B.abl_bn_relu_pack(x, M, ci, K, stats, a2t, packed)
+    B.abl_unpack(packed, M, ci, K, stats, a2t)
+    dW = torch.full((3, 3, ci, co), float("nan"), device="cuda")
+    B.abl_conv_wgrad_packed(s, K, packed, stats, dy, raw(B.abl_wgrad_scratch_bytes(s)), dW)
+    assert bool(torch.isfinite(dW).all())
+    for c0 in (0, ci // 2, ci - 96):
+        p = torch.nn.functional.pad(a2t[:, c0:c0 + 96].clamp(min=0).double().view(1, s[1], s[2], 96), (0, 0, 1, 1, 1, 1))
+        for r in range(3):
+            for q in range(3):
+                ref = p[:, r:r + s[1], q:q + s[2]].reshape(M, 96).t().contiguous() @ dy.double().view(M, co)
+                assert rel(dW[r, q, c0:c0 + 96], ref) < 2.0 ** -24 * ((3 * M / 32) ** 0.5 + 4)
