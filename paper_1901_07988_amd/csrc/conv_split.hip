@@ -9,9 +9,10 @@
 // faster; and the sum is rounded once per 32 terms and product instead of once per 4 terms.  The five small
 // products have an accumulator of their own: added to the large one they would each round at its magnitude
 // (relative error of a 2304-term contraction against 64 bits: fp32 matrix cores 8.6e-7, one accumulator
-// 7.4e-7, two 2.9e-7).  What the split cannot carry: an infinity becomes a NaN (inf - inf), so an output that
-// is not finite is computed again from the fp32 operands by exact_output(); below 2^-110 the lowest bits of a
-// value fall under the smallest bf16.
+// 7.4e-7, two 2.9e-7).  The parts are taken of 2^23 x: those of the smallest fp32 values (multiples of 2^-149) are normal
+// bf16 values then, and every other result is the same bit for bit.  What the split cannot carry - infinities, values
+// from 2^105 on, sums from 2^82 on - gives an infinity or a NaN; an output that is not finite is computed again from the
+// fp32 operands by exact_output().
 //
 // One block = a run of up to 112 consecutive pixels (of one image, or across images where that makes fewer
 // tiles) x 16 NT WN output channels.  Its input patch (the rows of those pixels and the filter's border) is
@@ -66,11 +67,15 @@ struct Tiling {
   int npos;          // positions of a patch
 };
 
-// x = h + m + l, eight values at a time (the parts of two values share a 32-bit word)
+constexpr float kUp = 0x1p23f, kDown = 0x1p-46f;   // both operands are split as 2^23 times their values
+
+// 2^23 x = h + m + l, eight values at a time (the parts of two values share a 32-bit word)
 __device__ inline void split3(const float (&x)[8], bf16x8_t& h, bf16x8_t& m, bf16x8_t& l) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   uint4 hw, mw, lw;
   auto two = [](float a, float b, uint32_t& u, uint32_t& v, uint32_t& w) __attribute__((always_inline)) {
+    a *= kUp;
+    b *= kUp;
     u = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
     const float ra = a - __uint_as_float(u << 16), rb = b - __uint_as_float(u & 0xFFFF0000u);
     v = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
@@ -86,14 +91,14 @@ __device__ inline void split3(const float (&x)[8], bf16x8_t& h, bf16x8_t& m, bf1
   l = __builtin_bit_cast(bf16x8_t, lw);
 }
 
-// One output in fp32 from the operands themselves, for values that are not finite.
+// One output from the operands themselves (products and sums in 64 bits), for values that are not finite.
 template <int MODE, int TAPS, int FUSE>
 __device__ inline float exact_output(const float* in, const float* wgt, const float* stats, int H, int W, int Cin, int Cout,
                                      int p, int n) {
   const int Cg = MODE == 0 ? Cin : Cout;
   const int HW = H * W;
   const int img = p / HW, h = (p - img * HW) / W, w = p - img * HW - h * W;
-  float s = 0.0f;
+  double s = 0.0;
   for (int tap = 0; tap < TAPS; ++tap) {
     const int hi = h + (TAPS == 9 ? tap / 3 - 1 : 0), wi = w + (TAPS == 9 ? tap % 3 - 1 : 0);
     const bool in_image = hi >= 0 && hi < H && wi >= 0 && wi < W;   // (the border's zeros take part)
@@ -106,11 +111,11 @@ __device__ inline float exact_output(const float* in, const float* wgt, const fl
         const float a2 = stats[P_GAMMA * Cin + c] * a1 + stats[P_BETA * Cin + c];
         x = a2 > 0.0f ? a2 : 0.0f;
       }
-      s = fmaf(x, MODE == 0 ? b[(size_t)c * Cout] : b[c], s);
-      if (s != s) return s;
+      s += (double)x * (double)(MODE == 0 ? b[(size_t)c * Cout] : b[c]);
+      if (s != s) return (float)s;
     }
   }
-  return s;
+  return (float)s;
 }
 
 // EPI: 0 none; 1 = sums of y and y^2 per channel (first pass of the next layer's Eq. 1); 4 / 8 = the Eq. 6-7
@@ -415,7 +420,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
-      for (int i = 0; i < MT; ++i) v[j][i] = NP == 3 ? hi[j][i] + lo[j][i] : hi[j][i];
+      for (int i = 0; i < MT; ++i) v[j][i] = NP == 3 ? kDown * (hi[j][i] + lo[j][i]) : hi[j][i];
       unsigned char* const cbuf = smem + exchange_bytes(NT, KS);
     if (KS == 2 || EPI > 1) __syncthreads();      // every wave has finished reading the patch
     if constexpr (EPI > 1) {

@@ -207,3 +207,33 @@ def test_forward_with_prologue(s, K):
     B.abl_bn_relu_pack(x, M, ci, K, stats2, a3, packed2)
     assert torch.equal(stats, stats2) and torch.equal(packed, packed2)
     assert rel(y, conv64(a3, w) + skip.double()) < tolerance(R * R * ci)
+
+
+SMALL = 2.0 ** -120   # products with values near 1 stay normal, two of the three bf16 parts of such a value do not
+
+
+@pytest.mark.parametrize("tiny", ["values", "weights"])
+@pytest.mark.parametrize("s", [SHAPES[1], SHAPES[5], SHAPES[8], SHAPES[10]], ids=lambda s: "x".join(map(str, s)))
+def test_small_operands(s, tiny):
+    """Operands far below 1 keep their 24 bits."""
+    print("case split operands, small", s, tiny, flush=True)
+    x, w, dy = draw(s)
+    R, ci, co = s[5], s[3], s[4]
+    if tiny == "values":
+        x, dy = x * SMALL, dy * SMALL
+    else:
+        w = w * SMALL
+    y, da3 = torch.empty_like(dy), torch.empty_like(x)
+    B.abl_conv_fwd(shape9(s), x, w, None, y)
+    B.abl_conv_dgrad(shape9(s), dy, w, da3)
+    # (outputs are rounded to multiples of 2^-149: 2^-29 of their size)
+    assert rel(y, conv64(x, w)) < tolerance(R * R * ci)
+    assert rel(da3, conv64(dy, grad_weights(w))) < tolerance(R * R * co)
+    if tiny == "weights" and R == 3 and B.abl_forward_is_fused(shape9(s), 4):
+        stats = torch.empty(32 * ci, dtype=torch.uint8, device="cuda")
+        packed = torch.empty(B.abl_packed_bytes(shape9(s), 4), dtype=torch.uint8, device="cuda")
+        scratch = torch.empty(B.abl_scratch_bytes(shape9(s), 4), dtype=torch.uint8, device="cuda")
+        ones, a3 = torch.ones(ci, device="cuda"), torch.empty_like(x)
+        B.abl_forward(shape9(s), 4, x, w, ones, ones * 0, None, scratch, y, packed, stats)
+        B.abl_bn_relu_pack(x, x.numel() // ci, ci, 4, stats, a3, packed)
+        assert rel(y, conv64(a3, w)) < tolerance(R * R * ci)
