@@ -237,3 +237,86 @@ def test_small_operands(s, tiny):
         B.abl_forward(shape9(s), 4, x, w, ones, ones * 0, None, scratch, y, packed, stats)
         B.abl_bn_relu_pack(x, x.numel() // ci, ci, 4, stats, a3, packed)
         assert rel(y, conv64(a3, w)) < tolerance(R * R * ci)
+
+
+def assert_same_kind(got, ref64):
+    """NaN, infinities and finite values where the 64-bit values have them (positive terms: no cancellation)."""
+    ref = ref64.float()
+    edge = (ref64.abs() > 3.3e38) & (ref64.abs() < 3.5e38)   # (within a rounding of the largest value either way)
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    assert torch.equal(torch.isinf(got)[~edge], torch.isinf(ref)[~edge])
+    ok = torch.isfinite(ref) & ~edge
+    assert float(((got - ref)[ok].abs() / ref[ok].abs().clamp(min=1e-30)).max()) < 1e-5
+
+
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("s", [SHAPES[1], SHAPES[5], SHAPES[8], SHAPES[10]], ids=lambda s: "x".join(map(str, s)))
+def test_gradients_the_split_cannot_carry(s, K):
+    """... in the data gradient (other indexing of the weights than the forward), and ahead of the sums of its epilogue."""
+    print("case split operands, gradient not finite", s, K, flush=True)
+    x, w, dy = draw(s)
+    N, H, W, ci, co, R = s
+    s9, M = shape9(s), N * H * W
+    dy, w = dy.abs() + 0.5, w.abs() + 0.01
+    w[:, :, 1] = 2.0 ** -20          # keeps the largest values finite
+    w[:, :, 2] = 0.0                 # infinity times zero
+    w[0, 0, 3, 6] = float("inf")
+    dy[0, 0, 0, 5] = float("inf")
+    dy[-1, -1, -1, 7] = float("nan")
+    dy[N // 2, H // 2, W // 2, 9] = 3.4e38
+    dy[0, -1, 0, 11] = -float("inf")
+    da3 = torch.empty_like(x)
+    B.abl_conv_dgrad(s9, dy, w, da3)
+    assert_same_kind(da3, conv64(dy, grad_weights(w)))
+    stats = torch.empty(32 * ci, dtype=torch.uint8, device="cuda")
+    packed = torch.empty(B.abl_packed_bytes(s9, K), dtype=torch.uint8, device="cuda")
+    scratch = torch.empty(B.abl_scratch_bytes(s9, K), dtype=torch.uint8, device="cuda")
+    a3, a2t, ones = torch.empty_like(x), torch.empty_like(x), torch.ones(ci, device="cuda")
+    B.abl_bn_stats(x, M, ci, ones, ones * 0.1, K, scratch, stats)
+    B.abl_bn_relu_pack(x, M, ci, K, stats, a3, packed)
+    B.abl_unpack(packed, M, ci, K, stats, a2t)
+    dx, dW, dg, db = torch.empty_like(x), torch.empty_like(w), torch.empty(ci, device="cuda"), torch.empty(ci, device="cuda")
+
+    def sums():
+        B.abl_backward(s9, K, packed, stats, dy, w, scratch, dx, dW, dg, db)
+        B.abl_conv_dgrad(s9, dy, w, da3)
+        return torch.where(a2t > 0, da3, torch.zeros_like(da3)).double().view(M, ci).sum(0)
+
+    ref = sums()
+    assert torch.equal(torch.isnan(db), torch.isnan(ref)) and torch.equal(torch.isfinite(db), torch.isfinite(ref.float()))
+    assert not bool(torch.isfinite(dg)[~torch.isfinite(ref)].any())
+    # a value that rounds to an infinite bf16, times small weights: everything stays finite
+    dy = torch.rand(dy.shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(4)) + 0.5
+    dy[N // 2, H // 2, W // 2, 9] = 3.4e38
+    w = w.clamp(max=1.0)
+    w[..., 9] = 2.0 ** -20
+    ref = sums()
+    a1 = (a2t.double().view(M, ci) - 0.1)
+    ref_g = (a1 * torch.where(a2t > 0, da3, torch.zeros_like(da3)).double().view(M, ci)).sum(0)
+    for got, want in ((db, ref), (dg, ref_g)):
+        assert bool(torch.isfinite(got).all())
+        assert float((got - want).abs().max()) <= 1e-5 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("s", [SHAPES[4], SHAPES[5]], ids=lambda s: "x".join(map(str, s)))
+def test_fused_forward_with_weights_the_split_cannot_carry(s):
+    """... in the forward that normalises while it stages, which computes such outputs from x itself."""
+    print("case split operands, fused forward not finite", s, flush=True)
+    x, w, _ = draw(s)
+    N, H, W, ci, co, R = s
+    s9 = shape9(s)
+    assert B.abl_forward_is_fused(s9, 4)
+    w = w.abs() + 0.01
+    w[0, 0, 3, 1] = float("inf")
+    w[1, 2, 4, 2] = float("nan")
+    w[2, 1, 5, 3] = 3.4e38
+    w[1, 1, 6, 4] = -float("inf")
+    g = torch.Generator(device="cuda").manual_seed(2)
+    gamma, beta = torch.rand(ci, device="cuda", generator=g) + 0.5, torch.rand(ci, device="cuda", generator=g) * 0.2
+    stats = torch.empty(32 * ci, dtype=torch.uint8, device="cuda")
+    packed = torch.empty(B.abl_packed_bytes(s9, 4), dtype=torch.uint8, device="cuda")
+    scratch = torch.empty(B.abl_scratch_bytes(s9, 4), dtype=torch.uint8, device="cuda")
+    y, a3 = torch.empty(N, H, W, co, device="cuda"), torch.empty_like(x)
+    B.abl_forward(s9, 4, x, w, gamma, beta, None, scratch, y, packed, stats)
+    B.abl_bn_relu_pack(x, N * H * W, ci, 4, stats, a3, packed)
+    assert_same_kind(y, conv64(a3, w))
