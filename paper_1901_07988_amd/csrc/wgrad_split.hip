@@ -4,7 +4,7 @@
 //   dW[tap][ci][co] = |step[ci]| / 2 * sum over pixels of v[pixel + tap][ci] * dy[pixel][co],
 //
 // where step (n + 1/2) is Eq. 10 and v = |2 n + 1| where that is positive, else 0.  v is a whole number below
-// 2^K + 2 |fb|, exact in one bf16 up to 256; dy is the exact sum of three bf16 values (as in conv_split.hip).  So
+// 2^K + 2 |fb|, exact in one bf16 up to 256; 2^23 dy is the exact sum of three bf16 values (as in conv_split.hip).  So
 // three bf16 products - each exact - replace one fp32 product, with nothing dropped: 32 pixels in the matrix-core
 // time of about six (1600 / 3 TFLOP/s against 154), and the sums are rounded once per 32 pixels and part instead of
 // once per 4 pixels (relative error of a sum over 12544 pixels against 64 bits 0.95e-6, fp32 matrix cores 1.4e-6).
@@ -62,14 +62,16 @@ int allow_full_lds(const void* kern) {
   return ABL_OK;
 }
 
-// One share's sum of one element in fp32 from dy and the codes themselves, for sums that are not finite.
+constexpr float kUp = 0x1p23f, kDown = 0x1p-23f;   // dy is split as 2^23 times its values: the parts of the smallest are normal
+
+// One share's sum of one element from dy and the codes themselves (summed in 64 bits), for sums that are not finite.
 template <int K>
 __device__ inline float exact_sum(const uint8_t* codes, const float* stats, const float* dy, int H, int W, int Cin,
                                   int Cout, int tap, int ci, int co, int px_begin, int px_end) {
   const float step = stats[P_STEP * Cin + ci];
   const int32_t fb = reinterpret_cast<const int32_t*>(stats)[P_FB * Cin + ci];
   const int dh = tap / 3 - 1, dw = tap % 3 - 1;
-  float s = 0.0f;
+  double s = 0.0;
   for (int p = px_begin; p < px_end; ++p) {
     const int row = p / W, w = p - row * W + dw, h = row % H + dh;
     float v = 0.0f;   // (the border's zeros take part: times an infinity they are NaN)
@@ -78,10 +80,10 @@ __device__ inline float exact_sum(const uint8_t* codes, const float* stats, cons
       const uint32_t code = K == 4 ? (codes[e >> 1] >> (4 * (e & 1))) & 15u : codes[e];
       v = fmaxf(dequant<K>(code, step, fb), 0.0f);
     }
-    s = fmaf(v, dy[(size_t)p * Cout + co], s);
-    if (s != s) return s;
+    s += (double)v * (double)dy[(size_t)p * Cout + co];
+    if (s != s) return (float)s;
   }
-  return s;
+  return (float)s;
 }
 
 // How a block's codes become v = max(s2 code + off, 0) - the sign of the step folded in - and how far they reach.
@@ -140,7 +142,7 @@ __device__ inline void split_dy(const float (&x)[8], uint4 (&u)[NP]) {
   uint32_t w[NP][4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    float a = x[2 * q], b = x[2 * q + 1];
+    float a = NP == 3 ? kUp * x[2 * q] : x[2 * q], b = NP == 3 ? kUp * x[2 * q + 1] : x[2 * q + 1];
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
       w[t][q] = __builtin_bit_cast(uint32_t, bf16x2_t{(__bf16)a, (__bf16)b});
@@ -429,6 +431,7 @@ __global__ __launch_bounds__(THREADS, 2) void split_wgrad_kernel(const uint8_t* 
       for (int o = 0; o < 2; ++o)
         if ((t < 5) == (kg == 0)) {
           acc[t][o] = half_step * (acc[t][o] + *reinterpret_cast<const floatx4*>(from + ((t < 5 ? t : t - 5) * 2 + o) * 1024));
+          if (NP == 3) acc[t][o] *= kDown;   // (last: the product before it is normal wherever the result is not zero)
 #pragma unroll
           for (int r = 0; r < 4; ++r) bad = fmaf(acc[t][o][r], 0.0f, bad);
         }
@@ -658,8 +661,10 @@ __global__ __launch_bounds__(THREADS, 2) void split_wgrad1_kernel(const uint8_t*
     const int ci = ci0 + ACH * (32 * wc + 16 * (i & 1) + li) + (i >> 1);
     const float half_step = NP == 1 ? 1.0f : 0.5f * fabsf(stats[P_STEP * Cin + ci]);
 #pragma unroll
-    for (int o = 0; o < OT; ++o)
+    for (int o = 0; o < OT; ++o) {
       acc[i][o] = half_step * (acc[i][o] + *reinterpret_cast<const floatx4*>(from + ((i % IH) * OT + o) * 1024));
+      if (NP == 3) acc[i][o] *= kDown;   // (last: the product before it is normal wherever the result is not zero)
+    }
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       // the lane's output channels co .. in order: element r of tile p (and of tile p + 2)

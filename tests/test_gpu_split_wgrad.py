@@ -141,3 +141,16 @@ def test_more_channels_than_32_bits_of_code_bits():
             for q in range(3):
                 ref = p[:, r:r + s[1], q:q + s[2]].reshape(M, 96).t().contiguous() @ dy.double().view(M, co)
                 assert rel(dW[r, q, c0:c0 + 96], ref) < 2.0 ** -24 * ((3 * M / 32) ** 0.5 + 4)
+
+
+@pytest.mark.parametrize("K,beta", [(4, 0.0), (8, 0.5), (8, 30.0)])
+@pytest.mark.parametrize("s", [SHAPES[0], SHAPES[4], SHAPES[6], SHAPES[7], SHAPES[8]], ids=lambda s: "x".join(map(str, s)))
+def test_small_gradients(s, K, beta):
+    """A gradient far below 1 keeps its 24 bits: its result is the ordinary one's, scaled."""
+    print("case split weight gradient, small", s, K, beta, flush=True)
+    layer = Layer(s, K, beta)
+    want = layer.run().double() * 2.0 ** -120
+    layer.dy *= 2.0 ** -120
+    got = layer.run().double()
+    # (copies of dW and their sum are rounded to multiples of 2^-149 where they are below 2^-126: far below the bound)
+    assert rel(got, want) < 2.0 ** -26
