@@ -679,6 +679,10 @@ __global__ __launch_bounds__(THREADS, 2) void split_wgrad1_kernel(const uint8_t*
       if (NP == 3 && __builtin_expect(bad != 0.0f, 0))   // (as above)
 #pragma unroll 1
         for (int r = 0; r < 4 * DCH; ++r) {
+          float was = 0.0f;
+#pragma unroll
+          for (int q = 0; q < 4 * DCH; ++q) was = q == r ? s[q] : was;
+          if (fabsf(was) < INFINITY) continue;
           const float x = exact_sum<K>(codes, stats, dy, 1, 1, Cin, Cout, 4, ci, co + r, c_begin * PX1, min(c_end * PX1, M));
 #pragma unroll
           for (int q = 0; q < 4 * DCH; ++q) s[q] = q == r ? x : s[q];

@@ -154,3 +154,18 @@ def test_small_gradients(s, K, beta):
     got = layer.run().double()
     # (copies of dW and their sum are rounded to multiples of 2^-149 where they are below 2^-126: far below the bound)
     assert rel(got, want) < 2.0 ** -26
+
+
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("s", [SHAPES[0], SHAPES[6], SHAPES[7], SHAPES[8], SHAPES[9]], ids=lambda s: "x".join(map(str, s)))
+def test_finite_sums_beside_infinite_ones(s, K):
+    """An infinity in one output channel of dy leaves the sums of the others as they are, bit for bit."""
+    print("case split weight gradient, neighbours", s, K, flush=True)
+    layer = Layer(s, K, 0.3)
+    want = layer.run()
+    layer.dy[0, 0, 0, 1] = float("inf")
+    layer.dy[-1, -1, -1, 38] = float("nan")
+    got = layer.run()
+    others = [c for c in range(s[4]) if c not in (1, 38)]
+    assert torch.equal(got[..., others], want[..., others])
+    assert not bool(torch.isfinite(got[..., 38]).any())
