@@ -47,11 +47,11 @@ class Layer:
         B.abl_bn_relu_pack(x, M, ci, K, self.stats, a3, self.packed)
         B.abl_unpack(self.packed, M, ci, K, self.stats, self.a2t)
 
-    def run(self):
+    def run(self, flags=0):
         ci, co, R = self.s[3:]
         ws = torch.empty(B.abl_wgrad_scratch_bytes(shape9(self.s)), dtype=torch.uint8, device="cuda")
         dW = torch.full((R, R, ci, co), float("nan"), device="cuda")
-        B.abl_conv_wgrad_packed(shape9(self.s), self.K, self.packed, self.stats, self.dy, ws, dW)
+        B.abl_conv_wgrad_packed(shape9(self.s), self.K, self.packed, self.stats, self.dy, ws, dW, flags=flags)
         return dW
 
     def ref(self):
@@ -169,3 +169,41 @@ def test_finite_sums_beside_infinite_ones(s, K):
     others = [c for c in range(s[4]) if c not in (1, 38)]
     assert torch.equal(got[..., others], want[..., others])
     assert not bool(torch.isfinite(got[..., 38]).any())
+
+
+# 8-bit codes that fit one bf16, whose missing ones come from the stored bits, and in two and three parts
+@pytest.mark.parametrize("beta", [0.0, 0.5, 30.0, 5000.0])
+@pytest.mark.parametrize("s", [SHAPES[0], SHAPES[5], SHAPES[6], SHAPES[7]], ids=lambda s: "x".join(map(str, s)))
+def test_wide_codes_and_values_the_split_cannot_carry(s, beta):
+    print("case split weight gradient, wide codes, not finite", s, beta, flush=True)
+    layer = Layer(s, 8, beta)
+    dy = layer.dy
+    dy.abs_()
+    dy[0, 0, 0, 1] = float("inf")
+    dy[-1, -1, -1, 3] = float("nan")
+    dy[0, 1, 1, 5] = -float("inf")
+    dy[..., 6] = 0.0
+    dy[s[0] // 2, 1, 1, 6] = 3.4e38      # alone in its channel
+    got, ref64 = layer.run(), layer.ref()
+    edge = (ref64.abs() > 3.3e38) & (ref64.abs() < 3.5e38)
+    ref = ref64.float()
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    assert torch.equal(torch.isinf(got)[~edge], torch.isinf(ref)[~edge])
+    ok = torch.isfinite(ref) & torch.isfinite(got) & ~edge
+    assert float(((got - ref)[ok].abs() / ref[ok].abs().clamp(min=1e-30)).max()) < 2e-5   # (positive terms)
+
+
+@pytest.mark.parametrize("K,beta", [(4, 0.1), (8, 0.1), (8, 30.0)])
+@pytest.mark.parametrize("s", SHAPES, ids=IDS)
+def test_bf16_operands(s, K, beta):
+    """ABL_MATH_BF16: the dequantized activation and dy rounded to bf16 once, exact products, sums in fp32."""
+    print("case split weight gradient, bf16 operands", s, K, beta, flush=True)
+    layer = Layer(s, K, beta)
+    got = layer.run(flags=B.ABL_MATH_BF16)
+    layer.a2t, layer.dy = layer.a2t.bfloat16().float(), layer.dy.bfloat16().float()
+    ref = layer.ref()
+    # (large activations of one sign: the products with dy cancel, by up to beta in the sums)
+    scale = float(layer.a2t.clamp(min=0).double().norm()) * float(layer.dy.double().norm())
+    n = s[0] * s[1] * s[2]
+    bound = layer.tolerance() * scale * (ref.numel() / (s[3] * s[4]) / n) ** 0.5
+    assert float((got.double() - ref).norm()) < bound * (1 if beta <= 1 else 2)
