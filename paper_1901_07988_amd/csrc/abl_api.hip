@@ -299,7 +299,7 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, t16, dx, dgamma, dbeta, &dwsum);
   }
   // the split-operand kernels, with the Eq. 6-7 sums in their epilogue
-  if (const int nb = K != 32 && !bf16 ? split_conv_blocks(g, 1) : 0) {
+  if (const int nb = K != 32 && !bf16 ? split_conv_blocks(g, 1, false, true) : 0) {
     if (int e = launch_split_dgrad_reduce(st, g, K, false, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
     DwSum dwsum;
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
@@ -469,7 +469,7 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
     return ABL_ERR_ARG;
   const ConvGeom g = geom_of(*s);
   if (scratch_bytes < bn_partial_bytes(rows_of(*s), s->Cin)) return ABL_ERR_SCRATCH;
-  if (const int nb = !(flags & ABL_MATH_BF16) && reduce_stage_accepts(g) ? split_conv_blocks(g, 1) : 0) {
+  if (const int nb = !(flags & ABL_MATH_BF16) && reduce_stage_accepts(g) ? split_conv_blocks(g, 1, false, true) : 0) {
     *rows = nb;
     return launch_split_dgrad_reduce((hipStream_t)stream, g, K, false, dy, W, packed, stats, da3,
                                      static_cast<double*>(scratch));

@@ -78,6 +78,8 @@ bool halo_fused_supported(const ConvGeom& g);
 // out_partial (nullable): [tiles][2][Cout] doubles = per-tile sum(y), sum(y^2) of the output,
 // the first pass of the next layer's statistics.  halo_tile_count gives `tiles` (0: unsupported).
 int halo_tile_count(const ConvGeom& g, int mode);
+// The layer takes tiles of 64 pixels, and at most one block per compute unit of them.
+bool halo_in_one_round(const ConvGeom& g, int mode);
 int launch_halo_fwd_fused(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* x,
                           const void* stats, const float* w, const float* skip, float* y, void* packed,
                           double* out_partial);
@@ -170,10 +172,11 @@ int launch_image_bf16(hipStream_t st, const ConvGeom& g, int mode, const float* 
 
 // ---- fp32 contractions on the bf16 matrix cores, operands split into three bf16 parts (conv_split.hip) ----
 // 'same' stride-1 3x3 and 1x1 layers with contraction channels in multiples of 32 (1x1: 64) and output channels
-// in multiples of 64, unless too small.  split_conv_blocks: rows of the sums ([rows][2][C] doubles: of y in mode
+// in multiples of 64, where they are the faster ones.  split_conv_blocks: rows of the sums ([rows][2][C] doubles: of y in mode
 // 0, Eq. 6-7 in launch_split_dgrad_reduce), 0 = not supported.
 // bf16: operands rounded to bf16 instead.
-int split_conv_blocks(const ConvGeom& g, int mode, bool bf16 = false);
+// sums: with the Eq. 6-7 sums (launch_split_dgrad_reduce).
+int split_conv_blocks(const ConvGeom& g, int mode, bool bf16 = false, bool sums = false);
 int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
                       const float* skip, float* out, double* sums);
 // The 3x3 forward with Eq. 1-3 and Eq. 9 applied while the patch is staged (fp32 operands, y not x).

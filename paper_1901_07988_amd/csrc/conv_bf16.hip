@@ -652,7 +652,7 @@ int launch_bf16_gemm(hipStream_t st, const ConvGeom& g, int mode, const float* i
 
 int bf16_dgrad_reduce_rows(const ConvGeom& g) {
   if (image_bf16_supported(g, 1)) return g.N <= kMaxPartialBlocks ? g.N : 0;
-  if (const int nb = split_conv_blocks(g, 1, true)) return nb;
+  if (const int nb = split_conv_blocks(g, 1, true, true)) return nb;
   return bf16_gemm_supported(g, 1) ? gemm_sum_rows(g, 1) : 0;
 }
 
@@ -662,7 +662,7 @@ int launch_bf16_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const flo
   const uint8_t* codes = static_cast<const uint8_t*>(packed);
   const float* sp = static_cast<const float*>(stats);
   if (image_bf16_supported(g, 1)) return launch_image_bf16_epi(st, g, K, dy, w, da3, partial, codes, sp);
-  if (split_conv_blocks(g, 1, true) > 0) return launch_split_dgrad_reduce(st, g, K, true, dy, w, packed, stats, da3, partial);
+  if (split_conv_blocks(g, 1, true, true) > 0) return launch_split_dgrad_reduce(st, g, K, true, dy, w, packed, stats, da3, partial);
   if (K == 4) return launch_gemm<1, 4>(st, g, dy, w, nullptr, da3, partial, codes, sp);
   return launch_gemm<1, 8>(st, g, dy, w, nullptr, da3, partial, codes, sp);
 }

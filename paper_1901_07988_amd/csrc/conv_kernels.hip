@@ -988,8 +988,7 @@ int launch_conv_dgrad(hipStream_t st, const abl_shape& s, bool bf16, const float
   if (!mfma_ok(g)) return launch_ragged_conv(st, g, 1, dy, w, nullptr, da3);
   if (bf16 && image_bf16_supported(g, 1)) return launch_image_bf16(st, g, 1, dy, w, nullptr, da3, nullptr);
   // (1x1: from contractions of 1024 channels on, 512 -> 2048 @7x7 44 -> 35 us, 256 -> 1024 @14x14 28 -> 26; shorter ones
-  // write more than they contract, 1024 -> 256 @14x14 27 against 31.  With the Eq. 6-7 sums the split kernels are the
-  // faster ones throughout)
+  // write more than they contract, 1024 -> 256 @14x14 27 against 31)
   if (bf16 && (g.R == 3 || g.Cout >= 1024) && split_conv_blocks(g, 1, true) > 0)
     return launch_split_conv(st, g, 1, true, dy, w, nullptr, da3, nullptr);
   if (bf16 && bf16_gemm_supported(g, 1)) return launch_bf16_gemm(st, g, 1, dy, w, nullptr, da3);

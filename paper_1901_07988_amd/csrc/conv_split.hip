@@ -635,14 +635,44 @@ bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
   return p.lds <= (size_t)160 * 1024;
 }
 
+// Whether a grid of four-wave blocks - two to a compute unit, 512 at a time - is faster than the kernel that would
+// run otherwise.  A grid a little over one block per unit, or a little over 512, takes as long as a much larger one (the
+// units with one block more decide), while the other kernels' tiles may just fit.  (us, here / the other kernel, n blocks.
+// fp32 1x1: 256 -> 1024 @13x13 N=12, n = 304, 17.1 / 13.8, N=14, n = 352, 17.1 / 22.6; 256 -> 64 @56x56 of two tiles per
+// block N=20, n = 280, 30.9 / 23.6, N=28, n = 392, 33.0 / 32.1; 64 -> 256 @56x56 N=6, n = 336, 12.4 / 12.1, N=8, n = 448,
+// 12.3 / 14.8, N=20, n = 560, 28.9 / 27.4, but 128 -> 512 @28x28 N=20, also 560, 23.8 / 26.7.  bf16 1x1: 128 -> 512
+// @28x28 N=10, n = 280, 10.4 / 9.0, N=12, n = 336, 10.7 / 11.5, N=20, n = 560, 14.5 / 13.2, N=24, n = 672, 14.7 / 17.2;
+// 64 -> 256 @56x56 N=14, n = 784, 15.3 / 13.4; 512 -> 128 @28x28 N=40, n = 280, 23.8 / 18.9, N=56, n = 392, 24.9 / 23.7;
+// gradient 256 <- 1024 @14x14 N=40, n = 280, 30.3 / 24.5.  bf16 3x3: 64 -> 64 @56x56 of two tiles per block N=20,
+// n = 280, 24.5 / 21.1; gradient 128 <- 128 @28x28 N=40, n = 280, 43.6 / 36.7.)
+bool four_waves_pay(const ConvGeom& g, int mode, int np, bool sums, const Plan& p) {
+  const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
+  const int64_t n = (int64_t)p.tl.gm * (Ng / p.bn);
+  const bool over_one = n > 256 && n < 320, over_two = n > 512 && n < 640, over_three = n > 768 && n < 832;
+  const bool first = n > 256 && n < 400;   // the first round less than three quarters full
+  if (g.R == 3) {
+    if (np == 3) return p.nt == 2 || !halo_in_one_round(g, mode);
+    return sums || !((p.tl.per > 1 && over_one) || (mode == 1 && p.nt == 2 && first));
+  }
+  // with the Eq. 6-7 sums the other kernels need a pass of their own or lose their weight gradient's launch: fp32 is faster
+  // here throughout, bf16 with 64 channels per block and less than 1024 to contract only (1024 <- 256 @14x14 N=40,
+  // n = 560 of 128 channels each, backward 65.6 / 57.9; 256 <- 1024 N=40 59.4 / 55.3)
+  if (np == 3) {
+    if (sums) return true;
+    if (p.nt == 2 && Cg >= 512) return true;   // (512 -> 128 @28x28 N=40, n = 280: 42.6 / 59.1)
+    return !(over_one || (first && (p.tl.per > 1 || Cg < 128)) || (over_two && Cg < 128));
+  }
+  if (mode == 1 && (!sums || p.nt == 2 || Cg >= 1024)) return false;
+  return !(over_one || over_two || over_three || (p.nt == 2 && Cg >= 512 && first));
+}
+
 // 128 output channels per block where that fills the chip, else 64.  About one block per compute unit: the
 // contraction in two groups of waves; more: four-wave blocks, two per unit.  (us, blocks of 8 / 4 waves: 3x3
 // 256 -> 256 @14x14, 256 blocks 79 / 89; 1x1 1024 -> 256 @14x14, 224 blocks 45 / 55; 3x3 128 -> 128 @28x28,
 // 448 blocks 79 / 74; 1x1 256 -> 1024 @14x14, 896 blocks 54 / 45; with 64 channels per block 3x3 512 -> 512 @7x7
-// 88 / 105 instead of 125 / 160 with 128 channels on 112 blocks.)  Small grids stay on the other kernels, which
-// need no pass of their own for Eq. 1-3 and 9 (3x3 64 -> 64 on 128 images of 8x8, 74 blocks: layer step 69 us
-// against 65).
-bool make_plan(const ConvGeom& g, int mode, int np, Plan& p) {
+// 88 / 105 instead of 125 / 160 with 128 channels on 112 blocks.)  Grids of fewer than 96 blocks stay on the other
+// kernels, and four-wave blocks where they do not pay.  sums: with the Eq. 6-7 sums in the epilogue.
+bool make_plan(const ConvGeom& g, int mode, int np, bool sums, Plan& p) {
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
   const bool k3 = g.R == 3 && g.S == 3 && g.pad == 1, k1 = g.R == 1 && g.S == 1 && g.pad == 0;
   if (g.stride != 1 || !(k3 || k1) || Cg % 32 != 0 || Ng % 64 != 0) return false;
@@ -652,7 +682,7 @@ bool make_plan(const ConvGeom& g, int mode, int np, Plan& p) {
     for (int ks = 2; ks >= 1; --ks) {
       if (!fit_plan(g, mode, np, nt, ks, p)) continue;
       const int64_t blocks = (int64_t)p.tl.gm * (Ng / p.bn);
-      if (blocks >= (nt == 2 ? 200 : 96) && (ks == 1 || blocks <= 256)) return true;
+      if (blocks >= (nt == 2 ? 200 : 96) && (ks == 1 || blocks <= 256)) return ks == 2 || four_waves_pay(g, mode, np, sums, p);
     }
   return false;
 }
@@ -698,22 +728,29 @@ int launch_fused(hipStream_t st, const ConvGeom& g, const Plan& p, const float* 
   return hip_status();
 }
 
-// The fused forward: 64 output channels per block (the constants of Eq. 1-3 take the registers of the second tile).
+// The fused forward: 64 output channels per block (the constants of Eq. 1-3 take the registers of the second tile) in
+// four waves, where the halo kernel's tiles of 64 pixels need more than one round of the compute units: such a round takes
+// as long as a 112-pixel tile here (forward step, us, here / halo kernel: 64 -> 64 @32x32 N=16 30.3 / 25.7, N=24 32.5 /
+// 54.0; 128 -> 128 @28x28 N=8 41.1 / 37.7, N=16 43.0 / 57.0; 256 -> 256 @14x14 N=16 70.7 / 65.1, N=32 73.3 / 101.3).
+// Blocks of two tiles each, little more of them than compute units, leave most units idle half the time (64 -> 64 @32x32
+// N=64, 293 blocks: 93.9 / 90.4).
 bool make_fused_plan(const ConvGeom& g, Plan& p) {
-  return g.R == 3 && make_plan(g, 0, 3, p) && fit_plan(g, 0, 3, 1, 1, p);
+  if (g.R != 3 || !make_plan(g, 0, 3, false, p) || halo_in_one_round(g, 0) || !fit_plan(g, 0, 3, 1, 1, p)) return false;
+  const int64_t n = (int64_t)p.tl.gm * (g.Cout / p.bn);
+  return p.tl.per == 1 || n <= 256 || n >= 320;
 }
 
 }  // namespace
 
-int split_conv_blocks(const ConvGeom& g, int mode, bool bf16) {
+int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
   Plan p;
-  return make_plan(g, mode, bf16 ? 1 : 3, p) ? p.tl.gm : 0;
+  return make_plan(g, mode, bf16 ? 1 : 3, sums, p) ? p.tl.gm : 0;
 }
 
 int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
                       const float* skip, float* out, double* sums) {
   Plan p;
-  if (!make_plan(g, mode, bf16 ? 1 : 3, p)) return ABL_ERR_SHAPE;
+  if (!make_plan(g, mode, bf16 ? 1 : 3, false, p)) return ABL_ERR_SHAPE;
   const int epi = sums != nullptr ? 1 : 0;
   if (mode == 0)
     return bf16 ? launch<0, 1>(st, g, p, in, w, skip, out, sums, nullptr, nullptr, epi)
@@ -742,7 +779,7 @@ int launch_split_fwd_fused(hipStream_t st, const ConvGeom& g, int K, const float
 int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* dy, const float* w,
                               const void* packed, const void* stats, float* da3, double* partial) {
   Plan p;
-  if (!make_plan(g, 1, bf16 ? 1 : 3, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
+  if (!make_plan(g, 1, bf16 ? 1 : 3, true, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
   const uint8_t* codes = static_cast<const uint8_t*>(packed);
   const float* sp = static_cast<const float*>(stats);
   return bf16 ? launch<1, 1>(st, g, p, dy, w, nullptr, da3, partial, codes, sp, K)
