@@ -187,10 +187,10 @@ int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, bool bf1
                               const void* packed, const void* stats, float* da3, double* partial);
 
 // Weight gradient of 'same' stride-1 3x3 and 1x1 layers from the codes, dy split into three bf16 parts
-// (wgrad_split.hip; Cin a multiple of 32 - 1x1: 64 - and Cout of 64).  split_wgrad_copies: copies of dW that launch_split_wgrad leaves in dst, at most
-// `room` bytes of them ([copies][R][S][Cin][Cout] floats); 0 = not supported or too small.  bf16: both operands rounded
-// to bf16 instead.
-int split_wgrad_copies(const ConvGeom& g, int K, size_t room);
+// (wgrad_split.hip; Cin a multiple of 32 - 1x1: 64 - and Cout of 64).  split_wgrad_copies: copies of dW that
+// launch_split_wgrad leaves in dst, at most `room` bytes of them ([copies][R][S][Cin][Cout] floats); 0 = not supported or
+// not the faster kernel.  bf16: both operands rounded to bf16 instead.
+int split_wgrad_copies(const ConvGeom& g, int K, bool bf16, size_t room);
 int launch_split_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, const void* packed, const float* stats,
                        const float* dy, float* dst, size_t room);
 

@@ -1048,7 +1048,7 @@ int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf1
   }
   // other 'same' stride-1 3x3 and 1x1 layers (3x3 64 -> 64 @56x56: fp32 177 -> 86 us, bf16 102 -> 55)
   const size_t part = wgrad_partial_bytes(s);
-  if (const int copies = !relu32 ? split_wgrad_copies(g, K, part) : 0) {
+  if (const int copies = !relu32 ? split_wgrad_copies(g, K, bf16, part) : 0) {
     float* dst = copies == 1 ? dw : static_cast<float*>(scratch);
     if (int e = launch_split_wgrad(st, g, K, bf16, packed, sp, dy, dst, part)) return e;
     const int64_t n = (int64_t)g.R * g.S * g.Cin * g.Cout;

@@ -737,7 +737,23 @@ int launch_1x1(hipStream_t st, const ConvGeom& g, const Tile1& t, const void* pa
                      : launch_tile1<K, NP, 64, 64>(st, g, t, packed, stats, dy, dst);
 }
 
-bool make_chunking(const ConvGeom& g, int K, size_t room, Chunking& c) {
+// Whether the shares are long enough for the multiplications they do: a share's launch costs some 5 us more than a tiled
+// kernel's and its k-steps about 1.9 us each, a tiled kernel 0.34 us per 10^6 multiplications and tap (bf16 operands a little
+// less).  What counts is the longest share, in k-steps of one of the two groups of waves: rows that fill no k-step and
+// images that fill no chunk make it long.  (us, here / tiled: 64 -> 64 @10x10 N=64, 5 steps for 26, 22.4 / 17.0; 64 -> 64
+// @15x15 N=32, 4 for 29, 21.1 / 17.8; 96 -> 192 @9x9 N=32, 8 for 48, 28.9 / 26.0; 64 -> 64 @16x16 N=32, 2 for 34, 18.1 /
+// 20.6; 96 -> 192 @11x11 N=64, 15 for 143, 41.8 / 50.0; bf16 128 -> 128 @9x9 N=32, 6 for 42, 21.8 / 20.3.)
+bool shares_pay(const ConvGeom& g, bool bf16, const Chunking& c) {
+  const int per = (c.chunks + c.splits - 1) / c.splits;   // chunks of the longest share
+  const int rows = c.TI > 1 ? c.TI * c.R : c.R, last = g.H - (c.nch - 1) * c.R;
+  const int short_ones = c.nch > 1 ? per / c.nch : 0;
+  auto steps = [&](int r) { return ((r * c.dw8 + 3) / 4 + 1) / 2; };
+  const double most = (double)(per - short_ones) * steps(rows) + (double)short_ones * steps(last);
+  const double work = 1e-6 * g.N * g.H * g.W * g.Cin * g.Cout;
+  return bf16 ? 6.5 * most + 20.0 < work : 5.5 * most + 14.0 < work;
+}
+
+bool make_chunking(const ConvGeom& g, int K, bool bf16, size_t room, Chunking& c) {
   if (g.R != 3 || g.S != 3 || g.stride != 1 || g.pad != 1 || (K != 4 && K != 8)) return false;
   if (g.Cin % TCI != 0 || g.Cout % TCO != 0) return false;
   const int64_t M = (int64_t)g.N * g.H * g.W;
@@ -766,16 +782,16 @@ bool make_chunking(const ConvGeom& g, int K, size_t room, Chunking& c) {
   if (s > c.chunks) s = c.chunks;
   if (s < 1) s = 1;
   c.splits = (int)s;
-  return s * tiles >= 96;
+  return s * tiles >= 96 && shares_pay(g, bf16, c);
 }
 
 }  // namespace
 
-int split_wgrad_copies(const ConvGeom& g, int K, size_t room) {
+int split_wgrad_copies(const ConvGeom& g, int K, bool bf16, size_t room) {
   Tile1 t;
   if (make_tile1(g, K, room, t)) return t.splits;
   Chunking c;
-  return make_chunking(g, K, room, c) ? c.splits : 0;
+  return make_chunking(g, K, bf16, room, c) ? c.splits : 0;
 }
 
 int launch_split_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, const void* packed, const float* stats,
@@ -786,7 +802,7 @@ int launch_split_wgrad(hipStream_t st, const ConvGeom& g, int K, bool bf16, cons
     return K == 4 ? launch_1x1<4, 3>(st, g, t, packed, stats, dy, dst) : launch_1x1<8, 3>(st, g, t, packed, stats, dy, dst);
   }
   Chunking c;
-  if (!make_chunking(g, K, room, c)) return ABL_ERR_SHAPE;
+  if (!make_chunking(g, K, bf16, room, c)) return ABL_ERR_SHAPE;
   size_t lds = 2 * ((size_t)(bf16 ? 1 : 3) * DPART + c.agroups * AGRP);
   if (lds < (size_t)80 * 1024) lds = (size_t)80 * 1024;   // the exchange of the two groups' sums
   const unsigned grid = (unsigned)(c.splits * (g.Cin / TCI) * (g.Cout / TCO));
