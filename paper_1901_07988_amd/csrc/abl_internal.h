@@ -145,7 +145,7 @@ inline bool channels_in_tiles(const ConvGeom& g) { return g.Cin % 16 == 0 && g.C
 int launch_ragged_conv(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
                        float* out);
 // Copies of dW ([copies][R][S][Cin][Cout] floats, 1 = dW itself) that launch_ragged_wgrad writes with `room` bytes
-// for them; 0: too few to keep the GPU busy.
+// for them; 0: the kernel with a block per element of dW is the faster one.
 int ragged_wgrad_copies(const ConvGeom& g, size_t room);
 int launch_ragged_wgrad(hipStream_t st, const ConvGeom& g, int K, const void* packed, const float* stats,
                         const float* dy, int copies, float* dst, bool relu32);

@@ -53,6 +53,34 @@ __device__ inline float output_inside(const float* in, const float* wgt, const C
   return (float)sum;
 }
 
+// Contractions of a few elements: one thread per output, the sum in order.  The tiles below spend a chunk of 32 on them.
+template <int MODE>
+__global__ __launch_bounds__(kThreads) void direct_conv_kernel(const float* __restrict__ in, const float* __restrict__ wgt,
+                                                               const float* skip, float* out, ConvGeom g) {
+  const int Hi = MODE == 0 ? g.H : g.Ho, Wi = MODE == 0 ? g.W : g.Wo;
+  const int Hq = MODE == 0 ? g.Ho : g.H, Wq = MODE == 0 ? g.Wo : g.W;
+  const int Cg = MODE == 0 ? g.Cin : g.Cout, Ng = MODE == 0 ? g.Cout : g.Cin;
+  const uint32_t o = blockIdx.x * kThreads + threadIdx.x;
+  if (o >= (uint32_t)(g.N * Hq * Wq) * Ng) return;
+  const int p = (int)(o / Ng), n = (int)(o - (uint32_t)p * Ng);
+  const int t = p / Wq, img = t / Hq, wq = p - t * Wq, hq = t - img * Hq;
+  float sum = 0.0f;
+  for (int r = 0; r < g.R; ++r) {
+    const int hh = MODE == 0 ? hq * g.stride + r - g.pad : hq + g.pad - r;
+    const int hi = MODE == 0 ? hh : hh / g.stride;
+    if (hh < 0 || hi >= Hi || (MODE == 1 && hi * g.stride != hh)) continue;
+    for (int s = 0; s < g.S; ++s) {
+      const int ww = MODE == 0 ? wq * g.stride + s - g.pad : wq + g.pad - s;
+      const int wi = MODE == 0 ? ww : ww / g.stride;
+      if (ww < 0 || wi >= Wi || (MODE == 1 && wi * g.stride != ww)) continue;
+      const float* a = in + (size_t)((img * Hi + hi) * Wi + wi) * Cg;
+      const float* b = wgt + (size_t)(r * g.S + s) * g.Cin * g.Cout + (MODE == 0 ? n : (size_t)n * g.Cout);
+      for (int c = 0; c < Cg; ++c) sum = fmaf(a[c], b[MODE == 0 ? (size_t)c * g.Cout : c], sum);
+    }
+  }
+  out[o] = skip != nullptr ? sum + skip[o] : sum;
+}
+
 // MODE 0: out[p][co] = sum_{tap, ci} a3[p at tap][ci] W[tap][ci][co] (+ skip)
 // MODE 1: out[p][ci] = sum_{tap, co} dy[p at tap][co] W[tap][ci][co]
 // STRIDED: stride other than 1 (in mode 1 a tap then reaches only every stride-th pixel).
@@ -349,6 +377,12 @@ template <int MODE>
 int launch_ragged(hipStream_t st, const ConvGeom& g, const float* in, const float* w, const float* skip, float* out) {
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
   const int64_t Mg = MODE == 0 ? (int64_t)g.N * g.Ho * g.Wo : (int64_t)g.N * g.H * g.W;
+  // (1x1, us, a thread per output / tiles: 3 -> 16 @112x112 N=8, 1.6 10^6 outputs, 7.7 / 11.4; 7 -> 9 8.1 / 10.3; gradient
+  // 16 <- 5 9.7 / 11.8; but 16 -> 5 12.6 / 10.1, 10 -> 64 30.7 / 22.5, gradient 64 <- 3, 6.4 10^6 outputs, 29.2 / 24.0)
+  if (g.R * g.S * (MODE == 0 ? g.Cin : g.Cout) <= 9 && Mg * Ng < 3000000) {
+    direct_conv_kernel<MODE><<<(unsigned)((Mg * Ng + kThreads - 1) / kThreads), kThreads, 0, st>>>(in, w, skip, out, g);
+    return hip_status();
+  }
   const int nt = ragged_nt(Ng);
   const dim3 grid = grid_of(((Mg + RB_M - 1) / RB_M) * ((Ng + 16 * nt - 1) / (16 * nt)));
   constexpr bool ST = MODE == 1;   // (the forward only multiplies by the stride)
@@ -382,6 +416,10 @@ int ragged_wgrad_copies(const ConvGeom& g, size_t room) {
   const int64_t MR = (int64_t)g.R * g.S * g.Cin;
   const int64_t tiles = ((MR + RB_M - 1) / RB_M) * ((g.Cout + 16 * nt - 1) / (16 * nt));
   const int64_t chunks = ((int64_t)g.N * g.Ho * g.Wo + RB_K - 1) / RB_K;
+  // A block per element of dW is over sooner than a walk over chunks, and needs no launch to sum copies (backward, us,
+  // elements / chunks: 1x1 64 -> 10 @14x14 N=16, 2.0 10^6 products, 26.5 / 30.4; 20 -> 36, 2.3 10^6, 27.0 / 33.2; 512 ->
+  // 10 on 128 pixels 23.1 / 28.0; but 33 -> 65 @14x14, 6.7 10^6, 49.5 / 38.7).
+  if (MR * g.Cout * (int64_t)g.N * g.Ho * g.Wo < 2500000) return 0;
   // about four blocks per compute unit, at least four chunks each (a chunk is a round trip to memory)
   int64_t split = 1024 / tiles;
   if (split > chunks / 4) split = chunks / 4;
