@@ -188,6 +188,11 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   return 0;
 }
 
+// Path 1 on the split-operand kernel (the halo kernel otherwise): rows of its sums of y, 0 = no.
+int fused_on_split(const abl_shape& s, const ConvGeom& g, int K, bool bf16) {
+  return !bf16 && forward_fused_path(s, g, K, bf16, false) == 1 ? split_fused_blocks(g) : 0;
+}
+
 // Forward: statistics -> (normalise, ReLU, quantize, pack) -> convolution.  A3 lives in the
 // workspace only until the convolution has read it (Sec. 3.2: full-precision intermediates
 // are overwritten as soon as they have been used); 'same' stride-1 convolutions do not even
@@ -216,7 +221,7 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
   // 'same' stride-1 convolutions normalise, quantize and pack while they stage their input
   // patch: x is read once and A3 never reaches memory.  (Not when y aliases x: a block would
   // overwrite input pixels that a neighbouring block has not staged yet.)
-  if (const int nb = path == 1 && !bf16 ? split_fused_blocks(g) : 0) {
+  if (const int nb = path == 1 ? fused_on_split(*s, g, K, bf16) : 0) {
     if (int e = launch_split_fwd_fused(st, g, K, x, stats, W, skip, y, packed, out_partial)) return e;
     if (out_partial != nullptr && out_nb != nullptr) *out_nb = nb;
     return ABL_OK;
@@ -430,12 +435,13 @@ int abl_bn_conv_fwd(void* stream, const abl_shape* s, int K, uint32_t flags, con
       (skip != nullptr && !aligned16(skip)) || static_cast<const void*>(x) == static_cast<const void*>(y))
     return ABL_ERR_ARG;
   const ConvGeom g = geom_of(*s);
+  const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   if (igemm_fused_supported(*s))
-    return launch_conv_fwd_fused((hipStream_t)stream, *s, K, (flags & ABL_MATH_BF16) != 0, x, stats, W, skip, y,
-                                 packed);
+    return launch_conv_fwd_fused((hipStream_t)stream, *s, K, bf16, x, stats, W, skip, y, packed);
+  if (fused_on_split(*s, g, K, bf16))   // (as abl_forward does)
+    return launch_split_fwd_fused((hipStream_t)stream, g, K, x, stats, W, skip, y, packed, nullptr);
   if (!halo_fused_supported(g)) return ABL_ERR_SHAPE;
-  return launch_halo_fwd_fused((hipStream_t)stream, g, K, (flags & ABL_MATH_BF16) != 0, x, stats, W, skip, y,
-                               packed, nullptr);
+  return launch_halo_fwd_fused((hipStream_t)stream, g, K, bf16, x, stats, W, skip, y, packed, nullptr);
 }
 
 }  // extern "C"

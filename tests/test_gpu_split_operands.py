@@ -320,3 +320,26 @@ def test_fused_forward_with_weights_the_split_cannot_carry(s):
     B.abl_forward(s9, 4, x, w, gamma, beta, None, scratch, y, packed, stats)
     B.abl_bn_relu_pack(x, N * H * W, ci, 4, stats, a3, packed)
     assert_same_kind(y, conv64(a3, w))
+
+
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("s", [SHAPES[3], SHAPES[4], SHAPES[5], SHAPES[7], SHAPES[6], (20, 28, 28, 64, 256, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_fused_stage_is_the_layers_kernel(s, K):
+    """Where abl_forward_is_fused answers 1, abl_bn_conv_fwd runs what abl_forward runs: the same output, bit for bit."""
+    print("case split operands, fused stage", s, K, flush=True)
+    x, w, skip = draw(s)
+    N, H, W, ci, co, R = s
+    s9 = shape9(s)
+    assert B.abl_forward_is_fused(s9, K)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    gamma, beta = torch.rand(ci, device="cuda", generator=g) + 0.5, torch.randn(ci, device="cuda", generator=g) * 0.1
+
+    def raw(n):
+        return torch.full((n,), 0xA5, dtype=torch.uint8, device="cuda")
+
+    y, packed, stats = torch.empty_like(skip), raw(B.abl_packed_bytes(s9, K)), raw(32 * ci)
+    B.abl_forward(s9, K, x, w, gamma, beta, skip, raw(B.abl_scratch_bytes(s9, K)), y, packed, stats)
+    y2, packed2 = torch.empty_like(skip), raw(B.abl_packed_bytes(s9, K))
+    B.abl_bn_conv_fwd(s9, K, x, stats, w, skip, y2, packed2)
+    assert torch.equal(y, y2) and torch.equal(packed, packed2)
