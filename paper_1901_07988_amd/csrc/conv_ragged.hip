@@ -378,8 +378,10 @@ int launch_ragged(hipStream_t st, const ConvGeom& g, const float* in, const floa
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
   const int64_t Mg = MODE == 0 ? (int64_t)g.N * g.Ho * g.Wo : (int64_t)g.N * g.H * g.W;
   // (1x1, us, a thread per output / tiles: 3 -> 16 @112x112 N=8, 1.6 10^6 outputs, 7.7 / 11.4; 7 -> 9 8.1 / 10.3; gradient
-  // 16 <- 5 9.7 / 11.8; but 16 -> 5 12.6 / 10.1, 10 -> 64 30.7 / 22.5, gradient 64 <- 3, 6.4 10^6 outputs, 29.2 / 24.0)
-  if (g.R * g.S * (MODE == 0 ? g.Cin : g.Cout) <= 9 && Mg * Ng < 3000000) {
+  // 16 <- 5 9.7 / 11.8; but 16 -> 5 12.6 / 10.1, 10 -> 64 30.7 / 22.5, gradient 64 <- 3, 6.4 10^6 outputs, 29.2 / 24.0.  Up to
+  // 16 elements on few outputs: a chunk's round trip is all there is; backward of 512 -> 10 on 128 pixels 22.5 / 25.9)
+  const int kk = g.R * g.S * (MODE == 0 ? g.Cin : g.Cout);
+  if ((kk <= 9 && Mg * Ng < 3000000) || (kk <= 16 && Mg * Ng < 100000)) {
     direct_conv_kernel<MODE><<<(unsigned)((Mg * Ng + kThreads - 1) / kThreads), kThreads, 0, st>>>(in, w, skip, out, g);
     return hip_status();
   }
