@@ -447,15 +447,16 @@ int abl_bn_conv_fwd(void* stream, const abl_shape* s, int K, uint32_t flags, con
 }  // extern "C"
 
 namespace {
-// Shapes that abl_conv_dgrad_bn_reduce has always taken (the layer calls use the split kernels' sums beyond them): 1x1
-// with at most 256 output channels, or 512 and more in 224 to 2048 blocks of about 200 rows x 64 channels; 3x3 with one
-// row of sums per image or per tile of at most kMaxPartialBlocks.
+// Shapes that abl_conv_dgrad_bn_reduce has always taken (include/abl.h names them; the layer calls use the split kernels'
+// sums beyond them): 1x1 with at most 256 output channels, or 512 and more in 224 to 2048 blocks of about 200 rows x 64
+// channels; 3x3 with one row of sums per image or per tile of at most kMaxPartialBlocks.
 bool reduce_stage_accepts(const ConvGeom& g) {
   if (g.R == 1) {
     const int64_t M = (int64_t)g.N * g.H * g.W;
     const int hw = g.H * g.W, rb = hw > 104 && hw <= 208 ? hw : 208;
     const int64_t nrb = (M + rb - 1) / rb, blocks = nrb * (g.Cin / 64);
-    return g.Cout <= 256 || (g.Cout >= 512 && nrb <= kMaxPartialBlocks && blocks >= 224 && blocks <= 2048);
+    return g.Cout <= 256 || (g.Cout >= 512 && M * g.Cout < ((int64_t)1 << 30) && nrb <= kMaxPartialBlocks && blocks >= 224 &&
+                             blocks <= 2048);
   }
   const int tiles = halo_conv_supported(g) ? halo_tile_count(g, 1) : 0;
   return image_f32_supported(g, 1) || (tiles > 0 && tiles <= kMaxPartialBlocks);
@@ -481,13 +482,13 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
                                      static_cast<double*>(scratch));
   }
   if (!halo_conv_supported(g) && pointwise_supported(g, 1)) {  // 1x1 stride 1: the pointwise kernel's epilogue
+    if (g.Cout > 256) return ABL_ERR_SHAPE;   // (its longer contractions keep no sums)
     int r = 0;
     if (int e = launch_pointwise_dgrad_reduce((hipStream_t)stream, g, K, (flags & ABL_MATH_BF16) != 0, dy, W, packed,
                                               stats, da3, static_cast<double*>(scratch), &r))
       return e;
     *rows = r;
-    // contractions of more than 256 channels run without the sums: dA3 is written, no rows
-    return r > 0 ? ABL_OK : ABL_ERR_SHAPE;
+    return ABL_OK;
   }
   if (!(flags & ABL_MATH_BF16) && image_f32_supported(g, 1)) {  // small images: one row of sums per image
     *rows = g.N;

@@ -137,3 +137,14 @@ def test_forward_path_query(B):
     with pytest.raises(B.AblError) as e:
         B.abl_forward_is_fused((64, 56, 56, 64, 64, 3, 3, 1, 1), 5)
     assert e.value.code == B.ABL_ERR_ARG
+
+
+@pytest.mark.parametrize("shape,flags", [((2, 5, 5, 256, 1024, 1, 1, 1, 0), 0), ((64, 14, 14, 256, 320, 1, 1, 1, 0), 0),
+                                         ((64, 14, 14, 256, 1024, 1, 1, 1, 0), 2), ((2, 5, 5, 256, 48, 1, 1, 1, 0), 0)])
+def test_gradient_with_sums_refuses_before_any_launch(B, shape, flags):
+    """Contractions that have no sums are an invalid shape, told before anything is launched on the made-up addresses
+    (which would be a launch failure here, and wrong work where there is a GPU)."""
+    rows = ctypes.c_int32(7)
+    r = B.lib.abl_conv_dgrad_bn_reduce(None, ctypes.byref(B.shape_struct(shape)), 4, flags, 16, 32, 48, 64, 80, 1 << 30, 96,
+                                       ctypes.byref(rows))
+    assert r == B.ABL_ERR_SHAPE and rows.value == 7
