@@ -24,6 +24,8 @@ SHAPES = [
     (3, 141, 143, 192, 64, 1),   # several tiles to a block
 ]
 IDS = ["x".join(map(str, s)) for s in SHAPES]
+# layers whose gradient with the sums is not taken as a stage of its own (more than 512 tiles of the halo kernel)
+STAGE_REFUSES = [(12, 57, 57, 64, 64, 3), (40, 56, 56, 64, 64, 3)]
 
 
 def shape9(s):
@@ -122,11 +124,12 @@ def test_sums_of_the_gradient(s, K):
     B.abl_backward(s9, K, packed, stats, dy, w, scratch, dx, dW, dg, db)
     for got, ref, bound in zip((db, dg), refs, bounds):
         assert float((got.double() - ref).abs().max()) <= bound + 2.0 ** -24 * float(ref.abs().max())
-    try:
-        rows = B.abl_conv_dgrad_bn_reduce(s9, K, dy, w, packed, stats, scratch, da3)
-    except B.AblError as e:   # (the stage on its own does not take every shape that the layer does)
-        assert e.code == B.ABL_ERR_SHAPE
+    if s in STAGE_REFUSES:
+        with pytest.raises(B.AblError) as e:
+            B.abl_conv_dgrad_bn_reduce(s9, K, dy, w, packed, stats, scratch, da3)
+        assert e.value.code == B.ABL_ERR_SHAPE
         return
+    rows = B.abl_conv_dgrad_bn_reduce(s9, K, dy, w, packed, stats, scratch, da3)
     assert torch.equal(da3, plain)
     sums = scratch[: rows * 2 * ci * 8].view(torch.float64).view(rows, 2, ci).sum(0)
     for got, ref, bound in zip(sums, refs, bounds):
