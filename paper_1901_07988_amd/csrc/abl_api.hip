@@ -1,7 +1,36 @@
 // C ABI of libabl: argument validation, workspace carving and the order in which the
 // kernels of one layer step (and of a residual stack) are enqueued.  No device code here.
 
+#include <mutex>
+#include <set>
+#include <utility>
+
 #include "abl_internal.h"
+
+namespace abl {
+
+int allow_full_lds(const void* kern) {
+  static std::mutex mu;
+  static std::set<std::pair<int, const void*>> done;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return ABL_ERR_HIP;
+  }
+  try {   // (no exception may leave the C entry points: without memory the kernel is asked for again next time)
+    const std::lock_guard<std::mutex> lock(mu);
+    if (done.count({dev, kern}) != 0) return ABL_OK;
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+      (void)hipGetLastError();
+      return ABL_ERR_HIP;
+    }
+    done.insert({dev, kern});
+  } catch (...) {
+  }
+  return ABL_OK;
+}
+
+}  // namespace abl
 
 using namespace abl;
 

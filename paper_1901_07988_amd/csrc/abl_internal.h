@@ -382,6 +382,10 @@ inline dim3 grid_of(int64_t blocks) {
 }
 __device__ inline uint32_t block_of_grid() { return blockIdx.x + gridDim.x * blockIdx.y; }
 
+// More than the default 64 KB of LDS per block has to be asked for, once per kernel and device (the full 160 KB, so that
+// the answer does not depend on the first shape seen); any thread.  An ABL_ code.
+int allow_full_lds(const void* kern);
+
 inline int hip_status() { return hipGetLastError() == hipSuccess ? ABL_OK : ABL_ERR_HIP; }
 
 }  // namespace abl

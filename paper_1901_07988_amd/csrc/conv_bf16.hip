@@ -18,10 +18,6 @@
 // The MFMA computes the transposed tile (first operand = weights), so a lane ends up with four
 // consecutive channels of one pixel: 16-byte stores and shortcut loads.
 
-#include <mutex>
-#include <set>
-#include <utility>
-
 #include "abl_internal.h"
 
 namespace abl {
@@ -691,28 +687,6 @@ bool image_bf16_supported(const ConvGeom& g, int mode) {
 }
 
 namespace {
-// more than the default 64 KB of LDS per block has to be asked for, once per kernel and device
-// (the full 160 KB, so that the answer does not depend on the first shape seen)
-int allow_full_lds_bf16(const void* kern) {
-  static std::mutex mu;
-  static std::set<std::pair<int, const void*>> done;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return ABL_ERR_HIP;
-  }
-  const std::pair<int, const void*> key(dev, kern);
-  std::lock_guard<std::mutex> lock(mu);
-  if (done.find(key) == done.end()) {
-    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
-      (void)hipGetLastError();
-      return ABL_ERR_HIP;
-    }
-    done.insert(key);
-  }
-  return ABL_OK;
-}
-
 template <int MODE, int EPI>
 int launch_image(hipStream_t st, const ConvGeom& g, const float* in, const float* w, const float* skip, float* out,
                  double* sums, const uint8_t* codes, const float* stats) {
@@ -722,7 +696,7 @@ int launch_image(hipStream_t st, const ConvGeom& g, const float* in, const float
   const unsigned grid = (unsigned)((g.N + 7) / 8 * 8 * (Ng / IMG_NB));
   auto kern = mt == 4 ? image_bf16_kernel<MODE, 4, EPI> : mt == 8 ? image_bf16_kernel<MODE, 8, EPI>
                                                                    : image_bf16_kernel<MODE, 13, EPI>;
-  if (int e = allow_full_lds_bf16(reinterpret_cast<const void*>(kern))) return e;
+  if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
   kern<<<grid, kThreads, lds, st>>>(in, w, skip, out, sums, g, codes, stats);
   return hip_status();
 }

@@ -28,10 +28,7 @@
 // k-step.  The compiler does not know these are matrix-core results, so the wait states they need
 // before another kind of instruction reads them are inserted by hand after the loop.
 
-#include <mutex>
-#include <set>
 #include <type_traits>
-#include <utility>
 
 #include "abl_internal.h"
 
@@ -41,28 +38,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int IMG_NB = 64;    // output channels per block
 constexpr int IMG_PC = 64;    // contraction channels per phase; two phases' patches are resident
-
-// More than the default 64 KB of LDS per block has to be asked for, once per kernel and device (the
-// full 160 KB, so that the answer does not depend on the first shape seen).
-int allow_full_lds(const void* kern) {
-  static std::mutex mu;
-  static std::set<std::pair<int, const void*>> done;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return ABL_ERR_HIP;
-  }
-  const std::pair<int, const void*> key(dev, kern);
-  std::lock_guard<std::mutex> lock(mu);
-  if (done.find(key) == done.end()) {
-    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
-      (void)hipGetLastError();
-      return ABL_ERR_HIP;
-    }
-    done.insert(key);
-  }
-  return ABL_OK;
-}
 
 template <int MODE, int MT, int EPI>
 __global__ __launch_bounds__(kThreads, 1) void image_f32_kernel(const float* __restrict__ in,

@@ -537,7 +537,10 @@ int resident_blocks(const void* kern, int threads) {
     (void)hipGetLastError();
     n = 1;
   }
-  cache.emplace(kern, n);
+  try {   // (no exception may leave the C entry points: without memory the runtime is asked again next time)
+    cache.emplace(kern, n);
+  } catch (...) {
+  }
   return n;
 }
 

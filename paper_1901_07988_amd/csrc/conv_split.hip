@@ -27,9 +27,6 @@
 // SIMD also where a layer gives only one block per compute unit - and the patch has two buffers.
 // KS = 1: one buffer, two blocks per compute unit cover each other's staging.
 // With bf16 operands (ABL_MATH_BF16) the same kernel runs with one part per operand: rounded once, one product.
-#include <mutex>
-#include <set>
-#include <utility>
 
 #include "abl_internal.h"
 
@@ -38,26 +35,6 @@ namespace {
 
 constexpr int MT = 7;   // 16-pixel tiles per wave and block
 constexpr int WN = 4;   // waves along the output channels
-
-int allow_full_lds(const void* kern) {
-  static std::mutex mu;
-  static std::set<std::pair<int, const void*>> done;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return ABL_ERR_HIP;
-  }
-  const std::pair<int, const void*> key(dev, kern);
-  std::lock_guard<std::mutex> lock(mu);
-  if (done.find(key) == done.end()) {
-    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
-      (void)hipGetLastError();
-      return ABL_ERR_HIP;
-    }
-    done.insert(key);
-  }
-  return ABL_OK;
-}
 
 struct Tiling {
   int run;           // pixels per tile

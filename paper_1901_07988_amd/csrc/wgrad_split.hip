@@ -27,10 +27,7 @@
 // stages the next chunk the other contracts this one and then they change places, so that on every SIMD the
 // staging arithmetic of a wave runs under the MFMAs of another.  Each share of the pixels leaves its own copy of
 // dW, summed in a fixed order by the caller's launch.
-#include <mutex>
-#include <set>
 #include <type_traits>
-#include <utility>
 
 #include "abl_internal.h"
 
@@ -41,26 +38,6 @@ constexpr int TCI = 32, TCO = 64, THREADS = 512;
 constexpr int POS = 128;                         // positions of dy per chunk
 constexpr int DPART = POS / 8 * TCO * 16;        // bytes of one part of dy
 constexpr int AGRP = TCI * 16;                   // bytes of a group of v
-
-int allow_full_lds(const void* kern) {
-  static std::mutex mu;
-  static std::set<std::pair<int, const void*>> done;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return ABL_ERR_HIP;
-  }
-  const std::pair<int, const void*> key(dev, kern);
-  std::lock_guard<std::mutex> lock(mu);
-  if (done.find(key) == done.end()) {
-    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
-      (void)hipGetLastError();
-      return ABL_ERR_HIP;
-    }
-    done.insert(key);
-  }
-  return ABL_OK;
-}
 
 constexpr float kUp = 0x1p23f, kDown = 0x1p-23f;   // dy is split as 2^23 times its values: the parts of the smallest are normal
 
