@@ -855,8 +855,9 @@ int launch_igemm(hipStream_t st, const ConvGeom& g, bool bf16, const float* in, 
     } else {
       ABL_IGEMM(128, 64, 64, 32, 32);
     }
-  } else if (blocks(256, 32) < 512) {  // small grids: a quarter of the pixels per block (3x3 stride 2 16 -> 32 @32x32 N=128,
-    // 128 blocks: layer step 80 us; 512 blocks 74)
+  } else if (blocks(256, 32) < (MODE == 0 ? 512 : 192)) {  // small grids: a quarter of the pixels per block (3x3 stride 2
+    // @32x32, us, tiles of 64 / 256 pixels: forward 16 -> 32 N=127, 127 blocks of 256, 9.3 / 15.0, 32 -> 16 10.6 / 18.1; gradient,
+    // which reads weights for every tile, 16 <- 16 N=40, 160 blocks, 10.6 / 11.4, N=64, 256 blocks, 12.8 / 12.0, N=127 21.3 / 15.1)
     if (Cg % 32 == 0) {
       if (Ng > 16) ABL_IGEMM(64, 32, 32, 16, 32);
       else ABL_IGEMM(64, 16, 16, 16, 32);

@@ -7,13 +7,14 @@ from paper_1901_07988_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 
-# N, H, W, Cin, Cout; 3x3, stride 2, padding 1.  512 blocks of 256 x 32 outputs: 131072 pixels
+# N, H, W, Cin, Cout; 3x3, stride 2, padding 1.  Forward: 512 blocks of 256 x 32 outputs, 131072 pixels; data gradient:
+# 192 blocks, 49152 pixels in four classes
 SHAPES = [
-    (127, 64, 64, 16, 32),    # forward below (130 048 pixels), data gradient beyond
+    (127, 64, 64, 16, 32),    # forward below, data gradient far beyond
     (128, 64, 64, 16, 32),    # forward at 512 blocks
     (130, 63, 65, 32, 16),    # 32-channel chunks, odd sizes
-    (33, 64, 64, 16, 16),     # data gradient (135 168 pixels in four classes) beyond, forward below
-    (31, 64, 64, 32, 32),     # data gradient below
+    (47, 32, 32, 16, 16),     # data gradient below
+    (48, 32, 32, 32, 32),     # data gradient at 192 blocks
     (9, 31, 33, 48, 16),
 ]
 
