@@ -203,11 +203,9 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   // once in the fused kernel wins)
   const bool bf16_gemm = bf16 && bf16_gemm_supported(g, 0) && 2 * g.Cout * g.R * g.S >= 512;
   if (K == 32 || naive || bf16_gemm) return 0;
-  // Split operands: 1x1 layers from 128 channels on both sides on are faster with the pack pass in front (28x28 128 ->
-  // 256: 51 us against 53.5; 14x14 256 -> 256: 33 against 37; but 56x56 64 -> 256 103 against 96 and 256 -> 64 185
-  // against 129: there reading x once wins).
-  // (And with contractions of 512 channels and more: 1024 -> 256 at 14x14 17 + 45 us against 81.)
-  if (!bf16 && g.R == 1 && (s.Cin >= 512 || (s.Cin >= 128 && s.Cout >= 128)) && split_conv_blocks(g, 0) > 0) return 0;
+  // Split operands, 1x1: long contractions are faster with the pack pass in front (14x14 1024 -> 256 17 + 45 us against 81);
+  // elsewhere reading x once wins (56x56 256 -> 64 129 against 185).
+  if (!bf16 && split_beats_prologue(g)) return 0;
   // (Not for the small images of the image-resident kernel: the pack pass plus that kernel is
   // faster than the fused one.)
   if (halo_fused_supported(g) && !(!bf16 && image_f32_supported(g, 0))) return 1;

@@ -78,8 +78,8 @@ bool halo_fused_supported(const ConvGeom& g);
 // out_partial (nullable): [tiles][2][Cout] doubles = per-tile sum(y), sum(y^2) of the output,
 // the first pass of the next layer's statistics.  halo_tile_count gives `tiles` (0: unsupported).
 int halo_tile_count(const ConvGeom& g, int mode);
-// The layer takes tiles of 64 pixels, and at most one block per compute unit of them.
-bool halo_in_one_round(const ConvGeom& g, int mode);
+// Pixels of its tiles and its blocks for this layer; false: not supported.
+bool halo_grid(const ConvGeom& g, int mode, int* pixels, int64_t* blocks);
 int launch_halo_fwd_fused(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* x,
                           const void* stats, const float* w, const float* skip, float* y, void* packed,
                           double* out_partial);
@@ -177,6 +177,9 @@ int launch_image_bf16(hipStream_t st, const ConvGeom& g, int mode, const float* 
 // bf16: operands rounded to bf16 instead.
 // sums: with the Eq. 6-7 sums (launch_split_dgrad_reduce).
 int split_conv_blocks(const ConvGeom& g, int mode, bool bf16 = false, bool sums = false);
+// The fp32 forward of a 1x1 layer with a pass of its own for Eq. 1-3 and 9 in front is faster than the pointwise kernel's
+// prologue.
+bool split_beats_prologue(const ConvGeom& g);
 int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
                       const float* skip, float* out, double* sums);
 // The 3x3 forward with Eq. 1-3 and Eq. 9 applied while the patch is staged (fp32 operands, y not x).

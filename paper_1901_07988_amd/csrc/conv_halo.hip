@@ -1299,12 +1299,13 @@ int halo_tile_count(const ConvGeom& g, int mode) {
   return p.tiles_i * p.tiles_h * p.tiles_w;
 }
 
-bool halo_in_one_round(const ConvGeom& g, int mode) {
-  // (256 blocks of 64 pixels and 64 channels: no need to look for tiles beyond that)
-  if ((int64_t)g.N * g.H * g.W * (mode == 0 ? g.Cout : g.Cin) > 256 * 64 * 64) return false;
+bool halo_grid(const ConvGeom& g, int mode, int* pixels, int64_t* blocks) {
   HaloPlan p;
-  return halo_conv_supported(g) && make_plan(g, mode, p) && kVariants[p.variant].mt * 16 == 64 && p.bn == 64 &&
-         (int64_t)p.tiles_i * p.tiles_h * p.tiles_w * p.nblk_n <= 256;
+  if (!halo_conv_supported(g) || !make_plan(g, mode, p)) return false;
+  const Variant& v = kVariants[p.variant];
+  *pixels = v.nw / v.waves_n * v.mt * 16;
+  *blocks = (int64_t)p.tiles_i * p.tiles_h * p.tiles_w * p.nblk_n;
+  return true;
 }
 
 int launch_halo_fwd_fused(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* x,

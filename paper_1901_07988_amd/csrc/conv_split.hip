@@ -612,6 +612,30 @@ bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
   return p.lds <= (size_t)160 * 1024;
 }
 
+// Whether the halo kernel is the faster one on a 3x3 layer's four-wave grid (fp32).  Its tiles of 64 pixels, all in one
+// round of the compute units, take less than a 112-pixel tile here (us, 64 input channels, here / halo kernel: 64 -> 64
+// @32x32 N=14 19.5 / 15.4, N=24, two rounds, 20.4 / 38.2; 128 -> 128 @28x28 N=8 step 41.1 / 37.7, N=16 43.0 / 57.0).  A patch
+// of more than 256 positions (cross-image runs of 32-pixel-wide images, rows of 57) leaves LDS for one block per unit
+// only; a tile then takes 18.3 us per 64 input channels, the halo kernel 11.1 per round of 64 pixels, 20 of 128, 35.5 of
+// 224 (64 -> 64 @33x33 N=56, 273 blocks of two tiles, 70.7 / 43.5, N=48, 467 blocks, 38.8 / 48.3; @32x32 N=72, 330 of two,
+// 71.1 / 59.9, N=56, 512 blocks, 39.9 / 73.7; 128 -> 128 @40x40 N=10 66.8 / 46.8).  Where both take about the same and the
+// last round is no small remainder this kernel stays: its sums are the closer ones.
+bool halo_is_faster(const ConvGeom& g, int mode, const Plan& p) {
+  const int Ng = mode == 0 ? g.Cout : g.Cin;
+  const bool alone = p.su > 4;
+  // (256 blocks of 64 pixels and 64 channels at most: no need to ask for a plan beyond)
+  if (!alone && (int64_t)g.N * g.H * g.W * Ng > 256 * 64 * 64) return false;
+  int pixels;
+  int64_t blocks;
+  if (!halo_grid(g, mode, &pixels, &blocks)) return false;
+  if (pixels == 64 && blocks <= 256) return true;
+  if (!alone) return false;
+  const int64_t rounds = (blocks + 255) / 256, n = (int64_t)p.tl.gm * (Ng / p.bn);
+  const double here = 1.5 + 18.3 * (double)(p.tl.per * ((n + 255) / 256));
+  const double there = pixels == 64 ? 3.7 + 11.1 * rounds : pixels == 128 ? 3.0 + 20.0 * rounds : 2.5 + 35.5 * rounds;
+  return (n % 256 == 0 || n % 256 >= 64 ? 1.03 : 1.0) * there < here;
+}
+
 // Whether a grid of four-wave blocks - two to a compute unit, 512 at a time - is faster than the kernel that would
 // run otherwise.  A grid a little over one block per unit, or a little over 512, takes as long as a much larger one (the
 // units with one block more decide), while the other kernels' tiles may just fit.  (us, here / the other kernel, n blocks.
@@ -621,15 +645,19 @@ bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
 // @28x28 N=10, n = 280, 10.4 / 9.0, N=12, n = 336, 10.7 / 11.5, N=20, n = 560, 14.5 / 13.2, N=24, n = 672, 14.7 / 17.2;
 // 64 -> 256 @56x56 N=14, n = 784, 15.3 / 13.4; 512 -> 128 @28x28 N=40, n = 280, 23.8 / 18.9, N=56, n = 392, 24.9 / 23.7;
 // gradient 256 <- 1024 @14x14 N=40, n = 280, 30.3 / 24.5.  bf16 3x3: 64 -> 64 @56x56 of two tiles per block N=20,
-// n = 280, 24.5 / 21.1; gradient 128 <- 128 @28x28 N=40, n = 280, 43.6 / 36.7.)
+// n = 280, 24.5 / 21.1; 64 -> 64 @57x57 of two tiles, patches of more than 256 positions, N=27, step 53.5 / 46.9; 128 ->
+// 128 @60x60 N=10, n = 644, 47.4 / 42.8, N=14, n = 900, 54.8 / 60.2, its gradient 62.8 / 53.4; gradient 128 <- 128 @28x28 N=40, n = 280 of 128 channels, 43.6 / 36.7, 256 <- 256
+// @17x17 N=100, n = 518, 120.7 / 89.6.)
 bool four_waves_pay(const ConvGeom& g, int mode, int np, bool sums, const Plan& p) {
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
   const int64_t n = (int64_t)p.tl.gm * (Ng / p.bn);
-  const bool over_one = n > 256 && n < 320, over_two = n > 512 && n < 640, over_three = n > 768 && n < 832;
+  const bool over_one = n > 256 && n < 320, over_two = n > 512 && n < 660, over_three = n > 768 && n < 832;
   const bool first = n > 256 && n < 400;   // the first round less than three quarters full
   if (g.R == 3) {
-    if (np == 3) return p.nt == 2 || !halo_in_one_round(g, mode);
-    return sums || !((p.tl.per > 1 && over_one) || (mode == 1 && p.nt == 2 && first));
+    if (np == 3) return p.nt == 2 || !halo_is_faster(g, mode, p);
+    if (sums) return true;
+    if (mode == 1 && p.nt == 2) return n <= 256;
+    return !(p.tl.per > 1 && over_one) && !(p.su > 4 && (p.tl.per > 1 || over_two || (mode == 1 && n > 512)));
   }
   // with the Eq. 6-7 sums the other kernels need a pass of their own or lose their weight gradient's launch: fp32 is faster
   // here throughout, bf16 with 64 channels per block and less than 1024 to contract only (1024 <- 256 @14x14 N=40,
@@ -659,7 +687,11 @@ bool make_plan(const ConvGeom& g, int mode, int np, bool sums, Plan& p) {
     for (int ks = 2; ks >= 1; --ks) {
       if (!fit_plan(g, mode, np, nt, ks, p)) continue;
       const int64_t blocks = (int64_t)p.tl.gm * (Ng / p.bn);
-      if (blocks >= (nt == 2 ? 200 : 96) && (ks == 1 || blocks <= 256)) return ks == 2 || four_waves_pay(g, mode, np, sums, p);
+      if (blocks < (nt == 2 ? 200 : 96) || (ks == 2 && blocks > 256)) continue;
+      // (the gradient of 1x1 layers with 64 channels to contract and more to write: two groups of waves have nothing to share;
+      // exact storage 256 <- 64 @16x16 N=12, backward 32.4 us against the pointwise kernel's 30.1)
+      if (ks == 2) return k3 || np != 3 || sums || mode == 0 || Cg >= 128 || Ng < 128;
+      return four_waves_pay(g, mode, np, sums, p);
     }
   return false;
 }
@@ -706,15 +738,9 @@ int launch_fused(hipStream_t st, const ConvGeom& g, const Plan& p, const float* 
 }
 
 // The fused forward: 64 output channels per block (the constants of Eq. 1-3 take the registers of the second tile) in
-// four waves, where the halo kernel's tiles of 64 pixels need more than one round of the compute units: such a round takes
-// as long as a 112-pixel tile here (forward step, us, here / halo kernel: 64 -> 64 @32x32 N=16 30.3 / 25.7, N=24 32.5 /
-// 54.0; 128 -> 128 @28x28 N=8 41.1 / 37.7, N=16 43.0 / 57.0; 256 -> 256 @14x14 N=16 70.7 / 65.1, N=32 73.3 / 101.3).
-// Blocks of two tiles each, little more of them than compute units, leave most units idle half the time (64 -> 64 @32x32
-// N=64, 293 blocks: 93.9 / 90.4).
+// four waves.
 bool make_fused_plan(const ConvGeom& g, Plan& p) {
-  if (g.R != 3 || !make_plan(g, 0, 3, false, p) || halo_in_one_round(g, 0) || !fit_plan(g, 0, 3, 1, 1, p)) return false;
-  const int64_t n = (int64_t)p.tl.gm * (g.Cout / p.bn);
-  return p.tl.per == 1 || n <= 256 || n >= 320;
+  return g.R == 3 && make_plan(g, 0, 3, false, p) && fit_plan(g, 0, 3, 1, 1, p) && !halo_is_faster(g, 0, p);
 }
 
 }  // namespace
@@ -722,6 +748,18 @@ bool make_fused_plan(const ConvGeom& g, Plan& p) {
 int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
   Plan p;
   return make_plan(g, mode, bf16 ? 1 : 3, sums, p) ? p.tl.gm : 0;
+}
+
+// Four-wave grids that fill less than three quarters of their 512 places are not (512 -> 128 @28x28, step, us, with the
+// pass / with the prologue: N=16, eight-wave blocks, 40.0 / 41.6; N=24, n = 336, 56.7 / 53.0; N=28, n = 392, 59.9 / 64.9),
+// nor are shorter contractions, but for 256 -> 256 (128 -> 256 @28x28 N=5 18.4 / 15.8, N=24 34.5 / 30.8, N=56 50.2 / 47.4;
+// 256 -> 128 @14x14 N=40 26.6 / 21.9; 320 -> 192 @13x13 N=56 40.8 / 31.7; but 384 -> 192 @28x28 N=20 45.1 / 53.1, 256 -> 256
+// @14x14 N=56 34.3 / 37.2; @28x28 N=40, n = 560, 62.7 / 59.7).
+bool split_beats_prologue(const ConvGeom& g) {
+  Plan p;
+  if (g.R != 1 || g.Cin < 256 || (g.Cin < 384 && g.Cout < 256) || !make_plan(g, 0, 3, false, p)) return false;
+  const int64_t n = (int64_t)p.tl.gm * (g.Cout / p.bn);
+  return p.ks == 2 || (p.nt == 2 ? g.Cin >= 384 || n <= 512 || n >= 660 : n >= 384);
 }
 
 int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
