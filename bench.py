@@ -24,20 +24,15 @@ MFMA_FP32_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix
 MFMA_BF16_PEAK_TFLOPS = 2500.0 # MI355X dense bf16 matrix
 
 
-def matrix_products(stage, s, math):
+def matrix_products(B, stage, s, K, flags):
     """bf16 products that the library spends on one fp32 product in this stage of an fp32 layer (its operands
-    split into three bf16 parts: six in the forward and the data gradient, three in the weight gradient from whole-
-    numbered codes), or 0: the products are the instruction's own."""
-    split = (math == "fp32" and s.stride == 1 and (s.R, s.S, s.pad) in ((1, 1, 0), (3, 3, 1)) and
-             s.Cin % 64 == 0 and s.Cout % 64 == 0)
-    if not split:
-        return 0
-    return {"conv_fwd": 6, "conv_dgrad": 6, "conv_dgrad_bn_reduce": 6, "conv_wgrad_packed": 3}.get(stage, 0)
+    split into bf16 parts), or 0: the products are the instruction's own."""
+    return B.abl_split_products(s.as_tuple(), K, stage, flags) if stage in B.STAGES else 0
 
 
-def mfma_frac(stage, s, math, tflops):
+def mfma_frac(B, stage, s, K, math, flags, tflops):
     """Share of the matrix cores' peak that a stage's rate takes, on the instruction it runs on."""
-    n = matrix_products(stage, s, math)
+    n = matrix_products(B, stage, s, K, flags)
     if n:
         return n * tflops / MFMA_BF16_PEAK_TFLOPS
     return tflops / (MFMA_BF16_PEAK_TFLOPS if math == "bf16" else MFMA_FP32_PEAK_TFLOPS)
@@ -425,14 +420,14 @@ def main():
     (dom_shape, dom_name), (_, dom) = max(per_step.items(),
                                           key=lambda kv: kv[1][0] * (1.0 if kv[1][1]["launches"] == 1 else 0.75))
     mfma_peak = MFMA_BF16_PEAK_TFLOPS if args.math == "bf16" else MFMA_FP32_PEAK_TFLOPS
-    frac = mfma_frac(dom_name, dom_shape, args.math, dom["tflops"])
+    frac = mfma_frac(B, dom_name, dom_shape, K, args.math, flags, dom["tflops"])
     flops_bound_ms = dom["ms"] * frac
     bytes_bound_ms = dom["bytes"] / (HBM_PEAK_GBS * 1e6)
     if dom["flops"] > 0 and flops_bound_ms >= bytes_bound_ms:
         # frac: the matrix cores' time at their peak over the kernel's; achieved: the same on the scale of the
         # fp32 (or bf16) matrix peak.  A kernel that spends several bf16 products on one fp32 product does more
         # useful work than that: useful_tflops
-        n = matrix_products(dom_name, dom_shape, args.math)
+        n = matrix_products(B, dom_name, dom_shape, K, flags)
         roof = {"bound": "mfma", "achieved": frac * mfma_peak, "peak": mfma_peak, "unit": "TFLOP/s", "frac": frac,
                 "useful_tflops": dom["tflops"], "bf16_products_per_fp32_product": n}
     else:
@@ -448,7 +443,7 @@ def main():
     roof["measured_mfma_ceiling_tflops"] = mfma_ceilings(G, B)
     # every contraction of the step against the peak of the matrix instruction that it runs on
     roof["contractions_frac_of_mfma_peak"] = {
-        "x".join(map(str, s.as_tuple())): {k: round(mfma_frac(k, s, args.math, v["tflops"]), 3) for k, v in bd.items()
+        "x".join(map(str, s.as_tuple())): {k: round(mfma_frac(B, k, s, K, args.math, flags, v["tflops"]), 3) for k, v in bd.items()
                                              if v["step"] and v["flops"] > 0}
         for s, bd in details.items()}
 

@@ -94,10 +94,22 @@ size_t abl_scratch_bytes(const abl_shape* shape, int K);
  * launches of a layer step): 1 = one kernel applies Eq. 1-3 and Eq. 9 while it stages the input of
  * the contraction (the one that abl_bn_conv_fwd launches), 0 = the normalise-ReLU-pack pass followed
  * by the plain contraction (abl_bn_relu_pack, abl_conv_fwd), also for shapes that abl_bn_conv_fwd
- * would take, where that is faster (1x1 layers of 128 channels and more on both sides, 3x3 layers on
- * small images).  Negative (an ABL_ERR_ code, negated) on invalid arguments.  flags as for
+ * would take, where that is faster (1x1 layers with long contractions, 3x3 layers on small images).
+ * Negative (an ABL_ERR_ code, negated) on invalid arguments.  flags as for
  * abl_forward. */
 int abl_forward_is_fused(const abl_shape* shape, int K, uint32_t flags);
+/* How the contraction of a stage call multiplies fp32 operands (for tools that relate its rate to the
+ * matrix cores'): the bf16 products that it spends on one fp32 product where it splits the operands
+ * (6; weight gradient 3, from codes that reach beyond one bf16 up to 9), or 0 where it does not (the
+ * fp32 matrix instruction, bf16 operands, a shape that the stage refuses).  flags as for the stage. */
+enum {
+  ABL_STAGE_CONV_FWD = 0,
+  ABL_STAGE_BN_CONV_FWD = 1,
+  ABL_STAGE_CONV_DGRAD = 2,
+  ABL_STAGE_CONV_DGRAD_BN_REDUCE = 3,
+  ABL_STAGE_CONV_WGRAD_PACKED = 4
+};
+int abl_split_products(const abl_shape* shape, int K, uint32_t flags, int stage);
 
 /* Forward of one layer (Sec. 3.2; Eq. 1-4 and Eq. 9).
  *   x      [N,H,W,Cin]      in

@@ -51,6 +51,7 @@ _SIGS = {
     "abl_stats_bytes": (_sz, [_shp]),
     "abl_scratch_bytes": (_sz, [_shp, ctypes.c_int]),
     "abl_forward_is_fused": (ctypes.c_int, [_shp, ctypes.c_int, ctypes.c_uint32]),
+    "abl_split_products": (ctypes.c_int, [_shp, ctypes.c_int, ctypes.c_uint32, ctypes.c_int]),
     "abl_bn_scratch_bytes": (_sz, [_i64, _i32]),
     "abl_wgrad_scratch_bytes": (_sz, [_shp]),
     "abl_forward": (ctypes.c_int, [_vp, _shp, ctypes.c_int, _u32, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp, _vp, _vp]),
@@ -148,6 +149,14 @@ def abl_forward_is_fused(shape, K, flags=0):
     if r < 0:
         raise AblError(-r, "abl_forward_is_fused")
     return r == 1
+
+
+STAGES = ("conv_fwd", "bn_conv_fwd", "conv_dgrad", "conv_dgrad_bn_reduce", "conv_wgrad_packed")
+
+
+def abl_split_products(shape, K, stage, flags=0):
+    """`stage`: one of STAGES."""
+    return lib.abl_split_products(ctypes.byref(shape_struct(shape)), K, flags, STAGES.index(stage))
 
 
 def abl_bn_scratch_bytes(M, C):

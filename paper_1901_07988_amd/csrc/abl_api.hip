@@ -529,6 +529,19 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
                                   da3, static_cast<double*>(scratch));
 }
 
+int abl_split_products(const abl_shape* s, int K, uint32_t flags, int stage) {
+  if (check_shape(s) != ABL_OK || check_k(K) != ABL_OK || (flags & ABL_MATH_BF16) != 0) return 0;
+  const ConvGeom g = geom_of(*s);
+  switch (stage) {
+    case ABL_STAGE_CONV_FWD: return split_conv_blocks(g, 0) > 0 ? 6 : 0;
+    case ABL_STAGE_BN_CONV_FWD: return K != 32 && !igemm_fused_supported(*s) && fused_on_split(*s, g, K, false) > 0 ? 6 : 0;
+    case ABL_STAGE_CONV_DGRAD: return split_conv_blocks(g, 1) > 0 ? 6 : 0;
+    case ABL_STAGE_CONV_DGRAD_BN_REDUCE: return K != 32 && reduce_stage_accepts(g) && split_conv_blocks(g, 1, false, true) > 0 ? 6 : 0;
+    case ABL_STAGE_CONV_WGRAD_PACKED: return split_wgrad_copies(g, K, false, wgrad_partial_bytes(*s)) > 0 ? 3 : 0;
+    default: return 0;
+  }
+}
+
 int abl_conv_bwd_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t flags, const float* dy, const float* W,
                            const void* packed, const void* stats, void* scratch, size_t scratch_bytes, float* da3,
                            float* dW, int32_t* rows) {

@@ -148,3 +148,17 @@ def test_gradient_with_sums_refuses_before_any_launch(B, shape, flags):
     r = B.lib.abl_conv_dgrad_bn_reduce(None, ctypes.byref(B.shape_struct(shape)), 4, flags, 16, 32, 48, 64, 80, 1 << 30, 96,
                                        ctypes.byref(rows))
     assert r == B.ABL_ERR_SHAPE and rows.value == 7
+
+
+def test_split_products_query(B):
+    """Which stages multiply in bf16 parts, from the shape alone: the deep 3x3 layer everywhere, the same layer on two
+    images, in exact storage or with bf16 operands where those have other kernels."""
+    deep, few = (64, 14, 14, 256, 256, 3, 3, 1, 1), (2, 14, 14, 256, 256, 3, 3, 1, 1)
+    assert [B.abl_split_products(deep, 4, n) for n in B.STAGES] == [6, 0, 6, 6, 3]      # (its forward is the plain one)
+    assert B.abl_split_products((64, 56, 56, 64, 64, 3, 3, 1, 1), 8, "bn_conv_fwd") == 6
+    assert [B.abl_split_products(few, 4, n) for n in B.STAGES] == [0] * 5
+    assert B.abl_split_products(deep, 32, "conv_wgrad_packed") == 0
+    assert B.abl_split_products(deep, 4, "conv_fwd", B.ABL_MATH_BF16) == 0
+    assert B.abl_split_products((64, 56, 56, 256, 64, 1, 1, 1, 0), 4, "bn_conv_fwd") == 0   # the pointwise kernel's prologue
+    assert B.lib.abl_split_products(ctypes.byref(B.shape_struct(deep)), 5, 0, 0) == 0
+    assert B.lib.abl_split_products(None, 4, 0, 0) == 0
