@@ -917,7 +917,9 @@ size_t wgrad_partial_bytes(const abl_shape& s) {
   }
   const WgradPlan p = wgrad_plan(g);
   const size_t n = (size_t)g.R * g.S * g.Cin * g.Cout * sizeof(float);
-  int img = image_wgrad_copies(g, 4);   // the register-resident kernels' copies (same count for K = 8)
+  // Room for more shares of the pixels where the layer gives one block per compute unit (the same for K = 8): the split
+  // kernels (wgrad_split.hip) make as many copies as fit, rows_wgrad_bf16_kernel exactly these.
+  int img = image_wgrad_copies(g, 4);
   const int pw = rows_wgrad_copies(g, 4, false);
   if (pw > img) img = pw;
   return ((size_t)(p.split > img ? p.split : img) * n + 255) / 256 * 256;

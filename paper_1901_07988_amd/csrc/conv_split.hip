@@ -3,10 +3,10 @@
 //
 // An fp32 value is the exact sum of three bf16 values (8 + 8 + 8 significant bits: x = h + m + l, each the
 // rounded remainder of the ones before), so a product of two is nine bf16 products, each exact in fp32.  Six
-// of them are taken - hh, hm, mh, mm, hl, lh; the dropped ones (ml, lm, ll) are below 2^-26 of the product,
-// a quarter of an fp32 rounding.  v_mfma_f32_16x16x32_bf16 does 32 of the contraction in the time in which
-// v_mfma_f32_16x16x4_f32 does about three (measured 1600 against 154 TFLOP/s), so six of them are 1.7 times
-// faster; and the sum is rounded once per 32 terms and product instead of once per 4 terms.  The five small
+// of them are taken - hh, hm, mh, mm, hl, lh; the dropped ones (ml, lm, ll) are 2^-28 of the product on average and
+// below 2^-24, an fp32 rounding, at worst (above 2^-26 for 3 pairs of significands in 100).  A loop of
+// v_mfma_f32_16x16x32_bf16 on registers does 1430 TFLOP/s, one of v_mfma_f32_16x16x4_f32 139: six of the former take
+// 0.58 of the time of the fp32 product; and the sum is rounded once per 32 terms and product instead of once per 4 terms.  The five small
 // products have an accumulator of their own: added to the large one they would each round at its magnitude
 // (relative error of a 2304-term contraction against 64 bits: fp32 matrix cores 8.6e-7, one accumulator
 // 7.4e-7, two 2.9e-7).  The parts are taken of 2^23 x: those of the smallest fp32 values (multiples of 2^-149) are normal
@@ -25,7 +25,8 @@
 // output channels of its own, so a block splits nothing twice.  A wave computes 112 pixels x 16 NT channels: 7 NT tiles, 12 NT reads and 42 NT MFMAs per k-step.
 // KS = 2: the chunks of a phase go to two groups of waves whose sums meet in LDS at the end - two waves per
 // SIMD also where a layer gives only one block per compute unit - and the patch has two buffers.
-// KS = 1: one buffer, two blocks per compute unit cover each other's staging.
+// KS = 1: one buffer, two blocks per compute unit cover each other's staging (one where a 3x3 patch has more than 256
+// positions).
 // With bf16 operands (ABL_MATH_BF16) the same kernel runs with one part per operand: rounded once, one product.
 
 #include "abl_internal.h"
@@ -486,7 +487,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       const int nch = n0 + 16 * j + 4 * lk;
       double s1[4] = {0.0, 0.0, 0.0, 0.0}, s2[4] = {0.0, 0.0, 0.0, 0.0};
       floatx4 st4;
-      float offh[4];   // code + offh = Eq. 10 over its step (exact: both are below 2^24)
+      float offh[4];   // code + offh = Eq. 10 over its step (exact below 2^23; from there on the half is rounded away)
       if constexpr (EPI > 1) {
         st4 = *reinterpret_cast<const floatx4*>(stats + P_STEP * Ng + nch);
         const int4 fb4 = *reinterpret_cast<const int4*>(stats + P_FB * Ng + nch);

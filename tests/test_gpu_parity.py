@@ -271,9 +271,10 @@ PW_WGRAD_CASES = [
 @pytest.mark.parametrize("K", [4, 8])
 def test_pointwise_wgrad_in_registers(G, oracle, s, K):
     """Weight gradient of 1x1 layers with at least 64 x 256 channels and 16 chunks of 16 pixels per
-    block: the kernel that keeps a 64 x 256 tile of dW in registers and applies the step of Eq. 10
-    to the sums.  Even and odd chunk counts per block, block counts that do and do not fill the
-    eight-way block mapping, a folded bias that moves the ReLU threshold between codes."""
+    block: fp32 runs split_wgrad1_kernel, which keeps a tile of dW in registers and applies the step of
+    Eq. 10 to the sums (the test below runs the bf16 kernel with its 64 x 256 tile).  Even and odd chunk
+    counts per block, block counts that do and do not fill the eight-way block mapping, a folded bias that
+    moves the ReLU threshold between codes."""
     o = oracle
     print("case pointwise wgrad", s.as_tuple(), K, flush=True)
     rng = np.random.default_rng(sum(s.as_tuple()) + K)

@@ -81,25 +81,26 @@ def test_random_stacks(G, oracle, seed):
 
 
 def _random_resident_layer(rng):
-    """A layer that one of the register-resident kernels takes in at least one direction: enough
-    images (or rows) for 224 blocks of 64 output channels."""
+    """A layer that fills the chip with one-block-per-compute-unit kernels in at least one direction (split
+    operands, or an image kernel where those do not take it): enough images (or rows) for 224 blocks of 64
+    output channels."""
     kind = int(rng.integers(0, 4))
-    if kind == 3:      # 1x1 with 64 x 256 channel tiles: rows_wgrad_kernel (tiles x shares of the pixels >= 224, >= 16 chunks each)
+    if kind == 3:      # 1x1 weight gradient with room for tiles x shares of the pixels >= 224, >= 16 chunks of 16 pixels each
         cin, cout = int(rng.choice([64, 128, 192, 320])), int(rng.choice([256, 512]))
         shares = 256 // ((cin // 64) * (cout // 256))
         return LayerShape(1, 16, 16 * shares + int(rng.integers(0, 40)), cin, cout, 1, 1, 1, 0)
-    if kind == 0:      # 3x3 'same' on a small image: image_f32_kernel forward and / or data gradient
+    if kind == 0:      # 3x3 'same' on a small image: image_f32_kernel (16 channels to contract) or split_conv_kernel
         H, W = int(rng.integers(2, 15)), int(rng.integers(2, 15))
         while H * W > 208:
             H -= 1
         cin, cout = int(rng.choice([16, 32, 64, 128, 192])), int(rng.choice([64, 128, 256]))
         N = -(-224 // (cout // 64)) + int(rng.integers(0, 5))
         return LayerShape(N, H, W, cin, cout)
-    if kind == 1:      # 3x3 'same', 14 pixels wide: image_wgrad_kernel (32 x 64 channel tiles x shares of the images >= 224)
+    if kind == 1:      # 3x3 'same', 14 pixels wide: split_wgrad_kernel with room for 32 x 64 channel tiles x shares >= 224
         H = int(rng.choice([2, 4, 6, 10, 14]))
         cin, cout = [(160, 320), (256, 128), (64, 512), (96, 320)][int(rng.integers(0, 4))]
         return LayerShape(16 + int(rng.integers(0, 3)), H, 14, cin, cout)
-    # 1x1 with a long contraction: rows_f32_kernel forward (Cin >= 512) or data gradient (Cout >= 512)
+    # 1x1 with a long contraction, forward (Cin >= 512) or data gradient (Cout >= 512): split_conv_kernel
     big, small = int(rng.choice([512, 576, 1024])), int(rng.choice([64, 128]))
     rows = -(-224 // (small // 64)) * 208 + int(rng.integers(1, 400))
     H = int(rng.integers(20, 60))
