@@ -207,7 +207,12 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   // elsewhere reading x once wins (56x56 256 -> 64 129 against 185).
   if (!bf16 && split_beats_prologue(g)) return 0;
   // (Not for the small images of the image-resident kernel: the pack pass plus that kernel is
-  // faster than the fused one.)
+  // faster than the fused one.  Nor where split operands carry the plain 3x3 convolution but not the one with the
+  // prologue, whose blocks have four waves and 64 output channels: normalise-ReLU-pack and split convolution take 0.50 to
+  // 1.03 of the fused halo kernel's time, 110 such layers of 5 to 40 pixels and 64 to 512 channels - the halo kernel / both,
+  // us: 64 -> 64 @8x8 N=128 25.0 / 24.6, @28x28 N=16 25.4 / 26.1, 256 -> 256 @14x14 N=16 64.7 / 54.8, 128 -> 128
+  // @40x40 N=28 154 / 94 - and the split sums are the closer ones.)
+  if (!bf16 && g.R == 3 && split_fused_blocks(g) == 0 && split_conv_blocks(g, 0) > 0) return 0;
   if (halo_fused_supported(g) && !(!bf16 && image_f32_supported(g, 0))) return 1;
   // With the prologue every block along the output channels repeats the normalization of its
   // input rows; measured against the separate pack kernel this pays up to 256 output channels.

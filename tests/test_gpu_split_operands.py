@@ -346,3 +346,36 @@ def test_fused_stage_is_the_layers_kernel(s, K):
     y2, packed2 = torch.empty_like(skip), raw(B.abl_packed_bytes(s9, K))
     B.abl_bn_conv_fwd(s9, K, x, stats, w, skip, y2, packed2)
     assert torch.equal(y, y2) and torch.equal(packed, packed2)
+
+
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("s", [SHAPES[1], (128, 8, 8, 64, 64, 3), (16, 14, 14, 256, 256, 3), (12, 20, 20, 64, 128, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_forward_with_the_pack_pass_in_front(s, K):
+    """3x3 layers whose plain convolution runs on split operands and whose fused one would run on the halo kernel: the
+    layer is the pack pass and the plain convolution, bit for bit; the fused stage still takes them."""
+    print("case split operands, pass in front", s, K, flush=True)
+    x, w, skip = draw(s)
+    N, H, W, ci, co, R = s
+    s9, M = shape9(s), N * H * W
+    assert not B.abl_forward_is_fused(s9, K)
+    assert B.abl_split_products(s9, K, "conv_fwd") == 6 and B.abl_split_products(s9, K, "bn_conv_fwd") == 0
+    g = torch.Generator(device="cuda").manual_seed(2)
+    gamma, beta = torch.rand(ci, device="cuda", generator=g) + 0.5, torch.randn(ci, device="cuda", generator=g) * 0.1
+
+    def raw(n):
+        return torch.full((n,), 0xA5, dtype=torch.uint8, device="cuda")
+
+    y, packed, stats = torch.empty_like(skip), raw(B.abl_packed_bytes(s9, K)), raw(32 * ci)
+    B.abl_forward(s9, K, x, w, gamma, beta, skip, raw(B.abl_scratch_bytes(s9, K)), y, packed, stats)
+    a3, packed2, y2 = torch.empty_like(x), raw(B.abl_packed_bytes(s9, K)), torch.empty_like(skip)
+    B.abl_bn_relu_pack(x, M, ci, K, stats, a3, packed2)
+    B.abl_conv_fwd(s9, a3, w, skip, y2)
+    assert torch.equal(packed, packed2) and torch.equal(y, y2)
+    ref = conv64(a3, w) + skip.double()
+    assert rel(y, ref) < tolerance(9 * ci)
+    y3, packed3 = torch.empty_like(skip), raw(B.abl_packed_bytes(s9, K))
+    B.abl_bn_conv_fwd(s9, K, x, stats, w, skip, y3, packed3)
+    assert torch.equal(packed, packed3)
+    # (fp32 matrix cores: rounded at every fourth term, twice that for sums of several partial ones)
+    assert rel(y3, ref) < 2.0 ** -23 * ((9 * ci / 4) ** 0.5 + 2)
