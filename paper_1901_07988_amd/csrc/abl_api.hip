@@ -195,7 +195,9 @@ namespace {
 // Which forward kernel a layer with separate input and output takes: 1 = the 'same' stride-1 kernel
 // with the Eq. 1-3 / Eq. 9 prologue, 2 = the 1x1 kernel with it, 0 = pack pass + plain contraction.
 inline bool aliased(const void* a, const void* b) { return a == b; }
-int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, bool naive) {
+// (*split_rows: path 1 on the split-operand kernel, rows of its sums of y; 0 = the halo kernel.)
+int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, bool naive, int* split_rows) {
+  *split_rows = 0;
   // bf16 operands: the contraction runs on the 32-deep bf16 matrix instruction with bf16 tiles in
   // LDS (its kernel has no BN prologue), so the layer takes the separate stages
   // - where the contraction is heavy enough to pay for the separate normalise-ReLU-pack pass
@@ -212,17 +214,14 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   // 1.03 of the fused halo kernel's time, 110 such layers of 5 to 40 pixels and 64 to 512 channels - the halo kernel / both,
   // us: 64 -> 64 @8x8 N=128 25.0 / 24.6, @28x28 N=16 25.4 / 26.1, 256 -> 256 @14x14 N=16 64.7 / 54.8, 128 -> 128
   // @40x40 N=28 154 / 94 - and the split sums are the closer ones.)
-  if (!bf16 && g.R == 3 && split_fused_blocks(g) == 0 && split_conv_blocks(g, 0) > 0) return 0;
+  const int split = !bf16 ? split_forward3(g, split_rows) : 0;
+  if (split < 0) return 0;
   if (halo_fused_supported(g) && !(!bf16 && image_f32_supported(g, 0))) return 1;
+  *split_rows = 0;
   // With the prologue every block along the output channels repeats the normalization of its
   // input rows; measured against the separate pack kernel this pays up to 256 output channels.
   if (igemm_fused_supported(s) && s.Cout <= 256) return 2;
   return 0;
-}
-
-// Path 1 on the split-operand kernel (the halo kernel otherwise): rows of its sums of y, 0 = no.
-int fused_on_split(const abl_shape& s, const ConvGeom& g, int K, bool bf16) {
-  return !bf16 && forward_fused_path(s, g, K, bf16, false) == 1 ? split_fused_blocks(g) : 0;
 }
 
 // Forward: statistics -> (normalise, ReLU, quantize, pack) -> convolution.  A3 lives in the
@@ -249,13 +248,14 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
     if (int e = launch_bn_stats(st, x, M, s->Cin, gamma, beta, K, red, stats)) return e;
   }
   const ConvGeom g = geom_of(*s);
-  const int path = aliased(x, y) ? 0 : forward_fused_path(*s, g, K, bf16, naive);
+  int split_rows = 0;
+  const int path = aliased(x, y) ? 0 : forward_fused_path(*s, g, K, bf16, naive, &split_rows);
   // 'same' stride-1 convolutions normalise, quantize and pack while they stage their input
   // patch: x is read once and A3 never reaches memory.  (Not when y aliases x: a block would
   // overwrite input pixels that a neighbouring block has not staged yet.)
-  if (const int nb = path == 1 ? fused_on_split(*s, g, K, bf16) : 0) {
+  if (split_rows > 0) {
     if (int e = launch_split_fwd_fused(st, g, K, x, stats, W, skip, y, packed, out_partial)) return e;
-    if (out_partial != nullptr && out_nb != nullptr) *out_nb = nb;
+    if (out_partial != nullptr && out_nb != nullptr) *out_nb = split_rows;
     return ABL_OK;
   }
   if (path == 1) {
@@ -280,7 +280,8 @@ int abl_forward_is_fused(const abl_shape* s, int K, uint32_t flags) {
   if (int e = check_shape(s)) return -e;
   if (int e = check_k(K)) return -e;
   if (flags & ~(uint32_t)(ABL_MATH_BF16 | ABL_NAIVE_FWD)) return -ABL_ERR_ARG;
-  return forward_fused_path(*s, geom_of(*s), K, (flags & ABL_MATH_BF16) != 0, (flags & ABL_NAIVE_FWD) != 0 && K != 32) != 0
+  int split_rows;
+  return forward_fused_path(*s, geom_of(*s), K, (flags & ABL_MATH_BF16) != 0, (flags & ABL_NAIVE_FWD) != 0 && K != 32, &split_rows) != 0
              ? 1
              : 0;
 }
@@ -470,7 +471,8 @@ int abl_bn_conv_fwd(void* stream, const abl_shape* s, int K, uint32_t flags, con
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   if (igemm_fused_supported(*s))
     return launch_conv_fwd_fused((hipStream_t)stream, *s, K, bf16, x, stats, W, skip, y, packed);
-  if (fused_on_split(*s, g, K, bf16))   // (as abl_forward does)
+  int split_rows;
+  if (forward_fused_path(*s, g, K, bf16, false, &split_rows) == 1 && split_rows > 0)   // (as abl_forward does)
     return launch_split_fwd_fused((hipStream_t)stream, g, K, x, stats, W, skip, y, packed, nullptr);
   if (!halo_fused_supported(g)) return ABL_ERR_SHAPE;
   return launch_halo_fwd_fused((hipStream_t)stream, g, K, bf16, x, stats, W, skip, y, packed, nullptr);
@@ -537,9 +539,10 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
 int abl_split_products(const abl_shape* s, int K, uint32_t flags, int stage) {
   if (check_shape(s) != ABL_OK || check_k(K) != ABL_OK || (flags & ABL_MATH_BF16) != 0) return 0;
   const ConvGeom g = geom_of(*s);
+  int rows;
   switch (stage) {
     case ABL_STAGE_CONV_FWD: return split_conv_blocks(g, 0) > 0 ? 6 : 0;
-    case ABL_STAGE_BN_CONV_FWD: return K != 32 && !igemm_fused_supported(*s) && fused_on_split(*s, g, K, false) > 0 ? 6 : 0;
+    case ABL_STAGE_BN_CONV_FWD: return K != 32 && forward_fused_path(*s, g, K, false, false, &rows) == 1 && rows > 0 ? 6 : 0;
     case ABL_STAGE_CONV_DGRAD: return split_conv_blocks(g, 1) > 0 ? 6 : 0;
     case ABL_STAGE_CONV_DGRAD_BN_REDUCE: return K != 32 && reduce_stage_accepts(g) && split_conv_blocks(g, 1, false, true) > 0 ? 6 : 0;
     case ABL_STAGE_CONV_WGRAD_PACKED: return split_wgrad_copies(g, K, false, wgrad_partial_bytes(*s)) > 0 ? 3 : 0;

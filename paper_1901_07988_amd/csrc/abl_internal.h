@@ -182,8 +182,9 @@ int split_conv_blocks(const ConvGeom& g, int mode, bool bf16 = false, bool sums 
 bool split_beats_prologue(const ConvGeom& g);
 int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
                       const float* skip, float* out, double* sums);
-// The 3x3 forward with Eq. 1-3 and Eq. 9 applied while the patch is staged (fp32 operands, y not x).
-int split_fused_blocks(const ConvGeom& g);
+// The 3x3 forward with Eq. 1-3 and Eq. 9 (fp32 operands, y not x): 1 = launch_split_fwd_fused, which applies them while the
+// patch is staged (*rows = rows of its sums), -1 = launch_split_conv with a pass of its own in front, 0 = other kernels.
+int split_forward3(const ConvGeom& g, int* rows);
 int launch_split_fwd_fused(hipStream_t st, const ConvGeom& g, int K, const float* x, const void* stats, const float* w,
                            const float* skip, float* y, void* packed, double* sums);
 int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* dy, const float* w,

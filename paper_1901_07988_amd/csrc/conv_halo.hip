@@ -741,6 +741,12 @@ bool make_plan(const ConvGeom& g, int mode, HaloPlan& p) {
   return p.lds_bytes <= 64 * 1024 && p.TI * p.HH * p.HW * 4 <= kPatchSlots && p.TH > 0;
 }
 
+bool halo_shape_ok(const ConvGeom& g) {
+  if (g.stride != 1 || g.R * g.S < 2 || g.R > 7 || g.S > 7) return false;
+  if (g.Cin % 16 != 0 || g.Cout % 16 != 0) return false;
+  return g.pad <= g.R - 1 && g.pad <= g.S - 1;
+}
+
 template <int MODE, int V, int FUSE>
 void launch_variant(hipStream_t st, const ConvGeom& g, const HaloPlan& p, bool bf16, const float* in, const float* w,
                     const float* skip, float* out, const float* stats, void* packed, const EpiReduce& epi) {
@@ -1270,11 +1276,8 @@ bool make_bwd16_plan(const ConvGeom& g, HaloPlan& p) {
 }  // namespace
 
 bool halo_conv_supported(const ConvGeom& g) {
-  if (g.stride != 1 || g.R * g.S < 2 || g.R > 7 || g.S > 7) return false;
-  if (g.Cin % 16 != 0 || g.Cout % 16 != 0) return false;
-  if (g.pad > g.R - 1 || g.pad > g.S - 1) return false;
   HaloPlan p;
-  return make_plan(g, 0, p) && make_plan(g, 1, p);
+  return halo_shape_ok(g) && make_plan(g, 0, p) && make_plan(g, 1, p);
 }
 
 int launch_halo_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
@@ -1300,8 +1303,9 @@ int halo_tile_count(const ConvGeom& g, int mode) {
 }
 
 bool halo_grid(const ConvGeom& g, int mode, int* pixels, int64_t* blocks) {
-  HaloPlan p;
-  if (!halo_conv_supported(g) || !make_plan(g, mode, p)) return false;
+  HaloPlan p, q;   // (a plan takes about 1 us here: the two directions of an equal number of channels have the same)
+  if (!halo_shape_ok(g) || !make_plan(g, mode, p)) return false;
+  if ((g.Cin != g.Cout || g.Ho != g.H || g.Wo != g.W) && !make_plan(g, 1 - mode, q)) return false;
   const Variant& v = kVariants[p.variant];
   *pixels = v.nw / v.waves_n * v.mt * 16;
   *blocks = (int64_t)p.tiles_i * p.tiles_h * p.tiles_w * p.nblk_n;

@@ -560,6 +560,14 @@ struct Plan {
   int bn;
 };
 
+bool supported(const ConvGeom& g, int mode) {
+  const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
+  const bool k3 = g.R == 3 && g.S == 3 && g.pad == 1, k1 = g.R == 1 && g.S == 1 && g.pad == 0;
+  const int64_t M = (int64_t)g.N * g.H * g.W;
+  return g.stride == 1 && (k3 || k1) && Cg % 32 == 0 && Ng % 64 == 0 && M * g.Cin < ((int64_t)1 << 31) &&
+         M * g.Cout < ((int64_t)1 << 31);
+}
+
 // The configuration with nt, ks for this layer; false where its sizes do not fit.
 bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
@@ -619,8 +627,9 @@ bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
 // of more than 256 positions (cross-image runs of 32-pixel-wide images, rows of 57) leaves LDS for one block per unit
 // only; a tile then takes 18.3 us per 64 input channels, the halo kernel 11.1 per round of 64 pixels, 20 of 128, 35.5 of
 // 224 (64 -> 64 @33x33 N=56, 273 blocks of two tiles, 70.7 / 43.5, N=48, 467 blocks, 38.8 / 48.3; @32x32 N=72, 330 of two,
-// 71.1 / 59.9, N=56, 512 blocks, 39.9 / 73.7; 128 -> 128 @40x40 N=10 66.8 / 46.8).  Where both take about the same and the
-// last round is no small remainder this kernel stays: its sums are the closer ones.
+// 71.1 / 59.9, N=56, 512 blocks, 39.9 / 73.7; 128 -> 128 @40x40 N=10 66.8 / 46.8).  Where both take about the same this
+// kernel stays (up to 8 % slower alone, @57x57 N=12 39.8 / 36.9; a layer's two passes are faster): its sums are the closer
+// ones.
 bool halo_is_faster(const ConvGeom& g, int mode, const Plan& p) {
   const int Ng = mode == 0 ? g.Cout : g.Cin;
   const bool alone = p.su > 4;
@@ -634,42 +643,56 @@ bool halo_is_faster(const ConvGeom& g, int mode, const Plan& p) {
   const int64_t rounds = (blocks + 255) / 256, n = (int64_t)p.tl.gm * (Ng / p.bn);
   const double here = 1.5 + 18.3 * (double)(p.tl.per * ((n + 255) / 256));
   const double there = pixels == 64 ? 3.7 + 11.1 * rounds : pixels == 128 ? 3.0 + 20.0 * rounds : 2.5 + 35.5 * rounds;
-  return (n % 256 == 0 || n % 256 >= 64 ? 1.03 : 1.0) * there < here;
+  return 1.1 * there < here;
 }
+
+// Tiles of 128 pixels x 64 channels that the other kernels have, each XCD's share rounded up.
+int64_t other_tiles(const ConvGeom& g, int Ng) { return ((int64_t)g.N * g.H * g.W + 1023) / 1024 * 8 * (Ng / 64); }
 
 // Whether a grid of four-wave blocks - two to a compute unit, 512 at a time - is faster than the kernel that would
 // run otherwise.  A grid a little over one block per unit, or a little over 512, takes as long as a much larger one (the
 // units with one block more decide), while the other kernels' tiles may just fit.  (us, here / the other kernel, n blocks.
-// fp32 1x1: 256 -> 1024 @13x13 N=12, n = 304, 17.1 / 13.8, N=14, n = 352, 17.1 / 22.6; 256 -> 64 @56x56 of two tiles per
-// block N=20, n = 280, 30.9 / 23.6, N=28, n = 392, 33.0 / 32.1; 64 -> 256 @56x56 N=6, n = 336, 12.4 / 12.1, N=8, n = 448,
-// 12.3 / 14.8, N=20, n = 560, 28.9 / 27.4, but 128 -> 512 @28x28 N=20, also 560, 23.8 / 26.7.  bf16 1x1: 128 -> 512
-// @28x28 N=10, n = 280, 10.4 / 9.0, N=12, n = 336, 10.7 / 11.5, N=20, n = 560, 14.5 / 13.2, N=24, n = 672, 14.7 / 17.2;
-// 64 -> 256 @56x56 N=14, n = 784, 15.3 / 13.4; 512 -> 128 @28x28 N=40, n = 280, 23.8 / 18.9, N=56, n = 392, 24.9 / 23.7;
-// gradient 256 <- 1024 @14x14 N=40, n = 280, 30.3 / 24.5.  bf16 3x3: 64 -> 64 @56x56 of two tiles per block N=20,
-// n = 280, 24.5 / 21.1; 64 -> 64 @57x57 of two tiles, patches of more than 256 positions, N=27, step 53.5 / 46.9; 128 ->
-// 128 @60x60 N=10, n = 644, 47.4 / 42.8, N=14, n = 900, 54.8 / 60.2, its gradient 62.8 / 53.4; gradient 128 <- 128 @28x28 N=40, n = 280 of 128 channels, 43.6 / 36.7, 256 <- 256
-// @17x17 N=100, n = 518, 120.7 / 89.6.)
+// fp32 1x1, where the pointwise kernel's tiles fit one round of the units (two for blocks of 128 channels): 256 -> 128
+// @27x27 N=20, n = 262, 16.1 / 13.5, 512 -> 64 @28x28 N=39, n = 274, 29.7 / 23.5, 64 -> 512 @16x16 N=32, n = 296 of 128
+// channels, 11.8 / 10.6, gradient 256 <- 128 @20x20 N=81, n = 290 of 128, 24.9 / 22.4; just beyond: 256 -> 256 @14x14 N=44,
+// n = 308, 16.6 / 22.7, 192 -> 256 @29x29 N=10, n = 304, 13.1 / 16.5, gradient 256 <- 128 @27x27 N=49, n = 319 of 128, 25.2 /
+// 29.8.  Longer contractions than 256 share the pointwise kernel's last round out: gradient 384 <- 64 @29x29 N=41, n = 308,
+// 23.6 / 20.4.  256 -> 64 @56x56 of two tiles per block N=20, n = 280, 30.9 / 23.6, N=28, n = 392, 33.0 / 32.1; 64 -> 256
+// @56x56 N=8, n = 448, 12.3 / 14.8, N=20, n = 560, 28.9 / 27.4, but 128 -> 512 @28x28 N=20, also 560, 23.8 / 26.7.  bf16
+// 1x1: 128 -> 512 @28x28 N=10, n = 280, 10.4 / 9.0, N=12, n = 336, 10.7 / 11.5, N=20, n = 560, 14.5 / 13.2, N=24, n = 672,
+// 14.7 / 17.2; 256 -> 512 @15x15 N=77, n = 620, 19.2 / 24.6; 64 -> 256 @56x56 N=14, n = 784, 15.3 / 13.4; 512 -> 128 @28x28
+// N=40, n = 280, 23.8 / 18.9, N=56, n = 392, 24.9 / 23.7; 512 -> 256 @15x15 N=77, n = 310, 21.0 / 23.4; 64 -> 128 @57x57 N=20
+// of two tiles, n = 291, 16.0 / 11.5; gradient 256 <- 1024 @14x14 N=40, n = 280, 30.3 / 24.5.  bf16 3x3: 64 -> 64 @56x56 of two tiles per block
+// N=20, n = 280, 24.5 / 21.1; 64 -> 64 @57x57 of two tiles, patches of more than 256 positions, N=27, step 53.5 / 46.9;
+// 128 -> 128 @60x60 N=10, n = 644, 47.4 / 42.8, N=14, n = 900, 54.8 / 60.2, its gradient 62.8 / 53.4; gradient 128 <- 128
+// @28x28 N=40, n = 280 of 128 channels, 43.6 / 36.7, N=67, n = 469, 44.2 / 51.9, @30x30 N=58 of two tiles 83.4 / 55.6, 256 <-
+// 256 @15x15 N=73, n = 294, 78.6 / 68.6, @17x17 N=100, n = 518, 120.7 / 89.6.)
 bool four_waves_pay(const ConvGeom& g, int mode, int np, bool sums, const Plan& p) {
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
   const int64_t n = (int64_t)p.tl.gm * (Ng / p.bn);
-  const bool over_one = n > 256 && n < 320, over_two = n > 512 && n < 660, over_three = n > 768 && n < 832;
-  const bool first = n > 256 && n < 400;   // the first round less than three quarters full
+  const bool over_one = n > 256 && n < 320, over_two = n > 512 && n < 660;
+  // whole rounds of one block per unit that this grid is larger than, and whether the other kernels fit them
+  const int64_t rounds = (n - 1) / 256, others = other_tiles(g, Ng);
+  const bool fit = rounds > 0 && others <= 256 * rounds * p.nt;
   if (g.R == 3) {
     if (np == 3) return p.nt == 2 || !halo_is_faster(g, mode, p);
     if (sums) return true;
-    if (mode == 1 && p.nt == 2) return n <= 256;
-    return !(p.tl.per > 1 && over_one) && !(p.su > 4 && (p.tl.per > 1 || over_two || (mode == 1 && n > 512)));
+    if (mode == 1 && p.nt == 2) return n <= 256 || (n >= 400 && n <= 512 && p.tl.per == 1);
+    return !(p.nt == 1 && p.tl.per > 1 && over_one) && !(p.su > 4 && (p.tl.per > 1 || over_two || (mode == 1 && n > 512)));
   }
   // with the Eq. 6-7 sums the other kernels need a pass of their own or lose their weight gradient's launch: fp32 is faster
   // here throughout, bf16 with 64 channels per block and less than 1024 to contract only (1024 <- 256 @14x14 N=40,
   // n = 560 of 128 channels each, backward 65.6 / 57.9; 256 <- 1024 N=40 59.4 / 55.3)
   if (np == 3) {
     if (sums) return true;
-    if (p.nt == 2 && Cg >= 512) return true;   // (512 -> 128 @28x28 N=40, n = 280: 42.6 / 59.1)
-    return !(over_one || (first && (p.tl.per > 1 || Cg < 128)) || (over_two && Cg < 128));
+    // (512 -> 128 @28x28 N=40, n = 280: 42.6 / 59.1; 128 -> 512 @20x20 N=18, n = 260: 14.1 / 16.3)
+    if (p.nt == 2 && (Cg >= 512 || Cg == 128)) return true;
+    if (fit && (rounds == 1 || (rounds == 2 && Cg < 128))) return false;
+    if (over_one && p.nt == 1 && Cg > 256 && (Ng == 64 || Ng % 128 == 0)) return false;
+    return !(n > 256 && n < 400 && p.tl.per > 1);
   }
-  if (mode == 1 && (!sums || p.nt == 2 || Cg >= 1024)) return false;
-  return !(over_one || over_two || over_three || (p.nt == 2 && Cg >= 512 && first));
+  if (mode == 1) return sums && p.nt == 1 && Cg < 1024;
+  return !fit && !(over_one && p.tl.per > 1);
 }
 
 // 128 output channels per block where that fills the chip, else 64.  About one block per compute unit: the
@@ -679,11 +702,9 @@ bool four_waves_pay(const ConvGeom& g, int mode, int np, bool sums, const Plan& 
 // 88 / 105 instead of 125 / 160 with 128 channels on 112 blocks.)  Grids of fewer than 96 blocks stay on the other
 // kernels, and four-wave blocks where they do not pay.  sums: with the Eq. 6-7 sums in the epilogue.
 bool make_plan(const ConvGeom& g, int mode, int np, bool sums, Plan& p) {
+  if (!supported(g, mode)) return false;
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
-  const bool k3 = g.R == 3 && g.S == 3 && g.pad == 1, k1 = g.R == 1 && g.S == 1 && g.pad == 0;
-  if (g.stride != 1 || !(k3 || k1) || Cg % 32 != 0 || Ng % 64 != 0) return false;
-  const int64_t M = (int64_t)g.N * g.H * g.W;
-  if (M * g.Cin >= ((int64_t)1 << 31) || M * g.Cout >= ((int64_t)1 << 31)) return false;
+  const bool k3 = g.R == 3;
   for (int nt = 2; nt >= 1; --nt)
     for (int ks = 2; ks >= 1; --ks) {
       if (!fit_plan(g, mode, np, nt, ks, p)) continue;
@@ -692,7 +713,13 @@ bool make_plan(const ConvGeom& g, int mode, int np, bool sums, Plan& p) {
       // (the gradient of 1x1 layers with 64 channels to contract and more to write: two groups of waves have nothing to share;
       // exact storage 256 <- 64 @16x16 N=12, backward 32.4 us against the pointwise kernel's 30.1)
       if (ks == 2) return k3 || np != 3 || sums || mode == 0 || Cg >= 128 || Ng < 128;
-      return four_waves_pay(g, mode, np, sums, p);
+      if (four_waves_pay(g, mode, np, sums, p)) return true;
+      // (long 1x1 contractions on 257 to 319 four-wave blocks: half as many of eight waves with 128 channels, which take what
+      // the pointwise kernel takes or less, and their sums are the closer ones.  us, here / pointwise kernel: 1024 -> 512
+      // @14x14 N=20 43.1 / 42.5, 384 -> 512 @15x15 N=18 19.3 / 18.8, 1024 -> 384 @20x20 N=14 43.7 / 60.7; gradient 512 <- 256
+      // @29x29 N=10 23.2 / 25.2, but 5 to 12 % slower where its tiles fit one round)
+      return !k3 && np == 3 && nt == 1 && blocks < 320 && Cg >= 384 && (mode == 0 || other_tiles(g, Ng) > 256) &&
+             fit_plan(g, mode, np, 2, 2, p);
     }
   return false;
 }
@@ -740,8 +767,8 @@ int launch_fused(hipStream_t st, const ConvGeom& g, const Plan& p, const float* 
 
 // The fused forward: 64 output channels per block (the constants of Eq. 1-3 take the registers of the second tile) in
 // four waves.
-bool make_fused_plan(const ConvGeom& g, Plan& p) {
-  return g.R == 3 && make_plan(g, 0, 3, false, p) && fit_plan(g, 0, 3, 1, 1, p) && !halo_is_faster(g, 0, p);
+bool fit_fused_plan(const ConvGeom& g, Plan& p) {
+  return g.R == 3 && supported(g, 0) && fit_plan(g, 0, 3, 1, 1, p);
 }
 
 }  // namespace
@@ -753,14 +780,19 @@ int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
 
 // Four-wave grids that fill less than three quarters of their 512 places are not (512 -> 128 @28x28, step, us, with the
 // pass / with the prologue: N=16, eight-wave blocks, 40.0 / 41.6; N=24, n = 336, 56.7 / 53.0; N=28, n = 392, 59.9 / 64.9),
-// nor are shorter contractions, but for 256 -> 256 (128 -> 256 @28x28 N=5 18.4 / 15.8, N=24 34.5 / 30.8, N=56 50.2 / 47.4;
-// 256 -> 128 @14x14 N=40 26.6 / 21.9; 320 -> 192 @13x13 N=56 40.8 / 31.7; but 384 -> 192 @28x28 N=20 45.1 / 53.1, 256 -> 256
-// @14x14 N=56 34.3 / 37.2; @28x28 N=40, n = 560, 62.7 / 59.7).
+// nor are shorter contractions, but for 256 -> 256 and where the pointwise kernel's tiles are more than a round of the units
+// and the ones here no more than their 512 places (128 -> 256 @28x28 N=5 18.4 / 15.8, N=24 34.5 / 30.8; 256 -> 128 @14x14
+// N=40 26.6 / 21.9, @27x27 N=36, n = 470, 40.3 / 44.1, @28x28 N=40, n = 560, 49.5 / 45.6; 320 -> 192 @13x13 N=56 40.8 / 31.7;
+// but 384 -> 192 @28x28 N=20 45.1 / 53.1, 256 -> 256 @14x14 N=56 34.3 / 37.2; @28x28 N=40, n = 560, 62.7 / 59.7).
 bool split_beats_prologue(const ConvGeom& g) {
   Plan p;
-  if (g.R != 1 || g.Cin < 256 || (g.Cin < 384 && g.Cout < 256) || !make_plan(g, 0, 3, false, p)) return false;
+  if (g.R != 1 || g.Cin < 256 || !make_plan(g, 0, 3, false, p)) return false;
   const int64_t n = (int64_t)p.tl.gm * (g.Cout / p.bn);
-  return p.ks == 2 || (p.nt == 2 ? g.Cin >= 384 || n <= 512 || n >= 660 : n >= 384);
+  if (g.Cin < 384 && g.Cout < 256)
+    return g.Cout >= 128 && other_tiles(g, g.Cout) > 256 && (int64_t)p.tl.tiles * (g.Cout / 64) <= 512;
+  if (p.ks == 2) return p.nt == 1 || n >= 200 || g.Cin >= 1024;
+  if (p.nt == 2 && n > 256 && n < 320 && g.Cin < 512) return false;   // (384 -> 128 @29x29 N=41 70.5 / 62.2)
+  return p.nt == 2 ? g.Cin >= 384 || n <= 512 || n >= 660 : n >= 350;
 }
 
 int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
@@ -775,15 +807,19 @@ int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, co
               : launch<1, 3>(st, g, p, in, w, nullptr, out, nullptr, nullptr, nullptr, 0);
 }
 
-int split_fused_blocks(const ConvGeom& g) {
+int split_forward3(const ConvGeom& g, int* rows) {
   Plan p;
-  return make_fused_plan(g, p) ? p.tl.gm : 0;
+  if (g.R != 3 || !make_plan(g, 0, 3, false, p)) return 0;
+  const bool weighed = p.nt == 1 && p.ks == 1;   // (make_plan has compared this one with the halo kernel)
+  if (!fit_fused_plan(g, p) || (!weighed && halo_is_faster(g, 0, p))) return -1;
+  *rows = p.tl.gm;
+  return 1;
 }
 
 int launch_split_fwd_fused(hipStream_t st, const ConvGeom& g, int K, const float* x, const void* stats, const float* w,
                            const float* skip, float* y, void* packed, double* sums) {
   Plan p;
-  if (!make_fused_plan(g, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
+  if (!fit_fused_plan(g, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
   const float* sp = static_cast<const float*>(stats);
   uint8_t* pk = static_cast<uint8_t*>(packed);
   if (p.su == 4) return K == 4 ? launch_fused<4, 1, 4>(st, g, p, x, sp, w, skip, y, pk, sums)

@@ -379,3 +379,27 @@ def test_forward_with_the_pack_pass_in_front(s, K):
     assert torch.equal(packed, packed3)
     # (fp32 matrix cores: rounded at every fourth term, twice that for sums of several partial ones)
     assert rel(y3, ref) < 2.0 ** -23 * ((9 * ci / 4) ** 0.5 + 2)
+
+
+@pytest.mark.parametrize("s,stage,split", [
+    ((20, 14, 14, 1024, 512, 1), "conv_fwd", True),     # 280 four-wave blocks: 140 of eight waves and 128 channels instead
+    ((10, 29, 29, 256, 512, 1), "conv_dgrad", True),    # 304, its tiles of 128 pixels do not fit one round
+    ((12, 13, 13, 1024, 1024, 1), "conv_dgrad", False), # 304, they do
+    ((44, 14, 14, 256, 256, 1), "conv_fwd", True),      # 308, they do not: four waves
+    ((20, 27, 27, 256, 128, 1), "conv_fwd", False),     # 262, they do
+    ((18, 20, 20, 128, 512, 1), "conv_fwd", True),      # 260 blocks of 128 channels
+    ((32, 16, 16, 64, 512, 1), "conv_fwd", False),      # 296 of 128 channels, 64 to contract
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_grids_a_little_over_a_round(s, stage, split):
+    """1x1 layers on a little more four-wave blocks than compute units: the kernel that they take and its result."""
+    print("case split operands, a little over a round", s, stage, flush=True)
+    assert B.abl_split_products(shape9(s), 4, stage) == (6 if split else 0)
+    x, w, dy = draw(s)
+    if stage == "conv_fwd":
+        out, ref, terms = torch.empty_like(dy), conv64(x, w), s[3]
+        B.abl_conv_fwd(shape9(s), x, w, None, out)
+    else:
+        out, ref, terms = torch.empty_like(x), conv64(dy, grad_weights(w)), s[4]
+        B.abl_conv_dgrad(shape9(s), dy, w, out)
+    # (fp32 matrix cores: rounded at every fourth term, twice that for sums of several partial ones)
+    assert rel(out, ref) < (tolerance(terms) if split else 2.0 ** -23 * ((terms / 4) ** 0.5 + 2))
