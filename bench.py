@@ -115,6 +115,8 @@ MEASURED_TRAFFIC = {
         ("64x56x56x64x64x3x3x1x1", "conv_fwd"): 139.21e6,
         ("64x56x56x64x64x3x3x1x1", "conv_dgrad_bn_reduce"): 148.71e6,
         ("64x56x56x256x64x1x1x1x0", "bn_conv_fwd"): 288.06e6,
+        ("64x56x56x256x64x1x1x1x0", "conv_dgrad_bn_reduce"): 333.22e6,
+        ("64x56x56x64x256x1x1x1x0", "conv_dgrad_bn_reduce"): 265.09e6,
     },
     ("config2", 4, "fp32"): {
         ("128x32x32x16x16x3x3x1x1", "bn_conv_fwd"): 23.77e6,         # in the stack: half the layers also read a shortcut
