@@ -224,6 +224,13 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   return 0;
 }
 
+// The parts of a layer's weights go where the copies of its weight gradient will be (`room` bytes, free in the forward
+// and until the weight gradient runs); a layer whose copies leave less room has its weights split by the convolution.
+SplitWeights weights_to_split(const abl_shape& s, int mode, int np, const float* W, void* at, size_t room) {
+  const size_t need = (size_t)2 * np * s.R * s.S * s.Cin * s.Cout;
+  return SplitWeights{W, need <= room ? static_cast<uint4*>(at) : nullptr, mode, np, s.R * s.S, s.Cin, s.Cout};
+}
+
 // Forward: statistics -> (normalise, ReLU, quantize, pack) -> convolution.  A3 lives in the
 // workspace only until the convolution has read it (Sec. 3.2: full-precision intermediates
 // are overwritten as soon as they have been used); 'same' stride-1 convolutions do not even
@@ -242,19 +249,24 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   const bool naive = (flags & ABL_NAIVE_FWD) != 0 && K != 32;
   if (out_nb != nullptr) *out_nb = 0;
-  if (in_partial != nullptr && in_nb > 0) {
-    if (int e = launch_bn_stats_finalize(st, in_partial, in_nb, nullptr, M, s->Cin, gamma, beta, K, stats)) return e;
-  } else {
-    if (int e = launch_bn_stats(st, x, M, s->Cin, gamma, beta, K, red, stats)) return e;
-  }
   const ConvGeom g = geom_of(*s);
   int split_rows = 0;
   const int path = aliased(x, y) ? 0 : forward_fused_path(*s, g, K, bf16, naive, &split_rows);
+  // weights of a split-operand convolution: split by the launch of the second pass of Eq. 1, which leaves most of the chip
+  // idle
+  SplitWeights sw{};
+  if (const int np = split_rows > 0 ? 3 : path == 0 ? conv_fwd_parts(g, bf16) : 0)
+    sw = weights_to_split(*s, 0, np, W, static_cast<char*>(red) + up256(bn_partial_bytes(M, s->Cin)), wgrad_partial_bytes(*s));
+  if (in_partial != nullptr && in_nb > 0) {
+    if (int e = launch_bn_stats_finalize(st, in_partial, in_nb, nullptr, M, s->Cin, gamma, beta, K, stats, sw)) return e;
+  } else {
+    if (int e = launch_bn_stats(st, x, M, s->Cin, gamma, beta, K, red, stats, sw)) return e;
+  }
   // 'same' stride-1 convolutions normalise, quantize and pack while they stage their input
   // patch: x is read once and A3 never reaches memory.  (Not when y aliases x: a block would
   // overwrite input pixels that a neighbouring block has not staged yet.)
   if (split_rows > 0) {
-    if (int e = launch_split_fwd_fused(st, g, K, x, stats, W, skip, y, packed, out_partial)) return e;
+    if (int e = launch_split_fwd_fused(st, g, K, x, stats, W, skip, y, packed, out_partial, sw.out)) return e;
     if (out_partial != nullptr && out_nb != nullptr) *out_nb = split_rows;
     return ABL_OK;
   }
@@ -269,7 +281,7 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
   // 1x1 convolutions do the same while they stage their A tile
   if (path == 2) return launch_conv_fwd_fused(st, *s, K, bf16, x, stats, W, skip, y, packed, out_partial, out_nb);
   if (int e = launch_bn_relu_pack(st, x, M, s->Cin, K, stats, a3, packed, naive)) return e;
-  return launch_conv_fwd(st, *s, bf16, a3, W, skip, y, out_partial, out_nb);
+  return launch_conv_fwd(st, *s, bf16, a3, W, skip, y, out_partial, out_nb, sw.out);
 }
 
 }  // namespace
@@ -300,20 +312,28 @@ int abl_forward(void* stream, const abl_shape* s, int K, uint32_t flags, const f
                       nullptr, 0, nullptr, nullptr);
 }
 
-// Backward: dgrad (exact) and wgrad (from the packed copy) consume dy; then the BN/ReLU
-// backward turns dA3 into dx.  dx may alias dy because dy is dead once both contractions
-// have been enqueued ahead of the kernel that writes dx.
-int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const void* packed,
-                 const void* stats, const float* dy, const float* W, void* scratch, size_t scratch_bytes,
-                 float* dx, float* dW, float* dgamma, float* dbeta) {
-  if (int e = check_shape(s)) return e;
-  if (int e = check_k(K)) return e;
-  if (flags & ~(uint32_t)(ABL_ACCUM_DX | ABL_MATH_BF16)) return ABL_ERR_ARG;
-  if (bad_ptr(packed) || bad_ptr(stats) || bad_ptr(dy) || bad_ptr(W) || bad_ptr(scratch) || bad_ptr(dx) ||
-      bad_ptr(dW) || bad_ptr(dgamma) || bad_ptr(dbeta))
-    return ABL_ERR_ARG;
-  if (scratch_bytes < abl_scratch_bytes(s, K)) return ABL_ERR_SCRATCH;
-  hipStream_t st = (hipStream_t)stream;
+}  // extern "C"
+
+namespace {
+
+// Parts of the weights that the data gradient of this layer can read, 0 = none.
+int backward_parts(const ConvGeom& g, int K, bool bf16) {
+  if (K == 32 || halo_bwd16_tiles(g) != 0) return 0;
+  if (!bf16) return split_conv_blocks(g, 1, false, true) > 0 ? 3 : 0;
+  return bf16_gemm_supported(g, 1) && bf16_dgrad_reduce_splits(g) ? 1 : 0;
+}
+
+// Offset of the copies of the weight gradient in a layer's workspace.
+size_t wpart_offset(const abl_shape& s) {
+  const int64_t M = rows_of(s);
+  return up256((size_t)M * s.Cin * sizeof(float)) + up256(bn_partial_bytes(M, s.Cin));
+}
+
+// abl_backward after its checks.  parts (nullable): the weights as the data gradient's kernel reads them.  next: weights for
+// the launch of the apply pass to split.
+int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, const void* packed, const void* stats,
+                  const float* dy, const float* W, void* scratch, float* dx, float* dW, float* dgamma, float* dbeta,
+                  const void* parts, const SplitWeights& next) {
   const int64_t M = rows_of(*s);
   const size_t act = up256((size_t)M * s->Cin * sizeof(float));
   const size_t redb = up256(bn_partial_bytes(M, s->Cin));
@@ -334,15 +354,15 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
       return e;
     // the second pass of the Eq. 7 sums and the sum of the per-tile copies of dW share a launch
     const DwSum dwsum{static_cast<const float*>(wpart), t16, (int64_t)9 * 16 * 16, dW};
-    return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, t16, dx, dgamma, dbeta, &dwsum);
+    return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, t16, dx, dgamma, dbeta, &dwsum, 0.0f, next);
   }
   // the split-operand kernels, with the Eq. 6-7 sums in their epilogue
   if (const int nb = K != 32 && !bf16 ? split_conv_blocks(g, 1, false, true) : 0) {
-    if (int e = launch_split_dgrad_reduce(st, g, K, false, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
+    if (int e = launch_split_dgrad_reduce(st, g, K, false, dy, W, packed, stats, da3, static_cast<double*>(red), parts)) return e;
     DwSum dwsum;
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nb, dx, dgamma, dbeta,
-                                dwsum.copies > 0 ? &dwsum : nullptr);
+                                dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
   // small images (3x3 'same' stride 1): the image-resident kernel, one row of sums per image
   if (K != 32 && !bf16 && image_f32_supported(g, 1)) {
@@ -350,15 +370,15 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
     DwSum dwsum;
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, g.N, dx, dgamma, dbeta,
-                                dwsum.copies > 0 ? &dwsum : nullptr);
+                                dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
   // bf16 operands on the 32-deep matrix instruction: the same sums in the epilogue of its kernels
   if (const int nr = (K != 32 && bf16_gemm) ? bf16_dgrad_reduce_rows(g) : 0) {
-    if (int e = launch_bf16_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
+    if (int e = launch_bf16_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red), parts)) return e;
     DwSum dwsum;
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nr, dx, dgamma, dbeta,
-                                dwsum.copies > 0 ? &dwsum : nullptr);
+                                dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
   const int tiles = K != 32 && !bf16_gemm && halo_conv_supported(g) ? halo_tile_count(g, 1) : 0;
   if (tiles > 0 && tiles <= kMaxPartialBlocks) {
@@ -368,7 +388,7 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
     DwSum dwsum;
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, tiles, dx, dgamma, dbeta,
-                                dwsum.copies > 0 ? &dwsum : nullptr);
+                                dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
   // 1x1 stride-1 layers: the same sums in the epilogue of the pointwise dgrad kernel
   if (K != 32 && !bf16_gemm && pointwise_supported(g, 1)) {
@@ -380,27 +400,53 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
       DwSum dwsum;
       if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
       return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, rows, dx, dgamma, dbeta,
-                                  dwsum.copies > 0 ? &dwsum : nullptr);
+                                  dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
     }
     // (long contractions: the kernel computed dA3 only)
     DwSum dwsum;
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
     return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta,
-                         dwsum.copies > 0 ? &dwsum : nullptr);
+                         dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
   // Channel counts that are not multiples of 16: the weight gradient goes first, while the workspace of dA3
   // is free to hold its copies.
   if (!channels_in_tiles(g)) {
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, da3, dW, K == 32, nullptr, act)) return e;
     if (int e = launch_conv_dgrad(st, *s, bf16, dy, W, da3)) return e;
-    return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta);
+    return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta, nullptr, 0.0f, next);
   }
   if (int e = launch_conv_dgrad(st, *s, bf16, dy, W, da3)) return e;
   // exact storage keeps the pre-ReLU A2: the weight gradient applies Eq. 3 on the way in
   DwSum dwsum;
   if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, K == 32, &dwsum)) return e;
   return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta,
-                       dwsum.copies > 0 ? &dwsum : nullptr);
+                       dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
+}
+
+}  // namespace
+
+extern "C" {
+
+// Backward: dgrad (exact) and wgrad (from the packed copy) consume dy; then the BN/ReLU
+// backward turns dA3 into dx.  dx may alias dy because dy is dead once both contractions
+// have been enqueued ahead of the kernel that writes dx.
+int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const void* packed,
+                 const void* stats, const float* dy, const float* W, void* scratch, size_t scratch_bytes,
+                 float* dx, float* dW, float* dgamma, float* dbeta) {
+  if (int e = check_shape(s)) return e;
+  if (int e = check_k(K)) return e;
+  if (flags & ~(uint32_t)(ABL_ACCUM_DX | ABL_MATH_BF16)) return ABL_ERR_ARG;
+  if (bad_ptr(packed) || bad_ptr(stats) || bad_ptr(dy) || bad_ptr(W) || bad_ptr(scratch) || bad_ptr(dx) ||
+      bad_ptr(dW) || bad_ptr(dgamma) || bad_ptr(dbeta))
+    return ABL_ERR_ARG;
+  if (scratch_bytes < abl_scratch_bytes(s, K)) return ABL_ERR_SCRATCH;
+  SplitWeights sw{};
+  if (const int np = backward_parts(geom_of(*s), K, (flags & ABL_MATH_BF16) != 0))
+    sw = weights_to_split(*s, 1, np, W, static_cast<char*>(scratch) + wpart_offset(*s), wgrad_partial_bytes(*s));
+  if (sw.out != nullptr)
+    if (int e = launch_split_weights((hipStream_t)stream, sw)) return e;
+  return backward_impl((hipStream_t)stream, s, K, flags, packed, stats, dy, W, scratch, dx, dW, dgamma, dbeta, sw.out,
+                       SplitWeights{});
 }
 
 // ---- the layer with a leaky ReLU (Sec. 3.4) ---------------------------------------------------
@@ -832,6 +878,20 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
     for (int i = 0; i < L; ++i)
       if (trace[i] != nullptr && !aligned16(trace[i])) return ABL_ERR_ARG;
   const size_t xbytes = stack_xpart_bytes(layers, L);
+  char* const lscratch = static_cast<char*>(scratch) + xbytes;
+  const size_t lbytes = abl_stack_scratch_bytes(layers, L, K) - xbytes;
+  // The weights that a layer's data gradient reads in parts are split by the launch of the layer above that comes before
+  // (its apply pass), at a place in the workspace that is free for both.
+  auto parts_of = [&](int i, size_t at) {
+    const abl_layer& l = layers[i];
+    const int np = backward_parts(geom_of(l.shape), K, (flags & ABL_MATH_BF16) != 0);
+    if (np == 0) return SplitWeights{};
+    const size_t from = wpart_offset(l.shape) > at ? wpart_offset(l.shape) : at;
+    return weights_to_split(l.shape, 1, np, l.W, lscratch + (from < lbytes ? from : 0), from < lbytes ? lbytes - from : 0);
+  };
+  SplitWeights sw = parts_of(L - 1, 0);
+  if (sw.out != nullptr)
+    if (int e = launch_split_weights((hipStream_t)stream, sw)) return e;
   for (int i = L - 1; i >= 0; --i) {
     const abl_layer& l = layers[i];
     const GroupInfo gi = group_info(layers, L, skip_every, i);
@@ -845,10 +905,11 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
     const size_t out_floats = (size_t)sh.N * out_dim(sh.H, sh.pad, sh.R, sh.stride) *
                               out_dim(sh.W, sh.pad, sh.S, sh.stride) * sh.Cout;
     if (int e = trace_copy((hipStream_t)stream, trace, i, dy, out_floats)) return e;
-    if (int e = abl_backward(stream, &l.shape, K, f, l.packed, l.stats, dy, l.W,
-                             static_cast<char*>(scratch) + xbytes, scratch_bytes - xbytes, dx, l.dW, l.dgamma,
-                             l.dbeta))
+    const SplitWeights next = i > 0 ? parts_of(i - 1, wpart_offset(l.shape)) : SplitWeights{};
+    if (int e = backward_impl((hipStream_t)stream, &l.shape, K, f, l.packed, l.stats, dy, l.W, lscratch, dx, l.dW, l.dgamma,
+                              l.dbeta, sw.out, next))
       return e;
+    sw = next;
   }
   return ABL_OK;
 }

@@ -17,9 +17,35 @@ constexpr int kMaxPartialBlocks = 512;  // upper bound on per-block reduction pa
 // Bytes of partial-sum workspace for the per-channel reductions over [M,C].
 size_t bn_partial_bytes(int64_t M, int C);
 
+// Division by a number that the host knows: 0 <= n < 2^31, exact.  (n m / 2^(31 + l) with m = 2^(31 + l) / d rounded up and
+// 2^l >= d is off by less than n 2^-(31 + l) < 1 / d.)
+struct Divisor {
+  uint32_t mul = 0x80000000u, shift = 0;
+  Divisor() = default;
+  explicit Divisor(int d) {
+    while (((int64_t)1 << shift) < d) ++shift;
+    mul = (uint32_t)((((uint64_t)1 << (31 + shift)) + (uint64_t)d - 1) / (uint64_t)d);
+  }
+  __device__ inline int of(int n) const { return (int)(__umulhi((uint32_t)n << 1, mul) >> shift); }
+};
+
+// ---- weights of the split-operand convolutions, split once per call -------------------------------------------
+// Parts of all weights in the order in which a wave of split_conv_kernel reads them: [tap][32 contraction channels][16
+// output channels][part][lane] 16-byte pieces, eight consecutive contraction channels of one output channel each.  (The
+// kernel splits its weights itself where no workspace is at hand; every block does so then.)
+struct SplitWeights {
+  const float* w;   // [R][S][Cin][Cout]
+  uint4* out;       // nullptr: nothing to do
+  int mode, np;     // 0 forward, 1 gradient to the input; 3 parts, or 1 = rounded to bf16
+  int taps, Cin, Cout;
+  __host__ __device__ int64_t items() const { return out != nullptr ? (int64_t)taps * Cin * Cout / 8 : 0; }
+};
+int launch_split_weights(hipStream_t st, const SplitWeights& sw);
+
 // ---- batch-norm / quantizer kernels (bn_kernels.hip) ----
+// sw / next: weights to be split by the launch as well, in blocks of their own.
 int launch_bn_stats(hipStream_t st, const float* x, int64_t M, int C, const float* gamma,
-                    const float* beta, int K, void* scratch, void* stats);
+                    const float* beta, int K, void* scratch, void* stats, const SplitWeights& sw = SplitWeights{});
 // naive: a3 = ReLU of the dequantized code instead of the exact A3 (the baseline of Sec. 4).
 // slope: 0 = ReLU (Eq. 3); > 0 = leaky ReLU (Sec. 3.4), in every launcher below that takes one.
 int launch_bn_relu_pack(hipStream_t st, const float* x, int64_t M, int C, int K, const void* stats,
@@ -32,7 +58,8 @@ int launch_unpack(hipStream_t st, const void* packed, int64_t M, int C, int K, c
 // The second halves of the two reductions, for partial sums produced elsewhere (conv epilogues).
 size_t bn_means_offset(int C);
 int launch_bn_stats_finalize(hipStream_t st, const double* partial, int nb, const float* shift_row, int64_t M,
-                             int C, const float* gamma, const float* beta, int K, void* stats);
+                             int C, const float* gamma, const float* beta, int K, void* stats,
+                             const SplitWeights& sw = SplitWeights{});
 // dwsum (nullable): a weight gradient left as `copies` partial copies of n floats by the conv
 // backward kernel; the finalize launch also sums them into dw (fixed order).
 struct DwSum {
@@ -46,10 +73,10 @@ int launch_sgd_momentum(hipStream_t st, int64_t n, float lr, float mu, float wd,
 // Backward of BN + ReLU from dA3 and the codes (Eq. 6-8): both passes.
 int launch_bn_bwd(hipStream_t st, const void* packed, const void* stats, const float* da3, int64_t M,
                   int C, int K, bool accum, void* scratch, float* dx, float* dgamma, float* dbeta,
-                  const DwSum* dwsum = nullptr, float slope = 0.0f);
+                  const DwSum* dwsum = nullptr, float slope = 0.0f, const SplitWeights& next = SplitWeights{});
 int launch_bn_bwd_finish(hipStream_t st, const void* packed, const void* stats, const float* da3, int64_t M,
                          int C, int K, bool accum, void* scratch, int nb, float* dx, float* dgamma,
-                         float* dbeta, const DwSum* dwsum = nullptr, float slope = 0.0f);
+                         float* dbeta, const DwSum* dwsum = nullptr, float slope = 0.0f, const SplitWeights& next = SplitWeights{});
 
 // Convolution geometry passed to the kernels by value.
 struct ConvGeom {
@@ -109,7 +136,9 @@ size_t wgrad_partial_bytes(const abl_shape& s);
 // sums / rows (nullable): where the kernel can, it leaves per-block fp64 sums of y and y^2
 // ([rows][2][Cout], *rows <= kMaxPartialBlocks) for the next layer's statistics; *rows = 0 if not.
 int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* a3, const float* w,
-                    const float* skip, float* y, double* sums = nullptr, int* rows = nullptr);
+                    const float* skip, float* y, double* sums = nullptr, int* rows = nullptr, const void* parts = nullptr);
+// Parts of the weights that launch_conv_fwd can read (SplitWeights::np), 0 = none.
+int conv_fwd_parts(const ConvGeom& g, bool bf16);
 int launch_conv_dgrad(hipStream_t st, const abl_shape& s, bool bf16, const float* dy, const float* w,
                       float* da3);
 // Forward of a 1x1 stride-1 convolution without padding with Eq. 1-3 and Eq. 9 applied while the
@@ -162,7 +191,10 @@ int launch_bf16_gemm(hipStream_t st, const ConvGeom& g, int mode, const float* i
 // whichever bf16 kernel takes the shape: partial = [rows][2][Cin] doubles; bf16_dgrad_reduce_rows = 0 if none does.
 int bf16_dgrad_reduce_rows(const ConvGeom& g);
 int launch_bf16_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
-                             const void* packed, const void* stats, float* da3, double* partial);
+                             const void* packed, const void* stats, float* da3, double* partial,
+                             const void* parts = nullptr);
+// Whether that is split_conv_kernel with one part, which can read `parts`.
+bool bf16_dgrad_reduce_splits(const ConvGeom& g);
 // 3x3 'same' stride-1 convolutions whose whole image fits in LDS as bf16 (up to 208 pixels, e.g.
 // 14x14 with 256 channels): one block per image and 64 output channels.
 // sums (nullable, mode 0): [N][2][Cout] doubles = per-image sum(y), sum(y^2) of the output.
@@ -176,19 +208,21 @@ int launch_image_bf16(hipStream_t st, const ConvGeom& g, int mode, const float* 
 // 0, Eq. 6-7 in launch_split_dgrad_reduce), 0 = not supported.
 // bf16: operands rounded to bf16 instead.
 // sums: with the Eq. 6-7 sums (launch_split_dgrad_reduce).
+// parts (nullable, in the launchers): the weights as SplitWeights leaves them, same mode and operands.
 int split_conv_blocks(const ConvGeom& g, int mode, bool bf16 = false, bool sums = false);
 // The fp32 forward of a 1x1 layer with a pass of its own for Eq. 1-3 and 9 in front is faster than the pointwise kernel's
 // prologue.
 bool split_beats_prologue(const ConvGeom& g);
 int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
-                      const float* skip, float* out, double* sums);
+                      const float* skip, float* out, double* sums, const void* parts = nullptr);
 // The 3x3 forward with Eq. 1-3 and Eq. 9 (fp32 operands, y not x): 1 = launch_split_fwd_fused, which applies them while the
 // patch is staged (*rows = rows of its sums), -1 = launch_split_conv with a pass of its own in front, 0 = other kernels.
 int split_forward3(const ConvGeom& g, int* rows);
 int launch_split_fwd_fused(hipStream_t st, const ConvGeom& g, int K, const float* x, const void* stats, const float* w,
-                           const float* skip, float* y, void* packed, double* sums);
+                           const float* skip, float* y, void* packed, double* sums, const void* parts = nullptr);
 int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* dy, const float* w,
-                              const void* packed, const void* stats, float* da3, double* partial);
+                              const void* packed, const void* stats, float* da3, double* partial,
+                              const void* parts = nullptr);
 
 // Weight gradient of 'same' stride-1 3x3 and 1x1 layers from the codes, dy split into three bf16 parts
 // (wgrad_split.hip; Cin a multiple of 32 - 1x1: 64 - and Cout of 64).  split_wgrad_copies: copies of dW that
@@ -294,6 +328,62 @@ __device__ inline bf16x8_t to_bf16x8(const float (&v)[8]) {
   return bf16x8_t{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3],
                   (__bf16)v[4], (__bf16)v[5], (__bf16)v[6], (__bf16)v[7]};
 }
+// ---- fp32 operands in three bf16 parts (conv_split.hip) ----
+constexpr float kUp = 0x1p23f, kDown = 0x1p-46f;   // both operands are split as 2^23 times their values
+// 2^23 x = h + m + l, eight values at a time (the parts of two values share a 32-bit word)
+__device__ inline void split3(const float (&x)[8], bf16x8_t& h, bf16x8_t& m, bf16x8_t& l) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  uint4 hw, mw, lw;
+  auto two = [](float a, float b, uint32_t& u, uint32_t& v, uint32_t& w) __attribute__((always_inline)) {
+    a *= kUp;
+    b *= kUp;
+    u = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+    const float ra = a - __uint_as_float(u << 16), rb = b - __uint_as_float(u & 0xFFFF0000u);
+    v = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
+    w = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)(ra - __uint_as_float(v << 16)),
+                                            (__bf16)(rb - __uint_as_float(v & 0xFFFF0000u))});
+  };
+  two(x[0], x[1], hw.x, mw.x, lw.x);
+  two(x[2], x[3], hw.y, mw.y, lw.y);
+  two(x[4], x[5], hw.z, mw.z, lw.z);
+  two(x[6], x[7], hw.w, mw.w, lw.w);
+  h = __builtin_bit_cast(bf16x8_t, hw);
+  m = __builtin_bit_cast(bf16x8_t, mw);
+  l = __builtin_bit_cast(bf16x8_t, lw);
+}
+
+__device__ inline void split_weights_item(const SplitWeights& s, int64_t it) {
+  const int Cg = s.mode == 0 ? s.Cin : s.Cout, Ng = s.mode == 0 ? s.Cout : s.Cin;
+  const int lane = (int)(it & 63), li = lane & 15, lk = lane >> 4;
+  const uint32_t tile = (uint32_t)(it >> 6);
+  const uint32_t step = tile / (uint32_t)(Ng / 16), n = 16 * (tile - step * (uint32_t)(Ng / 16)) + li;
+  const uint32_t tap = step / (uint32_t)(Cg / 32), c = 32 * (step - tap * (uint32_t)(Cg / 32)) + 8 * lk;
+  float x[8];
+  if (s.mode == 0) {
+    const float* p = s.w + ((size_t)tap * s.Cin + c) * s.Cout + n;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = p[(size_t)e * s.Cout];
+  } else {
+    const float* p = s.w + ((size_t)(s.taps - 1 - tap) * s.Cin + n) * s.Cout + c;
+#pragma unroll
+    for (int q = 0; q < 8; q += 4) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(p + q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[q + e] = v[e];
+    }
+  }
+  uint4* to = s.out + (size_t)tile * 64 * s.np + lane;
+  if (s.np == 3) {
+    bf16x8_t h, m, l;
+    split3(x, h, m, l);
+    to[0] = __builtin_bit_cast(uint4, h);
+    to[64] = __builtin_bit_cast(uint4, m);
+    to[128] = __builtin_bit_cast(uint4, l);
+  } else {
+    to[0] = __builtin_bit_cast(uint4, to_bf16x8(x));
+  }
+}
+
 __device__ inline shortx4 to_bf16x4(const float4& v) {
   const bf16x4_t b = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
   return __builtin_bit_cast(shortx4, b);

@@ -273,12 +273,20 @@ __device__ inline void reduce_partials(const double* __restrict__ partial, int n
 }
 
 // Eq. 1 statistics, pass 2, and the per-channel constants of Eq. 9/10.
+// SPLIT: blocks from nfin on split weights instead (a kernel of its own: the code costs registers and instruction fetches).
+template <bool SPLIT>
 __global__ __launch_bounds__(kFinThreads) void stats_finalize_kernel(const double* __restrict__ partial, int nb,
                                                                   const float* __restrict__ x, int64_t M,
                                                                   int C, const float* __restrict__ gamma,
                                                                   const float* __restrict__ beta, int K,
-                                                                  float* __restrict__ stats) {
+                                                                  float* __restrict__ stats, int nfin,
+                                                                  SplitWeights sw) {
   __shared__ double sm[32][32];
+  if (SPLIT && (int)blockIdx.x >= nfin) {
+    const int64_t it = (int64_t)(blockIdx.x - nfin) * kFinThreads + threadIdx.x;
+    if (it < sw.items()) split_weights_item(sw, it);
+    return;
+  }
   const int c = blockIdx.x * 16 + (threadIdx.x & 15);
   double t[2];
   reduce_partials(partial, nb, C, t, sm);
@@ -563,14 +571,20 @@ __global__ __launch_bounds__(kFinThreads) void bwd_finalize_dwsum_kernel(const d
   if (part == 0 && i < n) dw[i] = sw[0][o];
 }
 
+// SPLIT: rows of blocks from gridY on split the next layer's weights (72 registers become 76 with that code).
 // Backward, pass 2 (Eq. 8): dx = rstd * (dA1 - Mean(dA1) - A1~ * Mean(A1~ * dA1)).
-template <int K, int VEC, bool ACCUM, bool STREAM>
+template <int K, int VEC, bool ACCUM, bool STREAM, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void bwd_apply_kernel(const void* __restrict__ packed,
                                                              const float* da3, int64_t M, int C, RowGeom g,
                                                              const float* __restrict__ stats,
                                                              const float* __restrict__ means, float* dx,
-                                                             float slope) {
+                                                             float slope, SplitWeights sw) {
   using S = Stored<K, VEC>;
+  if (SPLIT && (int)blockIdx.y >= g.gridY) {
+    const int64_t it = ((int64_t)(blockIdx.y - g.gridY) * gridDim.x + blockIdx.x) * kThreads + threadIdx.x;
+    if (it < sw.items()) split_weights_item(sw, it);
+    return;
+  }
   const ThreadPos p = thread_pos<VEC>(g);
   if (!p.active) return;
   const bool leaky = slope != 0.0f;
@@ -767,6 +781,11 @@ int fast_vec(int K, int C, bool wide) {
 
 inline dim3 grid_of(const RowGeom& g) { return dim3(g.gridX, g.gridY, 1); }
 
+__global__ __launch_bounds__(kThreads) void split_weights_kernel(SplitWeights sw) {
+  const int64_t it = (int64_t)block_of_grid() * kThreads + threadIdx.x;
+  if (it < sw.items()) split_weights_item(sw, it);
+}
+
 }  // namespace
 
 // Room for kMaxPartialBlocks partial rows (the reduce kernels of this file use at most that
@@ -781,8 +800,13 @@ size_t bn_partial_bytes(int64_t M, int C) {
 
 size_t bn_means_offset(int C) { return (size_t)kMaxPartialBlocks * 2 * (size_t)C * sizeof(double); }
 
+int launch_split_weights(hipStream_t st, const SplitWeights& sw) {
+  split_weights_kernel<<<grid_of((sw.items() + kThreads - 1) / kThreads), kThreads, 0, st>>>(sw);
+  return hip_status();
+}
+
 int launch_bn_stats(hipStream_t st, const float* x, int64_t M, int C, const float* gamma,
-                    const float* beta, int K, void* scratch, void* stats) {
+                    const float* beta, int K, void* scratch, void* stats, const SplitWeights& sw) {
   double* partial = static_cast<double*>(scratch);
   const int vec = C % 4 == 0 ? 4 : 1;
   const RowGeom g = make_geom(M, C, vec, true);
@@ -790,15 +814,18 @@ int launch_bn_stats(hipStream_t st, const float* x, int64_t M, int C, const floa
     stats_partial_kernel<4><<<grid_of(g), kThreads, 0, st>>>(x, M, C, g, partial);
   else
     stats_partial_kernel<1><<<grid_of(g), kThreads, 0, st>>>(x, M, C, g, partial);
-  return launch_bn_stats_finalize(st, partial, g.gridY, x, M, C, gamma, beta, K, stats);
+  return launch_bn_stats_finalize(st, partial, g.gridY, x, M, C, gamma, beta, K, stats, sw);
 }
 
 // Second pass of the statistics from `nb` partial rows [nb][2][C]; `shift_row` is the row whose
 // values the sums were shifted by (nullptr: no shift).
 int launch_bn_stats_finalize(hipStream_t st, const double* partial, int nb, const float* shift_row, int64_t M,
-                             int C, const float* gamma, const float* beta, int K, void* stats) {
-  stats_finalize_kernel<<<(C + 15) / 16, kFinThreads, 0, st>>>(partial, nb, shift_row, M, C, gamma, beta, K,
-                                                            static_cast<float*>(stats));
+                             int C, const float* gamma, const float* beta, int K, void* stats, const SplitWeights& sw) {
+  const int nfin = (C + 15) / 16;
+  const unsigned extra = (unsigned)((sw.items() + kFinThreads - 1) / kFinThreads);
+  auto kern = extra > 0 ? stats_finalize_kernel<true> : stats_finalize_kernel<false>;
+  kern<<<nfin + extra, kFinThreads, 0, st>>>(partial, nb, shift_row, M, C, gamma, beta, K,
+                                                             static_cast<float*>(stats), nfin, sw);
   return hip_status();
 }
 
@@ -887,7 +914,7 @@ int launch_unpack(hipStream_t st, const void* packed, int64_t M, int C, int K, c
 
 int launch_bn_bwd(hipStream_t st, const void* packed, const void* stats, const float* da3, int64_t M,
                   int C, int K, bool accum, void* scratch, float* dx, float* dgamma, float* dbeta,
-                  const DwSum* dwsum, float slope) {
+                  const DwSum* dwsum, float slope, const SplitWeights& next) {
   const float* sp = static_cast<const float*>(stats);
   double* partial = static_cast<double*>(scratch);
   const int vec = fast_vec(K, C, false);
@@ -909,14 +936,14 @@ int launch_bn_bwd(hipStream_t st, const void* packed, const void* stats, const f
   }
   if (hipGetLastError() != hipSuccess) return ABL_ERR_HIP;
   return launch_bn_bwd_finish(st, packed, stats, da3, M, C, K, accum, scratch, gr.gridY, dx, dgamma, dbeta, dwsum,
-                              slope);
+                              slope, next);
 }
 
 // Eq. 7 totals and Eq. 8 from `nb` partial rows [nb][2][C] of (sum dA2, sum A1~ dA2) at the
 // start of `scratch`: finalize kernel, then the apply pass.
 int launch_bn_bwd_finish(hipStream_t st, const void* packed, const void* stats, const float* da3, int64_t M,
                          int C, int K, bool accum, void* scratch, int nb, float* dx, float* dgamma,
-                         float* dbeta, const DwSum* dwsum, float slope) {
+                         float* dbeta, const DwSum* dwsum, float slope, const SplitWeights& next) {
   const float* sp = static_cast<const float*>(stats);
   const double* partial = static_cast<const double*>(scratch);
   float* means = reinterpret_cast<float*>(static_cast<char*>(scratch) + bn_means_offset(C));
@@ -943,16 +970,23 @@ int launch_bn_bwd_finish(hipStream_t st, const void* packed, const void* stats, 
     else if (K == 8) flat_bwd_apply_kernel<8, false><<<blocks, kThreads, 0, st>>>(pk, da3, E, C, sp, means, dx, slope);
     else if (accum) flat_bwd_apply_kernel<32, true><<<blocks, kThreads, 0, st>>>(pk, da3, E, C, sp, means, dx, slope);
     else flat_bwd_apply_kernel<32, false><<<blocks, kThreads, 0, st>>>(pk, da3, E, C, sp, means, dx, slope);
+    if (next.out != nullptr && hipPeekAtLastError() == hipSuccess) return launch_split_weights(st, next);
     return hip_status();
   }
   const RowGeom ga = make_geom(M, C, vec, false);
+  // the next layer's weights in rows of blocks of their own (a grid has 65535 rows: huge ones in a launch of their own)
+  const int64_t rows = (next.items() + (int64_t)kThreads * ga.gridX - 1) / ((int64_t)kThreads * ga.gridX);
+  const bool ride = rows + ga.gridY <= 65535;
+  if (!ride)
+    if (int e = launch_split_weights(st, next)) return e;
+  const SplitWeights sw = ride ? next : SplitWeights{};
+  const dim3 grid(ga.gridX, ga.gridY + (ride ? (unsigned)rows : 0u));
   const bool stream = M * C * (int64_t)sizeof(float) >= kStreamBytes;
-#define ABL_APPLY1(KK, VV, AA)                                                                              \
-  do {                                                                                                      \
-    if (stream)                                                                                             \
-      bwd_apply_kernel<KK, VV, AA, true><<<grid_of(ga), kThreads, 0, st>>>(packed, da3, M, C, ga, sp, means, dx, slope); \
-    else                                                                                                    \
-      bwd_apply_kernel<KK, VV, AA, false><<<grid_of(ga), kThreads, 0, st>>>(packed, da3, M, C, ga, sp, means, dx, slope); \
+#define ABL_APPLY1(KK, VV, AA)                                                                                         \
+  do {                                                                                                                 \
+    auto kern = stream ? (rows > 0 && ride ? bwd_apply_kernel<KK, VV, AA, true, true> : bwd_apply_kernel<KK, VV, AA, true, false>)      \
+                       : (rows > 0 && ride ? bwd_apply_kernel<KK, VV, AA, false, true> : bwd_apply_kernel<KK, VV, AA, false, false>);   \
+    kern<<<grid, kThreads, 0, st>>>(packed, da3, M, C, ga, sp, means, dx, slope, sw);                                  \
   } while (0)
 #define ABL_APPLY(KK, VV)             \
   do {                                \

@@ -652,13 +652,18 @@ int bf16_dgrad_reduce_rows(const ConvGeom& g) {
   return bf16_gemm_supported(g, 1) ? gemm_sum_rows(g, 1) : 0;
 }
 
+bool bf16_dgrad_reduce_splits(const ConvGeom& g) {
+  return !image_bf16_supported(g, 1) && split_conv_blocks(g, 1, true, true) > 0;
+}
+
 int launch_bf16_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
-                             const void* packed, const void* stats, float* da3, double* partial) {
+                             const void* packed, const void* stats, float* da3, double* partial, const void* parts) {
   if ((K != 4 && K != 8) || bf16_dgrad_reduce_rows(g) == 0) return ABL_ERR_SHAPE;
   const uint8_t* codes = static_cast<const uint8_t*>(packed);
   const float* sp = static_cast<const float*>(stats);
   if (image_bf16_supported(g, 1)) return launch_image_bf16_epi(st, g, K, dy, w, da3, partial, codes, sp);
-  if (split_conv_blocks(g, 1, true, true) > 0) return launch_split_dgrad_reduce(st, g, K, true, dy, w, packed, stats, da3, partial);
+  if (bf16_dgrad_reduce_splits(g))
+    return launch_split_dgrad_reduce(st, g, K, true, dy, w, packed, stats, da3, partial, parts);
   if (K == 4) return launch_gemm<1, 4>(st, g, dy, w, nullptr, da3, partial, codes, sp);
   return launch_gemm<1, 8>(st, g, dy, w, nullptr, da3, partial, codes, sp);
 }

@@ -925,8 +925,16 @@ size_t wgrad_partial_bytes(const abl_shape& s) {
   return ((size_t)(p.split > img ? p.split : img) * n + 255) / 256 * 256;
 }
 
+// (bf16: 3x3 64 -> 64 @56x56 61 -> 53 us, 128 -> 128 @28x28 60 -> 30; 1x1 1024 -> 256 @14x14 31 -> 25, 2048 -> 512 @7x7
+// 53 -> 35; with 64 output channels per block not faster: 256 -> 64 @56x56 43 against 45)
+int conv_fwd_parts(const ConvGeom& g, bool bf16) {
+  if (!mfma_ok(g)) return 0;
+  if (!bf16) return split_conv_blocks(g, 0) > 0 ? 3 : 0;
+  return !image_bf16_supported(g, 0) && (g.R == 3 || g.Cout % 128 == 0) && split_conv_blocks(g, 0, true) > 0 ? 1 : 0;
+}
+
 int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* a3, const float* w,
-                    const float* skip, float* y, double* sums, int* rows) {
+                    const float* skip, float* y, double* sums, int* rows, const void* parts) {
   const ConvGeom g = geom_of(s);
   if (rows != nullptr) *rows = 0;
   if (!mfma_ok(g)) return launch_ragged_conv(st, g, 0, a3, w, skip, y);
@@ -936,19 +944,12 @@ int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* 
     if (want) *rows = g.N;
     return launch_image_bf16(st, g, 0, a3, w, skip, y, want ? sums : nullptr);
   }
-  // (3x3 64 -> 64 @56x56 61 -> 53 us, 128 -> 128 @28x28 60 -> 30; 1x1 1024 -> 256 @14x14 31 -> 25, 2048 -> 512 @7x7 53 -> 35;
-  // with 64 output channels per block not faster: 256 -> 64 @56x56 43 against 45)
-  if (const int nb = bf16 && (g.R == 3 || g.Cout % 128 == 0) ? split_conv_blocks(g, 0, true) : 0) {
+  if (conv_fwd_parts(g, bf16) > 0) {
     const bool want = sums != nullptr && rows != nullptr;
-    if (want) *rows = nb;
-    return launch_split_conv(st, g, 0, true, a3, w, skip, y, want ? sums : nullptr);
+    if (want) *rows = split_conv_blocks(g, 0, bf16);
+    return launch_split_conv(st, g, 0, bf16, a3, w, skip, y, want ? sums : nullptr, parts);
   }
   if (bf16 && bf16_gemm_supported(g, 0)) return launch_bf16_gemm(st, g, 0, a3, w, skip, y, sums, rows);
-  if (const int nb = !bf16 ? split_conv_blocks(g, 0) : 0) {
-    const bool want = sums != nullptr && rows != nullptr;
-    if (want) *rows = nb;
-    return launch_split_conv(st, g, 0, false, a3, w, skip, y, want ? sums : nullptr);
-  }
   // small images: the whole image resident in LDS, one row of sums per image
   if (!bf16 && image_f32_supported(g, 0)) {
     const bool want = sums != nullptr && rows != nullptr;

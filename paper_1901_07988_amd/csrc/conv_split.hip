@@ -29,7 +29,10 @@
 // positions).
 // With bf16 operands (ABL_MATH_BF16) the same kernel runs with one part per operand: rounded once, one product.
 
+#include <type_traits>
+
 #include "abl_internal.h"
+
 
 namespace abl {
 namespace {
@@ -43,31 +46,8 @@ struct Tiling {
   int tiles, per;    // tiles in all, tiles per block (consecutive)
   int gm;            // blocks along the pixels
   int npos;          // positions of a patch
+  Divisor w, pw, h, ph, hw, per_unit;   // by W, W + 2, H, H + 2, H W, ntr
 };
-
-constexpr float kUp = 0x1p23f, kDown = 0x1p-46f;   // both operands are split as 2^23 times their values
-
-// 2^23 x = h + m + l, eight values at a time (the parts of two values share a 32-bit word)
-__device__ inline void split3(const float (&x)[8], bf16x8_t& h, bf16x8_t& m, bf16x8_t& l) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  uint4 hw, mw, lw;
-  auto two = [](float a, float b, uint32_t& u, uint32_t& v, uint32_t& w) __attribute__((always_inline)) {
-    a *= kUp;
-    b *= kUp;
-    u = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
-    const float ra = a - __uint_as_float(u << 16), rb = b - __uint_as_float(u & 0xFFFF0000u);
-    v = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
-    w = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)(ra - __uint_as_float(v << 16)),
-                                            (__bf16)(rb - __uint_as_float(v & 0xFFFF0000u))});
-  };
-  two(x[0], x[1], hw.x, mw.x, lw.x);
-  two(x[2], x[3], hw.y, mw.y, lw.y);
-  two(x[4], x[5], hw.z, mw.z, lw.z);
-  two(x[6], x[7], hw.w, mw.w, lw.w);
-  h = __builtin_bit_cast(bf16x8_t, hw);
-  m = __builtin_bit_cast(bf16x8_t, mw);
-  l = __builtin_bit_cast(bf16x8_t, lw);
-}
 
 // One output from the operands themselves (products and sums in 64 bits), for values that are not finite.
 template <int MODE, int TAPS, int FUSE>
@@ -113,9 +93,10 @@ __host__ __device__ constexpr int area_bytes(int taps, int nt, int ks, int cpp, 
 // NP = 3: operands in three parts, as above; NP = 1: rounded to bf16.
 // FUSE = K (4 or 8, 3x3 forward): `in` is the layer input x; Eq. 1-3 are applied on the way into LDS and the K-bit codes of
 // the block's own pixels written to `packed` (the blocks along the output channels take turns over the phases).
-template <int MODE, int TAPS, int NT, int KS, int CPP, int SU, int EPI, int NP, int FUSE = 0>
+template <int MODE, int TAPS, int NT, int KS, int CPP, int SU, int EPI, int NP, bool PRE, int FUSE = 0>
 __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float* __restrict__ in,
                                                                           const float* __restrict__ wgt,
+                                                                          const uint4* __restrict__ parts,
                                                                           const float* skip, float* out,
                                                                           double* __restrict__ sums,
                                                                           const uint8_t* __restrict__ codes,
@@ -126,6 +107,11 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   constexpr int BN = 16 * NT * WN;
   constexpr bool DB = KS > 1;
   constexpr int C8 = CH / 8;                           // staging items per position
+  constexpr int STEPS = TAPS * CPP;                    // k-steps of a phase and wave
+  // pixel fragments of a k-step (7 tiles, NP parts), and registers for as many as are read ahead.  (A wave that has to wait
+  // for each tile's reads leaves its SIMD idle as soon as the other wave waits at a barrier.)
+  constexpr int NF = MT * NP, SLOTS = 7, LOOK = SLOTS - 1;
+  static_assert(NF % SLOTS == 0, "a k-step starts in the slot of the one before");
   // the patch: bytes from a position, eight channels, a part and a chunk to the next
   constexpr int NPOS = SU * THREADS / C8;
   constexpr int POS_B = TAPS == 9 ? 16 : 64 * NP * CHUNKS + 16, C8_B = TAPS == 9 ? 16 * NPOS : 16;
@@ -155,7 +141,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
 
   // weights of a k-step: forward: the lane's column in eight rows; gradient: 32 contiguous bytes
   uint32_t w_lane = 4u * (MODE == 0 ? (uint32_t)(8 * lk * g.Cout + li) : (uint32_t)(li * g.Cout + 8 * lk));
-  auto load_w = [&](float (&raw)[NT][8], int tap, int c0) __attribute__((always_inline)) {
+  auto load_w = [&](auto& raw, int tap, int c0) __attribute__((always_inline)) {
     // (opaque: the lane's 32-bit offset stays a register beside the scalar base instead of a 64-bit address)
     asm volatile("" : "+v"(w_lane));
     if constexpr (MODE == 0) {
@@ -164,7 +150,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       for (int e = 0; e < 8; ++e)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
-          raw[j][e] = *reinterpret_cast<const float*>(wb + (size_t)(4 * e) * g.Cout + 64 * j + w_lane);
+          raw[j][e] = *reinterpret_cast<const uint32_t*>(wb + (size_t)(4 * e) * g.Cout + 64 * j + w_lane);
     } else {
       const char* wb = reinterpret_cast<const char*>(wgt + ((size_t)((TAPS - 1 - tap) * g.Cin + n0) * g.Cout + c0));
 #pragma unroll
@@ -173,9 +159,21 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         for (int q = 0; q < 2; ++q) {
           const floatx4 v = *reinterpret_cast<const floatx4*>(wb + (size_t)(64 * j) * g.Cout + 16 * q + w_lane);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) raw[j][4 * q + e] = v[e];
+          for (int e = 0; e < 4; ++e) raw[j][4 * q + e] = __float_as_uint(v[e]);
         }
     }
+  };
+
+  // PRE: the parts of a k-step in fragment order, a kilobyte per output-channel tile and part
+  auto load_parts = [&](auto& raw, int tap, int c0) __attribute__((always_inline)) {
+    const uint4* wb = parts + ((size_t)(tap * (Cg / 32) + c0 / 32) * (Ng / 16) + n0 / 16) * (64 * NP);
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const uint4 v = wb[(j * NP + q) * 64 + lane];
+        raw[j][4 * q] = v.x, raw[j][4 * q + 1] = v.y, raw[j][4 * q + 2] = v.z, raw[j][4 * q + 3] = v.w;
+      }
   };
 
   if (FUSE != 0 && blockIdx.x == 0 && tid < pack_pad)   // the tail of the store's last 128-byte row
@@ -188,25 +186,48 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   int s_off[SU];   // element offset of the item's channels (phase 0), -1 = zeros
   uint32_t own = 0;   // (FUSE) items whose position is a pixel of the tile
   float sv[SU][8];
-  auto stage_load = [&](int ph) __attribute__((always_inline)) {
-    const float* src = in + ph * CH;
+  auto load_item = [&](int ph, int u, int keep) __attribute__((always_inline)) {
+    const float* src = in + ph * CH + ((s_off[u] < 0 ? 0 : s_off[u]) & keep);
 #pragma unroll
-    for (int u = 0; u < SU; ++u) {
-      const int o = s_off[u] < 0 ? 0 : s_off[u];
+    for (int q = 0; q < 2; ++q) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(src + 4 * q);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const floatx4 v = *reinterpret_cast<const floatx4*>(src + o + 4 * q);
+      for (int e = 0; e < 4; ++e) sv[u][4 * q + e] = v[e];
+    }
+  };
+  auto stage_load = [&](int ph, bool exists) __attribute__((always_inline)) {
+    // (past the last phase every lane reads the first channels again: no branch, behind which the compiler would wait for all
+    // that is in flight)
+    const bool none = !exists && ph >= nph;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sv[u][4 * q + e] = v[e];
-      }
+    for (int u = 0; u < SU; ++u) load_item(none ? 0 : ph, u, none ? 0 : -1);
+  };
+  auto store_item = [&](unsigned char* buf, int u) __attribute__((always_inline)) {
+    bf16x8_t h, m, l;   // (NP = 1: the first only)
+    if (TAPS == 9 || s_off[u] < 0)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sv[u][e] = s_off[u] < 0 ? 0.0f : sv[u][e];
+    if constexpr (NP == 3) split3(sv[u], h, m, l);
+    else h = to_bf16x8(sv[u]);
+    const int it = tid + THREADS * u;
+    const int pos = TAPS == 9 ? (it & 15) + 16 * (it / (16 * C8)) : it / C8;
+    const int c8 = TAPS == 9 ? (it >> 4) % C8 : it % C8;
+    unsigned char* to = buf + (c8 >> 2) * CHUNK_B + (c8 & 3) * C8_B + pos * POS_B;
+    *reinterpret_cast<bf16x8_t*>(to) = h;
+    if constexpr (NP == 3) {
+      *reinterpret_cast<bf16x8_t*>(to + PART_B) = m;
+      *reinterpret_cast<bf16x8_t*>(to + 2 * PART_B) = l;
     }
   };
   // a tile: pixels p0 .. p_end - 1; its patch starts a row above the first of them, in rows of images padded to H + 2
-  auto first_pixel = [&](int t) __attribute__((always_inline)) { return (t / tl.ntr) * tl.unit + (t % tl.ntr) * tl.run; };
-  auto last_pixel = [&](int t) __attribute__((always_inline)) {
-    return min(min(first_pixel(t) + tl.run, (t / tl.ntr + 1) * tl.unit), Mg);
+  auto first_pixel = [&](int t) __attribute__((always_inline)) { 
+    const int q = tl.per_unit.of(t);
+    return q * tl.unit + (t - q * tl.ntr) * tl.run;
   };
-  auto first_row = [&](int p0) __attribute__((always_inline)) { return p0 / W + 2 * (p0 / (H * W)); };
+  auto last_pixel = [&](int t) __attribute__((always_inline)) {
+    return min(min(first_pixel(t) + tl.run, (tl.per_unit.of(t) + 1) * tl.unit), Mg);
+  };
+  auto first_row = [&](int p0) __attribute__((always_inline)) { return tl.w.of(p0) + 2 * tl.hw.of(p0); };
   auto begin_tile = [&](int t) __attribute__((always_inline)) {
     const int p0 = first_pixel(t), p_end = last_pixel(t), row0 = first_row(p0);
     own = 0;
@@ -216,8 +237,8 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       const int pos = TAPS == 9 ? (it & 15) + 16 * (it / (16 * C8)) : it / C8;
       const int c8 = TAPS == 9 ? (it >> 4) % C8 : it % C8;
       if (TAPS == 9) {
-        const int prow = pos / PW, w = pos - prow * PW - 1;
-        const int n = (row0 + prow) / (H + 2), h = row0 + prow - n * (H + 2) - 1;
+        const int prow = tl.pw.of(pos), w = pos - prow * PW - 1;
+        const int n = tl.ph.of(row0 + prow), h = row0 + prow - n * (H + 2) - 1;
         s_off[u] = pos < tl.npos && n < g.N && h >= 0 && h < H && w >= 0 && w < W ? ((n * H + h) * W + w) * Cg + 8 * c8 : -1;
         if constexpr (FUSE != 0) {
           const int p = (n * H + h) * W + w;
@@ -227,7 +248,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         s_off[u] = p0 + pos < p_end ? (p0 + pos) * Cg + 8 * c8 : -1;
       }
     }
-    stage_load(0);
+    stage_load(0, true);
   };
   begin_tile(mb * tl.per);
   for (int t = mb * tl.per; t < t_end; ++t) {
@@ -277,23 +298,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         }
       }
 #pragma unroll
-      for (int u = 0; u < SU; ++u) {
-        bf16x8_t h, m, l;   // (NP = 1: the first only)
-        if (TAPS == 9 || s_off[u] < 0)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) sv[u][e] = s_off[u] < 0 ? 0.0f : sv[u][e];
-        if constexpr (NP == 3) split3(sv[u], h, m, l);
-        else h = to_bf16x8(sv[u]);
-        const int it = tid + THREADS * u;
-        const int pos = TAPS == 9 ? (it & 15) + 16 * (it / (16 * C8)) : it / C8;
-        const int c8 = TAPS == 9 ? (it >> 4) % C8 : it % C8;
-        unsigned char* to = buf + (c8 >> 2) * CHUNK_B + (c8 & 3) * C8_B + pos * POS_B;
-        *reinterpret_cast<bf16x8_t*>(to) = h;
-        if constexpr (NP == 3) {
-          *reinterpret_cast<bf16x8_t*>(to + PART_B) = m;
-          *reinterpret_cast<bf16x8_t*>(to + 2 * PART_B) = l;
-        }
-      }
+      for (int u = 0; u < SU; ++u) store_item(buf, u);
     };
     int a_base[MT];
 #pragma unroll
@@ -301,8 +306,8 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       int m = 16 * i + li;
       if (TAPS == 9) {
         const int p = p0 + m < p_end ? p0 + m : p_end - 1;   // slots past the tile: any position of it, never stored
-        const int row = p / W;
-        m = (row + 2 * (row / H) - row0) * PW + p - row * W;
+        const int row = tl.w.of(p);
+        m = (row + 2 * tl.h.of(row) - row0) * PW + p - row * W;
       }
       a_base[i] = m * POS_B + kg * CPP * CHUNK_B + lk * C8_B;
     }
@@ -320,18 +325,18 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     constexpr int CU = (16 * MT * CPR + THREADS - 1) / THREADS;              // ... per thread
     constexpr int CPITCH = 16 * CPR + 16;
     uint4 cq[CU];
-    float raw[NT][8];
-    load_w(raw, 0, kg * CPP * 32);
-    for (int ph = 0; ph < nph; ++ph) {
-      unsigned char* cur = smem + (DB ? (ph & 1) * bufsz : 0);
-      // (two buffers: this one was last read a phase ago, before the barrier that followed)
-      if (!DB || ph == 0) __syncthreads();
-      stage_store(cur, ph);
-      __syncthreads();
-      if (ph + 1 < nph) {
-        stage_load(ph + 1);
-      } else if constexpr (EPI > 1) {
-        // the epilogue's codes, behind the last k-steps
+    // Weights of two k-steps in turn: the set that a step reads and the one that it asks for.  (One set and a copy of it waits for
+    // everything in flight at the copy.)
+    constexpr int RW = PRE ? 4 * NP : 8;
+    uint32_t wset[2][NT][RW];
+    auto load_set = [&](uint32_t (&w)[NT][RW], int tap, int c0) __attribute__((always_inline)) {
+      if constexpr (PRE) load_parts(w, tap, c0);
+      else load_w(w, tap, c0);
+    };
+    load_set(wset[0], 0, kg * CPP * 32);
+    // the epilogue's codes, behind the last k-steps
+    auto load_codes = [&]() __attribute__((always_inline)) {
+      if constexpr (EPI > 1) {
         const uint8_t* cs = codes + ((size_t)p0 * Ng + nb) * EPI / 8;
 #pragma unroll
         for (int u = 0; u < CU; ++u) {
@@ -339,61 +344,119 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
           cq[u] = *reinterpret_cast<const uint4*>(cs + (uint32_t)(it / CPR * (Ng * EPI / 8) + it % CPR * 16));
         }
       }
-#pragma unroll 1
-      for (int ks = 0; ks < TAPS * CPP; ++ks) {
-        const int cc = ks / TAPS, tap = ks - cc * TAPS;
-        bf16x8_t bh[NT], bm[NT], bl[NT];
+    };
+    auto step_off = [&](int ks) __attribute__((always_inline)) {
+      const int cc = ks / TAPS, tap = ks - cc * TAPS;
+      return (TAPS == 9 ? (tap / 3) * PW + tap % 3 : 0) * POS_B + cc * CHUNK_B;
+    };
+    bf16x8_t a[SLOTS];
+    auto read_a = [&](const unsigned char* at, int f) __attribute__((always_inline)) {
+      a[f % SLOTS] = *reinterpret_cast<const bf16x8_t*>(at + a_base[f / NP] + (f % NP) * PART_B);
+    };
+    // k-step ks of phase ph, whose patch is at cur; last: 1 = the phase is the tile's last, 0 = it is not, 2 = either
+    auto k_step = [&](uint32_t (&use)[NT][RW], uint32_t (&fill)[NT][RW], int ph, int ks, const unsigned char* cur, bool first,
+                      int last) __attribute__((always_inline)) {
+      bf16x8_t bh[NT], bm[NT], bl[NT];
 #pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          if constexpr (NP == 3) split3(raw[j], bh[j], bm[j], bl[j]);
-          else bh[j] = to_bf16x8(raw[j]);
-        }
-        // the next k-step's weights (the very last step asks for its own again: no branch)
-        {
-          const bool wrap = ks + 1 == TAPS * CPP;
-          const bool end = wrap && ph + 1 == nph;
-          const int nks = end ? ks : wrap ? 0 : ks + 1;
-          const int ncc = nks / TAPS, ntap = nks - ncc * TAPS;
-          load_w(raw, ntap, (wrap && !end ? ph + 1 : ph) * CH + (kg * CPP + ncc) * 32);
-        }
-        const int off = (TAPS == 9 ? (tap / 3) * PW + tap % 3 : 0) * POS_B + cc * CHUNK_B;
-        const unsigned char* ab = cur + off;
-        bf16x8_t ah[2], am[2], al[2];
-        auto read_a = [&](int set, int i) __attribute__((always_inline)) {
-          ah[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i]);
+      for (int j = 0; j < NT; ++j) {
+        if constexpr (PRE) {
+          bh[j] = __builtin_bit_cast(bf16x8_t, make_uint4(use[j][0], use[j][1], use[j][2], use[j][3]));
           if constexpr (NP == 3) {
-            am[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + PART_B);
-            al[set] = *reinterpret_cast<const bf16x8_t*>(ab + a_base[i] + 2 * PART_B);
+            bm[j] = __builtin_bit_cast(bf16x8_t, make_uint4(use[j][4], use[j][5], use[j][6], use[j][7]));
+            bl[j] = __builtin_bit_cast(bf16x8_t, make_uint4(use[j][8], use[j][9], use[j][10], use[j][11]));
           }
-        };
-        read_a(0, 0);
+        } else {
+          float x[8];
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const int c = i & 1;
-          if (i + 1 < MT) read_a(c ^ 1, i + 1);
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (NP == 3) {
-#pragma unroll
-          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[j], ah[c], lo[j][i], 0, 0, 0);
-          }
-#pragma unroll
-          for (int j = 0; j < NT; ++j) hi[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], ah[c], hi[j][i], 0, 0, 0);
-          if constexpr (NP == 3) {
-#pragma unroll
-          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], al[c], lo[j][i], 0, 0, 0);
-#pragma unroll
-          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[j], am[c], lo[j][i], 0, 0, 0);
-#pragma unroll
-          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[j], ah[c], lo[j][i], 0, 0, 0);
-#pragma unroll
-          for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], am[c], lo[j][i], 0, 0, 0);
-          }
+          for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(use[j][e]);
+          if constexpr (NP == 3) split3(x, bh[j], bm[j], bl[j]);
+          else bh[j] = to_bf16x8(x);
         }
       }
+      // the next k-step's weights (the very last step asks for its own again: no branch)
+      const bool wrap = ks + 1 == STEPS, end = wrap && ph + 1 == nph;
+      {
+        const int nks = end ? ks : wrap ? 0 : ks + 1;
+        const int ncc = nks / TAPS, ntap = nks - ncc * TAPS;
+        load_set(fill, ntap, (wrap && !end ? ph + 1 : ph) * CH + (kg * CPP + ncc) * 32);
+      }
+      // after them the input of the next phase (two steps' weights come back before it has to)
+      if (first) {
+        if (last != 1) stage_load(ph + 1, last == 0);
+        if (last == 1 || (last == 2 && ph + 1 == nph)) load_codes();
+      }
+      const unsigned char *const ab = cur + step_off(ks), *const nab = cur + step_off(wrap ? ks : ks + 1);
+      // fragment by fragment, six reads in flight
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        const int i = f / NP, q = f % NP;
+        if (f + LOOK < NF) read_a(ab, f + LOOK);
+        else if (STEPS > 1) read_a(nab, f + LOOK - NF);   // (past a phase's last step: read, not used)
+        __builtin_amdgcn_sched_barrier(0);
+        const bf16x8_t& x = a[f % SLOTS];
+        if constexpr (NP == 3) {
+          if (q == 0)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[j], x, lo[j][i], 0, 0, 0);
+        }
+        if (q == 0)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) hi[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], x, hi[j][i], 0, 0, 0);
+        if constexpr (NP == 3) {
+          if (q < 2)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm[j], x, lo[j][i], 0, 0, 0);
+          if (q > 0)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], x, lo[j][i], 0, 0, 0);
+        }
+      }
+    };
+    auto phase = [&](int ph, auto last_c) __attribute__((always_inline)) {
+      constexpr int last = decltype(last_c)::value;
+      unsigned char* const cur = smem + (DB ? (ph & 1) * bufsz : 0);
+      // (two buffers: this one was last read a phase ago, before the barrier that followed)
+      if (!DB || ph == 0) __syncthreads();
+      stage_store(cur, ph);
+      __syncthreads();
+#pragma unroll
+      for (int f = 0; f < LOOK; ++f) read_a(cur + step_off(0), f);
+      // each set in its own registers; an odd number of steps leaves the next weights in the wrong one.  (Few copies of the
+      // step's code: a kernel starts with a cold instruction cache.)
+      if constexpr (STEPS >= 9) __builtin_amdgcn_s_setprio(3);
+      k_step(wset[0], wset[1], ph, 0, cur, true, last);
+      if constexpr (STEPS == 2) k_step(wset[1], wset[0], ph, 1, cur, false, last);
+      if constexpr (STEPS >= 9) {
+#pragma unroll 1
+        for (int ks = 1; ks < STEPS; ks += 2) {
+          // two waves of a SIMD that are to meet at the end of the phase: the one that is behind goes first
+          if (ks == 3) __builtin_amdgcn_s_setprio(2);
+          else if (ks == 5) __builtin_amdgcn_s_setprio(1);
+          else if (ks == 7) __builtin_amdgcn_s_setprio(0);
+          k_step(wset[1], wset[0], ph, ks, cur, false, last);
+          k_step(wset[0], wset[1], ph, ks + 1, cur, false, last);
+        }
+      }
+      if constexpr (STEPS % 2 == 1) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int e = 0; e < RW; ++e) wset[0][j][e] = wset[1][j][e];
+      }
+    };
+    if constexpr (NP == 1) {   // (short code: a tile's last phase apart)
+      for (int ph = 0; ph + 1 < nph; ++ph) phase(ph, std::integral_constant<int, 0>{});
+      phase(nph - 1, std::integral_constant<int, 1>{});
+    } else {
+      for (int ph = 0; ph < nph; ++ph) phase(ph, std::integral_constant<int, 2>{});
     }
 
     if (t + 1 < t_end) begin_tile(t + 1);
-    // ---- the lane holds channels n0 + 16 j + 4 lk .. +3 of pixel slot 16 (MT wm + i) + li
+    // ---- the lane holds channels n0 + 16 j + 4 lk .. +3 of pixel slot 16 i + li
+    // (opaque: addresses and constants of the epilogue, formed ahead of the contraction, had no registers to wait in)
+    int tid_e = tid;
+    asm volatile("" : "+v"(tid_e));
+    const int lane_e = tid_e & 63, li_e = lane_e & 15, lk_e = lane_e >> 4;
     floatx4 v[NT][MT];
 #pragma unroll
     for (int j = 0; j < NT; ++j)
@@ -404,20 +467,20 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     if constexpr (EPI > 1) {
 #pragma unroll
       for (int u = 0; u < CU; ++u) {
-        const int it = tid + THREADS * u;
+        const int it = tid_e + THREADS * u;
         if (it < 16 * MT * CPR) *reinterpret_cast<uint4*>(cbuf + it / CPR * CPITCH + it % CPR * 16) = cq[u];
       }
       if (KS == 1) __syncthreads();
     }
     if constexpr (KS == 2) {
-      unsigned char* dst = smem + (size_t)((wave ^ WN) * I0 * NT) * 1024 + lane * 16;
+      unsigned char* dst = smem + (size_t)((wave ^ WN) * I0 * NT) * 1024 + lane_e * 16;
 #pragma unroll
       for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int i = 0; i < MT; ++i)
           if ((i < I0) == (kg == 1)) *reinterpret_cast<floatx4*>(dst + (j * I0 + (i < I0 ? i : i - I0)) * 1024) = v[j][i];
       __syncthreads();
-      const unsigned char* srcp = smem + (size_t)(wave * I0 * NT) * 1024 + lane * 16;
+      const unsigned char* srcp = smem + (size_t)(wave * I0 * NT) * 1024 + lane_e * 16;
 #pragma unroll
       for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -427,7 +490,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     int px[MT];   // the lane's pixels, -1 = none
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-      px[i] = p0 + 16 * i + li;
+      px[i] = p0 + 16 * i + li_e;
       if (px[i] >= p_end) px[i] = -1;
     }
     // outputs that are not finite: again from the fp32 operands, one after the other
@@ -451,7 +514,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
               for (int r = 0; r < 4; ++r)
                 if (e == (j * MT + i) * 4 + r && (KS == 1 || (i < I0) == (kg == 0))) x = v[j][i][r], p = px[i];
           if (fabsf(x) < INFINITY || p < 0) continue;
-          x = exact_output<MODE, TAPS, FUSE>(in, wgt, stats, H, W, g.Cin, g.Cout, p, n0 + 16 * (e / (4 * MT)) + 4 * lk + (e & 3));
+          x = exact_output<MODE, TAPS, FUSE>(in, wgt, stats, H, W, g.Cin, g.Cout, p, n0 + 16 * (e / (4 * MT)) + 4 * lk_e + (e & 3));
 #pragma unroll
           for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -469,7 +532,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         if (KS == 2 && (i < I0) != (kg == 0)) continue;
 #pragma unroll
         for (int j = 0; j < NT; ++j)
-          v[j][i] += *reinterpret_cast<const floatx4*>(skip + (size_t)(px[i] < 0 ? 0 : px[i]) * Ng + n0 + 16 * j + 4 * lk);
+          v[j][i] += *reinterpret_cast<const floatx4*>(skip + (size_t)(px[i] < 0 ? 0 : px[i]) * Ng + n0 + 16 * j + 4 * lk_e);
       }
     }
 #pragma unroll
@@ -478,13 +541,13 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       if (px[i] < 0) continue;
 #pragma unroll
       for (int j = 0; j < NT; ++j)
-        *reinterpret_cast<floatx4*>(out + (size_t)px[i] * Ng + n0 + 16 * j + 4 * lk) = v[j][i];
+        *reinterpret_cast<floatx4*>(out + (size_t)px[i] * Ng + n0 + 16 * j + 4 * lk_e) = v[j][i];
     }
     // the sums, a channel tile at a time: one tile's sums and constants only are live
     if constexpr (EPI != 0)
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      const int nch = n0 + 16 * j + 4 * lk;
+      const int nch = n0 + 16 * j + 4 * lk_e;
       double s1[4] = {0.0, 0.0, 0.0, 0.0}, s2[4] = {0.0, 0.0, 0.0, 0.0};
       floatx4 st4;
       float offh[4];   // code + offh = Eq. 10 over its step (exact below 2^23; from there on the half is rounded away)
@@ -501,7 +564,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         const bool ok = px[i] >= 0;
         uint32_t cw = 0;
         if constexpr (EPI > 1) {
-          const unsigned char* ca = cbuf + (16 * i + li) * CPITCH + (16 * (NT * wn + j) + 4 * lk) * EPI / 8;
+          const unsigned char* ca = cbuf + (16 * i + li_e) * CPITCH + (16 * (NT * wn + j) + 4 * lk_e) * EPI / 8;
           cw = EPI == 4 ? (uint32_t) * reinterpret_cast<const uint16_t*>(ca) : *reinterpret_cast<const uint32_t*>(ca);
         }
 #pragma unroll
@@ -524,9 +587,9 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const double t1 = row16_sum(s1[r]), t2 = row16_sum(s2[r]);
-          if (li == 0) {
-            row[16 * j + 4 * lk + r] += t1;
-            row[BN + 16 * j + 4 * lk + r] += t2;
+          if (li_e == 0) {
+            row[16 * j + 4 * lk_e + r] += t1;
+            row[BN + 16 * j + 4 * lk_e + r] += t2;
           }
         }
       }
@@ -724,44 +787,78 @@ bool make_plan(const ConvGeom& g, int mode, int np, bool sums, Plan& p) {
   return false;
 }
 
-template <int MODE, int NP, int TAPS, int NT, int KS, int CPP, int SU>
-int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const float* skip,
+// How many consecutive tiles a block of an accepted plan takes: as the grid's rounds of the chip's places (two four-wave
+// blocks per compute unit, one where a patch has more than 256 positions) come out best.  BODY
+void balance(const ConvGeom& g, int mode, Plan& p) {
+  if (p.tl.per == 1) return;
+  const int64_t nblk = (mode == 0 ? g.Cout : g.Cin) / p.bn, places = p.su > 4 ? 256 : 512;
+  auto cost = [&](int per) {   // in half tiles: a block's start costs about one
+    const int64_t n = (p.tl.tiles + per - 1) / per * nblk;
+    return (n + places - 1) / places * (2 * per + 1);
+  };
+  int best = p.tl.per;
+  for (int per = p.tl.per + 1; per <= 16 * p.tl.per; ++per)
+    if (cost(per) < cost(best)) best = per;
+  p.tl.per = best;
+  p.tl.gm = (p.tl.tiles + best - 1) / best;
+}
+
+Tiling with_divisors(const ConvGeom& g, Tiling t) {
+  t.w = Divisor(g.W);
+  t.pw = Divisor(g.W + 2);
+  t.h = Divisor(g.H);
+  t.ph = Divisor(g.H + 2);
+  t.hw = Divisor(g.H * g.W);
+  t.per_unit = Divisor(t.ntr);
+  return t;
+}
+
+template <int MODE, int NP, bool PRE, int TAPS, int NT, int KS, int CPP, int SU>
+int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts, const float* skip,
                float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
   const unsigned grid = (unsigned)((p.tl.gm + 7) / 8 * 8 * (Ng / p.bn));
-  auto kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 0, NP>;
+  auto kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 0, NP, PRE>;
   if constexpr (MODE == 0) {
-    if (epi == 1) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 1, NP>;
+    if (epi == 1) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 1, NP, PRE>;
   } else {
-    if (epi == 4) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 4, NP>;
-    if (epi == 8) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8, NP>;
+    if (epi == 4) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 4, NP, PRE>;
+    if (epi == 8) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8, NP, PRE>;
   }
   if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
-  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, skip, out, sums, codes, stats, g, p.tl, nullptr, 0);
+  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, static_cast<const uint4*>(parts), skip, out, sums, codes, stats, g, with_divisors(g, p.tl), nullptr, 0);
   return hip_status();
 }
 
-template <int MODE, int NP>
-int launch(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const float* skip,
+template <int MODE, int NP, bool PRE>
+int launch_as(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts, const float* skip,
            float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
-  auto run = [&](auto f) { return f(st, g, p, in, w, skip, out, sums, codes, stats, epi); };
+  auto run = [&](auto f) { return f(st, g, p, in, w, parts, skip, out, sums, codes, stats, epi); };
   if (g.R == 3) {
-    if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, NP, 9, 2, 2, 1, 3> : launch_cfg<MODE, NP, 9, 1, 2, 1, 3>);
-    if (p.nt == 2) return run(launch_cfg<MODE, NP, 9, 2, 1, 1, 4>);
-    return run(p.su == 4 ? launch_cfg<MODE, NP, 9, 1, 1, 1, 4> : launch_cfg<MODE, NP, 9, 1, 1, 1, 7>);
+    if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, NP, PRE, 9, 2, 2, 1, 3> : launch_cfg<MODE, NP, PRE, 9, 1, 2, 1, 3>);
+    if (p.nt == 2) return run(launch_cfg<MODE, NP, PRE, 9, 2, 1, 1, 4>);
+    return run(p.su == 4 ? launch_cfg<MODE, NP, PRE, 9, 1, 1, 1, 4> : launch_cfg<MODE, NP, PRE, 9, 1, 1, 1, 7>);
   }
-  if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, NP, 1, 2, 2, 1, 2> : launch_cfg<MODE, NP, 1, 1, 2, 1, 2>);
-  return run(p.nt == 2 ? launch_cfg<MODE, NP, 1, 2, 1, 2, 4> : launch_cfg<MODE, NP, 1, 1, 1, 2, 4>);
+  if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, NP, PRE, 1, 2, 2, 1, 2> : launch_cfg<MODE, NP, PRE, 1, 1, 2, 1, 2>);
+  return run(p.nt == 2 ? launch_cfg<MODE, NP, PRE, 1, 2, 1, 2, 4> : launch_cfg<MODE, NP, PRE, 1, 1, 1, 2, 4>);
 }
 
-template <int FUSE, int KS, int SU>
+template <int MODE, int NP>
+int launch(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts, const float* skip,
+           float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
+  return parts != nullptr ? launch_as<MODE, NP, true>(st, g, p, in, w, parts, skip, out, sums, codes, stats, epi)
+                          : launch_as<MODE, NP, false>(st, g, p, in, w, parts, skip, out, sums, codes, stats, epi);
+}
+
+template <int FUSE, int KS, int SU, bool PRE>
 int launch_fused(hipStream_t st, const ConvGeom& g, const Plan& p, const float* x, const float* stats, const float* w,
-                 const float* skip, float* y, uint8_t* packed, double* sums) {
+                 const void* parts, const float* skip, float* y, uint8_t* packed, double* sums) {
   const unsigned grid = (unsigned)((p.tl.gm + 7) / 8 * 8 * (g.Cout / p.bn));
   const int64_t raw = (int64_t)g.N * g.H * g.W * g.Cin * FUSE / 8;
-  auto kern = sums != nullptr ? split_conv_kernel<0, 9, 1, KS, 1, SU, 1, 3, FUSE> : split_conv_kernel<0, 9, 1, KS, 1, SU, 0, 3, FUSE>;
+  auto kern = sums != nullptr ? split_conv_kernel<0, 9, 1, KS, 1, SU, 1, 3, PRE, FUSE>
+                              : split_conv_kernel<0, 9, 1, KS, 1, SU, 0, 3, PRE, FUSE>;
   if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
-  kern<<<grid, 64 * WN * KS, p.lds, st>>>(x, w, skip, y, sums, nullptr, stats, g, p.tl, packed, (int)((raw + 127) / 128 * 128 - raw));
+  kern<<<grid, 64 * WN * KS, p.lds, st>>>(x, w, static_cast<const uint4*>(parts), skip, y, sums, nullptr, stats, g, with_divisors(g, p.tl), packed, (int)((raw + 127) / 128 * 128 - raw));
   return hip_status();
 }
 
@@ -775,7 +872,9 @@ bool fit_fused_plan(const ConvGeom& g, Plan& p) {
 
 int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
   Plan p;
-  return make_plan(g, mode, bf16 ? 1 : 3, sums, p) ? p.tl.gm : 0;
+  if (!make_plan(g, mode, bf16 ? 1 : 3, sums, p)) return 0;
+  balance(g, mode, p);
+  return p.tl.gm;
 }
 
 // Four-wave grids that fill less than three quarters of their 512 places are not (512 -> 128 @28x28, step, us, with the
@@ -796,15 +895,16 @@ bool split_beats_prologue(const ConvGeom& g) {
 }
 
 int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, const float* in, const float* w,
-                      const float* skip, float* out, double* sums) {
+                      const float* skip, float* out, double* sums, const void* parts) {
   Plan p;
   if (!make_plan(g, mode, bf16 ? 1 : 3, false, p)) return ABL_ERR_SHAPE;
+  balance(g, mode, p);
   const int epi = sums != nullptr ? 1 : 0;
   if (mode == 0)
-    return bf16 ? launch<0, 1>(st, g, p, in, w, skip, out, sums, nullptr, nullptr, epi)
-                : launch<0, 3>(st, g, p, in, w, skip, out, sums, nullptr, nullptr, epi);
-  return bf16 ? launch<1, 1>(st, g, p, in, w, nullptr, out, nullptr, nullptr, nullptr, 0)
-              : launch<1, 3>(st, g, p, in, w, nullptr, out, nullptr, nullptr, nullptr, 0);
+    return bf16 ? launch<0, 1>(st, g, p, in, w, parts, skip, out, sums, nullptr, nullptr, epi)
+                : launch<0, 3>(st, g, p, in, w, parts, skip, out, sums, nullptr, nullptr, epi);
+  return bf16 ? launch<1, 1>(st, g, p, in, w, parts, nullptr, out, nullptr, nullptr, nullptr, 0)
+              : launch<1, 3>(st, g, p, in, w, parts, nullptr, out, nullptr, nullptr, nullptr, 0);
 }
 
 int split_forward3(const ConvGeom& g, int* rows) {
@@ -812,30 +912,36 @@ int split_forward3(const ConvGeom& g, int* rows) {
   if (g.R != 3 || !make_plan(g, 0, 3, false, p)) return 0;
   const bool weighed = p.nt == 1 && p.ks == 1;   // (make_plan has compared this one with the halo kernel)
   if (!fit_fused_plan(g, p) || (!weighed && halo_is_faster(g, 0, p))) return -1;
+  balance(g, 0, p);
   *rows = p.tl.gm;
   return 1;
 }
 
 int launch_split_fwd_fused(hipStream_t st, const ConvGeom& g, int K, const float* x, const void* stats, const float* w,
-                           const float* skip, float* y, void* packed, double* sums) {
+                           const float* skip, float* y, void* packed, double* sums, const void* parts) {
   Plan p;
   if (!fit_fused_plan(g, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
+  balance(g, 0, p);
   const float* sp = static_cast<const float*>(stats);
   uint8_t* pk = static_cast<uint8_t*>(packed);
-  if (p.su == 4) return K == 4 ? launch_fused<4, 1, 4>(st, g, p, x, sp, w, skip, y, pk, sums)
-                               : launch_fused<8, 1, 4>(st, g, p, x, sp, w, skip, y, pk, sums);
-  return K == 4 ? launch_fused<4, 1, 7>(st, g, p, x, sp, w, skip, y, pk, sums)
-                : launch_fused<8, 1, 7>(st, g, p, x, sp, w, skip, y, pk, sums);
+  auto run = [&](auto f) { return f(st, g, p, x, sp, w, parts, skip, y, pk, sums); };
+  if (parts != nullptr) {
+    if (p.su == 4) return run(K == 4 ? launch_fused<4, 1, 4, true> : launch_fused<8, 1, 4, true>);
+    return run(K == 4 ? launch_fused<4, 1, 7, true> : launch_fused<8, 1, 7, true>);
+  }
+  if (p.su == 4) return run(K == 4 ? launch_fused<4, 1, 4, false> : launch_fused<8, 1, 4, false>);
+  return run(K == 4 ? launch_fused<4, 1, 7, false> : launch_fused<8, 1, 7, false>);
 }
 
 int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* dy, const float* w,
-                              const void* packed, const void* stats, float* da3, double* partial) {
+                              const void* packed, const void* stats, float* da3, double* partial, const void* parts) {
   Plan p;
   if (!make_plan(g, 1, bf16 ? 1 : 3, true, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
+  balance(g, 1, p);
   const uint8_t* codes = static_cast<const uint8_t*>(packed);
   const float* sp = static_cast<const float*>(stats);
-  return bf16 ? launch<1, 1>(st, g, p, dy, w, nullptr, da3, partial, codes, sp, K)
-              : launch<1, 3>(st, g, p, dy, w, nullptr, da3, partial, codes, sp, K);
+  return bf16 ? launch<1, 1>(st, g, p, dy, w, parts, nullptr, da3, partial, codes, sp, K)
+              : launch<1, 3>(st, g, p, dy, w, parts, nullptr, da3, partial, codes, sp, K);
 }
 
 }  // namespace abl
