@@ -21,8 +21,22 @@
 // positions, four planes - then touch every bank once, whichever lanes the LDS serves together (with a position's
 // channels side by side they took twice the cycles; 64 -> 64 @56x56 95 -> 87 us).  1x1: a position's channels side
 // by side, which loads whole lines of the input (1024 -> 256 @14x14 45 us, in planes 48).  Weights go from the L2 straight
-// into registers, one k-step (32 contraction channels of one tap) ahead, and are split there: every wave has
-// output channels of its own, so a block splits nothing twice.  A wave computes 112 pixels x 16 NT channels: 7 NT tiles, 12 NT reads and 42 NT MFMAs per k-step.
+// into registers, one k-step (32 contraction channels of one tap) ahead; every wave has output channels of its own, so
+// a block reads nothing twice.  PRE: they come as the parts that SplitWeights describes, split once per call, in six whole
+// kilobytes a k-step instead of 16 gathers and 88 vector instructions.  (Where no workspace is at hand the kernel splits them.)
+// A wave computes 112 pixels x 16 NT channels: 7 NT tiles, 21 reads and 42 NT MFMAs per k-step.
+// What the k-loop needs to stay at the matrix cores' rate (us before / with all of it, in a stack: 3x3 256 -> 256 @14x14
+// 79 / 66, gradient with sums 85 / 71; 1x1 1024 -> 256 48 / 40, its mirror's gradient 50 / 42; 1x1 256 -> 1024 58 / 52,
+// gradient 60 / 53; 3x3 64 -> 64 @56x56 108 / 87, gradient 115 / 95, with bf16 operands 53 / 42 and 77 / 55):
+//  - two sets of weight registers in turn.  With one, its copy waits for everything in flight, the next phase's input too.
+//  - loads without branches around them, and the next phase's input after the weights of a step, not before.
+//  - the wave that is behind first: left to itself a SIMD runs its older wave to the barrier, and the other alone gets
+//    80 % of the matrix rate (a phase of nine steps 31.6 thousand cycles, with falling priorities 30.0, both at full rate 24.2).
+//  - nothing of the epilogue held in registers through the contraction: it spilled 58 registers of the 1x1 gradient.
+//  - few copies of the step's code: with all four variants of a phase written out (56 KB) the 3x3 layer went from 74 to 92 us;
+//    the instruction cache is cold when a kernel starts.
+// (Splits between the k-steps instead of in front of them gained nothing: vector and matrix instructions of a SIMD's two
+// waves overlap little.)
 // KS = 2: the chunks of a phase go to two groups of waves whose sums meet in LDS at the end - two waves per
 // SIMD also where a layer gives only one block per compute unit - and the patch has two buffers.
 // KS = 1: one buffer, two blocks per compute unit cover each other's staging (one where a 3x3 patch has more than 256
@@ -32,7 +46,6 @@
 #include <type_traits>
 
 #include "abl_internal.h"
-
 
 namespace abl {
 namespace {
@@ -788,7 +801,9 @@ bool make_plan(const ConvGeom& g, int mode, int np, bool sums, Plan& p) {
 }
 
 // How many consecutive tiles a block of an accepted plan takes: as the grid's rounds of the chip's places (two four-wave
-// blocks per compute unit, one where a patch has more than 256 positions) come out best.  BODY
+// blocks per compute unit, one where a patch has more than 256 positions) come out best.  (1x1 gradient
+// 256 <- 64 @56x56, two blocks along the channels: 896 blocks of four tiles, 1.75 rounds, 125 us; 512 of seven 116.  Grids of one
+// tile per block stay: 896 blocks of one or 448 of two, 1x1 256 -> 1024 @14x14 52 us both.)
 void balance(const ConvGeom& g, int mode, Plan& p) {
   if (p.tl.per == 1) return;
   const int64_t nblk = (mode == 0 ? g.Cout : g.Cin) / p.bn, places = p.su > 4 ? 256 : 512;
