@@ -133,6 +133,7 @@ int abl_forward(void* stream, const abl_shape* shape, int K, uint32_t flags,
  *   dy     [N,Ho,Wo,Cout]   in
  *   W      [R,S,Cin,Cout]   in
  *   dx     [N,H,W,Cin]      out (or accumulated into with ABL_ACCUM_DX).  May alias dy.
+ *                           (Apart from dy, it may hold partial sums of dW until it is written.)
  *   dW     [R,S,Cin,Cout]   out: approximate (uses the dequantized A3)
  *   dgamma, dbeta [Cin]     out: dgamma approximate, dbeta exact (Sec. 3.3)
  * flags: ABL_ACCUM_DX, ABL_MATH_BF16. */

@@ -330,10 +330,10 @@ size_t wpart_offset(const abl_shape& s) {
 }
 
 // abl_backward after its checks.  parts (nullable): the weights as the data gradient's kernel reads them.  next: weights for
-// the launch of the apply pass to split.
+// the launch of the apply pass to split.  wroom: bytes for the copies of the weight gradient at their place in the workspace.
 int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, const void* packed, const void* stats,
                   const float* dy, const float* W, void* scratch, float* dx, float* dW, float* dgamma, float* dbeta,
-                  const void* parts, const SplitWeights& next) {
+                  const void* parts, const SplitWeights& next, size_t wroom) {
   const int64_t M = rows_of(*s);
   const size_t act = up256((size_t)M * s->Cin * sizeof(float));
   const size_t redb = up256(bn_partial_bytes(M, s->Cin));
@@ -343,6 +343,20 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   const bool accum = (flags & ABL_ACCUM_DX) != 0;
   const ConvGeom g = geom_of(*s);
+  // Copies of a 3x3 weight gradient that the workspace has no room for go where dx will be, if nothing is read there: the launch
+  // that sums them comes before the one that writes dx.  (64 -> 64 @56x56 N=64, bf16 operands: 85 copies, 170 blocks on 256
+  // units, 50 us; 128 copies, 256 blocks, 38.  In a stack, whose workspace is the largest layer's, they fit there: fp32 86 to
+  // 64 us.)
+  void* wat = wpart;
+  const size_t dx_bytes = (size_t)M * s->Cin * sizeof(float), dy_bytes = (size_t)g.N * g.Ho * g.Wo * g.Cout * sizeof(float);
+  const char *dx_at = reinterpret_cast<const char*>(dx), *dy_at = reinterpret_cast<const char*>(dy);
+  if (K != 32 && !accum && g.R == 3 && dx_bytes > wroom && (dx_at + dx_bytes <= dy_at || dy_at + dy_bytes <= dx_at)) {
+    const int here = split_wgrad_copies(g, K, bf16, wroom);
+    if (here > 0 && split_wgrad_copies(g, K, bf16, dx_bytes) > here) {
+      wat = dx;
+      wroom = dx_bytes;
+    }
+  }
   // Stride-1 convolutions with a filter larger than 1x1 take the Eq. 6-7 sums in the epilogue of
   // the dgrad kernel (dA3 is still in registers there), which saves the reduce pass over dA3.
   // bf16 operands with a dgrad on the 32-deep bf16 matrix instruction: the separate stages
@@ -360,7 +374,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   if (const int nb = K != 32 && !bf16 ? split_conv_blocks(g, 1, false, true) : 0) {
     if (int e = launch_split_dgrad_reduce(st, g, K, false, dy, W, packed, stats, da3, static_cast<double*>(red), parts)) return e;
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
+    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nb, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -368,7 +382,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   if (K != 32 && !bf16 && image_f32_supported(g, 1)) {
     if (int e = launch_image_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
+    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, g.N, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -376,7 +390,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   if (const int nr = (K != 32 && bf16_gemm) ? bf16_dgrad_reduce_rows(g) : 0) {
     if (int e = launch_bf16_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red), parts)) return e;
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
+    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nr, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -386,7 +400,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
       return e;
     // split partial copies of dW are summed by the launch that finishes the Eq. 7 sums
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
+    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, tiles, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -398,13 +412,13 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
       return e;
     if (rows > 0) {
       DwSum dwsum;
-      if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
+      if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
       return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, rows, dx, dgamma, dbeta,
                                   dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
     }
     // (long contractions: the kernel computed dA3 only)
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, false, &dwsum)) return e;
+    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
     return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta,
                          dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -446,7 +460,7 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
   if (sw.out != nullptr)
     if (int e = launch_split_weights((hipStream_t)stream, sw)) return e;
   return backward_impl((hipStream_t)stream, s, K, flags, packed, stats, dy, W, scratch, dx, dW, dgamma, dbeta, sw.out,
-                       SplitWeights{});
+                       SplitWeights{}, wgrad_partial_bytes(*s));
 }
 
 // ---- the layer with a leaky ReLU (Sec. 3.4) ---------------------------------------------------
@@ -907,7 +921,7 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
     if (int e = trace_copy((hipStream_t)stream, trace, i, dy, out_floats)) return e;
     const SplitWeights next = i > 0 ? parts_of(i - 1, wpart_offset(l.shape)) : SplitWeights{};
     if (int e = backward_impl((hipStream_t)stream, &l.shape, K, f, l.packed, l.stats, dy, l.W, lscratch, dx, l.dW, l.dgamma,
-                              l.dbeta, sw.out, next))
+                              l.dbeta, sw.out, next, lbytes - wpart_offset(l.shape)))
       return e;
     sw = next;
   }

@@ -164,7 +164,8 @@ int launch_conv_fwd_fused(hipStream_t st, const abl_shape& s, int K, bool bf16, 
 // K = 32: `packed` is an fp32 tensor, used as it is or (relu32) as the pre-ReLU activation A2.
 // defer (nullable): where the kernel leaves split partial copies, describe them there instead of
 // summing them (copies = 0 when dw is already complete) - for launch_bn_bwd_finish.
-// room: bytes at `scratch` where channel counts are not multiples of 16 (wgrad_partial_bytes covers the others).
+// room: bytes at `scratch`; channel counts that are not multiples of 16 need it, the split kernels make more copies of more
+// (wgrad_partial_bytes at least are taken to be there).
 int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf16, const void* packed,
                              const void* stats, const float* dy, void* scratch, float* dw, bool relu32 = false,
                              DwSum* defer = nullptr, size_t room = 0);

@@ -1051,7 +1051,7 @@ int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf1
     return hip_status();
   }
   // other 'same' stride-1 3x3 and 1x1 layers (3x3 64 -> 64 @56x56: fp32 177 -> 86 us, bf16 102 -> 55)
-  const size_t part = wgrad_partial_bytes(s);
+  const size_t least = wgrad_partial_bytes(s), part = room > least ? room : least;
   if (const int copies = !relu32 ? split_wgrad_copies(g, K, bf16, part) : 0) {
     float* dst = copies == 1 ? dw : static_cast<float*>(scratch);
     if (int e = launch_split_wgrad(st, g, K, bf16, packed, sp, dy, dst, part)) return e;
