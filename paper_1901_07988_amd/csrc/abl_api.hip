@@ -224,6 +224,14 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   return 0;
 }
 
+// Whether splitting a layer's weights once saves more than it costs (a launch of its own in abl_backward, 4 us): 1x1 layers with
+// many pixels for each weight and, in the gradient, more than four k-steps.  (Layer, us, split by the blocks / once: gradient 2048 <-
+// 512 @7x7 N=14 48.2 / 52.3, 512 <- 128 @28x28 N=26 73.8 / 78.5, 256 <- 64 @56x56 N=26 94.0 / 96.8; forward 512 -> 2048 @7x7 N=14
+// 30.3 / 32.3, 256 -> 1024 @15x15 N=14 29.7 / 31.2, but 1024 -> 256 @14x14 N=40 72 / 64.)
+bool parts_pay(const ConvGeom& g, int mode) {
+  return g.R == 3 || ((int64_t)g.N * g.H * g.W >= 4096 && (mode == 0 || g.Cout >= 256));
+}
+
 // The parts of a layer's weights go where the copies of its weight gradient will be (`room` bytes, free in the forward
 // and until the weight gradient runs); a layer whose copies leave less room has its weights split by the convolution.
 SplitWeights weights_to_split(const abl_shape& s, int mode, int np, const float* W, void* at, size_t room) {
@@ -255,7 +263,7 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
   // weights of a split-operand convolution: split by the launch of the second pass of Eq. 1, which leaves most of the chip
   // idle
   SplitWeights sw{};
-  if (const int np = split_rows > 0 ? 3 : path == 0 ? conv_fwd_parts(g, bf16) : 0)
+  if (const int np = !parts_pay(g, 0) ? 0 : split_rows > 0 ? 3 : path == 0 ? conv_fwd_parts(g, bf16) : 0)
     sw = weights_to_split(*s, 0, np, W, static_cast<char*>(red) + up256(bn_partial_bytes(M, s->Cin)), wgrad_partial_bytes(*s));
   if (in_partial != nullptr && in_nb > 0) {
     if (int e = launch_bn_stats_finalize(st, in_partial, in_nb, nullptr, M, s->Cin, gamma, beta, K, stats, sw)) return e;
@@ -318,7 +326,7 @@ namespace {
 
 // Parts of the weights that the data gradient of this layer can read, 0 = none.
 int backward_parts(const ConvGeom& g, int K, bool bf16) {
-  if (K == 32 || halo_bwd16_tiles(g) != 0) return 0;
+  if (K == 32 || g.Cout % 32 != 0 || g.Cin % 64 != 0 || !parts_pay(g, 1)) return 0;   // (nor the 16-channel kernel's layers)
   if (!bf16) return split_conv_blocks(g, 1, false, true) > 0 ? 3 : 0;
   return bf16_gemm_supported(g, 1) && bf16_dgrad_reduce_splits(g) ? 1 : 0;
 }

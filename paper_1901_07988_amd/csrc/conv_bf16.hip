@@ -688,7 +688,7 @@ bool image_bf16_supported(const ConvGeom& g, int mode) {
   if (image_mt(g) == 0 || g.H * g.W * g.W >= 65536) return false;
   if (image_lds_bytes(g, mode) > (size_t)160 * 1024) return false;
   const int64_t e_in = (int64_t)g.N * g.H * g.W * g.Cin, e_out = (int64_t)g.N * g.Ho * g.Wo * g.Cout;
-  return e_in < ((int64_t)1 << 31) && e_out < ((int64_t)1 << 31);
+  return e_in < ((int64_t)1 << 31) && e_out < ((int64_t)1 << 31) && !split_beats_image(g, mode);
 }
 
 namespace {

@@ -697,15 +697,30 @@ bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
   return p.lds <= (size_t)160 * 1024;
 }
 
+// How many consecutive tiles a block of an accepted plan takes: fewer rounds of the chip's places (two four-wave blocks per compute
+// unit, one where a patch has more than 256 positions) that stay filled.  (1x1 gradient 256 <- 64 @56x56, two blocks along the
+// channels: 896 blocks of four tiles, 1.75 rounds, 125 us; 512 of seven 116; 256 of fourteen, one per unit, 147.  Grids of one tile
+// per block stay: 896 blocks of one or 448 of two, 1x1 256 -> 1024 @14x14 52 us both; and places are not left empty: 3x3 128 -> 128
+// @27x27 N=80, layer, 522 blocks of two 153, 348 of three 165.)
+void balance(const ConvGeom& g, int mode, Plan& p) {
+  if (p.tl.per == 1) return;
+  const int64_t nblk = (mode == 0 ? g.Cout : g.Cin) / p.bn, places = p.su > 4 ? 256 : 512, least = p.su > 4 ? 160 : 448;
+  auto blocks = [&](int per) { return (p.tl.tiles + per - 1) / per * nblk; };
+  auto cost = [&](int per) { return (blocks(per) + places - 1) / places * (2 * per + 1); };   // in half tiles: a start costs about one
+  int best = p.tl.per;
+  for (int per = p.tl.per + 1; per <= 16 * p.tl.per && blocks(per) >= least; ++per)
+    if (cost(per) < cost(best)) best = per;
+  p.tl.per = best;
+  p.tl.gm = (p.tl.tiles + best - 1) / best;
+}
+
 // Whether the halo kernel is the faster one on a 3x3 layer's four-wave grid (fp32).  Its tiles of 64 pixels, all in one
-// round of the compute units, take less than a 112-pixel tile here (us, 64 input channels, here / halo kernel: 64 -> 64
-// @32x32 N=14 19.5 / 15.4, N=24, two rounds, 20.4 / 38.2; 128 -> 128 @28x28 N=8 step 41.1 / 37.7, N=16 43.0 / 57.0).  A patch
-// of more than 256 positions (cross-image runs of 32-pixel-wide images, rows of 57) leaves LDS for one block per unit
-// only; a tile then takes 18.3 us per 64 input channels, the halo kernel 11.1 per round of 64 pixels, 20 of 128, 35.5 of
-// 224 (64 -> 64 @33x33 N=56, 273 blocks of two tiles, 70.7 / 43.5, N=48, 467 blocks, 38.8 / 48.3; @32x32 N=72, 330 of two,
-// 71.1 / 59.9, N=56, 512 blocks, 39.9 / 73.7; 128 -> 128 @40x40 N=10 66.8 / 46.8).  Where both take about the same this
-// kernel stays (up to 8 % slower alone, @57x57 N=12 39.8 / 36.9; a layer's two passes are faster): its sums are the closer
-// ones.
+// round of the compute units, take less than a 112-pixel tile here (us, layer, halo kernel / here: 64 -> 64 @32x32 N=12 25.5 /
+// 27.1, backward 45.8 / 51.3; with more of them it is two rounds, N=24 29.3 here).  A patch of more than 256 positions
+// (cross-image runs of 32-pixel-wide images, rows of 57) leaves LDS for one block per unit only; a tile then takes 15.5 us per
+// 64 input channels, the halo kernel 11.1 per round of 64 pixels, 20 of 128, 35.5 of 224 (layer, halo kernel / here: 64 -> 64
+// @33x33 N=64 77.9 / 64.7, N=56 58.5 / 63.3, N=28 37.3 / 46.4, @55x55 N=24 78.1 / 64.5, N=20 58.7 / 63.1, @32x32 N=80 78.2 /
+// 65.4).  Where both take about the same this kernel stays: its sums are the closer ones.
 bool halo_is_faster(const ConvGeom& g, int mode, const Plan& p) {
   const int Ng = mode == 0 ? g.Cout : g.Cin;
   const bool alone = p.su > 4;
@@ -716,8 +731,10 @@ bool halo_is_faster(const ConvGeom& g, int mode, const Plan& p) {
   if (!halo_grid(g, mode, &pixels, &blocks)) return false;
   if (pixels == 64 && blocks <= 256) return true;
   if (!alone) return false;
-  const int64_t rounds = (blocks + 255) / 256, n = (int64_t)p.tl.gm * (Ng / p.bn);
-  const double here = 1.5 + 18.3 * (double)(p.tl.per * ((n + 255) / 256));
+  const int64_t rounds = (blocks + 255) / 256;
+  Plan q = p;
+  balance(g, mode, q);
+  const double here = 1.5 + 15.5 * (double)(q.tl.per * (((int64_t)q.tl.gm * (Ng / q.bn) + 255) / 256));
   const double there = pixels == 64 ? 3.7 + 11.1 * rounds : pixels == 128 ? 3.0 + 20.0 * rounds : 2.5 + 35.5 * rounds;
   return 1.1 * there < here;
 }
@@ -767,8 +784,13 @@ bool four_waves_pay(const ConvGeom& g, int mode, int np, bool sums, const Plan& 
     if (over_one && p.nt == 1 && Cg > 256 && (Ng == 64 || Ng % 128 == 0)) return false;
     return !(n > 256 && n < 400 && p.tl.per > 1);
   }
-  if (mode == 1) return sums && p.nt == 1 && Cg < 1024;
-  return !fit && !(over_one && p.tl.per > 1);
+  // (bf16, layer, us, other kernel / here.  Gradient, blocks of 128 channels: 1024 <- 256 @14x14 N=64, n = 896, 80.0 / 75.5, N=40,
+  // n = 560, 58.0 / 60.6; 2048 <- 512 @7x7 N=64, n = 448, 65.8 / 60.6, N=40, n = 288, 51.6 / 54.3; 256 <- 64 @56x56 N=40, n = 748,
+  // 119 / 112, N=20, n = 560, 68.4 / 72.0; 512 <- 128 @28x28 N=64 112 / 106.  Forward: 1024 -> 256 @14x14 N=40 53.8 / 47.2; 2048 ->
+  // 512 @8x8 N=64 77.2 / 62.3; 256 -> 1024 @15x15 N=64, n = 1032, 48.7 / 42.0; 128 -> 512 @28x28 N=52, n = 1456, 46.6 / 42.4, N=20,
+  // n = 560, 29.1 / 29.6.)
+  if (mode == 1) return sums && (p.nt == 1 ? Cg < 1024 : (n >= 440 && n <= 512) || n >= 720);
+  return Cg >= 1024 || n >= 720 || (!fit && !(over_one && p.tl.per > 1));
 }
 
 // 128 output channels per block where that fills the chip, else 64.  About one block per compute unit: the
@@ -798,24 +820,6 @@ bool make_plan(const ConvGeom& g, int mode, int np, bool sums, Plan& p) {
              fit_plan(g, mode, np, 2, 2, p);
     }
   return false;
-}
-
-// How many consecutive tiles a block of an accepted plan takes: as the grid's rounds of the chip's places (two four-wave
-// blocks per compute unit, one where a patch has more than 256 positions) come out best.  (1x1 gradient
-// 256 <- 64 @56x56, two blocks along the channels: 896 blocks of four tiles, 1.75 rounds, 125 us; 512 of seven 116.  Grids of one
-// tile per block stay: 896 blocks of one or 448 of two, 1x1 256 -> 1024 @14x14 52 us both.)
-void balance(const ConvGeom& g, int mode, Plan& p) {
-  if (p.tl.per == 1) return;
-  const int64_t nblk = (mode == 0 ? g.Cout : g.Cin) / p.bn, places = p.su > 4 ? 256 : 512;
-  auto cost = [&](int per) {   // in half tiles: a block's start costs about one
-    const int64_t n = (p.tl.tiles + per - 1) / per * nblk;
-    return (n + places - 1) / places * (2 * per + 1);
-  };
-  int best = p.tl.per;
-  for (int per = p.tl.per + 1; per <= 16 * p.tl.per; ++per)
-    if (cost(per) < cost(best)) best = per;
-  p.tl.per = best;
-  p.tl.gm = (p.tl.tiles + best - 1) / best;
 }
 
 Tiling with_divisors(const ConvGeom& g, Tiling t) {
@@ -890,6 +894,22 @@ int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
   if (!make_plan(g, mode, bf16 ? 1 : 3, sums, p)) return 0;
   balance(g, mode, p);
   return p.tl.gm;
+}
+
+// (us, layer forward / backward, image kernel against here: 512 -> 512 @7x7 N=40, two rounds of images, 72 / 113 against 46 /
+// 74, N=120 125 / 224 against 57 / 116; 256 -> 256 @14x14 N=20 35.2 / 58.1 against 32.9 / 53.0, N=64 40.5 / 79.9 against 40.6 /
+// 78.1, N=120 65.4 / 134 against 59.1 / 119; 128 -> 128 @14x14 N=28 26.5 / 50.0 against 22.7 / 45.1, N=64 29.4 / 55.3 against
+// 26.6 / 49.6.  Four-wave blocks of 64 channels a little over one per unit lose: 256 -> 256 @14x14 N=40, n = 280, 37.1 / 68.1
+// against 46.3 / 72.9, 128 -> 128 N=80 30.9 / 56.1 against 33.2 / 56.3, n = 420 wins again, 33.9 / 63.0 against 32.9 / 60.2; so
+// do a few blocks with a long contraction beside one round of images: 512 -> 512 @7x7 N=28, n = 112, 43.4 / 70.4 against 45.5 /
+// 69.5.)
+bool split_beats_image(const ConvGeom& g, int mode) {
+  Plan p;
+  if (!make_plan(g, mode, 1, false, p)) return false;
+  const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
+  const int64_t n = (int64_t)p.tl.gm * (Ng / p.bn);
+  if (p.nt == 1 && p.ks == 1) return n >= 384;
+  return n >= 128 || Cg < 512 || (int64_t)g.N * (Ng / 64) > 256;
 }
 
 // Four-wave grids that fill less than three quarters of their 512 places are not (512 -> 128 @28x28, step, us, with the
