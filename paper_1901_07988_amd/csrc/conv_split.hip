@@ -106,7 +106,11 @@ __host__ __device__ constexpr int area_bytes(int taps, int nt, int ks, int cpp, 
 // NP = 3: operands in three parts, as above; NP = 1: rounded to bf16.
 // FUSE = K (4 or 8, 3x3 forward): `in` is the layer input x; Eq. 1-3 are applied on the way into LDS and the K-bit codes of
 // the block's own pixels written to `packed` (the blocks along the output channels take turns over the phases).
-template <int MODE, int TAPS, int NT, int KS, int CPP, int SU, int EPI, int NP, bool PRE, int FUSE = 0>
+// ONE: the contraction is a single phase (1x1 gradients with 64 channels to contract).  Code for both kinds of phase asks for
+// the next phase's input and for the epilogue's codes, and holds registers for both: with 128 channels per block and 8-bit
+// codes 14 of them were spilled (1x1 256 <- 64, backward, us, ONE / without: @55x55 N=14, K=8 62.5 / 66.3, N=40, K=8 140 / 151,
+// K=4 131 / 135; @56x56 N=64, K=8 231 / 247; with a branch between the two inside one kernel N=40, K=4 161).
+template <int MODE, int TAPS, int NT, int KS, int CPP, int SU, int EPI, int NP, bool PRE, int FUSE = 0, bool ONE = false>
 __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float* __restrict__ in,
                                                                           const float* __restrict__ wgt,
                                                                           const uint4* __restrict__ parts,
@@ -339,9 +343,10 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     constexpr int CPITCH = 16 * CPR + 16;
     uint4 cq[CU];
     // Weights of two k-steps in turn: the set that a step reads and the one that it asks for.  (One set and a copy of it waits for
-    // everything in flight at the copy.)
+    // everything in flight at the copy.)  Where the kernel splits them one set does: a step splits it before it asks for the next.
     constexpr int RW = PRE ? 4 * NP : 8;
-    uint32_t wset[2][NT][RW];
+    constexpr int ODD = PRE ? 1 : 0;   // set of the steps with odd numbers
+    uint32_t wset[1 + ODD][NT][RW];
     auto load_set = [&](uint32_t (&w)[NT][RW], int tap, int c0) __attribute__((always_inline)) {
       if constexpr (PRE) load_parts(w, tap, c0);
       else load_w(w, tap, c0);
@@ -437,8 +442,8 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       // each set in its own registers; an odd number of steps leaves the next weights in the wrong one.  (Few copies of the
       // step's code: a kernel starts with a cold instruction cache.)
       if constexpr (STEPS >= 9) __builtin_amdgcn_s_setprio(3);
-      k_step(wset[0], wset[1], ph, 0, cur, true, last);
-      if constexpr (STEPS == 2) k_step(wset[1], wset[0], ph, 1, cur, false, last);
+      k_step(wset[0], wset[ODD], ph, 0, cur, true, last);
+      if constexpr (STEPS == 2) k_step(wset[ODD], wset[0], ph, 1, cur, false, last);
       if constexpr (STEPS >= 9) {
 #pragma unroll 1
         for (int ks = 1; ks < STEPS; ks += 2) {
@@ -446,18 +451,20 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
           if (ks == 3) __builtin_amdgcn_s_setprio(2);
           else if (ks == 5) __builtin_amdgcn_s_setprio(1);
           else if (ks == 7) __builtin_amdgcn_s_setprio(0);
-          k_step(wset[1], wset[0], ph, ks, cur, false, last);
-          k_step(wset[0], wset[1], ph, ks + 1, cur, false, last);
+          k_step(wset[ODD], wset[0], ph, ks, cur, false, last);
+          k_step(wset[0], wset[ODD], ph, ks + 1, cur, false, last);
         }
       }
-      if constexpr (STEPS % 2 == 1) {
+      if constexpr (PRE && STEPS % 2 == 1) {
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
           for (int e = 0; e < RW; ++e) wset[0][j][e] = wset[1][j][e];
       }
     };
-    if constexpr (NP == 1) {   // (short code: a tile's last phase apart)
+    if constexpr (ONE) {
+      phase(0, std::integral_constant<int, 1>{});
+    } else if constexpr (NP == 1) {   // (short code: a tile's last phase apart)
       for (int ph = 0; ph + 1 < nph; ++ph) phase(ph, std::integral_constant<int, 0>{});
       phase(nph - 1, std::integral_constant<int, 1>{});
     } else {
@@ -843,6 +850,10 @@ int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in
   } else {
     if (epi == 4) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 4, NP, PRE>;
     if (epi == 8) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8, NP, PRE>;
+    if constexpr (TAPS == 1 && KS == 1 && NP == 3 && !PRE)
+      if (epi != 0 && g.Cout == 32 * KS * CPP)
+        kern = epi == 4 ? split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 4, NP, PRE, 0, true>
+                        : split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8, NP, PRE, 0, true>;
   }
   if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
   kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, static_cast<const uint4*>(parts), skip, out, sums, codes, stats, g, with_divisors(g, p.tl), nullptr, 0);
