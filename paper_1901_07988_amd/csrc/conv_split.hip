@@ -127,7 +127,14 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   constexpr int STEPS = TAPS * CPP;                    // k-steps of a phase and wave
   // pixel fragments of a k-step (7 tiles, NP parts), and registers for as many as are read ahead.  (A wave that has to wait
   // for each tile's reads leaves its SIMD idle as soon as the other wave waits at a barrier.)
-  constexpr int NF = MT * NP, SLOTS = 7, LOOK = SLOTS - 1;
+  // (1x1, bf16 operands and weights split here: six reads ahead of a step's fourteen products only put off its weights.
+  // Gradient with sums, us, one ahead / six: 512 <- 128 @28x28 N=40, K=8 79.3 / 81.9, N=64, K=4 101.6 / 106.4, 256 <- 64 @56x56
+  // N=14, K=8 55.9 / 58.2.)
+  constexpr bool SHORT = TAPS == 1 && NP == 1 && !PRE;
+  constexpr int NF = MT * NP, SLOTS = 7, LOOK = SHORT ? 1 : SLOTS - 1;
+  // the next phase's input asked for in front of a phase's only step (us, in front / behind its weights: gradient 512 <- 2048
+  // @7x7 N=26 53.9 / 61.9, 256 <- 1024 @14x14 N=14 38.4 / 42.1, forward 2048 -> 512 @8x8 N=26 43.4 / 48.9)
+  constexpr bool INPUT_FIRST = SHORT && KS == 2;
   static_assert(NF % SLOTS == 0, "a k-step starts in the slot of the one before");
   // the patch: bytes from a position, eight channels, a part and a chunk to the next
   constexpr int NPOS = SU * THREADS / C8;
@@ -399,12 +406,12 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
         load_set(fill, ntap, (wrap && !end ? ph + 1 : ph) * CH + (kg * CPP + ncc) * 32);
       }
       // after them the input of the next phase (two steps' weights come back before it has to)
-      if (first) {
+      if (first && !INPUT_FIRST) {
         if (last != 1) stage_load(ph + 1, last == 0);
         if (last == 1 || (last == 2 && ph + 1 == nph)) load_codes();
       }
       const unsigned char *const ab = cur + step_off(ks), *const nab = cur + step_off(wrap ? ks : ks + 1);
-      // fragment by fragment, six reads in flight
+      // fragment by fragment, LOOK reads in flight
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
         const int i = f / NP, q = f % NP;
@@ -437,6 +444,10 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       if (!DB || ph == 0) __syncthreads();
       stage_store(cur, ph);
       __syncthreads();
+      if constexpr (INPUT_FIRST) {
+        if constexpr (last == 1) load_codes();
+        else stage_load(ph + 1, last == 0);
+      }
 #pragma unroll
       for (int f = 0; f < LOOK; ++f) read_a(cur + step_off(0), f);
       // each set in its own registers; an odd number of steps leaves the next weights in the wrong one.  (Few copies of the

@@ -1,5 +1,6 @@
 """1x1 gradients whose kernel splits the weights itself (few channels to contract): one phase of 64 channels and several, 64 and
-128 channels per block, one tile to a block and more, 4- and 8-bit codes, against 64-bit values."""
+128 channels per block, one tile to a block and more, 4- and 8-bit codes; few pixels and a long contraction; against 64-bit
+values."""
 import pytest
 import torch
 
@@ -9,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 # N, H, W, Cin, Cout: the gradient contracts Cout channels
 SHAPES = [(1, 110, 101, 64, 64), (1, 150, 150, 128, 64), (3, 141, 143, 192, 64), (2, 150, 151, 256, 64),
-          (5, 117, 119, 256, 64), (2, 110, 103, 256, 128), (2, 150, 151, 512, 128)]
+          (5, 117, 119, 256, 64), (2, 110, 103, 256, 128), (2, 150, 151, 512, 128),
+          (26, 7, 7, 512, 2048), (15, 14, 13, 256, 1024)]   # two groups of waves
 IDS = ["x".join(map(str, s)) for s in SHAPES]
 
 
@@ -55,3 +57,20 @@ def test_backward(s, flags, K):
         assert float((got.double() - ref).norm() / ref.norm()) < tol
     # element by element: no tile left out or written twice (roundings of the largest terms)
     assert float((dx.view(M, ci).double() - rdx).abs().max()) < 2.0 ** -20 * float(rdx.abs().max()) * (4 if flags else 1)
+
+
+@pytest.mark.parametrize("flags", [0, B.ABL_MATH_BF16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("s", [(26, 7, 7, 2048, 512), (26, 8, 8, 2048, 512), (15, 14, 13, 1024, 256)], ids=lambda s: "x".join(map(str, s)))
+def test_forward(s, flags):
+    print("case 1x1 forward", s, flush=True)
+    N, H, W, ci, co = s
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x = torch.randn(N, H, W, ci, device="cuda", generator=g)
+    w = torch.randn(1, 1, ci, co, device="cuda", generator=g) * (2.0 / ci) ** 0.5
+    y = f32(N, H, W, co)
+    B.abl_conv_fwd(s + (1, 1, 1, 0), x, w, None, y, flags=flags)
+    a, v = (x.bfloat16().float(), w.bfloat16().float()) if flags else (x, w)
+    ref = a.double().view(-1, ci) @ v.double()[0, 0]
+    tol = 2.0 ** -24 * ((ci / 32) ** 0.5 + 2) * (3 if flags else 1)   # (as above)
+    assert float((y.view(-1, co).double() - ref).norm() / ref.norm()) < tol
+    assert float((y.view(-1, co).double() - ref).abs().max()) < 2.0 ** -20 * float(ref.abs().max()) * (4 if flags else 1)
