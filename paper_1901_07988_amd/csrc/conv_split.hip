@@ -662,6 +662,18 @@ bool supported(const ConvGeom& g, int mode) {
          M * g.Cout < ((int64_t)1 << 31);
 }
 
+// Positions of a 3x3 patch up to which four-wave blocks share a compute unit in pairs (fp32: its LDS; four staging items a thread).
+constexpr int kPairPositions = 256;
+
+// What `tiles` tiles in four-wave blocks take, nblk blocks along the output channels: rounds of one block per unit, or
+// of two (34 of 50 where the last round has one only).
+int64_t rounds_cost(int64_t tiles, int64_t nblk, bool pairs) {
+  const int64_t per = (tiles + kMaxPartialBlocks - 1) / kMaxPartialBlocks, n = (tiles + per - 1) / per * nblk;
+  if (!pairs) return per * 40 * ((n + 255) / 256);
+  const int64_t last = n % 512;
+  return per * (50 * (n / 512) + (last == 0 ? 0 : last <= 256 ? 34 : 50));
+}
+
 // The configuration with nt, ks for this layer; false where its sizes do not fit.
 bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
@@ -691,21 +703,29 @@ bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
     t.npos = (rows + 2) * (W + 2);
     // across images, where the patch has room for the two rows of border that each of them brings: runs of
     // any pixels, or of whole images
-    const int room = p.su * threads / c8;
+    const int room = p.su * threads / c8, xtiles = (M + bm - 1) / bm;
     int xrows = bm % W == 0 ? bm / W : (bm + W - 2) / W + 1;
     xrows += 2 + 2 * ((xrows + g.H - 2) / g.H);
     int imgs = bm / HW;
     if (imgs > room / ((g.H + 2) * (W + 2))) imgs = room / ((g.H + 2) * (W + 2));
-    if ((M + bm - 1) / bm < t.tiles && xrows * (W + 2) <= room) {
-      t.run = bm;
-      t.npos = xrows * (W + 2);
-      t.unit = M;
+    const bool run = xtiles < t.tiles && xrows * (W + 2) <= room;
+    Tiling x = t;
+    if (run) {
+      x.run = bm;
+      x.npos = xrows * (W + 2);
     } else if (imgs > 1) {
-      t.run = imgs * HW;
-      t.npos = imgs * (g.H + 2) * (W + 2);
-      t.unit = M;
+      x.run = imgs * HW;
+      x.npos = imgs * (g.H + 2) * (W + 2);
     }
-    if (t.unit == M) t.ntr = t.tiles = (M + t.run - 1) / t.run;
+    x.unit = M;
+    x.ntr = x.tiles = (M + x.run - 1) / x.run;
+    // (A few tiles less do not make up for the unit's second block.  us, forward of the layer, runs across images / image by
+    // image: 128 -> 128 @27x27 N=64 137 / 87, N=80 162 / 137, @29x29 N=56 137 / 87, 64 -> 64 @33x33 N=64 64 / 53, @40x40 N=64
+    // 83 / 60, 256 -> 256 @22x22 N=20 128 / 78; but one round of single blocks beats a few pairs: 64 -> 64 @32x32 N=28, 256
+    // blocks / 280, 29.5 / 31.4, 128 -> 128 @26x26 N=20, 242 / 280, 42.6 / 45.4.)
+    const bool loses_pairs = x.npos > kPairPositions && t.npos <= kPairPositions &&
+                             rounds_cost(x.tiles, Ng / p.bn, false) >= rounds_cost(t.tiles, Ng / p.bn, true);
+    if ((run || imgs > 1) && !loses_pairs) t = x;
   }
   if (t.npos * c8 > p.su * threads) return false;
   if (p.su == 7 && t.npos * c8 <= 4 * threads) p.su = 4;
@@ -716,10 +736,11 @@ bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
 }
 
 // How many consecutive tiles a block of an accepted plan takes: fewer rounds of the chip's places (two four-wave blocks per compute
-// unit, one where a patch has more than 256 positions) that stay filled.  (1x1 gradient 256 <- 64 @56x56, two blocks along the
+// unit, one where a patch has more than kPairPositions) that stay filled.  (1x1 gradient 256 <- 64 @56x56, two blocks along the
 // channels: 896 blocks of four tiles, 1.75 rounds, 125 us; 512 of seven 116; 256 of fourteen, one per unit, 147.  Grids of one tile
-// per block stay: 896 blocks of one or 448 of two, 1x1 256 -> 1024 @14x14 52 us both; and places are not left empty: 3x3 128 -> 128
-// @27x27 N=80, layer, 522 blocks of two 153, 348 of three 165.)
+// per block stay: 896 blocks of one or 448 of two, 1x1 256 -> 1024 @14x14 52 us both.  One block per unit: 64 -> 64 @55x55 N=64,
+// forward, 448 blocks of four 150, 256 of seven 135, @57x57 N=40 387 of three 119, 233 of five 102; but a last round that is
+// nearly empty costs less than it counts here: runs across images of 128 -> 128 @27x27 N=80, 522 blocks of two 142, 210 of five 162.)
 void balance(const ConvGeom& g, int mode, Plan& p) {
   if (p.tl.per == 1) return;
   const int64_t nblk = (mode == 0 ? g.Cout : g.Cin) / p.bn, places = p.su > 4 ? 256 : 512, least = p.su > 4 ? 160 : 448;

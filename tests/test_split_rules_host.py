@@ -1,0 +1,19 @@
+"""Grids that the split convolutions choose, pinned where they were measured (no GPU)."""
+import pytest
+
+from . import split_rules as R
+
+
+@pytest.mark.parametrize("s, want", [
+    # image by image, two blocks per compute unit: 560 tiles in blocks of two, one tile each
+    ((80, 27, 27, 128, 128, 3), 280), ((64, 27, 27, 128, 128, 3), 448), ((56, 29, 29, 128, 128, 3), 448),
+    ((64, 33, 33, 64, 64, 3), 320), ((64, 40, 40, 64, 64, 3), 480), ((20, 22, 22, 256, 256, 3), 100),
+    # runs across images, one block per unit: one round of them against more than a round's worth of pairs' first halves
+    ((28, 32, 32, 64, 64, 3), 256), ((20, 26, 26, 128, 128, 3), 121),
+    # patches beyond a pair's either way: fewer tiles, as many to a block as keep the units busy
+    ((64, 55, 55, 64, 64, 3), 256), ((40, 57, 57, 64, 64, 3), 233),
+    # patches within a pair's either way
+    ((64, 14, 14, 256, 256, 3), 112), ((64, 56, 56, 64, 64, 3), 448), ((64, 28, 28, 128, 128, 3), 448)],
+    ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_fused_forward(s, want):
+    assert R.fused_rows(s) == want
