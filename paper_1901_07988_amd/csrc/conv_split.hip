@@ -736,14 +736,17 @@ bool fit_plan(const ConvGeom& g, int mode, int np, int nt, int ks, Plan& p) {
 }
 
 // How many consecutive tiles a block of an accepted plan takes: fewer rounds of the chip's places (two four-wave blocks per compute
-// unit, one where a patch has more than kPairPositions) that stay filled.  (1x1 gradient 256 <- 64 @56x56, two blocks along the
+// unit; with fp32 operands one where a patch has more than kPairPositions) that stay filled.  (1x1 gradient 256 <- 64 @56x56, two blocks along the
 // channels: 896 blocks of four tiles, 1.75 rounds, 125 us; 512 of seven 116; 256 of fourteen, one per unit, 147.  Grids of one tile
 // per block stay: 896 blocks of one or 448 of two, 1x1 256 -> 1024 @14x14 52 us both.  One block per unit: 64 -> 64 @55x55 N=64,
 // forward, 448 blocks of four 150, 256 of seven 135, @57x57 N=40 387 of three 119, 233 of five 102; but a last round that is
-// nearly empty costs less than it counts here: runs across images of 128 -> 128 @27x27 N=80, 522 blocks of two 142, 210 of five 162.)
-void balance(const ConvGeom& g, int mode, Plan& p) {
+// nearly empty costs less than it counts here: runs across images of 128 -> 128 @27x27 N=80, 522 blocks of two 142, 210 of five 162.
+// With bf16 operands such patches leave room for two: gradient 64 <- 64 @55x55 N=64 448 blocks of four 114, 256 of seven 131, N=28
+// 392 of two 68.5, 196 of four 81.)
+void balance(const ConvGeom& g, int mode, int np, Plan& p) {
   if (p.tl.per == 1) return;
-  const int64_t nblk = (mode == 0 ? g.Cout : g.Cin) / p.bn, places = p.su > 4 ? 256 : 512, least = p.su > 4 ? 160 : 448;
+  const bool alone = np == 3 && p.su > 4;
+  const int64_t nblk = (mode == 0 ? g.Cout : g.Cin) / p.bn, places = alone ? 256 : 512, least = alone ? 160 : 448;
   auto blocks = [&](int per) { return (p.tl.tiles + per - 1) / per * nblk; };
   auto cost = [&](int per) { return (blocks(per) + places - 1) / places * (2 * per + 1); };   // in half tiles: a start costs about one
   int best = p.tl.per;
@@ -772,7 +775,7 @@ bool halo_is_faster(const ConvGeom& g, int mode, const Plan& p) {
   if (!alone) return false;
   const int64_t rounds = (blocks + 255) / 256;
   Plan q = p;
-  balance(g, mode, q);
+  balance(g, mode, 3, q);
   const double here = 1.5 + 15.5 * (double)(q.tl.per * (((int64_t)q.tl.gm * (Ng / q.bn) + 255) / 256));
   const double there = pixels == 64 ? 3.7 + 11.1 * rounds : pixels == 128 ? 3.0 + 20.0 * rounds : 2.5 + 35.5 * rounds;
   return 1.1 * there < here;
@@ -935,7 +938,7 @@ bool fit_fused_plan(const ConvGeom& g, Plan& p) {
 int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
   Plan p;
   if (!make_plan(g, mode, bf16 ? 1 : 3, sums, p)) return 0;
-  balance(g, mode, p);
+  balance(g, mode, bf16 ? 1 : 3, p);
   return p.tl.gm;
 }
 
@@ -976,7 +979,7 @@ int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, co
                       const float* skip, float* out, double* sums, const void* parts) {
   Plan p;
   if (!make_plan(g, mode, bf16 ? 1 : 3, false, p)) return ABL_ERR_SHAPE;
-  balance(g, mode, p);
+  balance(g, mode, bf16 ? 1 : 3, p);
   const int epi = sums != nullptr ? 1 : 0;
   if (mode == 0)
     return bf16 ? launch<0, 1>(st, g, p, in, w, parts, skip, out, sums, nullptr, nullptr, epi)
@@ -990,7 +993,7 @@ int split_forward3(const ConvGeom& g, int* rows) {
   if (g.R != 3 || !make_plan(g, 0, 3, false, p)) return 0;
   const bool weighed = p.nt == 1 && p.ks == 1;   // (make_plan has compared this one with the halo kernel)
   if (!fit_fused_plan(g, p) || (!weighed && halo_is_faster(g, 0, p))) return -1;
-  balance(g, 0, p);
+  balance(g, 0, 3, p);
   *rows = p.tl.gm;
   return 1;
 }
@@ -999,7 +1002,7 @@ int launch_split_fwd_fused(hipStream_t st, const ConvGeom& g, int K, const float
                            const float* skip, float* y, void* packed, double* sums, const void* parts) {
   Plan p;
   if (!fit_fused_plan(g, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
-  balance(g, 0, p);
+  balance(g, 0, 3, p);
   const float* sp = static_cast<const float*>(stats);
   uint8_t* pk = static_cast<uint8_t*>(packed);
   auto run = [&](auto f) { return f(st, g, p, x, sp, w, parts, skip, y, pk, sums); };
@@ -1015,7 +1018,7 @@ int launch_split_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, bool bf1
                               const void* packed, const void* stats, float* da3, double* partial, const void* parts) {
   Plan p;
   if (!make_plan(g, 1, bf16 ? 1 : 3, true, p) || (K != 4 && K != 8)) return ABL_ERR_SHAPE;
-  balance(g, 1, p);
+  balance(g, 1, bf16 ? 1 : 3, p);
   const uint8_t* codes = static_cast<const uint8_t*>(packed);
   const float* sp = static_cast<const float*>(stats);
   return bf16 ? launch<1, 1>(st, g, p, dy, w, parts, nullptr, da3, partial, codes, sp, K)

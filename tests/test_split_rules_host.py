@@ -17,3 +17,11 @@ from . import split_rules as R
     ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_fused_forward(s, want):
     assert R.fused_rows(s) == want
+
+
+@pytest.mark.parametrize("s, want", [((64, 55, 55, 64, 64, 3), 448), ((28, 55, 55, 64, 64, 3), 392), ((96, 57, 57, 64, 64, 3), 465),
+                                     ((64, 56, 56, 64, 64, 3), 448)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_bf16_gradient(s, want):
+    """With bf16 operands a large patch leaves room for two blocks per compute unit."""
+    assert R.rows(s, 1, True, True) == want
