@@ -830,9 +830,12 @@ bool four_waves_pay(const ConvGeom& g, int mode, int np, bool sums, const Plan& 
   // n = 560, 58.0 / 60.6; 2048 <- 512 @7x7 N=64, n = 448, 65.8 / 60.6, N=40, n = 288, 51.6 / 54.3; 256 <- 64 @56x56 N=40, n = 748,
   // 119 / 112, N=20, n = 560, 68.4 / 72.0; 512 <- 128 @28x28 N=64 112 / 106.  Forward: 1024 -> 256 @14x14 N=40 53.8 / 47.2; 2048 ->
   // 512 @8x8 N=64 77.2 / 62.3; 256 -> 1024 @15x15 N=64, n = 1032, 48.7 / 42.0; 128 -> 512 @28x28 N=52, n = 1456, 46.6 / 42.4, N=20,
-  // n = 560, 29.1 / 29.6.)
-  if (mode == 1) return sums && (p.nt == 1 ? Cg < 1024 : (n >= 440 && n <= 512) || n >= 720);
-  return Cg >= 1024 || n >= 720 || (!fit && !(over_one && p.tl.per > 1));
+  // n = 560, 29.1 / 29.6.
+  // Blocks of several tiles with 128 and more channels to contract, K = 8 / 4: 512 <- 128 @30x30 N=80 149 / 145 against 162 / 146,
+  // @28x28 N=80 135 / 133 against 138 / 132; with 64 here, 256 <- 64 @56x56 N=80 273 / 262 against 264 / 244.  Forward with 64
+  // channels to contract: 64 -> 256 @56x56 N=14, n = 784, 31.3 / 32.1, @55x55 N=16, n = 866, 31.6 / 32.4.)
+  if (mode == 1) return sums && (p.nt == 1 ? Cg < 1024 : (n >= 440 && n <= 512) || (n >= 720 && (p.tl.per == 1 || Cg < 128)));
+  return Cg >= 1024 || n >= (Cg < 128 ? 1024 : 720) || (!fit && !(over_one && p.tl.per > 1));
 }
 
 // 128 output channels per block where that fills the chip, else 64.  About one block per compute unit: the

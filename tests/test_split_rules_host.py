@@ -25,3 +25,15 @@ def test_fused_forward(s, want):
 def test_bf16_gradient(s, want):
     """With bf16 operands a large patch leaves room for two blocks per compute unit."""
     assert R.rows(s, 1, True, True) == want
+
+
+@pytest.mark.parametrize("s, mode, want", [
+    # gradients of several tiles per block: with 64 channels to contract, not with more
+    ((80, 30, 30, 512, 128, 1), 1, 0), ((80, 28, 28, 512, 128, 1), 1, 0), ((40, 30, 30, 512, 128, 1), 1, 322),
+    ((80, 56, 56, 256, 64, 1), 1, 249),
+    # forward with 64 channels to contract: larger grids
+    ((14, 56, 56, 64, 256, 1), 0, 0), ((16, 55, 55, 64, 256, 1), 0, 0), ((16, 56, 56, 64, 256, 1), 0, 448),
+    ((28, 28, 28, 128, 512, 1), 0, 196)],
+    ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_bf16_1x1(s, mode, want):
+    assert R.rows(s, mode, True, mode == 1) == want
