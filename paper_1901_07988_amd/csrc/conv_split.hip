@@ -127,11 +127,11 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   constexpr int STEPS = TAPS * CPP;                    // k-steps of a phase and wave
   // pixel fragments of a k-step (7 tiles, NP parts), and registers for as many as are read ahead.  (A wave that has to wait
   // for each tile's reads leaves its SIMD idle as soon as the other wave waits at a barrier.)
-  // (1x1, bf16 operands and weights split here: six reads ahead of a step's fourteen products only put off its weights.
-  // Gradient with sums, us, one ahead / six: 512 <- 128 @28x28 N=40, K=8 79.3 / 81.9, N=64, K=4 101.6 / 106.4, 256 <- 64 @56x56
-  // N=14, K=8 55.9 / 58.2.)
+  // (1x1 gradient, bf16 operands and weights split here: six reads ahead of a step's fourteen products only put off its
+  // weights, which are few.  With sums, us, one ahead / six: 512 <- 128 @28x28 N=40, K=8 79.3 / 81.9, N=64, K=4 101.6 / 106.4,
+  // 256 <- 64 @56x56 N=14, K=8 55.9 / 58.2; not so a long forward contraction: 2048 -> 512 @7x7 N=80 68.4 / 64.4.)
   constexpr bool SHORT = TAPS == 1 && NP == 1 && !PRE;
-  constexpr int NF = MT * NP, SLOTS = 7, LOOK = SHORT ? 1 : SLOTS - 1;
+  constexpr int NF = MT * NP, SLOTS = 7, LOOK = SHORT && MODE == 1 ? 1 : SLOTS - 1;
   // the next phase's input asked for in front of a phase's only step (us, in front / behind its weights: gradient 512 <- 2048
   // @7x7 N=26 53.9 / 61.9, 256 <- 1024 @14x14 N=14 38.4 / 42.1, forward 2048 -> 512 @8x8 N=26 43.4 / 48.9)
   constexpr bool INPUT_FIRST = SHORT && KS == 2;
