@@ -224,14 +224,6 @@ int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, 
   return 0;
 }
 
-// Whether splitting a layer's weights once saves more than it costs (a launch of its own in abl_backward, 4 us): 1x1 layers with
-// many pixels for each weight and, in the gradient, more than four k-steps.  (Layer, us, split by the blocks / once: gradient 2048 <-
-// 512 @7x7 N=14 48.2 / 52.3, 512 <- 128 @28x28 N=26 73.8 / 78.5, 256 <- 64 @56x56 N=26 94.0 / 96.8; forward 512 -> 2048 @7x7 N=14
-// 30.3 / 32.3, 256 -> 1024 @15x15 N=14 29.7 / 31.2, but 1024 -> 256 @14x14 N=40 72 / 64.)
-bool parts_pay(const ConvGeom& g, int mode) {
-  return g.R == 3 || ((int64_t)g.N * g.H * g.W >= 4096 && (mode == 0 || g.Cout >= 256));
-}
-
 // The parts of a layer's weights go where the copies of its weight gradient will be (`room` bytes, free in the forward
 // and until the weight gradient runs); a layer whose copies leave less room has its weights split by the convolution.
 SplitWeights weights_to_split(const abl_shape& s, int mode, int np, const float* W, void* at, size_t room) {
@@ -263,7 +255,7 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
   // weights of a split-operand convolution: split by the launch of the second pass of Eq. 1, which leaves most of the chip
   // idle
   SplitWeights sw{};
-  if (const int np = !parts_pay(g, 0) ? 0 : split_rows > 0 ? 3 : path == 0 ? conv_fwd_parts(g, bf16) : 0)
+  if (const int np = !parts_pay(g, 0, bf16, false) ? 0 : split_rows > 0 ? 3 : path == 0 ? conv_fwd_parts(g, bf16) : 0)
     sw = weights_to_split(*s, 0, np, W, static_cast<char*>(red) + up256(bn_partial_bytes(M, s->Cin)), wgrad_partial_bytes(*s));
   if (in_partial != nullptr && in_nb > 0) {
     if (int e = launch_bn_stats_finalize(st, in_partial, in_nb, nullptr, M, s->Cin, gamma, beta, K, stats, sw)) return e;
@@ -324,9 +316,10 @@ int abl_forward(void* stream, const abl_shape* s, int K, uint32_t flags, const f
 
 namespace {
 
-// Parts of the weights that the data gradient of this layer can read, 0 = none.
-int backward_parts(const ConvGeom& g, int K, bool bf16) {
-  if (K == 32 || g.Cout % 32 != 0 || g.Cin % 64 != 0 || !parts_pay(g, 1)) return 0;   // (nor the 16-channel kernel's layers)
+// Parts of the weights that the data gradient of this layer is to read, 0 = none.  own_launch: see parts_pay.
+int backward_parts(const ConvGeom& g, int K, bool bf16, bool own_launch) {
+  if (K == 32 || g.Cout % 32 != 0 || g.Cin % 64 != 0) return 0;   // (nor the 16-channel kernel's layers)
+  if (!parts_pay(g, 1, bf16, own_launch)) return 0;
   if (!bf16) return split_conv_blocks(g, 1, false, true) > 0 ? 3 : 0;
   return bf16_gemm_supported(g, 1) && bf16_dgrad_reduce_splits(g) ? 1 : 0;
 }
@@ -463,7 +456,7 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
     return ABL_ERR_ARG;
   if (scratch_bytes < abl_scratch_bytes(s, K)) return ABL_ERR_SCRATCH;
   SplitWeights sw{};
-  if (const int np = backward_parts(geom_of(*s), K, (flags & ABL_MATH_BF16) != 0))
+  if (const int np = backward_parts(geom_of(*s), K, (flags & ABL_MATH_BF16) != 0, true))
     sw = weights_to_split(*s, 1, np, W, static_cast<char*>(scratch) + wpart_offset(*s), wgrad_partial_bytes(*s));
   if (sw.out != nullptr)
     if (int e = launch_split_weights((hipStream_t)stream, sw)) return e;
@@ -906,7 +899,7 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
   // (its apply pass), at a place in the workspace that is free for both.
   auto parts_of = [&](int i, size_t at) {
     const abl_layer& l = layers[i];
-    const int np = backward_parts(geom_of(l.shape), K, (flags & ABL_MATH_BF16) != 0);
+    const int np = backward_parts(geom_of(l.shape), K, (flags & ABL_MATH_BF16) != 0, i == L - 1);
     if (np == 0) return SplitWeights{};
     const size_t from = wpart_offset(l.shape) > at ? wpart_offset(l.shape) : at;
     return weights_to_split(l.shape, 1, np, l.W, lscratch + (from < lbytes ? from : 0), from < lbytes ? lbytes - from : 0);

@@ -211,6 +211,9 @@ int launch_image_bf16(hipStream_t st, const ConvGeom& g, int mode, const float* 
 // sums: with the Eq. 6-7 sums (launch_split_dgrad_reduce).
 // parts (nullable, in the launchers): the weights as SplitWeights leaves them, same mode and operands.
 int split_conv_blocks(const ConvGeom& g, int mode, bool bf16 = false, bool sums = false);
+// Whether splitting the weights of a layer that split_conv_kernel takes once per call (SplitWeights) is faster than in the kernel.
+// own_launch: no other launch can do it (the gradient of abl_backward, and of a stack's last layer).
+bool parts_pay(const ConvGeom& g, int mode, bool bf16, bool own_launch);
 // Whether split_conv_kernel with bf16 operands is faster than the image-resident kernel on a 3x3 layer that both take.
 bool split_beats_image(const ConvGeom& g, int mode);
 // The fp32 forward of a 1x1 layer with a pass of its own for Eq. 1-3 and 9 in front is faster than the pointwise kernel's

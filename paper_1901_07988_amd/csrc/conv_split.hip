@@ -945,6 +945,29 @@ int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
   return p.tl.gm;
 }
 
+// On a launch that is there anyway: 3x3 layers, and 1x1 layers of 4096 pixels and more whose gradient contracts 256 channels and
+// more.  (Layer, us, split by the blocks / once: gradient 2048 <- 512 @7x7 N=14 48.2 / 52.3, 512 <- 128 @28x28 N=26 73.8 / 78.5,
+// 256 <- 64 @56x56 N=26 94.0 / 96.8; forward 512 -> 2048 @7x7 N=14 30.3 / 32.3, 256 -> 1024 @15x15 N=14 29.7 / 31.2, but 1024
+// -> 256 @14x14 N=40 72 / 64.)
+// A launch of its own costs 4 us: those whose waves take enough k-steps, counted over all of a grid's rounds; bf16 1x1 layers
+// split little at a step, and only more channels per block make it count.  (Backward, us, split by the blocks / once.  3x3: 64
+// <- 64 @8x8 N=128, 9 steps, 39.3 / 40.5, @28x28 N=24, 9, 46.0 / 47.3, N=40, 18, 60.3 / 60.7, bf16 46.8 / 45.0, N=128, 31, 98.3 /
+// 95.8; 128 <- 128 @14x14 N=64, 18, 63.4 / 63.3, bf16 50.0 / 49.8; 512 <- 512 @7x7 N=40, 72, 124 / 122, bf16 83 / 74.  1x1: 64
+// <- 256 @55x55 N=14, 8, 46.4 / 47.4, N=40, 16.9, 94.6 / 91.7; 128 <- 512 @28x28 N=14, 8, 45.5 / 46.8, N=26, 16, 63.3 / 61.9; 1024
+// <- 256 @14x14 N=40, 8.8, 84.9 / 87.7; 256 <- 1024 N=40, 32, 87.3 / 81.2.  bf16, steps times channel tiles: 64 <- 256 @56x56
+// N=34, 15, 65.4 / 68.3, N=64, 28, 130 / 127; 128 <- 512 @28x28 N=28, 16, 43.7 / 44.5; 256 <- 1024 @14x14 N=34, 16, 45.3 / 46.3,
+// N=64, 32, 58.8 / 56.8; 1024 <- 256 N=52, 23, 68.5 / 69.1, @15x15 N=52, 26, 79.6 / 77.5.)
+bool parts_pay(const ConvGeom& g, int mode, bool bf16, bool own_launch) {
+  if (g.R != 3 && ((int64_t)g.N * g.H * g.W < 4096 || (mode == 1 && g.Cout < 256))) return false;
+  if (!own_launch) return true;
+  Plan p;
+  if (!make_plan(g, mode, bf16 ? 1 : 3, mode == 1, p)) return false;
+  const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
+  const int64_t steps = (int64_t)g.R * g.S * (Cg / 32) / p.ks, n = (int64_t)p.tl.tiles * (Ng / p.bn);
+  const int64_t all = steps * (n > 512 ? n : 512) * (bf16 && g.R == 1 ? p.nt : 1);   // (places for 512 blocks)
+  return all >= 512 * (g.R == 3 ? 18 : bf16 ? 24 : 16);
+}
+
 // (us, layer forward / backward, image kernel against here: 512 -> 512 @7x7 N=40, two rounds of images, 72 / 113 against 46 /
 // 74, N=120 125 / 224 against 57 / 116; 256 -> 256 @14x14 N=20 35.2 / 58.1 against 32.9 / 53.0, N=64 40.5 / 79.9 against 40.6 /
 // 78.1, N=120 65.4 / 134 against 59.1 / 119; 128 -> 128 @14x14 N=28 26.5 / 50.0 against 22.7 / 45.1, N=64 29.4 / 55.3 against

@@ -21,6 +21,7 @@ def _fn(name, res, *args):
 _i, _b = ctypes.c_int, ctypes.c_bool
 _blocks = _fn("_ZN3abl17split_conv_blocksERKNS_8ConvGeomEibb", _i, _i, _b, _b)
 _forward3 = _fn("_ZN3abl14split_forward3ERKNS_8ConvGeomEPi", _i, ctypes.POINTER(_i))
+_parts_pay = _fn("_ZN3abl9parts_payERKNS_8ConvGeomEibb", _b, _i, _b, _b)
 
 
 def rows(s, mode, bf16=False, sums=False):
@@ -33,3 +34,8 @@ def fused_rows(s):
     n = _i(0)
     path = _forward3(ctypes.byref(geom(*s)), ctypes.byref(n))
     return n.value if path > 0 else path
+
+
+def parts_pay(s, mode, bf16=False, own_launch=False):
+    """Whether the weights of a layer are split once per call instead of by its blocks."""
+    return _parts_pay(ctypes.byref(geom(*s)), mode, bf16, own_launch)

@@ -37,3 +37,16 @@ def test_bf16_gradient(s, want):
     ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_bf16_1x1(s, mode, want):
     assert R.rows(s, mode, True, mode == 1) == want
+
+
+@pytest.mark.parametrize("s, bf16, want", [
+    ((128, 8, 8, 64, 64, 3), False, False), ((24, 28, 28, 64, 64, 3), False, False), ((40, 28, 28, 64, 64, 3), True, True),
+    ((64, 56, 56, 64, 64, 3), False, True), ((64, 14, 14, 256, 256, 3), False, True), ((40, 7, 7, 512, 512, 3), True, True),
+    ((14, 55, 55, 64, 256, 1), False, False), ((64, 55, 55, 64, 256, 1), False, True), ((14, 28, 28, 128, 512, 1), False, False),
+    ((26, 28, 28, 128, 512, 1), False, True), ((40, 14, 14, 1024, 256, 1), False, False), ((40, 14, 14, 256, 1024, 1), False, True),
+    ((34, 56, 56, 64, 256, 1), True, False), ((34, 14, 14, 256, 1024, 1), True, False), ((64, 14, 14, 256, 1024, 1), True, True),
+    ((52, 15, 15, 1024, 256, 1), True, True)],
+    ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_a_launch_of_its_own_to_split_weights(s, bf16, want):
+    assert R.parts_pay(s, 1, bf16, own_launch=True) == want
+    assert R.parts_pay(s, 1, bf16)   # in the launch of the layer above they all are split
