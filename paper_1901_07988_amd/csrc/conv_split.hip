@@ -127,11 +127,12 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   constexpr int STEPS = TAPS * CPP;                    // k-steps of a phase and wave
   // pixel fragments of a k-step (7 tiles, NP parts), and registers for as many as are read ahead.  (A wave that has to wait
   // for each tile's reads leaves its SIMD idle as soon as the other wave waits at a barrier.)
-  // (1x1 gradient, bf16 operands and weights split here: six reads ahead of a step's fourteen products only put off its
-  // weights, which are few.  With sums, us, one ahead / six: 512 <- 128 @28x28 N=40, K=8 79.3 / 81.9, N=64, K=4 101.6 / 106.4,
-  // 256 <- 64 @56x56 N=14, K=8 55.9 / 58.2; not so a long forward contraction: 2048 -> 512 @7x7 N=80 68.4 / 64.4.)
+  // (1x1, bf16 operands and weights split here: six reads ahead of a step's fourteen products only put off its weights, which
+  // are few.  us, one ahead / six: gradient with sums 512 <- 128 @28x28 N=40, K=8 79.3 / 81.9, N=64, K=4 101.6 / 106.4, 256 <- 64
+  // @56x56 N=14, K=8 55.9 / 58.2, forward 64 -> 256 @55x55 N=12 29.1 / 30.5; not so a long forward contraction, which takes 64
+  // channels per block, 2048 -> 512 @7x7 N=80 68.4 / 64.4.)
   constexpr bool SHORT = TAPS == 1 && NP == 1 && !PRE;
-  constexpr int NF = MT * NP, SLOTS = 7, LOOK = SHORT && MODE == 1 ? 1 : SLOTS - 1;
+  constexpr int NF = MT * NP, SLOTS = 7, LOOK = SHORT && (MODE == 1 || NT == 2) ? 1 : SLOTS - 1;
   // the next phase's input asked for in front of a phase's only step (us, in front / behind its weights: gradient 512 <- 2048
   // @7x7 N=26 53.9 / 61.9, 256 <- 1024 @14x14 N=14 38.4 / 42.1, forward 2048 -> 512 @8x8 N=26 43.4 / 48.9)
   constexpr bool INPUT_FIRST = SHORT && KS == 2;
@@ -946,9 +947,9 @@ int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
 }
 
 // On a launch that is there anyway: 3x3 layers, and 1x1 layers of 4096 pixels and more whose gradient contracts 256 channels and
-// more.  (Layer, us, split by the blocks / once: gradient 2048 <- 512 @7x7 N=14 48.2 / 52.3, 512 <- 128 @28x28 N=26 73.8 / 78.5,
+// more; a forward of two k-steps from three times as many pixels on.  (Layer, us, split by the blocks / once: gradient 2048 <- 512 @7x7 N=14 48.2 / 52.3, 512 <- 128 @28x28 N=26 73.8 / 78.5,
 // 256 <- 64 @56x56 N=26 94.0 / 96.8; forward 512 -> 2048 @7x7 N=14 30.3 / 32.3, 256 -> 1024 @15x15 N=14 29.7 / 31.2, but 1024
-// -> 256 @14x14 N=40 72 / 64.)
+// -> 256 @14x14 N=40 72 / 64; bf16 64 -> 256 @55x55 N=12 29.1 / 30.2, @56x56 N=20 36.9 / 36.5.)
 // A launch of its own costs 4 us: those whose waves take enough k-steps, counted over all of a grid's rounds; bf16 1x1 layers
 // split little at a step, and only more channels per block make it count.  (Backward, us, split by the blocks / once.  3x3: 64
 // <- 64 @8x8 N=128, 9 steps, 39.3 / 40.5, @28x28 N=24, 9, 46.0 / 47.3, N=40, 18, 60.3 / 60.7, bf16 46.8 / 45.0, N=128, 31, 98.3 /
@@ -958,7 +959,8 @@ int split_conv_blocks(const ConvGeom& g, int mode, bool bf16, bool sums) {
 // N=34, 15, 65.4 / 68.3, N=64, 28, 130 / 127; 128 <- 512 @28x28 N=28, 16, 43.7 / 44.5; 256 <- 1024 @14x14 N=34, 16, 45.3 / 46.3,
 // N=64, 32, 58.8 / 56.8; 1024 <- 256 N=52, 23, 68.5 / 69.1, @15x15 N=52, 26, 79.6 / 77.5.)
 bool parts_pay(const ConvGeom& g, int mode, bool bf16, bool own_launch) {
-  if (g.R != 3 && ((int64_t)g.N * g.H * g.W < 4096 || (mode == 1 && g.Cout < 256))) return false;
+  const int64_t pixels = (int64_t)g.N * g.H * g.W;
+  if (g.R != 3 && (pixels < 4096 || (mode == 1 && g.Cout < 256) || (mode == 0 && g.Cin < 128 && pixels < 3 << 14))) return false;
   if (!own_launch) return true;
   Plan p;
   if (!make_plan(g, mode, bf16 ? 1 : 3, mode == 1, p)) return false;

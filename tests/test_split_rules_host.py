@@ -50,3 +50,10 @@ def test_bf16_1x1(s, mode, want):
 def test_a_launch_of_its_own_to_split_weights(s, bf16, want):
     assert R.parts_pay(s, 1, bf16, own_launch=True) == want
     assert R.parts_pay(s, 1, bf16)   # in the launch of the layer above they all are split
+
+
+@pytest.mark.parametrize("s, want", [((12, 55, 55, 64, 256, 1), False), ((14, 56, 56, 64, 256, 1), False), ((16, 56, 56, 64, 256, 1), True),
+                                     ((12, 28, 28, 128, 512, 1), True), ((12, 8, 8, 64, 64, 3), True)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_weights_of_a_forward(s, want):
+    assert R.parts_pay(s, 0) == want and R.parts_pay(s, 0, True) == want
