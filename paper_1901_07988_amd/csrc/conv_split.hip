@@ -976,12 +976,15 @@ bool parts_pay(const ConvGeom& g, int mode, bool bf16, bool own_launch) {
 // 26.6 / 49.6.  Four-wave blocks of 64 channels a little over one per unit lose: 256 -> 256 @14x14 N=40, n = 280, 37.1 / 68.1
 // against 46.3 / 72.9, 128 -> 128 N=80 30.9 / 56.1 against 33.2 / 56.3, n = 420 wins again, 33.9 / 63.0 against 32.9 / 60.2; so
 // do a few blocks with a long contraction beside one round of images: 512 -> 512 @7x7 N=28, n = 112, 43.4 / 70.4 against 45.5 /
-// 69.5.)
+// 69.5.  Nor does an image that is no more than a tile here, while one round of the units takes them all - forward: 256 -> 256 @7x7
+// N=64 27.9 against 30.4, @8x8 N=40 25.7 / 29.1, @10x10 N=52 31.4 / 32.8, 128 -> 128 @8x8 N=64 19.3 / 20.5, but @12x12 N=64 27.3 /
+// 23.8; gradients, with the sums, below 64 pixels: @7x7 N=64 49.0 / 50.5, @8x8 N=40 48.1 / 47.8, @10x10 N=64 71.4 / 69.5.)
 bool split_beats_image(const ConvGeom& g, int mode) {
   Plan p;
   if (!make_plan(g, mode, 1, false, p)) return false;
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
   const int64_t n = (int64_t)p.tl.gm * (Ng / p.bn);
+  if ((int64_t)g.N * (Ng / 64) <= 256 && g.H * g.W <= (mode == 0 ? 16 * MT : 63)) return false;
   if (p.nt == 1 && p.ks == 1) return n >= 384;
   return n >= 128 || Cg < 512 || (int64_t)g.N * (Ng / 64) > 256;
 }

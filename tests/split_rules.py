@@ -22,6 +22,7 @@ _i, _b = ctypes.c_int, ctypes.c_bool
 _blocks = _fn("_ZN3abl17split_conv_blocksERKNS_8ConvGeomEibb", _i, _i, _b, _b)
 _forward3 = _fn("_ZN3abl14split_forward3ERKNS_8ConvGeomEPi", _i, ctypes.POINTER(_i))
 _parts_pay = _fn("_ZN3abl9parts_payERKNS_8ConvGeomEibb", _b, _i, _b, _b)
+_beats_image = _fn("_ZN3abl17split_beats_imageERKNS_8ConvGeomEi", _b, _i)
 
 
 def rows(s, mode, bf16=False, sums=False):
@@ -39,3 +40,8 @@ def fused_rows(s):
 def parts_pay(s, mode, bf16=False, own_launch=False):
     """Whether the weights of a layer are split once per call instead of by its blocks."""
     return _parts_pay(ctypes.byref(geom(*s)), mode, bf16, own_launch)
+
+
+def beats_image(s, mode):
+    """Whether a 3x3 layer with bf16 operands prefers the split convolution to the image-resident kernel."""
+    return _beats_image(ctypes.byref(geom(*s)), mode)

@@ -57,3 +57,12 @@ def test_a_launch_of_its_own_to_split_weights(s, bf16, want):
                          ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_weights_of_a_forward(s, want):
     assert R.parts_pay(s, 0) == want and R.parts_pay(s, 0, True) == want
+
+
+@pytest.mark.parametrize("s, fwd, bwd", [
+    ((64, 7, 7, 256, 256, 3), False, False), ((52, 7, 7, 256, 256, 3), False, False), ((80, 7, 7, 256, 256, 3), True, True),
+    ((128, 7, 7, 128, 128, 3), False, False), ((40, 8, 8, 256, 256, 3), False, True), ((64, 10, 10, 256, 256, 3), False, True),
+    ((64, 12, 12, 128, 128, 3), True, True), ((40, 7, 7, 512, 512, 3), True, True), ((64, 14, 14, 256, 256, 3), True, True)],
+    ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_small_images_with_bf16_operands(s, fwd, bwd):
+    assert (R.beats_image(s, 0), R.beats_image(s, 1)) == (fwd, bwd)
