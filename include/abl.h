@@ -133,7 +133,6 @@ int abl_forward(void* stream, const abl_shape* shape, int K, uint32_t flags,
  *   dy     [N,Ho,Wo,Cout]   in
  *   W      [R,S,Cin,Cout]   in
  *   dx     [N,H,W,Cin]      out (or accumulated into with ABL_ACCUM_DX).  May alias dy.
- *                           (Apart from dy, it may hold partial sums of dW until it is written.)
  *   dW     [R,S,Cin,Cout]   out: approximate (uses the dequantized A3)
  *   dgamma, dbeta [Cin]     out: dgamma approximate, dbeta exact (Sec. 3.3)
  * flags: ABL_ACCUM_DX, ABL_MATH_BF16. */
@@ -209,7 +208,9 @@ int abl_conv_dgrad(void* stream, const abl_shape* shape, uint32_t flags, const f
                    float* da3);
 /* Eq. 5, gradient to the weights, with A3 rebuilt on the fly from the packed codes
  * (Eq. 10 then Eq. 3); no full-precision copy of the activation is written to memory.
- * scratch: abl_wgrad_scratch_bytes(shape).  flags: ABL_MATH_BF16. */
+ * scratch: abl_wgrad_scratch_bytes(shape).  flags: ABL_MATH_BF16.
+ * (The pixels are summed in as many parts as the scratch holds.  abl_backward and the stack calls have room for more parts of a
+ * 3x3 layer with few channels: their dW can differ from this one's in the last bits, by an fp32 sum in another order.) */
 size_t abl_wgrad_scratch_bytes(const abl_shape* shape);
 int abl_conv_wgrad_packed(void* stream, const abl_shape* shape, int K, uint32_t flags, const void* packed,
                           const void* stats, const float* dy, void* scratch,

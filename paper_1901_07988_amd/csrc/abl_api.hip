@@ -330,11 +330,11 @@ size_t wpart_offset(const abl_shape& s) {
   return up256((size_t)M * s.Cin * sizeof(float)) + up256(bn_partial_bytes(M, s.Cin));
 }
 
-// abl_backward after its checks.  parts (nullable): the weights as the data gradient's kernel reads them.  next: weights for
-// the launch of the apply pass to split.  wroom: bytes for the copies of the weight gradient at their place in the workspace.
+// abl_backward after its checks.  sw: the weights as the data gradient's kernel reads them (out = nullptr: it splits them), still to
+// be split here or (ready) split by an earlier launch.  next: weights for the launch of the apply pass to split.
 int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, const void* packed, const void* stats,
                   const float* dy, const float* W, void* scratch, float* dx, float* dW, float* dgamma, float* dbeta,
-                  const void* parts, const SplitWeights& next, size_t wroom) {
+                  const SplitWeights& sw, bool ready, const SplitWeights& next) {
   const int64_t M = rows_of(*s);
   const size_t act = up256((size_t)M * s->Cin * sizeof(float));
   const size_t redb = up256(bn_partial_bytes(M, s->Cin));
@@ -344,20 +344,23 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   const bool accum = (flags & ABL_ACCUM_DX) != 0;
   const ConvGeom g = geom_of(*s);
-  // Copies of a 3x3 weight gradient that the workspace has no room for go where dx will be, if nothing is read there: the launch
-  // that sums them comes before the one that writes dx.  (64 -> 64 @56x56 N=64, bf16 operands: 85 copies, 170 blocks on 256
-  // units, 50 us; 128 copies, 256 blocks, 38.  In a stack, whose workspace is the largest layer's, they fit there: fp32 86 to
-  // 64 us.)
-  void* wat = wpart;
-  const size_t dx_bytes = (size_t)M * s->Cin * sizeof(float), dy_bytes = (size_t)g.N * g.Ho * g.Wo * g.Cout * sizeof(float);
-  const char *dx_at = reinterpret_cast<const char*>(dx), *dy_at = reinterpret_cast<const char*>(dy);
-  if (K != 32 && !accum && g.R == 3 && dx_bytes > wroom && (dx_at + dx_bytes <= dy_at || dy_at + dy_bytes <= dx_at)) {
-    const int here = split_wgrad_copies(g, K, bf16, wroom);
-    if (here > 0 && split_wgrad_copies(g, K, bf16, dx_bytes) > here) {
-      wat = dx;
-      wroom = dx_bytes;
-    }
-  }
+  // A 3x3 weight gradient whose copies do not fill the chip in their own room goes first, while the place of dA3 is free to hold
+  // more of them, and is summed before dA3 comes, by the launch that splits the weights where there is one: the rounding of dW
+  // depends on the layer's shape alone.  (64 -> 64 @56x56 N=64: 85 copies, 170 blocks on 256 units, 86 us, 50 with bf16 operands;
+  // 128 copies, 256 blocks, 64 and 38.  An eighth more at least: the sum is not in the launch of the Eq. 7 sums then.)
+  const size_t wroom = wgrad_partial_bytes(*s);
+  const int few = K != 32 && g.R == 3 && act > wroom ? split_wgrad_copies(g, K, bf16, wroom) : 0;
+  const bool w_first = few > 0 && 8 * split_wgrad_copies(g, K, bf16, act) >= 9 * few;
+  DwSum first{nullptr, 0, 0, nullptr};
+  if (w_first)
+    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, da3, dW, false, &first, act)) return e;
+  if (w_first || !ready)
+    if (int e = launch_split_weights(st, ready ? SplitWeights{} : sw, &first)) return e;
+  const void* const parts = sw.out;
+  auto weight_gradient = [&](DwSum* sum) -> int {
+    sum->copies = 0;
+    return w_first ? ABL_OK : launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, K == 32, sum);
+  };
   // Stride-1 convolutions with a filter larger than 1x1 take the Eq. 6-7 sums in the epilogue of
   // the dgrad kernel (dA3 is still in registers there), which saves the reduce pass over dA3.
   // bf16 operands with a dgrad on the 32-deep bf16 matrix instruction: the separate stages
@@ -375,7 +378,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   if (const int nb = K != 32 && !bf16 ? split_conv_blocks(g, 1, false, true) : 0) {
     if (int e = launch_split_dgrad_reduce(st, g, K, false, dy, W, packed, stats, da3, static_cast<double*>(red), parts)) return e;
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
+    if (int e = weight_gradient(&dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nb, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -383,7 +386,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   if (K != 32 && !bf16 && image_f32_supported(g, 1)) {
     if (int e = launch_image_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red))) return e;
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
+    if (int e = weight_gradient(&dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, g.N, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -391,7 +394,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   if (const int nr = (K != 32 && bf16_gemm) ? bf16_dgrad_reduce_rows(g) : 0) {
     if (int e = launch_bf16_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red), parts)) return e;
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
+    if (int e = weight_gradient(&dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, nr, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -401,7 +404,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
       return e;
     // split partial copies of dW are summed by the launch that finishes the Eq. 7 sums
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
+    if (int e = weight_gradient(&dwsum)) return e;
     return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, tiles, dx, dgamma, dbeta,
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -413,13 +416,13 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
       return e;
     if (rows > 0) {
       DwSum dwsum;
-      if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
+      if (int e = weight_gradient(&dwsum)) return e;
       return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, rows, dx, dgamma, dbeta,
                                   dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
     }
     // (long contractions: the kernel computed dA3 only)
     DwSum dwsum;
-    if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wat, dW, false, &dwsum, wroom)) return e;
+    if (int e = weight_gradient(&dwsum)) return e;
     return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta,
                          dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
@@ -433,7 +436,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   if (int e = launch_conv_dgrad(st, *s, bf16, dy, W, da3)) return e;
   // exact storage keeps the pre-ReLU A2: the weight gradient applies Eq. 3 on the way in
   DwSum dwsum;
-  if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, K == 32, &dwsum)) return e;
+  if (int e = weight_gradient(&dwsum)) return e;
   return launch_bn_bwd(st, packed, stats, da3, M, s->Cin, K, accum, red, dx, dgamma, dbeta,
                        dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
 }
@@ -458,10 +461,8 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
   SplitWeights sw{};
   if (const int np = backward_parts(geom_of(*s), K, (flags & ABL_MATH_BF16) != 0, true))
     sw = weights_to_split(*s, 1, np, W, static_cast<char*>(scratch) + wpart_offset(*s), wgrad_partial_bytes(*s));
-  if (sw.out != nullptr)
-    if (int e = launch_split_weights((hipStream_t)stream, sw)) return e;
-  return backward_impl((hipStream_t)stream, s, K, flags, packed, stats, dy, W, scratch, dx, dW, dgamma, dbeta, sw.out,
-                       SplitWeights{}, wgrad_partial_bytes(*s));
+  return backward_impl((hipStream_t)stream, s, K, flags, packed, stats, dy, W, scratch, dx, dW, dgamma, dbeta, sw, false,
+                       SplitWeights{});
 }
 
 // ---- the layer with a leaky ReLU (Sec. 3.4) ---------------------------------------------------
@@ -905,8 +906,6 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
     return weights_to_split(l.shape, 1, np, l.W, lscratch + (from < lbytes ? from : 0), from < lbytes ? lbytes - from : 0);
   };
   SplitWeights sw = parts_of(L - 1, 0);
-  if (sw.out != nullptr)
-    if (int e = launch_split_weights((hipStream_t)stream, sw)) return e;
   for (int i = L - 1; i >= 0; --i) {
     const abl_layer& l = layers[i];
     const GroupInfo gi = group_info(layers, L, skip_every, i);
@@ -922,7 +921,7 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
     if (int e = trace_copy((hipStream_t)stream, trace, i, dy, out_floats)) return e;
     const SplitWeights next = i > 0 ? parts_of(i - 1, wpart_offset(l.shape)) : SplitWeights{};
     if (int e = backward_impl((hipStream_t)stream, &l.shape, K, f, l.packed, l.stats, dy, l.W, lscratch, dx, l.dW, l.dgamma,
-                              l.dbeta, sw.out, next, lbytes - wpart_offset(l.shape)))
+                              l.dbeta, sw, i < L - 1, next))
       return e;
     sw = next;
   }

@@ -40,7 +40,9 @@ struct SplitWeights {
   int taps, Cin, Cout;
   __host__ __device__ int64_t items() const { return out != nullptr ? (int64_t)taps * Cin * Cout / 8 : 0; }
 };
-int launch_split_weights(hipStream_t st, const SplitWeights& sw);
+struct DwSum;
+// dwsum (nullable): copies of a weight gradient to be summed by the same launch.
+int launch_split_weights(hipStream_t st, const SplitWeights& sw, const DwSum* dwsum = nullptr);
 
 // ---- batch-norm / quantizer kernels (bn_kernels.hip) ----
 // sw / next: weights to be split by the launch as well, in blocks of their own.

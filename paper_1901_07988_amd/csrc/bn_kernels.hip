@@ -514,9 +514,27 @@ __global__ __launch_bounds__(kFinThreads) void bwd_finalize_kernel(const double*
   means[C + c] = (float)(gm * t[1] / (double)M);
 }
 
+// 64 outputs of a weight gradient from its copies: 16 interleaved parts of them, and a binary tree over the parts.
+__device__ inline void sum_of_copies(const float* __restrict__ wpartial, int ncopies, int64_t n, int block,
+                                     float* __restrict__ dw, float (*sw)[64]) {
+  const int o = threadIdx.x & 63, part = threadIdx.x >> 6;
+  const int64_t i = (int64_t)block * 64 + o;
+  float a = 0.f;
+  if (i < n) {
+#pragma unroll 8
+    for (int k = part; k < ncopies; k += 16) a += wpartial[(int64_t)k * n + i];
+  }
+  sw[part][o] = a;
+  __syncthreads();
+  for (int h = 8; h >= 1; h >>= 1) {
+    if (part < h) sw[part][o] += sw[part + h][o];
+    __syncthreads();
+  }
+  if (part == 0 && i < n) dw[i] = sw[0][o];
+}
+
 // The same second pass (blocks 0 .. nfin-1) and, in the other blocks of the same launch, the sum
-// of `ncopies` partial copies of a weight gradient of n floats (64 outputs x 16 interleaved parts
-// per block, a binary tree over the parts): two small dependent-free jobs that follow the conv
+// of `ncopies` partial copies of a weight gradient of n floats: two small dependent-free jobs that follow the conv
 // backward kernel share one launch.
 __global__ __launch_bounds__(kFinThreads) void bwd_finalize_dwsum_kernel(const double* __restrict__ partial, int nb,
                                                                       int64_t M, int C,
@@ -554,21 +572,7 @@ __global__ __launch_bounds__(kFinThreads) void bwd_finalize_dwsum_kernel(const d
     means[C + c] = (float)(gm * t[1] / (double)M);
     return;
   }
-  float(*sw)[64] = reinterpret_cast<float(*)[64]>(&sm[0][0]);  // [16][64]
-  const int o = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const int64_t i = (int64_t)(blockIdx.x - nfin) * 64 + o;
-  float a = 0.f;
-  if (i < n) {
-#pragma unroll 8
-    for (int k = part; k < ncopies; k += 16) a += wpartial[(int64_t)k * n + i];
-  }
-  sw[part][o] = a;
-  __syncthreads();
-  for (int h = 8; h >= 1; h >>= 1) {
-    if (part < h) sw[part][o] += sw[part + h][o];
-    __syncthreads();
-  }
-  if (part == 0 && i < n) dw[i] = sw[0][o];
+  sum_of_copies(wpartial, ncopies, n, (int)blockIdx.x - nfin, dw, reinterpret_cast<float(*)[64]>(&sm[0][0]));
 }
 
 // SPLIT: rows of blocks from gridY on split the next layer's weights (72 registers become 76 with that code).
@@ -786,6 +790,19 @@ __global__ __launch_bounds__(kThreads) void split_weights_kernel(SplitWeights sw
   if (it < sw.items()) split_weights_item(sw, it);
 }
 
+// The same (blocks 0 .. nsplit-1) and the sum of a weight gradient's copies: nothing between the two, one launch.
+__global__ __launch_bounds__(kFinThreads) void split_weights_dwsum_kernel(SplitWeights sw, int nsplit,
+                                                                       const float* __restrict__ wpartial, int ncopies,
+                                                                       int64_t n, float* __restrict__ dw) {
+  __shared__ float sm[16][64];
+  if ((int)blockIdx.x < nsplit) {
+    const int64_t it = (int64_t)blockIdx.x * kFinThreads + threadIdx.x;
+    if (it < sw.items()) split_weights_item(sw, it);
+    return;
+  }
+  sum_of_copies(wpartial, ncopies, n, (int)blockIdx.x - nsplit, dw, sm);
+}
+
 }  // namespace
 
 // Room for kMaxPartialBlocks partial rows (the reduce kernels of this file use at most that
@@ -800,7 +817,14 @@ size_t bn_partial_bytes(int64_t M, int C) {
 
 size_t bn_means_offset(int C) { return (size_t)kMaxPartialBlocks * 2 * (size_t)C * sizeof(double); }
 
-int launch_split_weights(hipStream_t st, const SplitWeights& sw) {
+int launch_split_weights(hipStream_t st, const SplitWeights& sw, const DwSum* dwsum) {
+  if (dwsum != nullptr && dwsum->copies > 0) {
+    const int nsplit = (int)((sw.items() + kFinThreads - 1) / kFinThreads);
+    split_weights_dwsum_kernel<<<nsplit + (unsigned)((dwsum->n + 63) / 64), kFinThreads, 0, st>>>(
+        sw, nsplit, dwsum->partial, dwsum->copies, dwsum->n, dwsum->dw);
+    return hip_status();
+  }
+  if (sw.items() == 0) return ABL_OK;
   split_weights_kernel<<<grid_of((sw.items() + kThreads - 1) / kThreads), kThreads, 0, st>>>(sw);
   return hip_status();
 }

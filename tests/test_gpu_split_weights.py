@@ -92,37 +92,67 @@ def test_stack_equals_layers(flags):
     for s, (s9, w), e in reversed(list(zip(shapes, params, descs))):
         dx, dw, dg, db = f32(*s[:4]), torch.empty_like(w), f32(s[3]), f32(s[3])
         B.abl_backward(s9, K, e["packed"], e["stats"], d, w, raw(B.abl_scratch_bytes(s9, K)), dx, dw, dg, db, flags=flags)
-        # (the stack's workspace has room for more copies of a weight gradient: its sums over the pixels fall into other parts)
-        assert float((dw.double() - e["dW"].double()).norm() / e["dW"].double().norm()) < 2e-6
-        assert torch.equal(dg, e["dgamma"]) and torch.equal(db, e["dbeta"])
+        assert torch.equal(dw, e["dW"].view(dw.shape)) and torch.equal(dg, e["dgamma"]) and torch.equal(db, e["dbeta"])
         d = dx
     assert torch.equal(d.view(-1), S[:x.numel()])
 
 
-@pytest.mark.parametrize("where", ["apart", "overlapping", "accumulated"])
 @pytest.mark.parametrize("flags", [0, B.ABL_MATH_BF16], ids=["fp32", "bf16"])
-def test_copies_of_dw_in_dx(flags, where):
-    """A layer whose workspace holds 85 copies of dW where 128 blocks would share its pixels: they go where dx will be, but not
-    where dy or a gradient to be added to is."""
-    s, K = (64, 56, 56, 64, 64, 3), 4
+def test_dw_depends_on_the_layer_alone(flags):
+    """A layer whose own room holds 85 copies of dW where 128 blocks would share its pixels: the same bits of dW wherever dx lies,
+    added to or not, and in a stack with a shortcut and larger layers."""
+    s, K, N = (64, 56, 56, 64, 64, 3), 4, 64 * 56 * 56 * 64
     s9 = shape9(s)
     x, w, gamma, beta, dy = draw(s, 31)
-    packed, stats, scratch = raw(B.abl_packed_bytes(s9, K)), raw(B.abl_stats_bytes(s9)), raw(B.abl_scratch_bytes(s9, K))
-    B.abl_forward(s9, K, x, w, gamma, beta, None, scratch, f32(*dy.shape), packed, stats, flags=flags)
-    dw_ref = f32(*w.shape)
-    B.abl_conv_wgrad_packed(s9, K, packed, stats, dy, raw(B.abl_wgrad_scratch_bytes(s9)), dw_ref, flags=flags)
-    n = dy.numel()
-    both = torch.empty(2 * n, device="cuda")
-    at = n // 2 if where == "overlapping" else n
-    dy2 = both[at:at + n].view(dy.shape)
-    dy2.copy_(dy)
-    dx, dw, dg, db = (both[:n] if where == "overlapping" else torch.ones(n, device="cuda")).view(x.shape), f32(*w.shape), f32(64), f32(64)
-    acc = where == "accumulated"
-    if where == "overlapping":   # dy is dead once both contractions have run
-        B.abl_backward(s9, K, packed, stats, dy2, w, scratch, dx, dw, dg, db, flags=flags)
-    else:
-        B.abl_backward(s9, K, packed, stats, dy2, w, scratch, dx, dw, dg, db, flags=flags | (B.ABL_ACCUM_DX if acc else 0))
-    assert float((dw.double() - dw_ref.double()).norm() / dw_ref.double().norm()) < 2e-6
-    plain, dw2, dg2, db2 = f32(*x.shape), f32(*w.shape), f32(64), f32(64)
-    B.abl_backward(s9, K, packed, stats, dy, w, scratch, plain, dw2, dg2, db2, flags=flags)
-    assert torch.equal(dg, dg2) and torch.equal(dx, 1.0 + plain if acc else plain)
+
+    def layer():
+        return dict(shape=s9, W=w, gamma=gamma, beta=beta, packed=raw(B.abl_packed_bytes(s9, K)), stats=raw(B.abl_stats_bytes(s9)),
+                    dW=f32(*w.shape), dgamma=f32(64), dbeta=f32(64))
+
+    one = layer()
+    scratch = raw(B.abl_scratch_bytes(s9, K))
+    B.abl_forward(s9, K, x, w, gamma, beta, None, scratch, f32(*dy.shape), one["packed"], one["stats"], flags=flags)
+
+    def backward(dy, dx, more=0):
+        dw, dg, db = f32(*w.shape), f32(64), f32(64)
+        scratch.fill_(255)
+        B.abl_backward(s9, K, one["packed"], one["stats"], dy, w, scratch, dx, dw, dg, db, flags=flags | more)
+        return dx, dw, dg, db
+
+    dx, dw, dg, db = backward(dy, torch.full_like(x, float("nan")))
+    stage = f32(*w.shape)
+    B.abl_conv_wgrad_packed(s9, K, one["packed"], one["stats"], dy, raw(B.abl_wgrad_scratch_bytes(s9)), stage, flags=flags)
+    assert float((dw.double() - stage.double()).norm() / stage.double().norm()) < 2e-6   # (sums over the pixels in other parts)
+    for at in (0, N // 2):   # dx over all of dy and over half of it; dy is dead once both contractions have run
+        both = torch.empty(2 * N, device="cuda")
+        dy2 = both[at:at + N].view(dy.shape)
+        dy2.copy_(dy)
+        for a, b in zip(backward(dy2, both[:N].view(x.shape)), (dx, dw, dg, db)):
+            assert torch.equal(a, b)
+    acc = backward(dy, torch.ones_like(x), B.ABL_ACCUM_DX)
+    assert torch.equal(acc[0], 1.0 + dx) and all(torch.equal(a, b) for a, b in zip(acc[1:], (dw, dg, db)))
+
+    # a pair of such layers with a shortcut, then one that widens: the last layer's incoming gradient is `top`
+    wide = (64, 56, 56, 64, 128, 1)
+    _, ww, wg, wb, top = draw(wide, 32)
+    third = dict(shape=shape9(wide), W=ww, gamma=wg, beta=wb, packed=raw(B.abl_packed_bytes(shape9(wide), K)),
+                 stats=raw(B.abl_stats_bytes(shape9(wide))), dW=f32(*ww.shape), dgamma=f32(64), dbeta=f32(64))
+    descs = [layer(), layer(), third]
+    layers = B.make_layers(descs)
+    nb = B.abl_stack_buffer_bytes(layers) // 4
+    S, T, ws = f32(nb), f32(nb), raw(B.abl_stack_scratch_bytes(layers, K))
+    S[:N] = x.view(-1)
+    B.abl_stack_forward(layers, K, 2, S, T, ws, flags=flags)
+    S[:top.numel()] = top.view(-1)
+    ws.fill_(255)
+    B.abl_stack_backward(layers, K, 2, S, T, ws, flags=flags)
+    own = raw(B.abl_scratch_bytes(shape9(wide), K))
+    d, w3, g3, b3 = f32(*x.shape), f32(*ww.shape), f32(64), f32(64)
+    B.abl_backward(shape9(wide), K, third["packed"], third["stats"], top, ww, own, d, w3, g3, b3, flags=flags)
+    assert torch.equal(w3.view(-1), third["dW"].view(-1))
+    skip = d
+    for e in (descs[1], descs[0]):
+        one = e
+        d, w3, g3, b3 = backward(d, torch.empty_like(x))
+        assert torch.equal(w3, e["dW"]) and torch.equal(g3, e["dgamma"]) and torch.equal(b3, e["dbeta"])
+    assert torch.equal(S[:N], (skip + d).view(-1))
