@@ -245,7 +245,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     }
   };
   // a tile: pixels p0 .. p_end - 1; its patch starts a row above the first of them, in rows of images padded to H + 2
-  auto first_pixel = [&](int t) __attribute__((always_inline)) { 
+  auto first_pixel = [&](int t) __attribute__((always_inline)) {
     const int q = tl.per_unit.of(t);
     return q * tl.unit + (t - q * tl.ntr) * tl.run;
   };
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int i = 0; i < MT; ++i) v[j][i] = NP == 3 ? kDown * (hi[j][i] + lo[j][i]) : hi[j][i];
-      unsigned char* const cbuf = smem + exchange_bytes(NT, KS);
+    unsigned char* const cbuf = smem + exchange_bytes(NT, KS);
     if (KS == 2 || EPI > 1) __syncthreads();      // every wave has finished reading the patch
     if constexpr (EPI > 1) {
 #pragma unroll
@@ -879,14 +879,16 @@ Tiling with_divisors(const ConvGeom& g, Tiling t) {
 }
 
 template <int MODE, int NP, bool PRE, int TAPS, int NT, int KS, int CPP, int SU>
-int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts, const float* skip,
-               float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
+int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts,
+               const float* skip, float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
   const int Ng = MODE == 0 ? g.Cout : g.Cin;
   const unsigned grid = (unsigned)((p.tl.gm + 7) / 8 * 8 * (Ng / p.bn));
-  auto kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 0, NP, PRE>;
+  // (weights are split once for gradients with sums only)
+  auto kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, MODE == 1 && PRE ? 4 : 0, NP, PRE>;
   if constexpr (MODE == 0) {
     if (epi == 1) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 1, NP, PRE>;
   } else {
+    if (PRE && epi == 0) return ABL_ERR_ARG;
     if (epi == 4) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 4, NP, PRE>;
     if (epi == 8) kern = split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8, NP, PRE>;
     if constexpr (TAPS == 1 && KS == 1 && NP == 3 && !PRE)
@@ -895,13 +897,14 @@ int launch_cfg(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in
                         : split_conv_kernel<MODE, TAPS, NT, KS, CPP, SU, 8, NP, PRE, 0, true>;
   }
   if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
-  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, static_cast<const uint4*>(parts), skip, out, sums, codes, stats, g, with_divisors(g, p.tl), nullptr, 0);
+  kern<<<grid, 64 * WN * KS, p.lds, st>>>(in, w, static_cast<const uint4*>(parts), skip, out, sums, codes, stats, g,
+                                          with_divisors(g, p.tl), nullptr, 0);
   return hip_status();
 }
 
 template <int MODE, int NP, bool PRE>
-int launch_as(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts, const float* skip,
-           float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
+int launch_as(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts,
+              const float* skip, float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
   auto run = [&](auto f) { return f(st, g, p, in, w, parts, skip, out, sums, codes, stats, epi); };
   if (g.R == 3) {
     if (p.ks == 2) return run(p.nt == 2 ? launch_cfg<MODE, NP, PRE, 9, 2, 2, 1, 3> : launch_cfg<MODE, NP, PRE, 9, 1, 2, 1, 3>);
@@ -913,8 +916,8 @@ int launch_as(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in,
 }
 
 template <int MODE, int NP>
-int launch(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts, const float* skip,
-           float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
+int launch(hipStream_t st, const ConvGeom& g, const Plan& p, const float* in, const float* w, const void* parts,
+           const float* skip, float* out, double* sums, const uint8_t* codes, const float* stats, int epi) {
   return parts != nullptr ? launch_as<MODE, NP, true>(st, g, p, in, w, parts, skip, out, sums, codes, stats, epi)
                           : launch_as<MODE, NP, false>(st, g, p, in, w, parts, skip, out, sums, codes, stats, epi);
 }
@@ -927,7 +930,8 @@ int launch_fused(hipStream_t st, const ConvGeom& g, const Plan& p, const float* 
   auto kern = sums != nullptr ? split_conv_kernel<0, 9, 1, KS, 1, SU, 1, 3, PRE, FUSE>
                               : split_conv_kernel<0, 9, 1, KS, 1, SU, 0, 3, PRE, FUSE>;
   if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
-  kern<<<grid, 64 * WN * KS, p.lds, st>>>(x, w, static_cast<const uint4*>(parts), skip, y, sums, nullptr, stats, g, with_divisors(g, p.tl), packed, (int)((raw + 127) / 128 * 128 - raw));
+  kern<<<grid, 64 * WN * KS, p.lds, st>>>(x, w, static_cast<const uint4*>(parts), skip, y, sums, nullptr, stats, g,
+                                          with_divisors(g, p.tl), packed, (int)((raw + 127) / 128 * 128 - raw));
   return hip_status();
 }
 
@@ -1015,8 +1019,8 @@ int launch_split_conv(hipStream_t st, const ConvGeom& g, int mode, bool bf16, co
   if (mode == 0)
     return bf16 ? launch<0, 1>(st, g, p, in, w, parts, skip, out, sums, nullptr, nullptr, epi)
                 : launch<0, 3>(st, g, p, in, w, parts, skip, out, sums, nullptr, nullptr, epi);
-  return bf16 ? launch<1, 1>(st, g, p, in, w, parts, nullptr, out, nullptr, nullptr, nullptr, 0)
-              : launch<1, 3>(st, g, p, in, w, parts, nullptr, out, nullptr, nullptr, nullptr, 0);
+  return bf16 ? launch<1, 1>(st, g, p, in, w, nullptr, nullptr, out, nullptr, nullptr, nullptr, 0)
+              : launch<1, 3>(st, g, p, in, w, nullptr, nullptr, out, nullptr, nullptr, nullptr, 0);
 }
 
 int split_forward3(const ConvGeom& g, int* rows) {
