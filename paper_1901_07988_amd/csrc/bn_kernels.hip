@@ -15,6 +15,8 @@
 // quantizer arithmetic is written one rounded operation at a time and this file is
 // compiled with floating-point contraction off.
 
+#include <type_traits>
+
 #include "abl_internal.h"
 
 #pragma clang fp contract(off)
@@ -273,19 +275,22 @@ __device__ inline void reduce_partials(const double* __restrict__ partial, int n
 }
 
 // Eq. 1 statistics, pass 2, and the per-channel constants of Eq. 9/10.
-// SPLIT: blocks from nfin on split weights instead (a kernel of its own: the code costs registers and instruction fetches).
-template <bool SPLIT>
+// SW = SplitWeights: blocks from nfin on split weights instead (a kernel of its own: the code costs registers and instruction
+// fetches); NoWeights: nothing else to do.
+struct NoWeights {};
+template <class SW>
 __global__ __launch_bounds__(kFinThreads) void stats_finalize_kernel(const double* __restrict__ partial, int nb,
                                                                   const float* __restrict__ x, int64_t M,
                                                                   int C, const float* __restrict__ gamma,
                                                                   const float* __restrict__ beta, int K,
-                                                                  float* __restrict__ stats, int nfin,
-                                                                  SplitWeights sw) {
+                                                                  float* __restrict__ stats, int nfin, SW sw) {
   __shared__ double sm[32][32];
-  if (SPLIT && (int)blockIdx.x >= nfin) {
-    const int64_t it = (int64_t)(blockIdx.x - nfin) * kFinThreads + threadIdx.x;
-    if (it < sw.items()) split_weights_item(sw, it);
-    return;
+  if constexpr (std::is_same<SW, SplitWeights>::value) {
+    if ((int)blockIdx.x >= nfin) {
+      const int64_t it = (int64_t)(blockIdx.x - nfin) * kFinThreads + threadIdx.x;
+      if (it < sw.items()) split_weights_item(sw, it);
+      return;
+    }
   }
   const int c = blockIdx.x * 16 + (threadIdx.x & 15);
   double t[2];
@@ -575,19 +580,21 @@ __global__ __launch_bounds__(kFinThreads) void bwd_finalize_dwsum_kernel(const d
   sum_of_copies(wpartial, ncopies, n, (int)blockIdx.x - nfin, dw, reinterpret_cast<float(*)[64]>(&sm[0][0]));
 }
 
-// SPLIT: rows of blocks from gridY on split the next layer's weights (72 registers become 76 with that code).
 // Backward, pass 2 (Eq. 8): dx = rstd * (dA1 - Mean(dA1) - A1~ * Mean(A1~ * dA1)).
-template <int K, int VEC, bool ACCUM, bool STREAM, bool SPLIT>
+// SW = SplitWeights: rows of blocks from gridY on split the next layer's weights (72 registers become 76 with that code).
+template <int K, int VEC, bool ACCUM, bool STREAM, class SW>
 __global__ __launch_bounds__(kThreads) void bwd_apply_kernel(const void* __restrict__ packed,
                                                              const float* da3, int64_t M, int C, RowGeom g,
                                                              const float* __restrict__ stats,
                                                              const float* __restrict__ means, float* dx,
-                                                             float slope, SplitWeights sw) {
+                                                             float slope, SW sw) {
   using S = Stored<K, VEC>;
-  if (SPLIT && (int)blockIdx.y >= g.gridY) {
-    const int64_t it = ((int64_t)(blockIdx.y - g.gridY) * gridDim.x + blockIdx.x) * kThreads + threadIdx.x;
-    if (it < sw.items()) split_weights_item(sw, it);
-    return;
+  if constexpr (std::is_same<SW, SplitWeights>::value) {
+    if ((int)blockIdx.y >= g.gridY) {
+      const int64_t it = ((int64_t)(blockIdx.y - g.gridY) * gridDim.x + blockIdx.x) * kThreads + threadIdx.x;
+      if (it < sw.items()) split_weights_item(sw, it);
+      return;
+    }
   }
   const ThreadPos p = thread_pos<VEC>(g);
   if (!p.active) return;
@@ -847,9 +854,11 @@ int launch_bn_stats_finalize(hipStream_t st, const double* partial, int nb, cons
                              int C, const float* gamma, const float* beta, int K, void* stats, const SplitWeights& sw) {
   const int nfin = (C + 15) / 16;
   const unsigned extra = (unsigned)((sw.items() + kFinThreads - 1) / kFinThreads);
-  auto kern = extra > 0 ? stats_finalize_kernel<true> : stats_finalize_kernel<false>;
-  kern<<<nfin + extra, kFinThreads, 0, st>>>(partial, nb, shift_row, M, C, gamma, beta, K,
-                                                             static_cast<float*>(stats), nfin, sw);
+  float* const out = static_cast<float*>(stats);
+  if (extra > 0)
+    stats_finalize_kernel<<<nfin + extra, kFinThreads, 0, st>>>(partial, nb, shift_row, M, C, gamma, beta, K, out, nfin, sw);
+  else
+    stats_finalize_kernel<<<nfin, kFinThreads, 0, st>>>(partial, nb, shift_row, M, C, gamma, beta, K, out, nfin, NoWeights{});
   return hip_status();
 }
 
@@ -1000,31 +1009,34 @@ int launch_bn_bwd_finish(hipStream_t st, const void* packed, const void* stats, 
   const RowGeom ga = make_geom(M, C, vec, false);
   // the next layer's weights in rows of blocks of their own (a grid has 65535 rows: huge ones in a launch of their own)
   const int64_t rows = (next.items() + (int64_t)kThreads * ga.gridX - 1) / ((int64_t)kThreads * ga.gridX);
-  const bool ride = rows + ga.gridY <= 65535;
-  if (!ride)
+  const bool ride = K != 32 && rows > 0 && rows + ga.gridY <= 65535;
+  if (rows > 0 && !ride)
     if (int e = launch_split_weights(st, next)) return e;
-  const SplitWeights sw = ride ? next : SplitWeights{};
   const dim3 grid(ga.gridX, ga.gridY + (ride ? (unsigned)rows : 0u));
   const bool stream = M * C * (int64_t)sizeof(float) >= kStreamBytes;
-#define ABL_APPLY1(KK, VV, AA)                                                                                         \
-  do {                                                                                                                 \
-    auto kern = stream ? (rows > 0 && ride ? bwd_apply_kernel<KK, VV, AA, true, true> : bwd_apply_kernel<KK, VV, AA, true, false>)      \
-                       : (rows > 0 && ride ? bwd_apply_kernel<KK, VV, AA, false, true> : bwd_apply_kernel<KK, VV, AA, false, false>);   \
-    kern<<<grid, kThreads, 0, st>>>(packed, da3, M, C, ga, sp, means, dx, slope, sw);                                  \
-  } while (0)
-#define ABL_APPLY(KK, VV)             \
-  do {                                \
-    if (accum) ABL_APPLY1(KK, VV, true); \
-    else ABL_APPLY1(KK, VV, false);   \
-  } while (0)
-  if (K == 4) ABL_APPLY(4, 4);
-  else if (K == 8) ABL_APPLY(8, 4);
-  else ABL_APPLY(32, 4);
-#undef ABL_APPLY1
+  auto apply = [&](auto accum_c, auto sw) {
+    constexpr bool A = decltype(accum_c)::value;
+    using SW = decltype(sw);
+#define ABL_APPLY(KK)                                                                                              \
+  if (stream) bwd_apply_kernel<KK, 4, A, true, SW><<<grid, kThreads, 0, st>>>(packed, da3, M, C, ga, sp, means, dx, slope, sw); \
+  else bwd_apply_kernel<KK, 4, A, false, SW><<<grid, kThreads, 0, st>>>(packed, da3, M, C, ga, sp, means, dx, slope, sw)
+    if constexpr (std::is_same<SW, NoWeights>::value) {   // (exact storage has no split gradient to split weights for)
+      if (K == 32) {
+        ABL_APPLY(32);
+        return;
+      }
+    }
+    if (K == 4) {
+      ABL_APPLY(4);
+    } else {
+      ABL_APPLY(8);
+    }
 #undef ABL_APPLY
+  };
+  if (ride) accum ? apply(std::true_type{}, next) : apply(std::false_type{}, next);
+  else accum ? apply(std::true_type{}, NoWeights{}) : apply(std::false_type{}, NoWeights{});
   return hip_status();
 }
-
 
 // ------------------------------------------------------------------------------------------
 // SGD with momentum and weight decay (Sec. 4), in place; four elements per lane, scalar tail.
