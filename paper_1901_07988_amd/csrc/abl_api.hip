@@ -331,10 +331,11 @@ size_t wpart_offset(const abl_shape& s) {
 }
 
 // abl_backward after its checks.  sw: the weights as the data gradient's kernel reads them (out = nullptr: it splits them), still to
-// be split here or (ready) split by an earlier launch.  next: weights for the launch of the apply pass to split.
+// be split here or (ready) split by an earlier launch.  next: weights for the launch of the apply pass to split.  wroom: bytes at the
+// place of the weight gradient's copies.
 int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, const void* packed, const void* stats,
                   const float* dy, const float* W, void* scratch, float* dx, float* dW, float* dgamma, float* dbeta,
-                  const SplitWeights& sw, bool ready, const SplitWeights& next) {
+                  const SplitWeights& sw, bool ready, const SplitWeights& next, size_t wroom) {
   const int64_t M = rows_of(*s);
   const size_t act = up256((size_t)M * s->Cin * sizeof(float));
   const size_t redb = up256(bn_partial_bytes(M, s->Cin));
@@ -344,13 +345,16 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   const bool accum = (flags & ABL_ACCUM_DX) != 0;
   const ConvGeom g = geom_of(*s);
-  // A 3x3 weight gradient whose copies do not fill the chip in their own room goes first, while the place of dA3 is free to hold
-  // more of them, and is summed before dA3 comes, by the launch that splits the weights where there is one: the rounding of dW
-  // depends on the layer's shape alone.  (64 -> 64 @56x56 N=64: 85 copies, 170 blocks on 256 units, 86 us, 50 with bf16 operands;
-  // 128 copies, 256 blocks, 64 and 38.  An eighth more at least: the sum is not in the launch of the Eq. 7 sums then.)
-  const size_t wroom = wgrad_partial_bytes(*s);
-  const int few = K != 32 && g.R == 3 && act > wroom ? split_wgrad_copies(g, K, bf16, wroom) : 0;
-  const bool w_first = few > 0 && 8 * split_wgrad_copies(g, K, bf16, act) >= 9 * few;
+  // A 3x3 weight gradient whose copies do not fill the chip in the layer's own room makes as many as the place of dA3 holds: there,
+  // before dA3 comes, summed by the launch that splits the weights where there is one - or behind dA3 as always, where a stack's
+  // workspace has the room.  How many they are, and with them the rounding of dW, depends on the layer's shape alone.  (64 -> 64
+  // @56x56 N=64: 85 copies, 170 blocks on 256 units, 86 us, 50 with bf16 operands; 128 copies, 256 blocks, 64 and 38.  An eighth
+  // more at least, for a sum that may take a launch of its own.)
+  const size_t own = wgrad_partial_bytes(*s);
+  const int few = K != 32 && g.R == 3 && act > own ? split_wgrad_copies(g, K, bf16, own) : 0;
+  const int more = few > 0 ? split_wgrad_copies(g, K, bf16, act) : 0;
+  const size_t room = few > 0 && 8 * more >= 9 * few ? act : own;
+  const bool w_first = room > own && wroom < (size_t)more * 9 * s->Cin * s->Cout * sizeof(float);
   DwSum first{nullptr, 0, 0, nullptr};
   if (w_first)
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, da3, dW, false, &first, act)) return e;
@@ -359,7 +363,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   const void* const parts = sw.out;
   auto weight_gradient = [&](DwSum* sum) -> int {
     sum->copies = 0;
-    return w_first ? ABL_OK : launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, K == 32, sum);
+    return w_first ? ABL_OK : launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, wpart, dW, K == 32, sum, room);
   };
   // Stride-1 convolutions with a filter larger than 1x1 take the Eq. 6-7 sums in the epilogue of
   // the dgrad kernel (dA3 is still in registers there), which saves the reduce pass over dA3.
@@ -462,7 +466,7 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
   if (const int np = backward_parts(geom_of(*s), K, (flags & ABL_MATH_BF16) != 0, true))
     sw = weights_to_split(*s, 1, np, W, static_cast<char*>(scratch) + wpart_offset(*s), wgrad_partial_bytes(*s));
   return backward_impl((hipStream_t)stream, s, K, flags, packed, stats, dy, W, scratch, dx, dW, dgamma, dbeta, sw, false,
-                       SplitWeights{});
+                       SplitWeights{}, wgrad_partial_bytes(*s));
 }
 
 // ---- the layer with a leaky ReLU (Sec. 3.4) ---------------------------------------------------
@@ -921,7 +925,7 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
     if (int e = trace_copy((hipStream_t)stream, trace, i, dy, out_floats)) return e;
     const SplitWeights next = i > 0 ? parts_of(i - 1, wpart_offset(l.shape)) : SplitWeights{};
     if (int e = backward_impl((hipStream_t)stream, &l.shape, K, f, l.packed, l.stats, dy, l.W, lscratch, dx, l.dW, l.dgamma,
-                              l.dbeta, sw, i < L - 1, next))
+                              l.dbeta, sw, i < L - 1, next, lbytes - wpart_offset(l.shape)))
       return e;
     sw = next;
   }

@@ -519,9 +519,23 @@ __global__ __launch_bounds__(kFinThreads) void bwd_finalize_kernel(const double*
   means[C + c] = (float)(gm * t[1] / (double)M);
 }
 
-// 64 outputs of a weight gradient from its copies: 16 interleaved parts of them, and a binary tree over the parts.
-__device__ inline void sum_of_copies(const float* __restrict__ wpartial, int ncopies, int64_t n, int block,
+// A block's outputs of a weight gradient from its copies.  Many small copies: 64 outputs, 16 interleaved parts of the copies and a
+// binary tree over the parts.  straight - large weight tensors in few copies: four consecutive outputs per thread (n is a
+// multiple of 4 then), the copies added in order.
+__device__ inline void sum_of_copies(const float* __restrict__ wpartial, int ncopies, int64_t n, int straight, int block,
                                      float* __restrict__ dw, float (*sw)[64]) {
+  if (straight != 0) {
+    const int64_t i = 4 * ((int64_t)block * kFinThreads + threadIdx.x);
+    if (i >= n) return;
+    float4 a = *reinterpret_cast<const float4*>(wpartial + i);
+#pragma unroll 8
+    for (int k = 1; k < ncopies; ++k) {
+      const float4 b = *reinterpret_cast<const float4*>(wpartial + (int64_t)k * n + i);
+      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    }
+    *reinterpret_cast<float4*>(dw + i) = a;
+    return;
+  }
   const int o = threadIdx.x & 63, part = threadIdx.x >> 6;
   const int64_t i = (int64_t)block * 64 + o;
   float a = 0.f;
@@ -551,20 +565,6 @@ __global__ __launch_bounds__(kFinThreads) void bwd_finalize_dwsum_kernel(const d
                                                                       int ncopies, int64_t n,
                                                                       float* __restrict__ dw, int straight) {
   __shared__ double sm[32][32];
-  if ((int)blockIdx.x >= nfin && straight != 0) {
-    // large weight tensors in few copies: four consecutive outputs per thread (n is a multiple of 4
-    // in this mode), the copies added in order
-    const int64_t i = 4 * ((int64_t)(blockIdx.x - nfin) * kFinThreads + threadIdx.x);
-    if (i >= n) return;
-    float4 a = *reinterpret_cast<const float4*>(wpartial + i);
-#pragma unroll 8
-    for (int k = 1; k < ncopies; ++k) {
-      const float4 b = *reinterpret_cast<const float4*>(wpartial + (int64_t)k * n + i);
-      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-    }
-    *reinterpret_cast<float4*>(dw + i) = a;
-    return;
-  }
   if ((int)blockIdx.x < nfin) {
     const int c = blockIdx.x * 16 + (threadIdx.x & 15);
     double t[2];
@@ -577,7 +577,7 @@ __global__ __launch_bounds__(kFinThreads) void bwd_finalize_dwsum_kernel(const d
     means[C + c] = (float)(gm * t[1] / (double)M);
     return;
   }
-  sum_of_copies(wpartial, ncopies, n, (int)blockIdx.x - nfin, dw, reinterpret_cast<float(*)[64]>(&sm[0][0]));
+  sum_of_copies(wpartial, ncopies, n, straight, (int)blockIdx.x - nfin, dw, reinterpret_cast<float(*)[64]>(&sm[0][0]));
 }
 
 // Backward, pass 2 (Eq. 8): dx = rstd * (dA1 - Mean(dA1) - A1~ * Mean(A1~ * dA1)).
@@ -800,14 +800,14 @@ __global__ __launch_bounds__(kThreads) void split_weights_kernel(SplitWeights sw
 // The same (blocks 0 .. nsplit-1) and the sum of a weight gradient's copies: nothing between the two, one launch.
 __global__ __launch_bounds__(kFinThreads) void split_weights_dwsum_kernel(SplitWeights sw, int nsplit,
                                                                        const float* __restrict__ wpartial, int ncopies,
-                                                                       int64_t n, float* __restrict__ dw) {
+                                                                       int64_t n, float* __restrict__ dw, int straight) {
   __shared__ float sm[16][64];
   if ((int)blockIdx.x < nsplit) {
     const int64_t it = (int64_t)blockIdx.x * kFinThreads + threadIdx.x;
     if (it < sw.items()) split_weights_item(sw, it);
     return;
   }
-  sum_of_copies(wpartial, ncopies, n, (int)blockIdx.x - nsplit, dw, sm);
+  sum_of_copies(wpartial, ncopies, n, straight, (int)blockIdx.x - nsplit, dw, sm);
 }
 
 }  // namespace
@@ -824,11 +824,17 @@ size_t bn_partial_bytes(int64_t M, int C) {
 
 size_t bn_means_offset(int C) { return (size_t)kMaxPartialBlocks * 2 * (size_t)C * sizeof(double); }
 
+// How sum_of_copies takes a weight gradient (the same in every launch that sums it), and the blocks that it needs.
+static bool sum_is_straight(const DwSum& d) { return d.copies <= 32 && d.n >= 131072 && d.n % 4 == 0; }
+static unsigned sum_blocks(const DwSum& d) {
+  return (unsigned)(sum_is_straight(d) ? (d.n / 4 + kFinThreads - 1) / kFinThreads : (d.n + 63) / 64);
+}
+
 int launch_split_weights(hipStream_t st, const SplitWeights& sw, const DwSum* dwsum) {
   if (dwsum != nullptr && dwsum->copies > 0) {
     const int nsplit = (int)((sw.items() + kFinThreads - 1) / kFinThreads);
-    split_weights_dwsum_kernel<<<nsplit + (unsigned)((dwsum->n + 63) / 64), kFinThreads, 0, st>>>(
-        sw, nsplit, dwsum->partial, dwsum->copies, dwsum->n, dwsum->dw);
+    split_weights_dwsum_kernel<<<nsplit + sum_blocks(*dwsum), kFinThreads, 0, st>>>(
+        sw, nsplit, dwsum->partial, dwsum->copies, dwsum->n, dwsum->dw, sum_is_straight(*dwsum) ? 1 : 0);
     return hip_status();
   }
   if (sw.items() == 0) return ABL_OK;
@@ -984,14 +990,9 @@ int launch_bn_bwd_finish(hipStream_t st, const void* packed, const void* stats, 
   const int vec = fast_vec(K, C, false);
   const int nfin = (C + 15) / 16;
   if (dwsum != nullptr) {
-    // many small copies (one per pixel tile): 16 interleaved parts per output and a tree;
-    // few large ones (split contraction): one thread per output
-    const bool straight = dwsum->copies <= 32 && dwsum->n >= 131072 && dwsum->n % 4 == 0;
-    const unsigned wblocks = straight ? (unsigned)((dwsum->n / 4 + kFinThreads - 1) / kFinThreads)
-                                      : (unsigned)((dwsum->n + 63) / 64);
-    bwd_finalize_dwsum_kernel<<<nfin + wblocks, kFinThreads, 0, st>>>(partial, nb, M, C, sp, dgamma, dbeta, means, nfin,
-                                                                      dwsum->partial, dwsum->copies, dwsum->n,
-                                                                      dwsum->dw, straight ? 1 : 0);
+    bwd_finalize_dwsum_kernel<<<nfin + sum_blocks(*dwsum), kFinThreads, 0, st>>>(
+        partial, nb, M, C, sp, dgamma, dbeta, means, nfin, dwsum->partial, dwsum->copies, dwsum->n, dwsum->dw,
+        sum_is_straight(*dwsum) ? 1 : 0);
   } else
     bwd_finalize_kernel<<<nfin, kFinThreads, 0, st>>>(partial, nb, M, C, sp, dgamma, dbeta, means);
   if (vec == 0) {

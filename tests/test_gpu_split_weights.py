@@ -132,27 +132,30 @@ def test_dw_depends_on_the_layer_alone(flags):
     acc = backward(dy, torch.ones_like(x), B.ABL_ACCUM_DX)
     assert torch.equal(acc[0], 1.0 + dx) and all(torch.equal(a, b) for a, b in zip(acc[1:], (dw, dg, db)))
 
-    # a pair of such layers with a shortcut, then one that widens: the last layer's incoming gradient is `top`
-    wide = (64, 56, 56, 64, 128, 1)
-    _, ww, wg, wb, top = draw(wide, 32)
-    third = dict(shape=shape9(wide), W=ww, gamma=wg, beta=wb, packed=raw(B.abl_packed_bytes(shape9(wide), K)),
-                 stats=raw(B.abl_stats_bytes(shape9(wide))), dW=f32(*ww.shape), dgamma=f32(64), dbeta=f32(64))
-    descs = [layer(), layer(), third]
-    layers = B.make_layers(descs)
-    nb = B.abl_stack_buffer_bytes(layers) // 4
-    S, T, ws = f32(nb), f32(nb), raw(B.abl_stack_scratch_bytes(layers, K))
-    S[:N] = x.view(-1)
-    B.abl_stack_forward(layers, K, 2, S, T, ws, flags=flags)
-    S[:top.numel()] = top.view(-1)
-    ws.fill_(255)
-    B.abl_stack_backward(layers, K, 2, S, T, ws, flags=flags)
-    own = raw(B.abl_scratch_bytes(shape9(wide), K))
-    d, w3, g3, b3 = f32(*x.shape), f32(*ww.shape), f32(64), f32(64)
-    B.abl_backward(shape9(wide), K, third["packed"], third["stats"], top, ww, own, d, w3, g3, b3, flags=flags)
-    assert torch.equal(w3.view(-1), third["dW"].view(-1))
-    skip = d
-    for e in (descs[1], descs[0]):
-        one = e
-        d, w3, g3, b3 = backward(d, torch.empty_like(x))
-        assert torch.equal(w3, e["dW"]) and torch.equal(g3, e["dgamma"]) and torch.equal(b3, e["dbeta"])
-    assert torch.equal(S[:N], (skip + d).view(-1))
+    # in stacks, pairs of layers with a shortcut: alone (the layer's own room) and below layers with a larger workspace
+    for widths in ((), (64, 256, 64)):
+        shapes = [s, s] + [(64, 56, 56, a, b, 1) for a, b in zip(widths, widths[1:])]
+        descs = [layer(), layer()]
+        for i, t in enumerate(shapes[2:]):
+            _, tw, tg, tb, _ = draw(t, 40 + i)
+            descs.append(dict(shape=shape9(t), W=tw, gamma=tg, beta=tb, packed=raw(B.abl_packed_bytes(shape9(t), K)),
+                              stats=raw(B.abl_stats_bytes(shape9(t))), dW=f32(*tw.shape), dgamma=f32(t[3]), dbeta=f32(t[3])))
+        layers = B.make_layers(descs)
+        nb = B.abl_stack_buffer_bytes(layers) // 4
+        S, T, ws = f32(nb), f32(nb), raw(B.abl_stack_scratch_bytes(layers, K))
+        S[:N] = x.view(-1)
+        B.abl_stack_forward(layers, K, 2, S, T, ws, flags=flags)
+        S[:N] = dy.view(-1)
+        ws.fill_(255)
+        B.abl_stack_backward(layers, K, 2, S, T, ws, flags=flags)
+        d = dy
+        for pair in reversed(range(0, len(descs), 2)):
+            skip = d
+            for t, e in reversed(list(zip(shapes[pair:pair + 2], descs[pair:pair + 2]))):
+                dx, dw, dg, db = f32(*t[:4]), f32(*e["W"].shape), f32(t[3]), f32(t[3])
+                B.abl_backward(shape9(t), K, e["packed"], e["stats"], d, e["W"], raw(B.abl_scratch_bytes(shape9(t), K)), dx, dw, dg, db,
+                               flags=flags)
+                assert torch.equal(dw, e["dW"]) and torch.equal(dg, e["dgamma"]) and torch.equal(db, e["dbeta"])
+                d = dx
+            d = skip + d
+        assert torch.equal(S[:N], d.view(-1))
