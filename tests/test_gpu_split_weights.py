@@ -1,15 +1,18 @@
 """Weights split once per call: the layer and stack calls, whose convolutions read the parts from the workspace, against the
-stage calls, which have no workspace and split in the kernel.  Same parts, same order of sums: the same bits."""
+stage calls, which have no workspace and split in the kernel.  Same parts, same order of sums: the same bits, where the stage
+takes the same grid."""
 import pytest
 import torch
 
 from paper_1901_07988_amd import binding as B
 
+from . import split_rules as R
+
 pytestmark = pytest.mark.gpu
 
 # N, H, W, Cin, Cout, R: every kernel of the plan (blocks of four and eight waves, 64 and 128 channels), patches of more
 # than 256 positions, several tiles to a block, one phase and an odd number of them
-SHAPES = [(220, 7, 7, 64, 64, 3), (64, 14, 14, 192, 128, 3), (100, 12, 11, 32, 64, 3), (12, 57, 57, 64, 64, 3),
+SHAPES = [(220, 7, 7, 64, 64, 3), (64, 14, 14, 192, 128, 3), (64, 14, 14, 128, 128, 3), (100, 12, 11, 32, 64, 3), (12, 57, 57, 64, 64, 3),
           (40, 28, 28, 128, 128, 3), (40, 56, 56, 64, 64, 3), (1, 110, 101, 64, 64, 1), (64, 14, 14, 1024, 256, 1),
           (2, 150, 151, 128, 256, 1), (9, 141, 143, 192, 64, 1), (40, 56, 56, 64, 256, 1)]
 IDS = ["x".join(map(str, s)) for s in SHAPES]
@@ -56,13 +59,26 @@ def test_layer_equals_stages(s, flags):
     assert torch.equal(packed, p2) and torch.equal(y, y2)
     dx, dw, dg, db = torch.empty_like(x), torch.empty_like(w), f32(C), f32(C)
     B.abl_backward(s9, K, packed, stats, dy, w, scratch, dx, dw, dg, db, flags=flags)
-    da3, dx2, dg2, db2 = f32(*x.shape), torch.empty_like(x), f32(C), f32(C)
+    da3, dx2, dw2, dg2, db2 = f32(*x.shape), torch.empty_like(x), f32(*w.shape), f32(C), f32(C)
     B.abl_conv_dgrad(s9, dy, w, da3, flags=flags)
+    # dA3 stays at the start of the workspace
+    mine = scratch[:4 * x.numel()].view(torch.float32).view(x.shape)
+    grids = [R.rows(s, 1, bool(flags), sums) for sums in (False, True)]
+    stage_splits = grids[0] > 0 and not (flags and s[5] == 1 and s[4] < 1024)   # (shorter bf16 1x1 stages: another kernel)
+    if grids[0] == grids[1] and stage_splits and not (flags and R.beats_image(s, 1) != (grids[0] > 0)):
+        assert torch.equal(mine, da3)
+    else:
+        assert float((mine - da3).abs().max()) < 2.0 ** -19 * float(da3.abs().max())
+    B.abl_conv_wgrad_packed(s9, K, packed, stats, dy, raw(B.abl_wgrad_scratch_bytes(s9)), dw2, flags=flags)
     B.abl_bn_bwd(packed, stats, da3, M, C, K, raw(B.abl_bn_scratch_bytes(M, C)), dx2, dg2, db2)
     # the sums of Eq. 7 are taken in another order and by another kernel, whose data gradient may be another one as well:
     # roundings of an fp32 accumulator per 32 terms (2e-6 for 2304 terms), bf16 operands the same but for their order
-    for a, b in ((dx, dx2), (dg, dg2), (db, db2)):
+    # (dW: the same products, the pixels in other parts)
+    for a, b in ((dx, dx2), (dw, dw2), (dg, dg2), (db, db2)):
         assert float((a.double() - b.double()).norm() / b.double().norm()) < 4e-6
+    # no element left out or written twice: roundings of the largest
+    for a, b in ((dx, dx2), (dw, dw2)):
+        assert float((a - b).abs().max()) < 2.0 ** -19 * float(b.abs().max())
 
 
 @pytest.mark.parametrize("flags", [0, B.ABL_MATH_BF16], ids=["fp32", "bf16"])
