@@ -5,8 +5,8 @@
 // rounded remainder of the ones before), so a product of two is nine bf16 products, each exact in fp32.  Six
 // of them are taken - hh, hm, mh, mm, hl, lh; the dropped ones (ml, lm, ll) are 2^-28 of the product on average and
 // below 2^-24, an fp32 rounding, at worst (above 2^-26 for 3 pairs of significands in 100).  A loop of
-// v_mfma_f32_16x16x32_bf16 on registers does 1430 TFLOP/s, one of v_mfma_f32_16x16x4_f32 139: six of the former take
-// 0.58 of the time of the fp32 product; and the sum is rounded once per 32 terms and product instead of once per 4 terms.  The five small
+// v_mfma_f32_16x16x32_bf16 on random registers does 2070 TFLOP/s, one of v_mfma_f32_16x16x4_f32 154: six of the former take
+// 0.45 of the time of the fp32 product; and the sum is rounded once per 32 terms and product instead of once per 4 terms.  The five small
 // products have an accumulator of their own: added to the large one they would each round at its magnitude
 // (relative error of a 2304-term contraction against 64 bits: fp32 matrix cores 8.6e-7, one accumulator
 // 7.4e-7, two 2.9e-7).  The parts are taken of 2^23 x: those of the smallest fp32 values (multiples of 2^-149) are normal
@@ -28,7 +28,8 @@
 // What the k-loop needs to stay at the matrix cores' rate (us before / with all of it, in a stack: 3x3 256 -> 256 @14x14
 // 79 / 66, gradient with sums 85 / 71; 1x1 1024 -> 256 48 / 40, its mirror's gradient 50 / 42; 1x1 256 -> 1024 58 / 52,
 // gradient 60 / 53; 3x3 64 -> 64 @56x56 108 / 87, gradient 115 / 95, with bf16 operands 53 / 42 and 77 / 55):
-//  - two sets of weight registers in turn.  With one, its copy waits for everything in flight, the next phase's input too.
+//  - two sets of weight registers in turn.  With one, its copy at every step waits for everything in flight, the next phase's
+//    input too.  (An odd number of steps leaves one copy, at the end of a phase, where the input is awaited anyway.)
 //  - loads without branches around them, and the next phase's input after the weights of a step, not before.
 //  - the wave that is behind first: left to itself a SIMD runs its older wave to the barrier, and the other alone gets
 //    80 % of the matrix rate (a phase of nine steps 31.6 thousand cycles, with falling priorities 30.0, both at full rate 24.2).

@@ -35,30 +35,44 @@ __global__ __launch_bounds__(kProbeThreads) void probe_copy_kernel(const vec4f* 
   dst[i] = src[i];
 }
 
-// Matrix-core probe: every wave issues `iters` rounds of eight independent MFMAs (eight
-// accumulator tiles, so no instruction waits for the previous one's result); operands stay in
-// registers.  MODE 0: v_mfma_f32_16x16x4_f32 (2048 flops each), MODE 1: v_mfma_f32_16x16x32_bf16
-// (16384 flops each).
-constexpr int kMfmaProbeBlocks = 2048, kMfmaProbeAcc = 8;
+// Matrix-core probe: every wave issues `iters` rounds of twelve independent MFMAs (twelve accumulator tiles, so no instruction
+// waits for the previous one's result); operands stay in registers.  They are random: the matrix cores draw power by the bits that
+// change, and a loop on zeros or on one constant runs at a clock that no contraction keeps (bf16: zeros 2340 TFLOP/s, random
+// 2070, in fp32 154).  Two waves per SIMD and half of the registers each: with eight accumulators and no bound the compiler moved
+// accumulators about in the loop and waited for them (1430 and 140).
+// MODE 0: v_mfma_f32_16x16x4_f32 (2048 flops each), MODE 1: v_mfma_f32_16x16x32_bf16 (16384 flops each).
+constexpr int kMfmaProbeBlocks = 2048, kMfmaProbeAcc = 12;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 template <int MODE>
-__global__ __launch_bounds__(kProbeThreads) void probe_mfma_kernel(float* __restrict__ out, int iters, float seed) {
+__global__ __launch_bounds__(kProbeThreads, 2) void probe_mfma_kernel(float* __restrict__ out, int iters, uint32_t seed) {
+  uint32_t r = seed + threadIdx.x * 2654435761u + blockIdx.x * 40503u;
+  auto next = [&]() {   // in (-1, 1)
+    r = r * 1664525u + 1013904223u;
+    return (float)((int)(r >> 8) - (1 << 23)) * 0x1p-23f;
+  };
+  constexpr int OPS = 4;
+  float a[OPS], b[OPS];
+  bf16x8 a8[OPS], b8[OPS];
+#pragma unroll
+  for (int i = 0; i < OPS; ++i) {
+    a[i] = next();
+    b[i] = next();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      a8[i][e] = (__bf16)next();
+      b8[i][e] = (__bf16)next();
+    }
+  }
   floatx4 acc[kMfmaProbeAcc];
 #pragma unroll
   for (int i = 0; i < kMfmaProbeAcc; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const float av = seed + (float)threadIdx.x * 1e-6f, bv = seed;
-  bf16x8 a8, b8;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    a8[i] = (__bf16)(av + (float)i);
-    b8[i] = (__bf16)bv;
-  }
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
     for (int i = 0; i < kMfmaProbeAcc; ++i) {
-      if constexpr (MODE == 0) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[i], 0, 0, 0);
-      else acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b8, acc[i], 0, 0, 0);
+      if constexpr (MODE == 0) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i % OPS], b[i / 2 % OPS], acc[i], 0, 0, 0);
+      else acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8[i % OPS], b8[i / 2 % OPS], acc[i], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   float s = 0.f;
@@ -86,8 +100,8 @@ extern "C" int abl_mfma_probe(void* stream, int mode, int iters, void* out, size
   if (out == nullptr || (reinterpret_cast<uintptr_t>(out) & 15u)) return ABL_ERR_ARG;
   if (out_bytes < abl_mfma_probe_out_bytes()) return ABL_ERR_SCRATCH;
   hipStream_t st = (hipStream_t)stream;
-  if (mode == 0) probe_mfma_kernel<0><<<kMfmaProbeBlocks, kProbeThreads, 0, st>>>(static_cast<float*>(out), iters, 1.0f);
-  else probe_mfma_kernel<1><<<kMfmaProbeBlocks, kProbeThreads, 0, st>>>(static_cast<float*>(out), iters, 1.0f);
+  if (mode == 0) probe_mfma_kernel<0><<<kMfmaProbeBlocks, kProbeThreads, 0, st>>>(static_cast<float*>(out), iters, 1u);
+  else probe_mfma_kernel<1><<<kMfmaProbeBlocks, kProbeThreads, 0, st>>>(static_cast<float*>(out), iters, 1u);
   return hip_status();
 }
 
