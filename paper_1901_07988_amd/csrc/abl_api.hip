@@ -332,7 +332,7 @@ size_t wpart_offset(const abl_shape& s) {
 
 // abl_backward after its checks.  sw: the weights as the data gradient's kernel reads them (out = nullptr: it splits them), still to
 // be split here or (ready) split by an earlier launch.  next: weights for the launch of the apply pass to split.  wroom: bytes at the
-// place of the weight gradient's copies.
+// place of the weight gradient's copies, 0 = the layer's own room for them.
 int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, const void* packed, const void* stats,
                   const float* dy, const float* W, void* scratch, float* dx, float* dW, float* dgamma, float* dbeta,
                   const SplitWeights& sw, bool ready, const SplitWeights& next, size_t wroom) {
@@ -350,11 +350,17 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   // workspace has the room.  How many they are, and with them the rounding of dW, depends on the layer's shape alone.  (64 -> 64
   // @56x56 N=64: 85 copies, 170 blocks on 256 units, 86 us, 50 with bf16 operands; 128 copies, 256 blocks, 64 and 38.  An eighth
   // more at least, for a sum that may take a launch of its own.)
-  const size_t own = wgrad_partial_bytes(*s);
-  const int few = K != 32 && g.R == 3 && act > own ? split_wgrad_copies(g, K, bf16, own) : 0;
-  const int more = few > 0 ? split_wgrad_copies(g, K, bf16, act) : 0;
-  const size_t room = few > 0 && 8 * more >= 9 * few ? act : own;
-  const bool w_first = room > own && wroom < (size_t)more * 9 * s->Cin * s->Cout * sizeof(float);
+  size_t room = 0;   // (0: the layer's own)
+  bool w_first = false;
+  if (K != 32 && g.R == 3 && g.Cin % 32 == 0 && g.Cout % 64 == 0) {   // (narrow layers are bound by the host: not a call more)
+    const size_t own = wgrad_partial_bytes(*s);
+    const int few = act > own ? split_wgrad_copies(g, K, bf16, own) : 0;
+    const int more = few > 0 ? split_wgrad_copies(g, K, bf16, act) : 0;
+    if (few > 0 && 8 * more >= 9 * few) {
+      room = act;
+      w_first = wroom < (size_t)more * 9 * s->Cin * s->Cout * sizeof(float);
+    }
+  }
   DwSum first{nullptr, 0, 0, nullptr};
   if (w_first)
     if (int e = launch_conv_wgrad_packed(st, *s, K, bf16, packed, stats, dy, da3, dW, false, &first, act)) return e;
@@ -466,7 +472,7 @@ int abl_backward(void* stream, const abl_shape* s, int K, uint32_t flags, const 
   if (const int np = backward_parts(geom_of(*s), K, (flags & ABL_MATH_BF16) != 0, true))
     sw = weights_to_split(*s, 1, np, W, static_cast<char*>(scratch) + wpart_offset(*s), wgrad_partial_bytes(*s));
   return backward_impl((hipStream_t)stream, s, K, flags, packed, stats, dy, W, scratch, dx, dW, dgamma, dbeta, sw, false,
-                       SplitWeights{}, wgrad_partial_bytes(*s));
+                       SplitWeights{}, 0);
 }
 
 // ---- the layer with a leaky ReLU (Sec. 3.4) ---------------------------------------------------
