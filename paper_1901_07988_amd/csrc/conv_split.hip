@@ -5,7 +5,7 @@
 // rounded remainder of the ones before), so a product of two is nine bf16 products, each exact in fp32.  Six
 // of them are taken - hh, hm, mh, mm, hl, lh; the dropped ones (ml, lm, ll) are 2^-28 of the product on average and
 // below 2^-24, an fp32 rounding, at worst (above 2^-26 for 3 pairs of significands in 100).  A loop of
-// v_mfma_f32_16x16x32_bf16 on random registers does 2070 TFLOP/s, one of v_mfma_f32_16x16x4_f32 154: six of the former take
+// v_mfma_f32_16x16x32_bf16 on random registers does 2050 TFLOP/s, one of v_mfma_f32_16x16x4_f32 154: six of the former take
 // 0.45 of the time of the fp32 product; and the sum is rounded once per 32 terms and product instead of once per 4 terms.  The five small
 // products have an accumulator of their own: added to the large one they would each round at its magnitude
 // (relative error of a 2304-term contraction against 64 bits: fp32 matrix cores 8.6e-7, one accumulator
@@ -25,9 +25,11 @@
 // a block reads nothing twice.  PRE: they come as the parts that SplitWeights describes, split once per call, in six whole
 // kilobytes a k-step instead of 16 gathers and 88 vector instructions.  (Where no workspace is at hand the kernel splits them.)
 // A wave computes 112 pixels x 16 NT channels: 7 NT tiles, 21 reads and 42 NT MFMAs per k-step.
-// What the k-loop needs to stay at the matrix cores' rate (us before / with all of it, in a stack: 3x3 256 -> 256 @14x14
-// 79 / 66, gradient with sums 85 / 71; 1x1 1024 -> 256 48 / 40, its mirror's gradient 50 / 42; 1x1 256 -> 1024 58 / 52,
-// gradient 60 / 53; 3x3 64 -> 64 @56x56 108 / 87, gradient 115 / 95, with bf16 operands 53 / 42 and 77 / 55):
+// What the k-loop needs to stay at the matrix cores' rate (us before / with all of it, in a stack, both traced on one card: 3x3
+// 256 -> 256 @14x14 75.7 / 71.9, gradient with sums 80.1 / 75.9; 1x1 1024 -> 256 48.3 / 44.5, its mirror's gradient 49.7 / 46.2;
+// 1x1 256 -> 1024 58.0 / 56.4, gradient 58.6 / 56.9; 3x3 64 -> 64 @56x56 106 / 89, gradient 114 / 97; layer call with bf16 operands
+// and 8-bit codes 53 / 43 and 76 / 56.  In the first four the card's power is the bound: the weight gradients between them, the same
+// kernels on both sides, took 58 and 62):
 //  - two sets of weight registers in turn.  With one, its copy at every step waits for everything in flight, the next phase's
 //    input too.  (An odd number of steps leaves one copy, at the end of a phase, where the input is awaited anyway.)
 //  - loads without branches around them, and the next phase's input after the weights of a step, not before.

@@ -38,8 +38,8 @@ __global__ __launch_bounds__(kProbeThreads) void probe_copy_kernel(const vec4f* 
 // Matrix-core probe: every wave issues `iters` rounds of twelve independent MFMAs (twelve accumulator tiles, so no instruction
 // waits for the previous one's result); operands stay in registers.  They are random: the matrix cores draw power by the bits that
 // change, and a loop on zeros or on one constant runs at a clock that no contraction keeps (bf16: zeros 2340 TFLOP/s, random
-// 2070, in fp32 154).  Two waves per SIMD and half of the registers each: with eight accumulators and no bound the compiler moved
-// accumulators about in the loop and waited for them (1430 and 140).
+// 2020 to 2070 by card, in fp32 154).  Two waves per SIMD and half of the registers each: with eight accumulators and no bound
+// the compiler moved accumulators about in the loop and waited for them (1430 and 140).
 // MODE 0: v_mfma_f32_16x16x4_f32 (2048 flops each), MODE 1: v_mfma_f32_16x16x32_bf16 (16384 flops each).
 constexpr int kMfmaProbeBlocks = 2048, kMfmaProbeAcc = 12;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

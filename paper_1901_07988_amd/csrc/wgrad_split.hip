@@ -6,7 +6,7 @@
 // where step (n + 1/2) is Eq. 10 and v = |2 n + 1| where that is positive, else 0.  v is a whole number below
 // 2^K + 2 |fb|, exact in one bf16 up to 256; 2^23 dy is the exact sum of three bf16 values (as in conv_split.hip).  So
 // three bf16 products - each exact - replace one fp32 product, with nothing dropped, in 0.22 of its matrix-core time
-// (loops on registers: 2070 TFLOP/s of bf16, 154 of fp32), and the sums are rounded once per 32 pixels and part instead of
+// (loops on registers: 2050 TFLOP/s of bf16, 154 of fp32), and the sums are rounded once per 32 pixels and part instead of
 // once per 4 pixels (relative error of a sum over 12544 pixels against 64 bits 0.95e-6, fp32 matrix cores 1.4e-6).
 // A block whose channels reach beyond 256 (8-bit codes with a positive fb) but not beyond 511 stores v - 1 there - v
 // is odd - and the missing ones are made from the stored bits: two more products, with the upper two parts of dy
