@@ -209,8 +209,8 @@ int abl_conv_dgrad(void* stream, const abl_shape* shape, uint32_t flags, const f
 /* Eq. 5, gradient to the weights, with A3 rebuilt on the fly from the packed codes
  * (Eq. 10 then Eq. 3); no full-precision copy of the activation is written to memory.
  * scratch: abl_wgrad_scratch_bytes(shape).  flags: ABL_MATH_BF16.
- * (The pixels are summed in as many parts as the scratch holds.  abl_backward and the stack calls have room for more parts of a
- * 3x3 layer with few channels: their dW can differ from this one's in the last bits, by an fp32 sum in another order.) */
+ * (Partial sums over the pixels are added in another order than in abl_backward and the stack calls, whose workspace can also hold
+ * more of them: their dW can differ from this one's in the last bits.) */
 size_t abl_wgrad_scratch_bytes(const abl_shape* shape);
 int abl_conv_wgrad_packed(void* stream, const abl_shape* shape, int K, uint32_t flags, const void* packed,
                           const void* stats, const float* dy, void* scratch,

@@ -353,12 +353,15 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   size_t room = 0;   // (0: the layer's own)
   bool w_first = false;
   if (K != 32 && g.R == 3 && g.Cin % 32 == 0 && g.Cout % 64 == 0) {   // (narrow layers are bound by the host: not a call more)
+    // (dW over W, which the data gradient reads, can only be written behind it)
+    const int64_t n = (int64_t)9 * s->Cin * s->Cout;
+    const bool apart = dW + n <= W || W + n <= dW;
     const size_t own = wgrad_partial_bytes(*s);
-    const int few = act > own ? split_wgrad_copies(g, K, bf16, own) : 0;
+    const int few = apart && act > own ? split_wgrad_copies(g, K, bf16, own) : 0;
     const int more = few > 0 ? split_wgrad_copies(g, K, bf16, act) : 0;
     if (few > 0 && 8 * more >= 9 * few) {
       room = act;
-      w_first = wroom < (size_t)more * 9 * s->Cin * s->Cout * sizeof(float);
+      w_first = wroom < (size_t)more * n * sizeof(float);
     }
   }
   DwSum first{nullptr, 0, 0, nullptr};

@@ -145,6 +145,11 @@ def test_dw_depends_on_the_layer_alone(flags):
         dy2.copy_(dy)
         for a, b in zip(backward(dy2, both[:N].view(x.shape)), (dx, dw, dg, db)):
             assert torch.equal(a, b)
+    over = w.clone()   # dW over the weights: written behind the data gradient, which reads them
+    dx2, dg2, db2 = torch.empty_like(x), f32(64), f32(64)
+    B.abl_backward(s9, K, one["packed"], one["stats"], dy, over, scratch, dx2, over, dg2, db2, flags=flags)
+    assert torch.equal(dx2, dx) and torch.equal(dg2, dg)
+    assert float((over.double() - stage.double()).norm() / stage.double().norm()) < 2e-6
     acc = backward(dy, torch.ones_like(x), B.ABL_ACCUM_DX)
     assert torch.equal(acc[0], 1.0 + dx) and all(torch.equal(a, b) for a, b in zip(acc[1:], (dw, dg, db)))
 
