@@ -42,8 +42,8 @@
 // waves overlap little.)
 // KS = 2: the chunks of a phase go to two groups of waves whose sums meet in LDS at the end - two waves per
 // SIMD also where a layer gives only one block per compute unit - and the patch has two buffers.
-// KS = 1: one buffer, two blocks per compute unit cover each other's staging (one where a 3x3 patch has more than 256
-// positions).
+// KS = 1: one buffer, two blocks per compute unit cover each other's staging (with fp32 operands one where a 3x3 patch has more
+// than 256 positions).
 // With bf16 operands (ABL_MATH_BF16) the same kernel runs with one part per operand: rounded once, one product.
 
 #include <type_traits>
@@ -763,10 +763,9 @@ void balance(const ConvGeom& g, int mode, int np, Plan& p) {
 // Whether the halo kernel is the faster one on a 3x3 layer's four-wave grid (fp32).  Its tiles of 64 pixels, all in one
 // round of the compute units, take less than a 112-pixel tile here (us, layer, halo kernel / here: 64 -> 64 @32x32 N=12 25.5 /
 // 27.1, backward 45.8 / 51.3; with more of them it is two rounds, N=24 29.3 here).  A patch of more than 256 positions
-// (cross-image runs of 32-pixel-wide images, rows of 57) leaves LDS for one block per unit only; a tile then takes 15.5 us per
-// 64 input channels, the halo kernel 11.1 per round of 64 pixels, 20 of 128, 35.5 of 224 (layer, halo kernel / here: 64 -> 64
-// @33x33 N=64 77.9 / 64.7, N=56 58.5 / 63.3, N=28 37.3 / 46.4, @55x55 N=24 78.1 / 64.5, N=20 58.7 / 63.1, @32x32 N=80 78.2 /
-// 65.4).  Where both take about the same this kernel stays: its sums are the closer ones.
+// (a round of runs across 32-pixel-wide images, rows of 45 and more) leaves LDS for one block per unit only; a tile then takes 15.5
+// us per 64 input channels, the halo kernel 11.1 per round of 64 pixels, 20 of 128, 35.5 of 224 (layer, halo kernel / here: 64 -> 64
+// @55x55 N=24 78.1 / 64.5, N=20 58.7 / 63.1).  Where both take about the same this kernel stays: its sums are the closer ones.
 bool halo_is_faster(const ConvGeom& g, int mode, const Plan& p) {
   const int Ng = mode == 0 ? g.Cout : g.Cin;
   const bool alone = p.su > 4;
