@@ -252,6 +252,17 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
   const ConvGeom g = geom_of(*s);
   int split_rows = 0;
   const int path = aliased(x, y) ? 0 : forward_fused_path(*s, g, K, bf16, naive, &split_rows);
+  // 16-channel 3x3 layers: the second pass of Eq. 1 goes along with the convolution
+  if (path == 1 && !bf16 && split_rows == 0)
+    if (const int tiles = c16_tiles(g, 0)) {
+      const bool chained = in_partial != nullptr && in_nb > 0;
+      int nb = in_nb;
+      if (!chained)
+        if (int e = launch_bn_stats_partial(st, x, M, s->Cin, red, &nb)) return e;
+      if (out_nb != nullptr && out_partial != nullptr) *out_nb = tiles;
+      return launch_c16_fwd(st, g, K, x, W, chained ? in_partial : static_cast<const double*>(red), nb, chained ? nullptr : x, gamma,
+                            beta, stats, skip, y, packed, out_partial);
+    }
   // weights of a split-operand convolution: split by the launch of the second pass of Eq. 1, which leaves most of the chip
   // idle
   SplitWeights sw{};
@@ -379,6 +390,11 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   // bf16 operands with a dgrad on the 32-deep bf16 matrix instruction: the separate stages
   const bool bf16_gemm = bf16 && bf16_gemm_supported(g, 1);
   // 16-channel 3x3 layers: both contractions and the Eq. 6-7 sums in one kernel
+  if (const int tiles = K != 32 && !bf16 ? c16_tiles(g, 1) : 0) {
+    if (int e = launch_c16_bwd(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red), static_cast<float*>(wpart))) return e;
+    const DwSum dwsum{static_cast<const float*>(wpart), tiles, (int64_t)9 * 16 * 16, dW};
+    return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, tiles, dx, dgamma, dbeta, &dwsum, 0.0f, next);
+  }
   if (const int t16 = K != 32 ? halo_bwd16_tiles(g) : 0) {
     if (int e = launch_halo_bwd16(st, g, K, bf16, dy, W, packed, stats, da3, static_cast<double*>(red), wpart,
                                   nullptr))
@@ -550,6 +566,9 @@ int abl_bn_conv_fwd(void* stream, const abl_shape* s, int K, uint32_t flags, con
   if (forward_fused_path(*s, g, K, bf16, false, &split_rows) == 1 && split_rows > 0)   // (as abl_forward does)
     return launch_split_fwd_fused((hipStream_t)stream, g, K, x, stats, W, skip, y, packed, nullptr);
   if (!halo_fused_supported(g)) return ABL_ERR_SHAPE;
+  if (!bf16 && c16_tiles(g, 0) > 0)
+    return launch_c16_fwd((hipStream_t)stream, g, K, x, W, nullptr, 0, nullptr, nullptr, nullptr, const_cast<void*>(stats), skip, y,
+                          packed, nullptr);
   return launch_halo_fwd_fused((hipStream_t)stream, g, K, bf16, x, stats, W, skip, y, packed, nullptr);
 }
 
@@ -639,6 +658,13 @@ int abl_conv_bwd_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t fla
   if (tiles <= 0) return ABL_ERR_SHAPE;
   const size_t redb = up256(bn_partial_bytes(rows_of(*s), s->Cin));
   if (scratch_bytes < redb + wgrad_partial_bytes(*s)) return ABL_ERR_SCRATCH;
+  if (const int t = (flags & ABL_MATH_BF16) == 0 ? c16_tiles(g, 1) : 0) {
+    *rows = t;
+    float* const copies = reinterpret_cast<float*>(static_cast<char*>(scratch) + redb);
+    if (int e = launch_c16_bwd((hipStream_t)stream, g, K, dy, W, packed, stats, da3, static_cast<double*>(scratch), copies)) return e;
+    const DwSum sum{copies, t, (int64_t)9 * 16 * 16, dW};
+    return dW != nullptr ? launch_split_weights((hipStream_t)stream, SplitWeights{}, &sum) : ABL_OK;
+  }
   *rows = tiles;
   return launch_halo_bwd16((hipStream_t)stream, g, K, (flags & ABL_MATH_BF16) != 0, dy, W, packed, stats, da3,
                            static_cast<double*>(scratch), static_cast<char*>(scratch) + redb, dW);
@@ -909,6 +935,24 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
   const size_t xbytes = stack_xpart_bytes(layers, L);
   char* const lscratch = static_cast<char*>(scratch) + xbytes;
   const size_t lbytes = abl_stack_scratch_bytes(layers, L, K) - xbytes;
+  // Equal 16-channel layers: Eq. 7-8 of a layer go along with the contractions of the layer below (a traced call wants every dy in
+  // memory).
+  const size_t wat = wpart_offset(layers[0].shape);
+  if (trace == nullptr && (flags & ABL_MATH_BF16) == 0 && c16_stack_tiles(layers, L, K, skip_every, lbytes > wat ? lbytes - wat : 0)) {
+    const abl_layer& l = layers[0];
+    const int64_t M = rows_of(l.shape);
+    float* const da3 = reinterpret_cast<float*>(lscratch);
+    char* const red = lscratch + up256((size_t)M * l.shape.Cin * sizeof(float));
+    float* const copies = reinterpret_cast<float*>(lscratch + wat);
+    double* const rows[2] = {reinterpret_cast<double*>(red), static_cast<double*>(scratch)};
+    const int tiles = c16_tiles(geom_of(l.shape), 1);
+    if (int e = launch_c16_stack_bwd((hipStream_t)stream, layers, L, K, buf_s, buf_t, da3, rows, copies,
+                                     reinterpret_cast<float*>(red + bn_means_offset(l.shape.Cin))))
+      return e;
+    const DwSum dwsum{copies, tiles, (int64_t)9 * 16 * 16, l.dW};
+    return launch_bn_bwd_finish((hipStream_t)stream, l.packed, l.stats, da3, M, l.shape.Cin, K, true, red, tiles, buf_s, l.dgamma,
+                                l.dbeta, &dwsum);
+  }
   // The weights that a layer's data gradient reads in parts are split by the launch of the layer above that comes before
   // (its apply pass), at a place in the workspace that is free for both.
   auto parts_of = [&](int i, size_t at) {

@@ -57,6 +57,8 @@ int launch_pack(hipStream_t st, const float* a2, int64_t M, int C, int K, const 
 // act: apply the non-linearity to the dequantized values (the A3~ the weight gradient contracts).
 int launch_unpack(hipStream_t st, const void* packed, int64_t M, int C, int K, const void* stats,
                   float* a2t, bool act = false, float slope = 0.0f);
+// The first pass of launch_bn_stats alone: *nb rows of sums around x's first row, in scratch.
+int launch_bn_stats_partial(hipStream_t st, const float* x, int64_t M, int C, void* scratch, int* nb);
 // The second halves of the two reductions, for partial sums produced elsewhere (conv epilogues).
 size_t bn_means_offset(int C);
 int launch_bn_stats_finalize(hipStream_t st, const double* partial, int nb, const float* shift_row, int64_t M,
@@ -132,6 +134,23 @@ int halo_bwd16_tiles(const ConvGeom& g);
 int launch_halo_bwd16(hipStream_t st, const ConvGeom& g, int K, bool bf16, const float* dy, const float* w,
                       const void* packed, const void* stats, float* da3, double* partial, void* wscratch,
                       float* dw);
+
+// ---- the same layers on split operands, fp32 (conv_c16.hip) ----
+// Blocks of the forward (mode 0) or of the backward of a layer: rows of sums, copies of dW; 0: not supported.
+int c16_tiles(const ConvGeom& g, int mode);
+// Forward with Eq. 1's second pass (nb > 0 rows of sums around `shift`, nullable; nb = 0: `stats` is given) and Eq. 1-3, 9.  y is not x.
+int launch_c16_fwd(hipStream_t st, const ConvGeom& g, int K, const float* x, const float* w, const double* partial, int nb,
+                   const float* shift, const float* gamma, const float* beta, void* stats, const float* skip, float* y, void* packed,
+                   double* out_partial);
+// As launch_halo_bwd16 without the sum of dW's copies.
+int launch_c16_bwd(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w, const void* packed, const void* stats,
+                   float* da3, double* partial, float* copies);
+// The backward of a stack of equal such layers in pairs with a shortcut around each, up to Eq. 7-8 of the bottom layer (its rows
+// are in rows[0], its dA3 in da3, its copies of dW in front): Eq. 7-8 of the others go along with the layer below.
+// c16_stack_tiles: blocks, 0 = not such a stack; room: bytes for two sets of copies.  means: room for 4 x 16 floats.
+int c16_stack_tiles(const abl_layer* layers, int L, int K, int skip_every, size_t room);
+int launch_c16_stack_bwd(hipStream_t st, const abl_layer* layers, int L, int K, float* s, float* t, float* da3, double* const (&rows)[2],
+                         float* copies, float* means);
 
 // ---- convolution kernels (conv_kernels.hip) ----
 size_t wgrad_partial_bytes(const abl_shape& s);
@@ -287,6 +306,28 @@ __device__ inline uint32_t quant_code(float a2, float cq, int32_t fb) {
     v = v > (1 << K) - 1 ? (1 << K) - 1 : v;
     return (uint32_t)v;
   }
+}
+
+// The planes of one channel's statistics (StatPlane; fb as its bits) from its two sums, taken around `shift`.
+__device__ inline void channel_constants(double t0, double t1, float shift, int64_t M, float gm, float bt, int K, float (&out)[8]) {
+  const double k = (double)shift;
+  const double mk = t0 / (double)M;
+  double var = t1 / (double)M - mk * mk;
+  var = var > 0.0 ? var : 0.0;
+  const float var_f = (float)var;
+  out[P_MEAN] = (float)(k + mk);
+  out[P_VAR] = var_f;
+  out[P_RSTD] = (float)(1.0 / sqrt((double)var_f + (double)ABL_BN_EPS));
+  // K = 32 (exact storage) has no quantizer: the constants are written as zeros
+  const float two_k = K < 32 ? (float)(1 << K) : 0.0f;
+  const float six_g = 6.0f * gm;
+  // double division then one rounding == correctly rounded fp32 division
+  const float cq = K < 32 ? (float)((double)two_k / (double)six_g) : 0.0f;
+  out[P_GAMMA] = gm;
+  out[P_BETA] = bt;
+  out[P_CQ] = cq;
+  out[P_STEP] = K < 32 ? (float)((double)six_g / (double)two_k) : 0.0f;
+  out[P_FB] = __int_as_float(K < 32 ? (int32_t)limit_floor(bt * cq) : 0);
 }
 
 // Eq. 10 for one code.

@@ -296,29 +296,10 @@ __global__ __launch_bounds__(kFinThreads) void stats_finalize_kernel(const doubl
   double t[2];
   reduce_partials(partial, nb, C, t, sm);
   if (c >= C || threadIdx.x >= 16) return;
-  const double k = x != nullptr ? (double)x[c] : 0.0;  // the shift the partial sums were taken with
-  const double mk = t[0] / (double)M;
-  double var = t[1] / (double)M - mk * mk;
-  var = var > 0.0 ? var : 0.0;
-  const float mean_f = (float)(k + mk);
-  const float var_f = (float)var;
-  const float rstd = (float)(1.0 / sqrt((double)var_f + (double)ABL_BN_EPS));
-  const float gm = gamma[c], bt = beta[c];
-  // K = 32 (exact storage) has no quantizer: the constants are written as zeros
-  const float two_k = K < 32 ? (float)(1 << K) : 0.0f;
-  const float six_g = 6.0f * gm;
-  // double division then one rounding == correctly rounded fp32 division
-  const float cq = K < 32 ? (float)((double)two_k / (double)six_g) : 0.0f;
-  const float step = K < 32 ? (float)((double)six_g / (double)two_k) : 0.0f;
-  const int32_t fb = K < 32 ? (int32_t)limit_floor(bt * cq) : 0;
-  stats[P_MEAN * C + c] = mean_f;
-  stats[P_VAR * C + c] = var_f;
-  stats[P_RSTD * C + c] = rstd;
-  stats[P_GAMMA * C + c] = gm;
-  stats[P_BETA * C + c] = bt;
-  stats[P_CQ * C + c] = cq;
-  stats[P_STEP * C + c] = step;
-  reinterpret_cast<int32_t*>(stats)[P_FB * C + c] = fb;
+  float v[8];
+  channel_constants(t[0], t[1], x != nullptr ? x[c] : 0.0f, M, gamma[c], beta[c], K, v);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) stats[i * C + c] = v[i];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -842,8 +823,7 @@ int launch_split_weights(hipStream_t st, const SplitWeights& sw, const DwSum* dw
   return hip_status();
 }
 
-int launch_bn_stats(hipStream_t st, const float* x, int64_t M, int C, const float* gamma,
-                    const float* beta, int K, void* scratch, void* stats, const SplitWeights& sw) {
+int launch_bn_stats_partial(hipStream_t st, const float* x, int64_t M, int C, void* scratch, int* nb) {
   double* partial = static_cast<double*>(scratch);
   const int vec = C % 4 == 0 ? 4 : 1;
   const RowGeom g = make_geom(M, C, vec, true);
@@ -851,7 +831,15 @@ int launch_bn_stats(hipStream_t st, const float* x, int64_t M, int C, const floa
     stats_partial_kernel<4><<<grid_of(g), kThreads, 0, st>>>(x, M, C, g, partial);
   else
     stats_partial_kernel<1><<<grid_of(g), kThreads, 0, st>>>(x, M, C, g, partial);
-  return launch_bn_stats_finalize(st, partial, g.gridY, x, M, C, gamma, beta, K, stats, sw);
+  *nb = g.gridY;
+  return hip_status();
+}
+
+int launch_bn_stats(hipStream_t st, const float* x, int64_t M, int C, const float* gamma,
+                    const float* beta, int K, void* scratch, void* stats, const SplitWeights& sw) {
+  int nb;
+  if (int e = launch_bn_stats_partial(st, x, M, C, scratch, &nb)) return e;
+  return launch_bn_stats_finalize(st, static_cast<double*>(scratch), nb, x, M, C, gamma, beta, K, stats, sw);
 }
 
 // Second pass of the statistics from `nb` partial rows [nb][2][C]; `shift_row` is the row whose
