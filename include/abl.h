@@ -93,8 +93,9 @@ size_t abl_scratch_bytes(const abl_shape* shape, int K);
 /* Which kernels abl_forward uses for this shape when y does not alias x (for tools that report the
  * launches of a layer step): 1 = one kernel applies Eq. 1-3 and Eq. 9 while it stages the input of
  * the contraction (the one that abl_bn_conv_fwd launches), 0 = the normalise-ReLU-pack pass followed
- * by the plain contraction (abl_bn_relu_pack, abl_conv_fwd), also for shapes that abl_bn_conv_fwd
- * would take, where that is faster (1x1 layers with long contractions, many 3x3 layers).
+ * by the plain contraction (abl_bn_relu_pack, abl_conv_fwd) or a kernel with their results bit for
+ * bit (layers of few channels), also for shapes that abl_bn_conv_fwd would take, where that is
+ * faster (1x1 layers with long contractions, many 3x3 layers).
  * Negative (an ABL_ERR_ code, negated) on invalid arguments.  flags as for
  * abl_forward. */
 int abl_forward_is_fused(const abl_shape* shape, int K, uint32_t flags);

@@ -27,6 +27,7 @@ UNITS = {
     "conv_image.hip": ["-ffp-contract=off"],
     "conv_ragged.hip": ["-ffp-contract=off"],
     "conv_c16.hip": ["-ffp-contract=off"],
+    "conv_narrow.hip": ["-ffp-contract=off"],
     "conv_split.hip": ["-ffp-contract=off"],
     "wgrad_split.hip": ["-ffp-contract=off"],
     "abl_api.hip": [],

@@ -195,6 +195,8 @@ namespace {
 // Which forward kernel a layer with separate input and output takes: 1 = the 'same' stride-1 kernel
 // with the Eq. 1-3 / Eq. 9 prologue, 2 = the 1x1 kernel with it, 0 = pack pass + plain contraction.
 inline bool aliased(const void* a, const void* b) { return a == b; }
+// Layers of few channels whose forward has the prologue.
+bool narrow_fuses(const ConvGeom& g) { return g.Cin % 4 == 0 && g.Cout % 4 == 0 && c16_tiles(g, 0) == 0 && narrow_pays(g); }
 // (*split_rows: path 1 on the split-operand kernel, rows of its sums of y; 0 = the halo kernel.)
 int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, bool naive, int* split_rows) {
   *split_rows = 0;
@@ -263,6 +265,19 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
       return launch_c16_fwd(st, g, K, x, W, chained ? in_partial : static_cast<const double*>(red), nb, chained ? nullptr : x, gamma,
                             beta, stats, skip, y, packed, out_partial);
     }
+  // layers of few channels, in fours: the same
+  if (!bf16 && !naive && K != 32 && !aliased(x, y) && narrow_fuses(g)) {
+    const bool chained = in_partial != nullptr && in_nb > 0, fold = !chained || in_nb <= 2 * narrow_fwd_rows(g);
+    int nb = in_nb;
+    if (!chained)
+      if (int e = launch_bn_stats_partial(st, x, M, s->Cin, red, &nb, narrow_fwd_rows(g))) return e;
+    const double* const rows = chained ? in_partial : static_cast<const double*>(red);
+    const float* const shift = chained ? nullptr : x;
+    if (!fold)
+      if (int e = launch_bn_stats_finalize(st, rows, nb, shift, M, s->Cin, gamma, beta, K, stats)) return e;
+    if (out_nb != nullptr && out_partial != nullptr) *out_nb = narrow_fwd_blocks(g);
+    return launch_narrow_fwd(st, g, K, x, W, rows, fold ? nb : 0, shift, gamma, beta, stats, skip, y, packed, out_partial);
+  }
   // weights of a split-operand convolution: split by the launch of the second pass of Eq. 1, which leaves most of the chip
   // idle
   SplitWeights sw{};
@@ -304,9 +319,7 @@ int abl_forward_is_fused(const abl_shape* s, int K, uint32_t flags) {
   if (int e = check_k(K)) return -e;
   if (flags & ~(uint32_t)(ABL_MATH_BF16 | ABL_NAIVE_FWD)) return -ABL_ERR_ARG;
   int split_rows;
-  return forward_fused_path(*s, geom_of(*s), K, (flags & ABL_MATH_BF16) != 0, (flags & ABL_NAIVE_FWD) != 0 && K != 32, &split_rows) != 0
-             ? 1
-             : 0;
+  return forward_fused_path(*s, geom_of(*s), K, (flags & ABL_MATH_BF16) != 0, (flags & ABL_NAIVE_FWD) != 0 && K != 32, &split_rows) != 0 ? 1 : 0;
 }
 
 int abl_forward(void* stream, const abl_shape* s, int K, uint32_t flags, const float* x, const float* W,
@@ -330,6 +343,7 @@ namespace {
 // Parts of the weights that the data gradient of this layer is to read, 0 = none.  own_launch: see parts_pay.
 int backward_parts(const ConvGeom& g, int K, bool bf16, bool own_launch) {
   if (K == 32 || g.Cout % 32 != 0 || g.Cin % 64 != 0) return 0;   // (nor the 16-channel kernel's layers)
+  if (!bf16 && narrow_pays(g)) return 0;
   if (!parts_pay(g, 1, bf16, own_launch)) return 0;
   if (!bf16) return split_conv_blocks(g, 1, false, true) > 0 ? 3 : 0;
   return bf16_gemm_supported(g, 1) && bf16_dgrad_reduce_splits(g) ? 1 : 0;
@@ -356,6 +370,26 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   const bool accum = (flags & ABL_ACCUM_DX) != 0;
   const ConvGeom g = geom_of(*s);
+  if (K != 32 && !bf16 && c16_tiles(g, 1) == 0 && narrow_pays(g)) {
+    const int64_t n = (int64_t)g.R * g.S * s->Cin * s->Cout;
+    const int64_t own = (int64_t)(wgrad_partial_bytes(*s) / (n * sizeof(float))), all = M * s->Cin / n;
+    int rows = 0, copies = 0;
+    // both contractions in one launch, the copies of dW in their own place; or one after the other, the copies in that of dA3
+    const bool one = own >= 1 && (own >= 16 || own >= all);
+    if (narrow_bwd_blocks(g, one ? own : all, one, &rows, &copies)) {
+      float* const at = one ? static_cast<float*>(wpart) : da3;
+      DwSum dwsum{at, copies, n, dW};
+      if (one) {
+        if (int e = launch_narrow_bwd(st, g, K, 3, dy, W, packed, stats, da3, static_cast<double*>(red), at, own)) return e;
+      } else {
+        if (int e = launch_narrow_bwd(st, g, K, 2, dy, W, packed, stats, nullptr, nullptr, at, all)) return e;
+        if (int e = launch_split_weights(st, SplitWeights{}, &dwsum)) return e;
+        if (int e = launch_narrow_bwd(st, g, K, 1, dy, W, packed, stats, da3, static_cast<double*>(red), nullptr, 0)) return e;
+      }
+      return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, rows, dx, dgamma, dbeta, one ? &dwsum : nullptr, 0.0f,
+                                  next);
+    }
+  }
   // A 3x3 weight gradient whose copies do not fill the chip in the layer's own room makes as many as the place of dA3 holds: there,
   // before dA3 comes, summed by the launch that splits the weights where there is one - or behind dA3 as always, where a stack's
   // workspace has the room.  How many they are, and with them the rounding of dW, depends on the layer's shape alone.  (64 -> 64
@@ -562,8 +596,11 @@ int abl_bn_conv_fwd(void* stream, const abl_shape* s, int K, uint32_t flags, con
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   if (igemm_fused_supported(*s))
     return launch_conv_fwd_fused((hipStream_t)stream, *s, K, bf16, x, stats, W, skip, y, packed);
+  if (!bf16 && narrow_fuses(g) && halo_fused_supported(g))   // (as abl_forward does, here and below)
+    return launch_narrow_fwd((hipStream_t)stream, g, K, x, W, nullptr, 0, nullptr, nullptr, nullptr, const_cast<void*>(stats), skip, y,
+                             packed, nullptr);
   int split_rows;
-  if (forward_fused_path(*s, g, K, bf16, false, &split_rows) == 1 && split_rows > 0)   // (as abl_forward does)
+  if (forward_fused_path(*s, g, K, bf16, false, &split_rows) == 1 && split_rows > 0)
     return launch_split_fwd_fused((hipStream_t)stream, g, K, x, stats, W, skip, y, packed, nullptr);
   if (!halo_fused_supported(g)) return ABL_ERR_SHAPE;
   if (!bf16 && c16_tiles(g, 0) > 0)
@@ -604,6 +641,10 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
     return ABL_ERR_ARG;
   const ConvGeom g = geom_of(*s);
   if (scratch_bytes < bn_partial_bytes(rows_of(*s), s->Cin)) return ABL_ERR_SCRATCH;
+  if (!(flags & ABL_MATH_BF16) && g.stride == 1 && narrow_pays(g) && reduce_stage_accepts(g)) {   // the kernel of abl_conv_dgrad
+    *rows = narrow_dgrad_rows(g);
+    return launch_narrow_bwd((hipStream_t)stream, g, K, 1, dy, W, packed, stats, da3, static_cast<double*>(scratch), nullptr, 0);
+  }
   if (const int nb = !(flags & ABL_MATH_BF16) && reduce_stage_accepts(g) ? split_conv_blocks(g, 1, false, true) : 0) {
     *rows = nb;
     return launch_split_dgrad_reduce((hipStream_t)stream, g, K, false, dy, W, packed, stats, da3,

@@ -58,7 +58,8 @@ int launch_pack(hipStream_t st, const float* a2, int64_t M, int C, int K, const 
 int launch_unpack(hipStream_t st, const void* packed, int64_t M, int C, int K, const void* stats,
                   float* a2t, bool act = false, float slope = 0.0f);
 // The first pass of launch_bn_stats alone: *nb rows of sums around x's first row, in scratch.
-int launch_bn_stats_partial(hipStream_t st, const float* x, int64_t M, int C, void* scratch, int* nb);
+int launch_bn_stats_partial(hipStream_t st, const float* x, int64_t M, int C, void* scratch, int* nb,
+                            int max_rows = kMaxPartialBlocks);
 // The second halves of the two reductions, for partial sums produced elsewhere (conv epilogues).
 size_t bn_means_offset(int C);
 int launch_bn_stats_finalize(hipStream_t st, const double* partial, int nb, const float* shift_row, int64_t M,
@@ -151,6 +152,24 @@ int launch_c16_bwd(hipStream_t st, const ConvGeom& g, int K, const float* dy, co
 int c16_stack_tiles(const abl_layer* layers, int L, int K, int skip_every, size_t room);
 int launch_c16_stack_bwd(hipStream_t st, const abl_layer* layers, int L, int K, float* s, float* t, float* da3, double* const (&rows)[2],
                          float* copies, float* means);
+
+// ---- layers of few channels on split operands, fp32 (conv_narrow.hip) ----
+bool narrow_pays(const ConvGeom& g);
+// Blocks of the forward (rows of its sums of y); 0: not supported.
+int narrow_fwd_blocks(const ConvGeom& g);
+// Rows of the statistics' sums that its blocks should have to add up at most.
+int narrow_fwd_rows(const ConvGeom& g);
+// As launch_c16_fwd (K = 4 / 8: both channel counts in fours), or the convolution of a given A3 (K = 0; x is A3).  y is not x.
+int launch_narrow_fwd(hipStream_t st, const ConvGeom& g, int K, const float* x, const float* w, const double* partial, int nb,
+                      const float* shift, const float* gamma, const float* beta, void* stats, const float* skip, float* y, void* packed,
+                      double* out_partial);
+// Rows of the Eq. 6-7 sums, and copies of dW, at most `room` of them, of both in one launch or of one after the other; false: not
+// supported.
+bool narrow_bwd_blocks(const ConvGeom& g, int64_t room, bool both, int* rows, int* copies);
+int narrow_dgrad_rows(const ConvGeom& g);   // rows of what = 1
+// what: 1 = dA3 and the Eq. 6-7 sums (partial = nullptr: dA3), 2 = the copies of dW, 3 = both.
+int launch_narrow_bwd(hipStream_t st, const ConvGeom& g, int K, int what, const float* dy, const float* w, const void* packed,
+                      const void* stats, float* da3, double* partial, float* copies, int64_t room);
 
 // ---- convolution kernels (conv_kernels.hip) ----
 size_t wgrad_partial_bytes(const abl_shape& s);

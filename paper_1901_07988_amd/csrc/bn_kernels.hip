@@ -41,7 +41,7 @@ struct RowGeom {
 // reduce == true bounds gridY (partials) and keeps >= 64 rows per block so that the
 // partial sums stay below 1/16 of the tensor's bytes.  rows: rows in flight per thread of the
 // element-wise kernel this geometry is for (its ROWS template parameter).
-RowGeom make_geom(int64_t M, int C, int VEC, bool reduce, int rows = kUnroll) {
+RowGeom make_geom(int64_t M, int C, int VEC, bool reduce, int rows = kUnroll, int max_partials = kMaxPartialBlocks) {
   RowGeom g;
   g.CV = C / VEC;
   g.TX = g.CV < 64 ? g.CV : 64;
@@ -57,7 +57,7 @@ RowGeom make_geom(int64_t M, int C, int VEC, bool reduce, int rows = kUnroll) {
   if (reduce) {
     const int64_t min_rpt = (64 + g.TY - 1) / g.TY;
     if (rpt < min_rpt) rpt = min_rpt;
-    const int64_t cap = (passes + kMaxPartialBlocks - 1) / kMaxPartialBlocks;
+    const int64_t cap = (passes + max_partials - 1) / max_partials;
     if (rpt < cap) rpt = cap;
   } else {
     // one batch of rows per thread and no loop: measured best from 50 MB tensors up
@@ -823,10 +823,10 @@ int launch_split_weights(hipStream_t st, const SplitWeights& sw, const DwSum* dw
   return hip_status();
 }
 
-int launch_bn_stats_partial(hipStream_t st, const float* x, int64_t M, int C, void* scratch, int* nb) {
+int launch_bn_stats_partial(hipStream_t st, const float* x, int64_t M, int C, void* scratch, int* nb, int max_rows) {
   double* partial = static_cast<double*>(scratch);
   const int vec = C % 4 == 0 ? 4 : 1;
-  const RowGeom g = make_geom(M, C, vec, true);
+  const RowGeom g = make_geom(M, C, vec, true, kUnroll, max_rows);
   if (vec == 4)
     stats_partial_kernel<4><<<grid_of(g), kThreads, 0, st>>>(x, M, C, g, partial);
   else

@@ -326,15 +326,15 @@ __global__ __launch_bounds__(kT) void c16_fwd_kernel(C16Fwd a, C16Plan p) {
 #pragma unroll 1
     for (int tap = 0; tap < 9; ++tap) {
       const int ih = h0 + h + tap / 3 - 1, iw = wq + tap % 3 - 1;
-      if ((unsigned)ih >= (unsigned)p.H || (unsigned)iw >= (unsigned)p.W) continue;
+      const bool in = (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;   // (zeros outside take part, as in the patch)
 #pragma unroll 1
       for (int c = 0; c < kC; ++c) {
-        const float d = a.x[((img * p.H + ih) * p.W + iw) * kC + c] - cst[P_MEAN * kC + c];
+        const float d = (in ? a.x[((img * p.H + ih) * p.W + iw) * kC + c] : 0.0f) - cst[P_MEAN * kC + c];
         const float a1 = d * cst[P_RSTD * kC + c];
         const float u = cst[P_GAMMA * kC + c] * a1;
         const float a2 = u + cst[P_BETA * kC + c];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[r] = __builtin_fmaf(a2 > 0.0f ? a2 : 0.0f, a.w[(tap * kC + c) * kC + 4 * lk + r], o[r]);
+        for (int r = 0; r < 4; ++r) o[r] = __builtin_fmaf(in && a2 > 0.0f ? a2 : 0.0f, a.w[(tap * kC + c) * kC + 4 * lk + r], o[r]);
       }
     }
     float4 sk = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -741,10 +741,10 @@ __global__ __launch_bounds__(kT) void c16_bwd_kernel(C16Bwd a, C16Plan p) {
 #pragma unroll 1
       for (int tap = 0; tap < 9; ++tap) {
         const int ih = h0 + h + 1 - tap / 3, iw = wq + 1 - tap % 3;
-        if ((unsigned)ih >= (unsigned)p.H || (unsigned)iw >= (unsigned)p.W) continue;
+        const bool in = (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
 #pragma unroll 1
         for (int c = 0; c < kC; ++c) {
-          const float d = dy_at(((img * p.H + ih) * p.W + iw) * kC, c);
+          const float d = in ? dy_at(((img * p.H + ih) * p.W + iw) * kC, c) : 0.0f;
 #pragma unroll
           for (int r = 0; r < 4; ++r) o[r] = __builtin_fmaf(d, a.w[(tap * kC + 4 * lk + r) * kC + c], o[r]);
         }
@@ -836,9 +836,10 @@ __global__ __launch_bounds__(kT) void c16_bwd_kernel(C16Bwd a, C16Plan p) {
 #pragma unroll 1
       for (int m = 0; m < npix; ++m) {
         const int h = p.by_w.of(m), ih = h0 + h + tap / 3 - 1, iw = m - h * p.W + tap % 3 - 1;
-        if ((unsigned)ih >= (unsigned)p.H || (unsigned)iw >= (unsigned)p.W) continue;
-        const float a2t = dequant<K>(code_at<K>(a.packed, ((img * p.H + ih) * p.W + iw) * kC + c), cst[L_STEP * kC + c],
-                                     __float_as_int(cst[L_FB * kC + c]));
+        const bool in = (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
+        const float a2t = in ? dequant<K>(code_at<K>(a.packed, ((img * p.H + ih) * p.W + iw) * kC + c), cst[L_STEP * kC + c],
+                                          __float_as_int(cst[L_FB * kC + c]))
+                             : 0.0f;
         t = __builtin_fmaf(a2t > 0.0f ? a2t : 0.0f, dy_at(base + m * kC, co), t);
       }
     }

@@ -126,15 +126,12 @@ def test_values_the_split_cannot_carry():
             dy[1, 5, 5, 5] = 3e37
         da3, dW = f32(*x.shape), f32(3, 3, C, C)
         B.abl_conv_bwd_bn_reduce(s9, K, dy, w, packed, stats, scratch, da3, dW)
-        # (positions outside the image take no part: no product of their zeros with an infinity)
-        p, q = torch.nn.functional.pad(dy.double(), (0, 0, 1, 1, 1, 1)), a2t.clamp(min=0).double()
+        # (zeros around the image take part, where they meet an infinity too)
+        p, q = (torch.nn.functional.pad(t, (0, 0, 1, 1, 1, 1)) for t in (dy.double(), a2t.clamp(min=0).double()))
         wd = w.double().flip(0, 1)
         ref = sum((p[:, r:r + 12, c:c + 20, None, :] * wd[r, c]).sum(-1) for r in range(3) for c in range(3))
-        refW = torch.zeros(3, 3, C, C, dtype=torch.float64, device="cuda")
-        for r in range(3):
-            for c in range(3):
-                h0, h1, w0, w1 = max(0, 1 - r), min(12, 13 - r), max(0, 1 - c), min(20, 21 - c)
-                refW[r, c] = (q[:, h0 + r - 1:h1 + r - 1, w0 + c - 1:w1 + c - 1, :, None] * dy.double()[:, h0:h1, w0:w1, None, :]).sum((0, 1, 2))
+        refW = torch.stack([torch.stack([(q[:, r:r + 12, c:c + 20, :, None] * dy.double()[..., None, :]).sum((0, 1, 2)) for c in range(3)])
+                            for r in range(3)])
         for got, want in ((da3, ref.float()), (dW, refW.float())):
             assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
             ok = torch.isfinite(want)
