@@ -398,7 +398,24 @@ __device__ inline bf16x8_t to_bf16x8(const float (&v)[8]) {
 }
 // ---- fp32 operands in three bf16 parts (conv_split.hip) ----
 constexpr float kUp = 0x1p23f, kDown = 0x1p-46f;   // both operands are split as 2^23 times their values
-// 2^23 x = h + m + l, eight values at a time (the parts of two values share a 32-bit word)
+// u holds two bf16 values: a minus the lower or the upper one in one instruction (fp32 result of exact products, here exact).  The
+// selector stays in a scalar register: as a literal constant of the instruction the lower one came out as zero.
+__device__ inline float less_low(float a, uint32_t u) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  uint32_t minus_one = 0x0000BF80u;
+  asm("" : "+s"(minus_one));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, u), __builtin_bit_cast(bf16x2, minus_one), a, false);
+}
+__device__ inline float less_high(float a, uint32_t u) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  uint32_t minus_one = 0xBF800000u;
+  asm("" : "+s"(minus_one));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, u), __builtin_bit_cast(bf16x2, minus_one), a, false);
+}
+// 2^23 x = h + m + l, eight values at a time (the parts of two values share a 32-bit word).
+// TOGETHER: the eight go into the same sums.  Then the remainders of a pair may share an instruction's operand, where an infinity
+// of one makes the other NaN: 9 instead of 13 instructions a pair (a loop of splits 2.10 -> 1.45 ms), the same bits otherwise.
+template <bool TOGETHER = true>
 __device__ inline void split3(const float (&x)[8], bf16x8_t& h, bf16x8_t& m, bf16x8_t& l) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   uint4 hw, mw, lw;
@@ -406,10 +423,16 @@ __device__ inline void split3(const float (&x)[8], bf16x8_t& h, bf16x8_t& m, bf1
     a *= kUp;
     b *= kUp;
     u = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
-    const float ra = a - __uint_as_float(u << 16), rb = b - __uint_as_float(u & 0xFFFF0000u);
-    v = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
-    w = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)(ra - __uint_as_float(v << 16)),
-                                            (__bf16)(rb - __uint_as_float(v & 0xFFFF0000u))});
+    if constexpr (TOGETHER) {
+      const float ra = less_low(a, u), rb = less_high(b, u);
+      v = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
+      w = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)less_low(ra, v), (__bf16)less_high(rb, v)});
+    } else {
+      const float ra = a - __uint_as_float(u << 16), rb = b - __uint_as_float(u & 0xFFFF0000u);
+      v = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)ra, (__bf16)rb});
+      w = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)(ra - __uint_as_float(v << 16)),
+                                              (__bf16)(rb - __uint_as_float(v & 0xFFFF0000u))});
+    }
   };
   two(x[0], x[1], hw.x, mw.x, lw.x);
   two(x[2], x[3], hw.y, mw.y, lw.y);

@@ -621,7 +621,7 @@ __global__ __launch_bounds__(kT) void c16_bwd_kernel(C16Bwd a, C16Plan p) {
         t2[e] = ok && st8[e] * t > 0.0f ? t + t : 0.0f;     // Eq. 10, Eq. 3
       }
       bf16x8_t h, m, l;
-      split3(v, h, m, l);
+      split3<false>(v, h, m, l);   // (the channels of a pixel are columns of dW)
       char* const to = lds + half * kPlane + pos * 16;
       put(to, h);
       put(to + 2 * kPlane, m);
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(kT) void c16_bwd_kernel(C16Bwd a, C16Plan p) {
       } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) t2[e] *= kDown * kUp;    // (split3 takes 2^23 times its argument)
-        split3(t2, h, m, l);
+        split3<false>(t2, h, m, l);
         put(to + kOperand, h);
         put(to + kOperand + 2 * kPlane, m);
         put(to + kOperand + 4 * kPlane, l);

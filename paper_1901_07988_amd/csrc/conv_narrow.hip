@@ -760,7 +760,7 @@ __device__ inline void narrow_wgrad(const NarrowBwd& a, const NarrowPlan& p, cha
       if (idx >= t.ditems) continue;
       below(m < t.npix ? p.Cout - 8 * c : 0, dv[s]);
       bf16x8_t x, y, z;
-      split3(dv[s], x, y, z);
+      split3<false>(dv[s], x, y, z);   // (columns of dW)
       char* const to = lds + c * dplane + m * kPitch;
       put(to, x);
       put(to + 16, y);
@@ -833,7 +833,7 @@ __device__ inline void narrow_wgrad(const NarrowBwd& a, const NarrowPlan& p, cha
           t2[e] *= kDown * kUp;           // (split3 takes 2^23 times its argument)
         }
         bf16x8_t h, m, l;
-        split3(t2, h, m, l);
+        split3<false>(t2, h, m, l);
         x = part == 0 ? h : part == 1 ? m : l;
       }
       put(act + c * plane + pos * 16, x);

@@ -123,8 +123,9 @@ __device__ inline void split_dy(const float (&x)[8], uint4 (&u)[NP]) {
 #pragma unroll
     for (int t = 0; t < NP; ++t) {
       w[t][q] = __builtin_bit_cast(uint32_t, bf16x2_t{(__bf16)a, (__bf16)b});
-      a -= __uint_as_float(w[t][q] << 16);
-      b -= __uint_as_float(w[t][q] & 0xFFFF0000u);
+      if (t + 1 == NP) break;
+      a = less_low(a, w[t][q]);    // (pixels of one channel: the same sums)
+      b = less_high(b, w[t][q]);
     }
   }
 #pragma unroll
