@@ -28,7 +28,7 @@
 // What the k-loop needs to stay at the matrix cores' rate (us before / with all of it, in a stack, both traced on one card: 3x3
 // 256 -> 256 @14x14 75.7 / 71.9, gradient with sums 80.1 / 75.9; 1x1 1024 -> 256 48.3 / 44.5, its mirror's gradient 49.7 / 46.2;
 // 1x1 256 -> 1024 58.0 / 56.4, gradient 58.6 / 56.9; 3x3 64 -> 64 @56x56 106 / 89, gradient 114 / 97; layer call with bf16 operands
-// and 8-bit codes 53 / 43 and 76 / 56.  In the first four the card's power is the bound: the weight gradients between them, the same
+// and 8-bit codes 53 / 43 and 76 / 56 (with its weights further ahead 33 and 45, see AHEAD).  In the first four the card's power is the bound: the weight gradients between them, the same
 // kernels on both sides, took 58 and 62):
 //  - two sets of weight registers in turn.  With one, its copy at every step waits for everything in flight, the next phase's
 //    input too.  (An odd number of steps leaves one copy, at the end of a phase, where the input is awaited anyway.)
@@ -139,6 +139,17 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   // the next phase's input asked for in front of a phase's only step (us, in front / behind its weights: gradient 512 <- 2048
   // @7x7 N=26 53.9 / 61.9, 256 <- 1024 @14x14 N=14 38.4 / 42.1, forward 2048 -> 512 @8x8 N=26 43.4 / 48.9)
   constexpr bool INPUT_FIRST = SHORT && KS == 2;
+  // 3x3 layers with bf16 operands: weights are asked for AHEAD steps before their use, into the registers of the step that has
+  // read them.  A step is 7 or 14 products, 112 or 224 cycles, and with weights one step ahead it waited for the L2; loads come
+  // back in order, so weights that are asked for behind the next phase's input wait for that as well, and with all nine taps'
+  // in flight the input has the whole phase.  With 128 channels per block three sets fit.  (us, forward / gradient, one step
+  // ahead, three, nine: 64 -> 64 @56x56 N=64, 8-bit codes, 43.1 / 56.4, 35.5 / 49.1, 33.4 / 44.5; 256 -> 256 @14x14 N=64 27.4 /
+  // 28.6, 24.3 / 25.3.  fp32 operands, 42 products a step: 64 -> 64 84.5 / 92.3, three ahead 84.1 / 91.3, and five times the code.)
+  constexpr int AHEAD = PRE && NP == 1 && STEPS == 9 ? (NT == 1 ? 9 : 3) : 0;
+  // the lane's offset into the parts, opaque as that of the weights below: 60 registers less with three sets of 128 channels (11
+  // spilled without).  Elsewhere the free order of the loads is worth more (us: nine sets 33.4 / 44.5, opaque 36.8 / 50.6; fp32 256
+  // -> 256 @14x14 70.2 / 76.3, opaque 73.2 / 79.1; bf16 1x1 1024 -> 256 22.0 / 23.0, opaque 22.6 / 24.0, four waves 33.3 / 32.1)
+  constexpr bool OPAQUE = NP == 1 && NT == 2 && (TAPS == 9 || KS == 1);
   static_assert(NF % SLOTS == 0, "a k-step starts in the slot of the one before");
   // the patch: bytes from a position, eight channels, a part and a chunk to the next
   constexpr int NPOS = SU * THREADS / C8;
@@ -193,13 +204,15 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   };
 
   // PRE: the parts of a k-step in fragment order, a kilobyte per output-channel tile and part
+  uint32_t p_lane = 16u * lane;
   auto load_parts = [&](auto& raw, int tap, int c0) __attribute__((always_inline)) {
-    const uint4* wb = parts + ((size_t)(tap * (Cg / 32) + c0 / 32) * (Ng / 16) + n0 / 16) * (64 * NP);
+    if constexpr (OPAQUE) asm volatile("" : "+v"(p_lane));   // (as above)
+    const char* wb = reinterpret_cast<const char*>(parts + ((size_t)(tap * (Cg / 32) + c0 / 32) * (Ng / 16) + n0 / 16) * (64 * NP));
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int q = 0; q < NP; ++q) {
-        const uint4 v = wb[(j * NP + q) * 64 + lane];
+        const uint4 v = *reinterpret_cast<const uint4*>(wb + (j * NP + q) * 1024 + p_lane);
         raw[j][4 * q] = v.x, raw[j][4 * q + 1] = v.y, raw[j][4 * q + 2] = v.z, raw[j][4 * q + 3] = v.w;
       }
   };
@@ -357,12 +370,13 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     // everything in flight at the copy.)  Where the kernel splits them one set does: a step splits it before it asks for the next.
     constexpr int RW = PRE ? 4 * NP : 8;
     constexpr int ODD = PRE ? 1 : 0;   // set of the steps with odd numbers
-    uint32_t wset[1 + ODD][NT][RW];
+    uint32_t wset[AHEAD > 0 ? AHEAD : 1 + ODD][NT][RW];
     auto load_set = [&](uint32_t (&w)[NT][RW], int tap, int c0) __attribute__((always_inline)) {
       if constexpr (PRE) load_parts(w, tap, c0);
       else load_w(w, tap, c0);
     };
-    load_set(wset[0], 0, kg * CPP * 32);
+#pragma unroll
+    for (int d = 0; d < (AHEAD > 0 ? AHEAD : 1); ++d) load_set(wset[d], d, kg * CPP * 32);
     // the epilogue's codes, behind the last k-steps
     auto load_codes = [&]() __attribute__((always_inline)) {
       if constexpr (EPI > 1) {
@@ -404,7 +418,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       }
       // the next k-step's weights (the very last step asks for its own again: no branch)
       const bool wrap = ks + 1 == STEPS, end = wrap && ph + 1 == nph;
-      {
+      if constexpr (AHEAD == 0) {
         const int nks = end ? ks : wrap ? 0 : ks + 1;
         const int ncc = nks / TAPS, ntap = nks - ncc * TAPS;
         load_set(fill, ntap, (wrap && !end ? ph + 1 : ph) * CH + (kg * CPP + ncc) * 32);
@@ -440,6 +454,10 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
             for (int j = 0; j < NT; ++j) lo[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], x, lo[j][i], 0, 0, 0);
         }
       }
+      if constexpr (AHEAD > 0) {   // into the registers that the step has read
+        if (ks + AHEAD < STEPS) load_set(fill, ks + AHEAD, ph * CH + kg * 32);
+        else if (last != 1) load_set(fill, ks + AHEAD - STEPS, (last == 2 && ph + 1 == nph ? ph : ph + 1) * CH + kg * 32);
+      }
     };
     auto phase = [&](int ph, auto last_c) __attribute__((always_inline)) {
       constexpr int last = decltype(last_c)::value;
@@ -457,6 +475,16 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
       // each set in its own registers; an odd number of steps leaves the next weights in the wrong one.  (Few copies of the
       // step's code: a kernel starts with a cold instruction cache.)
       if constexpr (STEPS >= 9) __builtin_amdgcn_s_setprio(3);
+      if constexpr (AHEAD > 0) {
+#pragma unroll
+        for (int ks = 0; ks < STEPS; ++ks) {
+          if (ks == 3) __builtin_amdgcn_s_setprio(2);
+          else if (ks == 5) __builtin_amdgcn_s_setprio(1);
+          else if (ks == 7) __builtin_amdgcn_s_setprio(0);
+          k_step(wset[ks % AHEAD], wset[ks % AHEAD], ph, ks, cur, ks == 0, last);
+        }
+        return;
+      }
       k_step(wset[0], wset[ODD], ph, 0, cur, true, last);
       if constexpr (STEPS == 2) k_step(wset[ODD], wset[0], ph, 1, cur, false, last);
       if constexpr (STEPS >= 9) {
