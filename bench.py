@@ -120,8 +120,8 @@ MEASURED_TRAFFIC = {
         ("64x56x56x64x256x1x1x1x0", "conv_dgrad_bn_reduce"): 265.67e6,
     },
     ("config2", 4, "fp32"): {
-        ("128x32x32x16x16x3x3x1x1", "bn_conv_fwd"): 23.77e6,         # in the stack: half the layers also read a shortcut
-        ("128x32x32x16x16x3x3x1x1", "conv_bwd_bn_reduce"): 25.79e6,  # includes 4.7 MB of per-tile dW copies
+        ("128x32x32x16x16x3x3x1x1", "bn_conv_fwd"): 18.62e6,         # in the stack: half the layers also read a shortcut
+        ("128x32x32x16x16x3x3x1x1", "conv_bwd_bn_reduce"): 21.16e6,  # includes 2.4 MB of per-block dW copies
     },
 }
 
