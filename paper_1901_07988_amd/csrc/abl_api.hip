@@ -346,7 +346,7 @@ int backward_parts(const ConvGeom& g, int K, bool bf16, bool own_launch) {
   if (!bf16 && narrow_pays(g)) return 0;
   if (!parts_pay(g, 1, bf16, own_launch)) return 0;
   if (!bf16) return split_conv_blocks(g, 1, false, true) > 0 ? 3 : 0;
-  return bf16_gemm_supported(g, 1) && bf16_dgrad_reduce_splits(g) ? 1 : 0;
+  return bf16_gemm_supported(g, 1) && bf16_dgrad_reduce_splits(g, true) ? 1 : 0;
 }
 
 // Offset of the copies of the weight gradient in a layer's workspace.
@@ -454,7 +454,7 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
                                 dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
   }
   // bf16 operands on the 32-deep matrix instruction: the same sums in the epilogue of its kernels
-  if (const int nr = (K != 32 && bf16_gemm) ? bf16_dgrad_reduce_rows(g) : 0) {
+  if (const int nr = (K != 32 && bf16_gemm) ? bf16_dgrad_reduce_rows(g, parts != nullptr) : 0) {
     if (int e = launch_bf16_dgrad_reduce(st, g, K, dy, W, packed, stats, da3, static_cast<double*>(red), parts)) return e;
     DwSum dwsum;
     if (int e = weight_gradient(&dwsum)) return e;

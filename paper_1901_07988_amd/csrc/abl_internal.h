@@ -229,17 +229,19 @@ bool bf16_gemm_supported(const ConvGeom& g, int mode);
 int launch_bf16_gemm(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
                      float* out, double* sums = nullptr, int* rows = nullptr);
 // Gradient to the conv input with the Eq. 6-7 sums from the layer's codes (K = 4 / 8) in the epilogue of
-// whichever bf16 kernel takes the shape: partial = [rows][2][Cin] doubles; bf16_dgrad_reduce_rows = 0 if none does.
-int bf16_dgrad_reduce_rows(const ConvGeom& g);
+// whichever bf16 kernel takes the shape: partial = [rows][2][Cin] doubles; bf16_dgrad_reduce_rows = 0 if none does.  parts:
+// whether the weights come in parts as well.
+int bf16_dgrad_reduce_rows(const ConvGeom& g, bool parts);
 int launch_bf16_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
                              const void* packed, const void* stats, float* da3, double* partial,
                              const void* parts = nullptr);
 // Whether that is split_conv_kernel with one part, which can read `parts`.
-bool bf16_dgrad_reduce_splits(const ConvGeom& g);
+bool bf16_dgrad_reduce_splits(const ConvGeom& g, bool parts);
 // 3x3 'same' stride-1 convolutions whose whole image fits in LDS as bf16 (up to 208 pixels, e.g.
 // 14x14 with 256 channels): one block per image and 64 output channels.
 // sums (nullable, mode 0): [N][2][Cout] doubles = per-image sum(y), sum(y^2) of the output.
-bool image_bf16_supported(const ConvGeom& g, int mode);
+// parts: the weights come in parts as well, which split_conv_kernel reads.
+bool image_bf16_supported(const ConvGeom& g, int mode, bool parts = false);
 int launch_image_bf16(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w,
                       const float* skip, float* out, double* sums);
 
@@ -256,6 +258,7 @@ int split_conv_blocks(const ConvGeom& g, int mode, bool bf16 = false, bool sums 
 bool parts_pay(const ConvGeom& g, int mode, bool bf16, bool own_launch);
 // Whether split_conv_kernel with bf16 operands is faster than the image-resident kernel on a 3x3 layer that both take.
 bool split_beats_image(const ConvGeom& g, int mode);
+bool split_parts_beat_image(const ConvGeom& g, int mode);   // ... with the weights in parts
 // The fp32 forward of a 1x1 layer with a pass of its own for Eq. 1-3 and 9 in front is faster than the pointwise kernel's
 // prologue.
 bool split_beats_prologue(const ConvGeom& g);

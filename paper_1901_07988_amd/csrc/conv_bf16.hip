@@ -646,23 +646,23 @@ int launch_bf16_gemm(hipStream_t st, const ConvGeom& g, int mode, const float* i
   return launch_gemm<1, 0>(st, g, in, w, nullptr, out, nullptr, nullptr, nullptr);
 }
 
-int bf16_dgrad_reduce_rows(const ConvGeom& g) {
-  if (image_bf16_supported(g, 1)) return g.N <= kMaxPartialBlocks ? g.N : 0;
+int bf16_dgrad_reduce_rows(const ConvGeom& g, bool parts) {
+  if (image_bf16_supported(g, 1, parts)) return g.N <= kMaxPartialBlocks ? g.N : 0;
   if (const int nb = split_conv_blocks(g, 1, true, true)) return nb;
   return bf16_gemm_supported(g, 1) ? gemm_sum_rows(g, 1) : 0;
 }
 
-bool bf16_dgrad_reduce_splits(const ConvGeom& g) {
-  return !image_bf16_supported(g, 1) && split_conv_blocks(g, 1, true, true) > 0;
+bool bf16_dgrad_reduce_splits(const ConvGeom& g, bool parts) {
+  return !image_bf16_supported(g, 1, parts) && split_conv_blocks(g, 1, true, true) > 0;
 }
 
 int launch_bf16_dgrad_reduce(hipStream_t st, const ConvGeom& g, int K, const float* dy, const float* w,
                              const void* packed, const void* stats, float* da3, double* partial, const void* parts) {
-  if ((K != 4 && K != 8) || bf16_dgrad_reduce_rows(g) == 0) return ABL_ERR_SHAPE;
+  if ((K != 4 && K != 8) || bf16_dgrad_reduce_rows(g, parts != nullptr) == 0) return ABL_ERR_SHAPE;
   const uint8_t* codes = static_cast<const uint8_t*>(packed);
   const float* sp = static_cast<const float*>(stats);
-  if (image_bf16_supported(g, 1)) return launch_image_bf16_epi(st, g, K, dy, w, da3, partial, codes, sp);
-  if (bf16_dgrad_reduce_splits(g))
+  if (image_bf16_supported(g, 1, parts != nullptr)) return launch_image_bf16_epi(st, g, K, dy, w, da3, partial, codes, sp);
+  if (bf16_dgrad_reduce_splits(g, parts != nullptr))
     return launch_split_dgrad_reduce(st, g, K, true, dy, w, packed, stats, da3, partial, parts);
   if (K == 4) return launch_gemm<1, 4>(st, g, dy, w, nullptr, da3, partial, codes, sp);
   return launch_gemm<1, 8>(st, g, dy, w, nullptr, da3, partial, codes, sp);
@@ -681,14 +681,15 @@ size_t image_lds_bytes(const ConvGeom& g, int mode) {
 }
 }  // namespace
 
-bool image_bf16_supported(const ConvGeom& g, int mode) {
+bool image_bf16_supported(const ConvGeom& g, int mode, bool parts) {
   const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
   if (g.R != 3 || g.S != 3 || g.stride != 1 || g.pad != 1) return false;
   if (Cg < 32 || Cg > 1024 || (Cg & (Cg - 1)) != 0 || Ng % IMG_NB != 0) return false;
   if (image_mt(g) == 0 || g.H * g.W * g.W >= 65536) return false;
   if (image_lds_bytes(g, mode) > (size_t)160 * 1024) return false;
   const int64_t e_in = (int64_t)g.N * g.H * g.W * g.Cin, e_out = (int64_t)g.N * g.Ho * g.Wo * g.Cout;
-  return e_in < ((int64_t)1 << 31) && e_out < ((int64_t)1 << 31) && !split_beats_image(g, mode);
+  return e_in < ((int64_t)1 << 31) && e_out < ((int64_t)1 << 31) &&
+         !(parts ? split_parts_beat_image(g, mode) : split_beats_image(g, mode));
 }
 
 namespace {

@@ -930,7 +930,7 @@ size_t wgrad_partial_bytes(const abl_shape& s) {
 int conv_fwd_parts(const ConvGeom& g, bool bf16) {
   if (!mfma_ok(g)) return 0;
   if (!bf16) return split_conv_blocks(g, 0) > 0 ? 3 : 0;
-  return !image_bf16_supported(g, 0) && (g.R == 3 || g.Cout % 128 == 0) && split_conv_blocks(g, 0, true) > 0 ? 1 : 0;
+  return !image_bf16_supported(g, 0, true) && (g.R == 3 || g.Cout % 128 == 0) && split_conv_blocks(g, 0, true) > 0 ? 1 : 0;
 }
 
 int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* a3, const float* w,
@@ -944,7 +944,7 @@ int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* 
   }
   if (!mfma_ok(g)) return launch_ragged_conv(st, g, 0, a3, w, skip, y);
   // bf16 operands: the 32-deep bf16 matrix instruction with bf16 tiles in LDS
-  if (bf16 && image_bf16_supported(g, 0)) {
+  if (bf16 && image_bf16_supported(g, 0, parts != nullptr)) {
     const bool want = sums != nullptr && rows != nullptr && g.N <= kMaxPartialBlocks;
     if (want) *rows = g.N;
     return launch_image_bf16(st, g, 0, a3, w, skip, y, want ? sums : nullptr);

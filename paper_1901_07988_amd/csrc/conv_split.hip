@@ -1023,6 +1023,14 @@ bool split_beats_image(const ConvGeom& g, int mode) {
   return n >= 128 || Cg < 512 || (int64_t)g.N * (Ng / 64) > 256;
 }
 
+// ... and where the weights come in parts, which the image kernel does not read: with 512 channels and more to contract, on every
+// grid (us, layer, image kernel / here: 512 -> 512 @8x8 N=40 192 / 117, N=14 112 / 93, @7x7 N=28 115 / 100; 256 -> 256 about the
+// same on both, @14x14 N=40 105.7 / 106.4, @10x10 N=52 91.0 / 87.8).
+bool split_parts_beat_image(const ConvGeom& g, int mode) {
+  Plan p;
+  return split_beats_image(g, mode) || ((mode == 0 ? g.Cin : g.Cout) >= 512 && make_plan(g, mode, 1, mode == 1, p));
+}
+
 // Four-wave grids that fill less than three quarters of their 512 places are not (512 -> 128 @28x28, step, us, with the
 // pass / with the prologue: N=16, eight-wave blocks, 40.0 / 41.6; N=24, n = 336, 56.7 / 53.0; N=28, n = 392, 59.9 / 64.9),
 // nor are shorter contractions, but for 256 -> 256 and where the pointwise kernel's tiles are more than a round of the units
