@@ -237,54 +237,60 @@ SplitWeights weights_to_split(const abl_shape& s, int mode, int np, const float*
 // workspace only until the convolution has read it (Sec. 3.2: full-precision intermediates
 // are overwritten as soon as they have been used); 'same' stride-1 convolutions do not even
 // write it.
-//   in_partial / in_nb : first-pass sums of x's statistics left by the producer of x (nullable)
-//   out_partial        : where to leave the first-pass sums of y's statistics (nullable);
-//                        *out_nb = number of partial rows written, 0 if this layer could not
+// Rows of first-pass sums of a tensor's statistics that its producer left (nb = 0: none).
+struct SumRows {
+  double* at;
+  int nb;
+};
+//   in          : the sums of x
+//   out_partial : where to leave those of y (nullable); out->nb = 0 if this layer could not
+//   out_apart   : the same, for a convolution that adds up the rows of `in` itself where those are in out_partial: its blocks
+//                 read all of them at their start and write their own at their end, when others have yet to begin
 int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, const float* x, const float* W,
                  const float* gamma, const float* beta, const float* skip, void* scratch, float* y,
-                 void* packed, void* stats, const double* in_partial, int in_nb, double* out_partial,
-                 int* out_nb) {
+                 void* packed, void* stats, const SumRows& in, double* out_partial, double* out_apart, SumRows* out) {
   const int64_t M = rows_of(*s);
   const size_t act = up256((size_t)M * s->Cin * sizeof(float));
   float* a3 = static_cast<float*>(scratch);
   void* red = static_cast<char*>(scratch) + act;
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   const bool naive = (flags & ABL_NAIVE_FWD) != 0 && K != 32;
-  if (out_nb != nullptr) *out_nb = 0;
+  *out = SumRows{nullptr, 0};
   const ConvGeom g = geom_of(*s);
+  const bool chained = in.nb > 0;
+  double* const apart = chained && in.at == out_partial ? out_apart : out_partial;
   int split_rows = 0;
   const int path = aliased(x, y) ? 0 : forward_fused_path(*s, g, K, bf16, naive, &split_rows);
   // 16-channel 3x3 layers: the second pass of Eq. 1 goes along with the convolution
   if (path == 1 && !bf16 && split_rows == 0)
     if (const int tiles = c16_tiles(g, 0)) {
-      const bool chained = in_partial != nullptr && in_nb > 0;
-      int nb = in_nb;
+      int nb = in.nb;
       if (!chained)
         if (int e = launch_bn_stats_partial(st, x, M, s->Cin, red, &nb)) return e;
-      if (out_nb != nullptr && out_partial != nullptr) *out_nb = tiles;
-      return launch_c16_fwd(st, g, K, x, W, chained ? in_partial : static_cast<const double*>(red), nb, chained ? nullptr : x, gamma,
-                            beta, stats, skip, y, packed, out_partial);
+      if (apart != nullptr) *out = SumRows{apart, tiles};
+      return launch_c16_fwd(st, g, K, x, W, chained ? in.at : static_cast<const double*>(red), nb, chained ? nullptr : x, gamma,
+                            beta, stats, skip, y, packed, apart);
     }
   // layers of few channels, in fours: the same
   if (!bf16 && !naive && K != 32 && !aliased(x, y) && narrow_fuses(g)) {
-    const bool chained = in_partial != nullptr && in_nb > 0, fold = !chained || in_nb <= 2 * narrow_fwd_rows(g);
-    int nb = in_nb;
+    const bool fold = !chained || in.nb <= 2 * narrow_fwd_rows(g);
+    int nb = in.nb;
     if (!chained)
       if (int e = launch_bn_stats_partial(st, x, M, s->Cin, red, &nb, narrow_fwd_rows(g))) return e;
-    const double* const rows = chained ? in_partial : static_cast<const double*>(red);
+    const double* const rows = chained ? in.at : static_cast<const double*>(red);
     const float* const shift = chained ? nullptr : x;
     if (!fold)
       if (int e = launch_bn_stats_finalize(st, rows, nb, shift, M, s->Cin, gamma, beta, K, stats)) return e;
-    if (out_nb != nullptr && out_partial != nullptr) *out_nb = narrow_fwd_blocks(g);
-    return launch_narrow_fwd(st, g, K, x, W, rows, fold ? nb : 0, shift, gamma, beta, stats, skip, y, packed, out_partial);
+    if (apart != nullptr) *out = SumRows{apart, narrow_fwd_blocks(g)};
+    return launch_narrow_fwd(st, g, K, x, W, rows, fold ? nb : 0, shift, gamma, beta, stats, skip, y, packed, apart);
   }
   // weights of a split-operand convolution: split by the launch of the second pass of Eq. 1, which leaves most of the chip
   // idle
   SplitWeights sw{};
   if (const int np = !parts_pay(g, 0, bf16, false) ? 0 : split_rows > 0 ? 3 : path == 0 ? conv_fwd_parts(g, bf16) : 0)
     sw = weights_to_split(*s, 0, np, W, static_cast<char*>(red) + up256(bn_partial_bytes(M, s->Cin)), wgrad_partial_bytes(*s));
-  if (in_partial != nullptr && in_nb > 0) {
-    if (int e = launch_bn_stats_finalize(st, in_partial, in_nb, nullptr, M, s->Cin, gamma, beta, K, stats, sw)) return e;
+  if (chained) {
+    if (int e = launch_bn_stats_finalize(st, in.at, in.nb, nullptr, M, s->Cin, gamma, beta, K, stats, sw)) return e;
   } else {
     if (int e = launch_bn_stats(st, x, M, s->Cin, gamma, beta, K, red, stats, sw)) return e;
   }
@@ -293,7 +299,7 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
   // overwrite input pixels that a neighbouring block has not staged yet.)
   if (split_rows > 0) {
     if (int e = launch_split_fwd_fused(st, g, K, x, stats, W, skip, y, packed, out_partial, sw.out)) return e;
-    if (out_partial != nullptr && out_nb != nullptr) *out_nb = split_rows;
+    if (out_partial != nullptr) *out = SumRows{out_partial, split_rows};
     return ABL_OK;
   }
   if (path == 1) {
@@ -301,13 +307,14 @@ int forward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, cons
     const bool want = out_partial != nullptr && tiles > 0 && tiles <= kMaxPartialBlocks;
     if (int e = launch_halo_fwd_fused(st, g, K, bf16, x, stats, W, skip, y, packed, want ? out_partial : nullptr))
       return e;
-    if (want && out_nb != nullptr) *out_nb = tiles;
+    if (want) *out = SumRows{out_partial, tiles};
     return ABL_OK;
   }
   // 1x1 convolutions do the same while they stage their A tile
-  if (path == 2) return launch_conv_fwd_fused(st, *s, K, bf16, x, stats, W, skip, y, packed, out_partial, out_nb);
+  out->at = out_partial;
+  if (path == 2) return launch_conv_fwd_fused(st, *s, K, bf16, x, stats, W, skip, y, packed, out_partial, &out->nb);
   if (int e = launch_bn_relu_pack(st, x, M, s->Cin, K, stats, a3, packed, naive)) return e;
-  return launch_conv_fwd(st, *s, bf16, a3, W, skip, y, out_partial, out_nb, sw.out);
+  return launch_conv_fwd(st, *s, bf16, a3, W, skip, y, out_partial, &out->nb, sw.out);
 }
 
 }  // namespace
@@ -332,8 +339,9 @@ int abl_forward(void* stream, const abl_shape* s, int K, uint32_t flags, const f
       bad_ptr(packed) || bad_ptr(stats) || (skip != nullptr && !aligned16(skip)))
     return ABL_ERR_ARG;
   if (scratch_bytes < abl_scratch_bytes(s, K)) return ABL_ERR_SCRATCH;
-  return forward_impl((hipStream_t)stream, s, K, flags, x, W, gamma, beta, skip, scratch, y, packed, stats,
-                      nullptr, 0, nullptr, nullptr);
+  SumRows none;
+  return forward_impl((hipStream_t)stream, s, K, flags, x, W, gamma, beta, skip, scratch, y, packed, stats, SumRows{nullptr, 0},
+                      nullptr, nullptr, &none);
 }
 
 }  // extern "C"
@@ -931,8 +939,8 @@ int abl_stack_forward_traced(void* stream, const abl_layer* layers, int32_t L, i
       if (trace[i] != nullptr && !aligned16(trace[i])) return ABL_ERR_ARG;
   const size_t xbytes = stack_xpart_bytes(layers, L);
   double* xpart = static_cast<double*>(scratch);
-  void* lscratch = static_cast<char*>(scratch) + xbytes;
-  int in_nb = 0;
+  char* const lscratch = static_cast<char*>(scratch) + xbytes;
+  SumRows in{nullptr, 0};
   for (int i = 0; i < L; ++i) {
     const abl_layer& l = layers[i];
     const GroupInfo gi = group_info(layers, L, skip_every, i);
@@ -942,14 +950,18 @@ int abl_stack_forward_traced(void* stream, const abl_layer* layers, int32_t L, i
     float* y = y_is_s ? buf_s : buf_t;
     const float* skip = gi.in_group && gi.last && gi.shortcut ? buf_s : nullptr;
     if (int e = trace_copy((hipStream_t)stream, trace, i, x, (size_t)rows_of(l.shape) * l.shape.Cin)) return e;
-    // layer i's convolution leaves the first-pass statistics of its output (= layer i+1's input)
-    // in `xpart` when it can; layer i+1 then only runs the finalize kernel
-    int out_nb = 0;
+    // layer i's convolution leaves the first-pass statistics of its output (= layer i+1's input) when it can, in `xpart` or, while
+    // it reads its own there, where layer i+1 would have the rows of a first pass of its own: behind that layer's tensor in the
+    // workspace, which layer i does not use then.  Layer i+1 starts with the second pass
+    double* const xout = i + 1 < L ? xpart : nullptr;
+    double* const apart =
+        i + 1 < L ? reinterpret_cast<double*>(lscratch + up256((size_t)rows_of(layers[i + 1].shape) * layers[i + 1].shape.Cin * sizeof(float)))
+                  : nullptr;
+    SumRows rows;
     if (int e = forward_impl((hipStream_t)stream, &l.shape, K, flags, x, l.W, l.gamma, l.beta, skip, lscratch, y,
-                             l.packed, l.stats, in_nb > 0 ? xpart : nullptr, in_nb,
-                             i + 1 < L ? xpart : nullptr, &out_nb))
+                             l.packed, l.stats, in, xout, apart, &rows))
       return e;
-    in_nb = out_nb;
+    in = rows;
   }
   return ABL_OK;
 }

@@ -139,7 +139,8 @@ int launch_halo_bwd16(hipStream_t st, const ConvGeom& g, int K, bool bf16, const
 // ---- the same layers on split operands, fp32 (conv_c16.hip) ----
 // Blocks of the forward (mode 0) or of the backward of a layer: rows of sums, copies of dW; 0: not supported.
 int c16_tiles(const ConvGeom& g, int mode);
-// Forward with Eq. 1's second pass (nb > 0 rows of sums around `shift`, nullable; nb = 0: `stats` is given) and Eq. 1-3, 9.  y is not x.
+// Forward with Eq. 1's second pass (nb > 0 rows of sums around `shift`, nullable; nb = 0: `stats` is given) and Eq. 1-3, 9.  y is not
+// x, out_partial (nullable) not partial.
 int launch_c16_fwd(hipStream_t st, const ConvGeom& g, int K, const float* x, const float* w, const double* partial, int nb,
                    const float* shift, const float* gamma, const float* beta, void* stats, const float* skip, float* y, void* packed,
                    double* out_partial);

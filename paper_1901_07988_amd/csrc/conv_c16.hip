@@ -896,6 +896,7 @@ int launch_c16_fwd(hipStream_t st, const ConvGeom& g, int K, const float* x, con
                    double* out_partial) {
   C16Plan p;
   if (!make_plan(g, kMaxPartialBlocks, p)) return ABL_ERR_SHAPE;
+  if (nb > 0 && partial == out_partial) return ABL_ERR_ARG;   // (a block reads all rows and leaves its own before others begin)
   const int64_t M = (int64_t)g.N * g.H * g.W, raw = M * kC * K / 8;
   const C16Fwd a{x, w, skip, partial, nb, shift, gamma, beta, static_cast<float*>(stats), y, static_cast<uint8_t*>(packed),
                  (int)((raw + 127) / 128 * 128 - raw), out_partial, M};

@@ -1233,6 +1233,7 @@ int launch_narrow_fwd(hipStream_t st, const ConvGeom& g, int K, const float* x, 
                       double* out_partial) {
   const Planned& plan = planned(g, FWD);
   if (!plan.ok) return ABL_ERR_SHAPE;
+  if (nb > 0 && partial == out_partial) return ABL_ERR_ARG;   // (a block reads all rows and leaves its own before others begin)
   const NarrowPlan& p = plan.p;
   const int mt = plan.mt;
   const int64_t M = (int64_t)g.N * g.H * g.W, raw = (M * g.Cin * K + 7) / 8;
