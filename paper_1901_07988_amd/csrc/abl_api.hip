@@ -382,8 +382,10 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
     const int64_t n = (int64_t)g.R * g.S * s->Cin * s->Cout;
     const int64_t own = (int64_t)(wgrad_partial_bytes(*s) / (n * sizeof(float))), all = M * s->Cin / n;
     int rows = 0, copies = 0;
-    // both contractions in one launch, the copies of dW in their own place; or one after the other, the copies in that of dA3
-    const bool one = own >= 1 && (own >= 16 || own >= all);
+    // both contractions in one launch, the copies of dW in their own place; or one after the other, the copies in that of dA3 (dW
+    // over W, which the data gradient reads, can only be written behind it)
+    const bool apart = dW + n <= W || W + n <= dW;
+    const bool one = own >= 1 && (own >= 16 || own >= all || !apart);
     if (narrow_bwd_blocks(g, one ? own : all, one, &rows, &copies)) {
       float* const at = one ? static_cast<float*>(wpart) : da3;
       DwSum dwsum{at, copies, n, dW};

@@ -93,6 +93,31 @@ def test_layer_step(s, K, beta):
     assert rel(dW, rdW) < worse * 2.0 ** -24 * ((M / 32) ** 0.5 + 5)
 
 
+# strided layers whose own room holds few copies of dW, 8, 12 and one: two launches, where dW lies apart from W
+@pytest.mark.parametrize("s", [(64, 8, 8, 64, 64, 1, 2, 0), (32, 14, 14, 64, 32, 3, 2, 1), (2, 16, 16, 16, 16, 3, 2, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradient_over_the_weights(s):
+    """dW over all of W and over a part of it: the data gradient reads W before."""
+    print("case layer of few channels, dW over W", s, flush=True)
+    N, H, W, ci, co, R, st, pad = s
+    s9, K = (N, H, W, ci, co, R, R, st, pad), 4
+    x, w, gamma, beta, dy = draw(s, 0.0)
+    packed, stats, scratch = raw(B.abl_packed_bytes(s9, K)), raw(B.abl_stats_bytes(s9)), raw(B.abl_scratch_bytes(s9, K))
+    B.abl_forward(s9, K, x, w, gamma, beta, None, scratch, f32(*dy.shape), packed, stats)
+    want = [f32(*x.shape), f32(*w.shape), f32(ci), f32(ci)]
+    B.abl_backward(s9, K, packed, stats, dy, w, scratch, *want)
+    n = w.numel()
+    for at in (0, n // 2, n):   # (n: side by side)
+        both = torch.empty(2 * n, device="cuda")
+        both[:n] = w.view(-1)
+        got = [f32(*x.shape), both[at:at + n].view(w.shape), f32(ci), f32(ci)]
+        B.abl_backward(s9, K, packed, stats, dy, both[:n].view(w.shape), scratch, *got)
+        # the same products in other tiles and copies: the bounds of test_layer_step, twice
+        for a, b, tol in zip(got, want, (20, 2, 20, 20)):
+            assert rel(a, b.double()) < tol * 2.0 ** -24 * ((max(R * R * max(ci, co), N * H * W) / 32) ** 0.5 + 5)
+            assert at < n or torch.equal(a, b)
+
+
 @pytest.mark.parametrize("s", [SHAPES[0], SHAPES[3], SHAPES[4], SHAPES[6]], ids=lambda s: "x".join(map(str, s)))
 def test_values_the_split_cannot_carry(s):
     """An infinity and a NaN of dy reach the outputs that they reach in fp32 products, and no others."""
