@@ -915,15 +915,14 @@ int check_stack(const abl_layer* layers, int L, int K, int skip_every, const flo
   return ABL_OK;
 }
 
-// Inspection copy of a layer's input (or incoming gradient) before the layer runs.
-int trace_copy(hipStream_t st, float* const* trace, int i, const float* src, size_t floats) {
+}  // namespace
+
+int abl::trace_copy(hipStream_t st, float* const* trace, int i, const float* src, size_t floats) {
   if (trace == nullptr || trace[i] == nullptr) return ABL_OK;
   return hipMemcpyAsync(trace[i], src, floats * sizeof(float), hipMemcpyDeviceToDevice, st) == hipSuccess
              ? ABL_OK
              : ABL_ERR_HIP;
 }
-
-}  // namespace
 
 extern "C" {
 
@@ -990,10 +989,9 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
   const size_t xbytes = stack_xpart_bytes(layers, L);
   char* const lscratch = static_cast<char*>(scratch) + xbytes;
   const size_t lbytes = abl_stack_scratch_bytes(layers, L, K) - xbytes;
-  // Equal 16-channel layers: Eq. 7-8 of a layer go along with the contractions of the layer below (a traced call wants every dy in
-  // memory).
+  // Equal 16-channel layers: Eq. 7-8 of a layer go along with the contractions of the layer below.
   const size_t wat = wpart_offset(layers[0].shape);
-  if (trace == nullptr && (flags & ABL_MATH_BF16) == 0 && c16_stack_tiles(layers, L, K, skip_every, lbytes > wat ? lbytes - wat : 0)) {
+  if ((flags & ABL_MATH_BF16) == 0 && c16_stack_tiles(layers, L, K, skip_every, lbytes > wat ? lbytes - wat : 0)) {
     const abl_layer& l = layers[0];
     const int64_t M = rows_of(l.shape);
     float* const da3 = reinterpret_cast<float*>(lscratch);
@@ -1002,7 +1000,7 @@ int abl_stack_backward_traced(void* stream, const abl_layer* layers, int32_t L, 
     double* const rows[2] = {reinterpret_cast<double*>(red), static_cast<double*>(scratch)};
     const int tiles = c16_tiles(geom_of(l.shape), 1);
     if (int e = launch_c16_stack_bwd((hipStream_t)stream, layers, L, K, buf_s, buf_t, da3, rows, copies,
-                                     reinterpret_cast<float*>(red + bn_means_offset(l.shape.Cin))))
+                                     reinterpret_cast<float*>(red + bn_means_offset(l.shape.Cin)), trace))
       return e;
     const DwSum dwsum{copies, tiles, (int64_t)9 * 16 * 16, l.dW};
     return launch_bn_bwd_finish((hipStream_t)stream, l.packed, l.stats, da3, M, l.shape.Cin, K, true, red, tiles, buf_s, l.dgamma,

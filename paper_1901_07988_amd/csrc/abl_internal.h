@@ -82,6 +82,11 @@ int launch_bn_bwd(hipStream_t st, const void* packed, const void* stats, const f
 int launch_bn_bwd_finish(hipStream_t st, const void* packed, const void* stats, const float* da3, int64_t M,
                          int C, int K, bool accum, void* scratch, int nb, float* dx, float* dgamma,
                          float* dbeta, const DwSum* dwsum = nullptr, float slope = 0.0f, const SplitWeights& next = SplitWeights{});
+// Its last launch: Eq. 8 with the means [2][C] at hand.
+int launch_bn_bwd_apply(hipStream_t st, const void* packed, const void* stats, const float* da3, int64_t M, int C, int K, bool accum,
+                        const float* means, float* dx, float slope = 0.0f, const SplitWeights& next = SplitWeights{});
+// Inspection copy of a layer's input (or incoming gradient); trace and its entries may be null.
+int trace_copy(hipStream_t st, float* const* trace, int i, const float* src, size_t floats);
 
 // Convolution geometry passed to the kernels by value.
 struct ConvGeom {
@@ -149,10 +154,11 @@ int launch_c16_bwd(hipStream_t st, const ConvGeom& g, int K, const float* dy, co
                    float* da3, double* partial, float* copies);
 // The backward of a stack of equal such layers in pairs with a shortcut around each, up to Eq. 7-8 of the bottom layer (its rows
 // are in rows[0], its dA3 in da3, its copies of dW in front): Eq. 7-8 of the others go along with the layer below.
-// c16_stack_tiles: blocks, 0 = not such a stack; room: bytes for two sets of copies.  means: room for 4 x 16 floats.
+// c16_stack_tiles: blocks, 0 = not such a stack; room: bytes for two sets of copies.  means: room for 4 x 16 floats.  trace (nullable):
+// where each layer's dy goes (nullable).
 int c16_stack_tiles(const abl_layer* layers, int L, int K, int skip_every, size_t room);
 int launch_c16_stack_bwd(hipStream_t st, const abl_layer* layers, int L, int K, float* s, float* t, float* da3, double* const (&rows)[2],
-                         float* copies, float* means);
+                         float* copies, float* means, float* const* trace);
 
 // ---- layers of few channels on split operands, fp32 (conv_narrow.hip) ----
 bool narrow_pays(const ConvGeom& g);

@@ -974,8 +974,6 @@ int launch_bn_bwd_finish(hipStream_t st, const void* packed, const void* stats, 
   const float* sp = static_cast<const float*>(stats);
   const double* partial = static_cast<const double*>(scratch);
   float* means = reinterpret_cast<float*>(static_cast<char*>(scratch) + bn_means_offset(C));
-  const uint8_t* pk = static_cast<const uint8_t*>(packed);
-  const int vec = fast_vec(K, C, false);
   const int nfin = (C + 15) / 16;
   if (dwsum != nullptr) {
     bwd_finalize_dwsum_kernel<<<nfin + sum_blocks(*dwsum), kFinThreads, 0, st>>>(
@@ -983,6 +981,14 @@ int launch_bn_bwd_finish(hipStream_t st, const void* packed, const void* stats, 
         sum_is_straight(*dwsum) ? 1 : 0);
   } else
     bwd_finalize_kernel<<<nfin, kFinThreads, 0, st>>>(partial, nb, M, C, sp, dgamma, dbeta, means);
+  return launch_bn_bwd_apply(st, packed, stats, da3, M, C, K, accum, means, dx, slope, next);
+}
+
+int launch_bn_bwd_apply(hipStream_t st, const void* packed, const void* stats, const float* da3, int64_t M, int C, int K, bool accum,
+                        const float* means, float* dx, float slope, const SplitWeights& next) {
+  const float* sp = static_cast<const float*>(stats);
+  const uint8_t* pk = static_cast<const uint8_t*>(packed);
+  const int vec = fast_vec(K, C, false);
   if (vec == 0) {
     const int64_t E = M * C;
     const unsigned blocks = (unsigned)((E + kThreads - 1) / kThreads);

@@ -943,11 +943,13 @@ int c16_stack_tiles(const abl_layer* layers, int L, int K, int skip_every, size_
 // first layer takes Eq. 8 of that and leaves its dA3 in da3; S itself moves on to the group's own output there, when no block
 // reads its neighbours' pixels of it.
 int launch_c16_stack_bwd(hipStream_t st, const abl_layer* layers, int L, int K, float* s, float* t, float* da3, double* const (&rows)[2],
-                         float* copies, float* means) {
+                         float* copies, float* means, float* const* trace) {
   const ConvGeom g = geom_of(layers[0].shape);
   C16Plan p;
   if (!make_plan(g, p)) return ABL_ERR_SHAPE;
   const size_t copy = (size_t)p.tiles * 2304;
+  const int64_t M = (int64_t)g.N * g.H * g.W;
+  if (int e = trace_copy(st, trace, L - 1, s, (size_t)M * kC)) return e;
   auto apply_of = [&](int i) {
     return C16Apply{i % 2 == 0 ? da3 : t, static_cast<const uint8_t*>(layers[i].packed), static_cast<const float*>(layers[i].stats),
                     means + 2 * kC * (i & 1)};
@@ -962,7 +964,7 @@ int launch_c16_stack_bwd(hipStream_t st, const abl_layer* layers, int L, int K, 
     a.da3 = i % 2 == 0 ? da3 : t;
     a.partial = rows[i & 1];
     a.wpartial = copies + copy * (i & 1);
-    a.M = (int64_t)g.N * g.H * g.W;
+    a.M = M;
     const bool chain = i < L - 1;
     if (chain) {
       const abl_layer& u = layers[i + 1];
@@ -987,6 +989,12 @@ int launch_c16_stack_bwd(hipStream_t st, const abl_layer* layers, int L, int K, 
     if (int e = allow_full_lds(reinterpret_cast<const void*>(kern))) return e;
     kern<<<p.tiles, kT, kBwdLds, st>>>(a, p);
     if (int e = hip_status()) return e;
+    // its dy, which the kernel had in registers: what that was made of is still there
+    if (chain && trace != nullptr && trace[i] != nullptr) {
+      if (a.add != nullptr)
+        if (int e = trace_copy(st, trace, i, a.add, (size_t)M * kC)) return e;
+      if (int e = launch_bn_bwd_apply(st, a.up.packed, a.up.stats, a.up.da3, M, kC, K, a.add != nullptr, a.up_means, trace[i])) return e;
+    }
   }
   return ABL_OK;
 }

@@ -73,39 +73,58 @@ def test_layer_step(s, K, beta):
 
 
 @pytest.mark.parametrize("K", [4, 8])
-@pytest.mark.parametrize("N,hw,count", [(2, 7, 2), (9, 33, 4), (24, 32, 6)])
+@pytest.mark.parametrize("N,hw,count", [(2, 7, 2), (9, 33, 4), (24, 32, 6), (100, 33, 4)])   # (500 blocks a layer, two rounds of the chip)
 def test_stack_equals_traced(N, hw, count, K):
-    """A traced call keeps every layer's gradient in memory: one layer after the other, against the layers that share launches."""
+    """Layers that share launches: every layer against 64-bit values on the gradient that the traced call says it received; the plain
+    call's results are the traced one's bit for bit."""
     print("case 16-channel stack", N, hw, count, K, flush=True)
-    s9 = (N, hw, hw, C, C, 3, 3, 1, 1)
+    s9, M = (N, hw, hw, C, C, 3, 3, 1, 1), N * hw * hw
     descs = []
     for i in range(count):
         _, w, gamma, beta, _ = draw((N, hw, hw), 0.0, 30 + i)
         descs.append(dict(shape=s9, W=w, gamma=gamma, beta=beta, packed=raw(B.abl_packed_bytes(s9, K)), stats=raw(B.abl_stats_bytes(s9)),
                           dW=f32(3, 3, C, C), dgamma=f32(C), dbeta=f32(C)))
     layers = B.make_layers(descs)
-    n = N * hw * hw * C
+    n = M * C
     S, T = f32(B.abl_stack_buffer_bytes(layers) // 4), f32(B.abl_stack_buffer_bytes(layers) // 4)
     scratch = raw(B.abl_stack_scratch_bytes(layers, K))
     x, _, _, _, dy = draw((N, hw, hw), 0.0, 5)
     S[:n] = x.view(-1)
     B.abl_stack_forward(layers, K, 2, S, T, scratch)
-    got = []
-    for traced in (False, True):
+    got, trace = [], [f32(N, hw, hw, C) for _ in descs]
+    for wanted in (None, trace, [t if i % 3 == 1 else None for i, t in enumerate(trace)]):
         S[:n] = dy.view(-1)
         T.fill_(float("nan"))
         scratch.fill_(255)
-        if traced:
-            B.abl_stack_backward_traced(layers, K, 2, S, T, scratch, [f32(n) for _ in descs])
-        else:
+        if wanted is None:
             B.abl_stack_backward(layers, K, 2, S, T, scratch)
+        else:
+            B.abl_stack_backward_traced(layers, K, 2, S, T, scratch, wanted)
         got.append([S[:n].clone()] + [t.clone() for d in descs for t in (d["dW"], d["dgamma"], d["dbeta"])])
         for d in descs:
             for t in (d["dW"], d["dgamma"], d["dbeta"]):
                 t.fill_(float("nan"))
-    # the same operations on the same values but for the order of the sums: of doubles in Eq. 7, of a few hundred copies in dW
-    for a, b in zip(*got):
-        assert rel(a, b.double()) < 2.0 ** -20
+    for run in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], run))
+    assert torch.equal(trace[-1], dy)
+    for i, d in enumerate(descs):
+        a2t, gamma, beta = f32(M, C), d["gamma"].double(), d["beta"].double()
+        B.abl_unpack(d["packed"], M, C, K, d["stats"], a2t)
+        a2t, dyr = a2t.double(), trace[i].double().view(M, C)
+        da3 = conv64(trace[i], d["W"].flip(0, 1).transpose(2, 3).contiguous()).view(M, C)
+        da2, a1 = torch.where(a2t > 0, da3, 0.0), (a2t - beta) / gamma
+        rstd = d["stats"][: 28 * C].view(torch.float32).view(7, C)[2].double()
+        rdb, rdg = da2.sum(0), (da2 * a1).sum(0)
+        rdx = gamma * rstd * (da2 - rdb / M - a1 * (rdg / M))
+        if i % 2 == 0:
+            rdx = rdx + trace[i + 1].double().view(M, C)
+        dW, dg, db = got[0][1 + 3 * i:4 + 3 * i]
+        # (bounds of test_layer_step)
+        assert rel((trace[i - 1] if i > 0 else got[0][0]).view(M, C), rdx) < 2.0 ** -24 * 8, i
+        assert rel(dg, rdg) < 10 * 2.0 ** -24 * 8 and rel(db, rdb) < 10 * 2.0 ** -24 * 8, i
+        at = torch.nn.functional.pad(a2t.clamp(min=0).view(N, hw, hw, C), (0, 0, 1, 1, 1, 1))
+        rdW = torch.stack([at[:, r:r + hw, q:q + hw].reshape(M, C).t().contiguous() @ dyr for r in range(3) for q in range(3)])
+        assert rel(dW.view(9, C, C), rdW) < 2.0 ** -24 * ((M / 32) ** 0.5 + 5), i
 
 
 def test_values_the_split_cannot_carry():
