@@ -685,11 +685,15 @@ int abl_split_products(const abl_shape* s, int K, uint32_t flags, int stage) {
   if (check_shape(s) != ABL_OK || check_k(K) != ABL_OK || (flags & ABL_MATH_BF16) != 0) return 0;
   const ConvGeom g = geom_of(*s);
   int rows;
-  switch (stage) {
-    case ABL_STAGE_CONV_FWD: return split_conv_blocks(g, 0) > 0 ? 6 : 0;
-    case ABL_STAGE_BN_CONV_FWD: return K != 32 && forward_fused_path(*s, g, K, false, false, &rows) == 1 && rows > 0 ? 6 : 0;
-    case ABL_STAGE_CONV_DGRAD: return split_conv_blocks(g, 1) > 0 ? 6 : 0;
-    case ABL_STAGE_CONV_DGRAD_BN_REDUCE: return K != 32 && reduce_stage_accepts(g) && split_conv_blocks(g, 1, false, true) > 0 ? 6 : 0;
+  switch (stage) {   // (each as its stage call decides)
+    case ABL_STAGE_CONV_FWD: return narrow_pays(g) || split_conv_blocks(g, 0) > 0 ? 6 : 0;
+    case ABL_STAGE_BN_CONV_FWD:
+      if (K == 32 || igemm_fused_supported(*s) || !halo_fused_supported(g)) return 0;
+      return narrow_fuses(g) || c16_tiles(g, 0) > 0 || (forward_fused_path(*s, g, K, false, false, &rows) == 1 && rows > 0) ? 6 : 0;
+    case ABL_STAGE_CONV_DGRAD: return narrow_pays(g) || split_conv_blocks(g, 1) > 0 ? 6 : 0;
+    case ABL_STAGE_CONV_DGRAD_BN_REDUCE:
+      if (K == 32 || !reduce_stage_accepts(g)) return 0;
+      return (g.stride == 1 && narrow_pays(g)) || split_conv_blocks(g, 1, false, true) > 0 ? 6 : 0;
     case ABL_STAGE_CONV_WGRAD_PACKED: return split_wgrad_copies(g, K, false, wgrad_partial_bytes(*s)) > 0 ? 3 : 0;
     default: return 0;
   }

@@ -162,3 +162,16 @@ def test_split_products_query(B):
     assert B.abl_split_products((64, 56, 56, 256, 64, 1, 1, 1, 0), 4, "bn_conv_fwd") == 0   # the pointwise kernel's prologue
     assert B.lib.abl_split_products(ctypes.byref(B.shape_struct(deep)), 5, 0, 0) == 0
     assert B.lib.abl_split_products(None, 4, 0, 0) == 0
+
+
+@pytest.mark.parametrize("shape,K,want", [
+    ((128, 32, 32, 16, 16, 3, 3, 1, 1), 4, [6, 6, 6, 6, 0]),       # the 16-channel kernel with the prologue
+    ((128, 32, 32, 16, 16, 3, 3, 1, 1), 32, [6, 0, 6, 0, 0]),
+    ((128, 8, 8, 64, 64, 3, 3, 1, 1), 8, [6, 6, 6, 6, 3]),         # few channels, weight gradient of csrc/wgrad_split.hip
+    ((128, 32, 32, 16, 32, 3, 3, 2, 1), 4, [6, 0, 6, 0, 0]),       # strided: no stage with the prologue or the sums
+    ((50, 27, 21, 20, 36, 3, 3, 1, 1), 4, [6, 0, 6, 0, 0]),        # channel counts off sixteen
+    ((128, 64, 64, 16, 16, 3, 3, 1, 1), 4, [0, 0, 0, 0, 0])])      # too large for either
+def test_split_products_of_few_channels(B, shape, K, want):
+    """The kernels for few channels split their operands too."""
+    assert [B.abl_split_products(shape, K, n) for n in B.STAGES] == want
+    assert [B.abl_split_products(shape, K, n, B.ABL_MATH_BF16) for n in B.STAGES] == [0] * 5
