@@ -9,10 +9,11 @@
  *
  * General rules, valid for every entry point unless it says otherwise:
  *   - every tensor pointer is a DEVICE pointer owned by the caller, 16-byte
- *     aligned; the library allocates nothing, keeps no state (abl_backward_noalloc apart:
- *     it remembers where its fixed workspace lives), enqueues its
- *     kernels on `stream` (a hipStream_t passed as void*, NULL = default stream)
- *     and never synchronises.  Shapes and sizes are host values.
+ *     aligned; the library allocates nothing on the device, keeps no state that a result
+ *     depends on (abl_backward_noalloc remembers where its fixed workspace lives; each thread
+ *     keeps how it cut its last layers into tiles, host values that follow from the shape
+ *     alone), enqueues its kernels on `stream` (a hipStream_t passed as void*, NULL = default
+ *     stream) and never synchronises.  Shapes and sizes are host values.
  *   - activations are fp32, NHWC ("first dim = sample, last dim = channel",
  *     Sec. 3.1); conv weights are fp32 [R][S][Cin][Cout]; the linear transform of
  *     Eq. 4 is a zero-padded cross-correlation without bias.

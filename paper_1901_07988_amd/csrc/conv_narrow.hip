@@ -974,9 +974,22 @@ inline int up256(int v) { return (v + 255) / 256 * 256; }
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 inline int fdiv(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 
+// (nothing is planned for others)
+bool in_range(const ConvGeom& g) {
+  return g.R <= 5 && g.S <= 5 && g.stride <= 2 && g.Cin <= 64 && g.Cout <= 128 && (int64_t)g.N * g.H * g.W * g.Cin < (1 << 30) &&
+         (int64_t)g.N * g.Ho * g.Wo * g.Cout < (1 << 30);
+}
+
+// Number of tiles of the next smaller height that cuts `rows` rows into more of them, 0 = none: about 2 sqrt(rows) ways in all.
+int next_cut(int rows, int* th) {
+  if (*th == 1) return 0;
+  const int n = cdiv(rows, *th - 1);
+  *th = cdiv(rows, n);
+  return n;
+}
+
 bool base_plan(const ConvGeom& g, NarrowPlan& p) {
-  if (g.R > 5 || g.S > 5 || g.stride > 2 || g.Cin > 64 || g.Cout > 128) return false;
-  if ((int64_t)g.N * g.H * g.W * g.Cin >= (1 << 30) || (int64_t)g.N * g.Ho * g.Wo * g.Cout >= (1 << 30)) return false;
+  if (!in_range(g)) return false;
   p.N = g.N; p.H = g.H; p.W = g.W; p.Ho = g.Ho; p.Wo = g.Wo; p.Cin = g.Cin; p.Cout = g.Cout;
   p.R = g.R; p.S = g.S; p.st = g.stride; p.pad = g.pad;
   p.outside = channels_in_tiles(g);
@@ -988,7 +1001,8 @@ bool base_plan(const ConvGeom& g, NarrowPlan& p) {
   return true;
 }
 
-// Patches of tiles of th output rows.
+// Patches of tiles of th output rows.  (The first tile's are the largest but for those of the last, which owns what is left of the
+// input: the others are the first one moved along, cut off at the input's end.)
 void patch(const NarrowPlan& p, int th, bool own, Tiles& t) {
   t.TH = th;
   t.per_image = cdiv(p.Ho, th);
@@ -996,7 +1010,7 @@ void patch(const NarrowPlan& p, int th, bool own, Tiles& t) {
   t.PW = std::max(p.W + p.pad, (p.Wo - 1) * p.st + p.S);
   t.DW = fdiv(p.W - 1 + p.pad, p.st) - fdiv(p.pad - (p.S - 1), p.st) + 1;
   t.PH = t.DH = t.rows = 1;
-  for (int i = 0; i < t.per_image; ++i) {
+  for (int i = 0; i < t.per_image; i += std::max(1, t.per_image - 1)) {
     const int h0 = i * th, h1 = std::min(h0 + th, p.Ho);
     const int r0 = std::min(h0 * p.st, p.H), r1 = i + 1 < t.per_image ? std::min(h1 * p.st, p.H) : p.H;
     const int need = (h1 - 1) * p.st - p.pad + p.R, top = h0 * p.st - p.pad;
@@ -1037,9 +1051,7 @@ bool fwd_plan(const ConvGeom& g, NarrowPlan& p, int* mt) {
   p.entries = 4 * p.steps;
   p.masked = p.Cin % 8 != 0 || p.Cout % 16 != 0 || p.R * p.S * p.ip % 4 != 0;
   double best = 1e30;
-  for (int n = 1; n <= p.Ho; ++n) {
-    const int th = cdiv(p.Ho, n);
-    if (cdiv(p.Ho, th) != n) continue;
+  for (int n = 1, th = p.Ho; n > 0; n = next_cut(p.Ho, &th)) {
     if ((int64_t)p.N * n > kMaxPartialBlocks) break;
     Tiles t;
     patch(p, th, true, t);
@@ -1076,9 +1088,7 @@ double dgrad_plan(NarrowPlan& p, int places, int* mt) {
     steps += (double)n / (p.st * p.st);
   }
   double best = 1e30;
-  for (int n = 1; n <= p.Ho; ++n) {
-    const int th = cdiv(p.Ho, n);
-    if (cdiv(p.Ho, th) != n) continue;
+  for (int n = 1, th = p.Ho; n > 0; n = next_cut(p.Ho, &th)) {
     if ((int64_t)p.N * n > kMaxPartialBlocks) break;
     Tiles t;
     patch(p, th, true, t);
@@ -1111,9 +1121,7 @@ double dgrad_plan(NarrowPlan& p, int places, int* mt) {
 double wgrad_plan(NarrowPlan& p, int64_t room, int places) {
   const int units = cdiv(p.R * p.S, 3) * cdiv(p.Cin, 16) * cdiv(p.Cout, 16);
   double best = 1e30;
-  for (int n = 1; n <= p.Ho; ++n) {
-    const int th = cdiv(p.Ho, n);
-    if (cdiv(p.Ho, th) != n) continue;
+  for (int n = 1, th = p.Ho; n > 0; n = next_cut(p.Ho, &th)) {
     Tiles t;
     patch(p, th, false, t);
     const int pixels = cdiv(th * p.Wo, 32) * 32;
@@ -1167,7 +1175,8 @@ bool bwd_plan(NarrowPlan& p, int64_t room, int* mt) {
   return true;
 }
 
-// A plan is a few microseconds of arithmetic: the last few of a thread are kept by their shapes.
+// A plan is a few microseconds of arithmetic.  A thread keeps the last ones by their shapes, three a layer, room for a network's
+// (eight layers in turn, us a layer for the rule and its plans: 3.8 with sixteen kept, 0.05 with 256).
 enum What { FWD = 0, DGRAD = 1, WGRAD = 2, BOTH = 3 };
 struct Planned {
   ConvGeom g{};
@@ -1177,11 +1186,16 @@ struct Planned {
   NarrowPlan p{};
 };
 const Planned& planned(const ConvGeom& g, int what, int64_t room = 0) {
-  thread_local Planned kept[16];
+  constexpr int kWays = 8, kSets = 32;
+  thread_local Planned kept[kSets][kWays];
   thread_local unsigned next = 0;
-  for (const Planned& k : kept)
+  uint32_t words[sizeof g / 4], h = (uint32_t)what;
+  std::memcpy(words, &g, sizeof g);
+  for (const uint32_t w : words) h = (h ^ w) * 0x9E3779B1u, h ^= h >> 15;
+  Planned(&set)[kWays] = kept[h % kSets];
+  for (const Planned& k : set)
     if (k.what == what && k.room == room && std::memcmp(&k.g, &g, sizeof g) == 0) return k;
-  Planned& k = kept[next++ % 16];
+  Planned& k = set[next++ % kWays];
   k = Planned{};
   k.g = g;
   k.room = room;
@@ -1213,7 +1227,7 @@ int launch(hipStream_t st, Kern kern, unsigned blocks, int lds, const Args& a, c
 bool narrow_pays(const ConvGeom& g) {
   const int64_t M = (int64_t)g.N * g.H * g.W;
   if (g.R == 1 && g.S == 1 && (g.stride == 1 || g.Cout > 64 || M * g.Cin > 3 << 19)) return false;
-  if (M * g.Cin > 4 << 20) return false;
+  if (M * g.Cin > 4 << 20 || !in_range(g)) return false;
   if (g.R == 3 && g.S == 3 && g.pad == 1 && g.stride == 1 && g.Cin % 32 == 0 && g.Cout % 64 == 0 && M * g.Cin * g.Cout > 53 << 20) return false;
   if (g.Cin < 4 && M < 1 << 14) return false;
   return planned(g, FWD).ok && planned(g, DGRAD).ok;

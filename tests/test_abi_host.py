@@ -3,6 +3,7 @@ include/abl.h declares, and its size queries and argument validation behave as d
 import ctypes
 import os
 import re
+import time
 
 import pytest
 
@@ -137,6 +138,19 @@ def test_forward_path_query(B):
     with pytest.raises(B.AblError) as e:
         B.abl_forward_is_fused((64, 56, 56, 64, 64, 3, 3, 1, 1), 5)
     assert e.value.code == B.ABL_ERR_ARG
+
+
+def test_rules_of_many_shapes_cost_little(B):
+    """What decides for the kernels for few channels plans their tiles: a network's layers in turn, and images of thousands of rows,
+    cost a call microseconds at most (ctypes' own share is one or two)."""
+    layers = [(1, 4000 - 16 * i, 4, 8, 8, 3, 3, 1, 1) for i in range(30)]
+    best = 1e9
+    for _ in range(5):
+        t0 = time.perf_counter()
+        for s in layers:
+            assert B.abl_split_products(s, 4, "conv_fwd") == 6
+        best = min(best, (time.perf_counter() - t0) / len(layers))
+    assert best < 20e-6
 
 
 @pytest.mark.parametrize("shape,flags", [((2, 5, 5, 256, 1024, 1, 1, 1, 0), 0), ((64, 14, 14, 256, 320, 1, 1, 1, 0), 0),
