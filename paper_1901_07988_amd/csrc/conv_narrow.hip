@@ -482,6 +482,7 @@ struct NarrowBwd {
   double* partial;      // a row of the Eq. 6-7 sums per block of the data gradient; nullptr: no sums
   float* copies;        // of dW
   int nd;               // blocks of the data gradient; the others take the weights'
+  int pair;             // two parts of the activations at a time in LDS
 };
 
 // Eq. 5, gradient to the input, and the Eq. 6-7 sums.
@@ -693,7 +694,7 @@ template <int K, bool VEC>
 __device__ inline void narrow_wgrad(const NarrowBwd& a, const NarrowPlan& p, char* lds, int block) {
   const int ip = p.ip, op = p.op, cp = 8 * ip, plane = p.w.plane, dplane = p.w.dplane;
   char* const act = lds + op * dplane;
-  float* const cst = reinterpret_cast<float*>(act + ip * plane);   // of the channels: step, fb; 2 t of code 0, its limits (below)
+  float* const cst = reinterpret_cast<float*>(act + (1 + a.pair) * ip * plane);   // of the channels: step, fb; 2 t of code 0, its limits
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lk = lane >> 4;
   const int copy = block / p.nsub, sub = block - copy * p.nsub;
   const int t0 = (int)((int64_t)copy * p.w.count / p.copies), t1 = (int)((int64_t)(copy + 1) * p.w.count / p.copies);
@@ -797,13 +798,19 @@ __device__ inline void narrow_wgrad(const NarrowBwd& a, const NarrowPlan& p, cha
     cst[4 * cp + c] = step > 0.0f ? inf : 0.0f;
   }
   __syncthreads();
-  // whether these whole numbers are exact in one bf16
-  bool ok = true;
+  // whether these whole numbers are exact in one bf16, in two
+  bool ok = true, ok2 = true;
   for (int c = lane; c < p.Cin; c += 64) {
     const int32_t fb = __float_as_int(cst[cp + c]);
-    ok = ok && (1 << K) - 1 + 2 * (cst[c] > 0.0f ? fb : -fb) <= 256;
+    const int32_t top = (1 << K) - 1 + 2 * (cst[c] > 0.0f ? fb : -fb);
+    ok = ok && top <= 256;
+    ok2 = ok2 && top <= 65536;
   }
   const bool narrow = __all(ok) != 0;
+  // Two parts lie in LDS at a time where there is room, as 8-bit codes need them wherever a beta is positive (backward of 32 -> 32
+  // @16x16 N=128: 33.5 us, as with one part; 52.5 with the parts one after the other).
+  const bool both = K == 8 && !narrow && a.pair != 0 && __all(ok2) != 0;
+  const int passes = narrow || both ? 1 : __all(ok2) != 0 ? 2 : 3;
   auto put_act = [&](const Tile& t, int first, int part) __attribute__((always_inline)) {
     const int me = here();
 #pragma unroll
@@ -835,6 +842,7 @@ __device__ inline void narrow_wgrad(const NarrowBwd& a, const NarrowPlan& p, cha
         bf16x8_t h, m, l;
         split3<false>(t2, h, m, l);
         x = part == 0 ? h : part == 1 ? m : l;
+        if (both) put(act + (ip + c) * plane + pos * 16, m);
       }
       put(act + c * plane + pos * 16, x);
     }
@@ -844,7 +852,7 @@ __device__ inline void narrow_wgrad(const NarrowBwd& a, const NarrowPlan& p, cha
     const Tile t = next;
     const int npix = t.npix, npad = t.npad;
 #pragma unroll 1
-    for (int part = 0; part < (narrow ? 1 : 3); ++part) {
+    for (int part = 0; part < passes; ++part) {
       if (tt > t0 || part > 0) __syncthreads();    // the operands before have been read
       if (part == 0) {
         put_dy(t, 0);
@@ -862,7 +870,7 @@ __device__ inline void narrow_wgrad(const NarrowBwd& a, const NarrowPlan& p, cha
         ask_act(t, first);
         put_act(t, first, part);
       }
-      if (part + 1 == (narrow ? 1 : 3) && tt + 1 < t1) {
+      if (part + 1 == passes && tt + 1 < t1) {
         next = tile_of(tt + 1);
         ask_dy(next, 0);
         ask_act(next, 0);
@@ -893,8 +901,13 @@ __device__ inline void narrow_wgrad(const NarrowBwd& a, const NarrowPlan& p, cha
             for (int t = 0; t < 3; ++t) rest[k][t] = mfma32(g[2], x[t], rest[k][t]);
 #pragma unroll
             for (int t = 0; t < 3; ++t) rest[k][t] = mfma32(g[1], x[t], rest[k][t]);
-          } else {
-            if (part == 1)
+            if (!both) continue;
+            const char* const low = act + ip * plane + ua[k];
+#pragma unroll
+            for (int t = 0; t < 3; ++t) x[t] = transposed(low + uoff[k][t] + pa[0], low + uoff[k][t] + pa[1]);
+          }
+          if (part > 0 || both) {
+            if (part < 2)
 #pragma unroll
               for (int t = 0; t < 3; ++t) rest[k][t] = mfma32(g[1], x[t], rest[k][t]);
 #pragma unroll
@@ -1282,15 +1295,16 @@ int launch_narrow_bwd(hipStream_t st, const ConvGeom& g, int K, int what, const 
   if (!plan.ok) return ABL_ERR_SHAPE;
   const NarrowPlan& p = plan.p;
   const int mt = plan.mt;
+  const int second = p.ip * p.w.plane, pair = (what & 2) != 0 && K == 8 && p.wlds + second <= kLds ? 1 : 0;
   const NarrowBwd a{dy, w, static_cast<const uint8_t*>(packed), static_cast<const float*>(stats), da3, partial, copies,
-                    (what & 1) != 0 ? p.blocks : 0};
+                    (what & 1) != 0 ? p.blocks : 0, pair};
   const unsigned blocks = (unsigned)(a.nd + ((what & 2) != 0 ? p.copies * p.nsub : 0));
   const bool vec = g.Cin % 4 == 0 && g.Cout % 4 == 0;
   auto kern = vec ? (K == 4 ? ABL_MT(narrow_bwd_kernel, 4, true)
                             : ABL_MT(narrow_bwd_kernel, 8, true))
                   : (K == 4 ? ABL_MT(narrow_bwd_kernel, 4, false)
                             : ABL_MT(narrow_bwd_kernel, 8, false));
-  return launch(st, kern, blocks, std::max((what & 1) != 0 ? p.lds : 0, (what & 2) != 0 ? p.wlds : 0), a, p);
+  return launch(st, kern, blocks, std::max((what & 1) != 0 ? p.lds : 0, (what & 2) != 0 ? p.wlds + pair * second : 0), a, p);
 }
 
 }  // namespace abl

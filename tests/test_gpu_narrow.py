@@ -56,7 +56,8 @@ def gradients64(s, a3t, dy, w):
     return dp[:, pad:pad + H, pad:pad + W], dW
 
 
-@pytest.mark.parametrize("K,beta", [(4, 0.0), (8, 0.3), (4, 45.0)])
+# (2 t of the codes in one bf16; in two, both in LDS at a time or one after the other; in three)
+@pytest.mark.parametrize("K,beta", [(4, 0.0), (8, 0.3), (4, 45.0), (8, 45.0), (8, 2000.0)])
 @pytest.mark.parametrize("s", SHAPES, ids=IDS)
 def test_layer_step(s, K, beta):
     print("case layer of few channels", s, K, beta, flush=True)
@@ -76,7 +77,8 @@ def test_layer_step(s, K, beta):
         ref += (p[:, hs, ws].reshape(-1, ci) @ w[r, q].double()).view(ref.shape)
     # roundings of 2^-24: a random walk of one per 32 terms, the small products, the final sums; of terms that may be 45 / 0.5 times
     # their sum where beta is large
-    worse = 1 if float(beta.abs().max()) < 1 else 20
+    top = float(beta.abs().max())
+    worse = 1 if top < 1 else 20 if top < 50 else 900
     terms = 2.0 ** -24 * ((R * R * max(ci, co) / 32) ** 0.5 + 5)
     assert rel(y, ref) < worse * terms
     B.abl_unpack(packed, M, ci, K, stats, a2t)
