@@ -28,7 +28,7 @@ def matrix_products(B, stage, s, K, flags):
     """bf16 products that the library spends on one fp32 product in this stage of an fp32 layer (its operands
     split into bf16 parts), or 0: the products are the instruction's own."""
     if stage == "conv_bwd_bn_reduce":   # both contractions: six products for the data gradient, three for the weights'
-        return 4.5 if B.abl_split_products(s.as_tuple(), K, "conv_dgrad", flags) else 0
+        return 4.5 if B.abl_split_products(s.as_tuple(), K, "bn_conv_fwd", flags) else 0
     return B.abl_split_products(s.as_tuple(), K, stage, flags) if stage in B.STAGES else 0
 
 

@@ -196,7 +196,7 @@ namespace {
 // with the Eq. 1-3 / Eq. 9 prologue, 2 = the 1x1 kernel with it, 0 = pack pass + plain contraction.
 inline bool aliased(const void* a, const void* b) { return a == b; }
 // Layers of few channels whose forward has the prologue.
-bool narrow_fuses(const ConvGeom& g) { return g.Cin % 4 == 0 && g.Cout % 4 == 0 && c16_tiles(g, 0) == 0 && narrow_pays(g); }
+bool narrow_fuses(const ConvGeom& g) { return g.Cin % 4 == 0 && g.Cout % 4 == 0 && narrow_fwd_pays(g); }
 // (*split_rows: path 1 on the split-operand kernel, rows of its sums of y; 0 = the halo kernel.)
 int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, bool naive, int* split_rows) {
   *split_rows = 0;
@@ -351,7 +351,7 @@ namespace {
 // Parts of the weights that the data gradient of this layer is to read, 0 = none.  own_launch: see parts_pay.
 int backward_parts(const ConvGeom& g, int K, bool bf16, bool own_launch) {
   if (K == 32 || g.Cout % 32 != 0 || g.Cin % 64 != 0) return 0;   // (nor the 16-channel kernel's layers)
-  if (!bf16 && narrow_pays(g)) return 0;
+  if (!bf16 && narrow_bwd_pays(g)) return 0;
   if (!parts_pay(g, 1, bf16, own_launch)) return 0;
   if (!bf16) return split_conv_blocks(g, 1, false, true) > 0 ? 3 : 0;
   return bf16_gemm_supported(g, 1) && bf16_dgrad_reduce_splits(g, true) ? 1 : 0;
@@ -378,25 +378,29 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   const bool accum = (flags & ABL_ACCUM_DX) != 0;
   const ConvGeom g = geom_of(*s);
-  if (K != 32 && !bf16 && c16_tiles(g, 1) == 0 && narrow_pays(g)) {
+  // layers of few channels
+  const bool narrow = K != 32 && !bf16 && narrow_bwd_pays(g);
+  if (narrow) {
     const int64_t n = (int64_t)g.R * g.S * s->Cin * s->Cout;
     const int64_t own = (int64_t)(wgrad_partial_bytes(*s) / (n * sizeof(float))), all = M * s->Cin / n;
     int rows = 0, copies = 0;
-    // both contractions in one launch, the copies of dW in their own place; or one after the other, the copies in that of dA3 (dW
-    // over W, which the data gradient reads, can only be written behind it)
-    const bool apart = dW + n <= W || W + n <= dW;
-    const bool one = own >= 1 && (own >= 16 || own >= all || !apart);
-    if (narrow_bwd_blocks(g, one ? own : all, one, &rows, &copies)) {
-      float* const at = one ? static_cast<float*>(wpart) : da3;
-      DwSum dwsum{at, copies, n, dW};
-      if (one) {
-        if (int e = launch_narrow_bwd(st, g, K, 3, dy, W, packed, stats, da3, static_cast<double*>(red), at, own)) return e;
-      } else {
-        if (int e = launch_narrow_bwd(st, g, K, 2, dy, W, packed, stats, nullptr, nullptr, at, all)) return e;
+    // both contractions in one launch, the copies of dW in their own place
+    if (channels_in_tiles(g) && narrow_wgrad_pays(g, own, true) && narrow_bwd_blocks(g, own, true, &rows, &copies)) {
+      if (int e = launch_narrow_bwd(st, g, K, 3, dy, W, packed, stats, da3, static_cast<double*>(red), static_cast<float*>(wpart), own)) return e;
+      const DwSum dwsum{static_cast<const float*>(wpart), copies, n, dW};
+      return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, rows, dx, dgamma, dbeta, &dwsum, 0.0f, next);
+    }
+    // channel counts off sixteen: the weight gradient goes first, its copies in the place of dA3
+    if (!channels_in_tiles(g)) {
+      if (all >= 1 && narrow_wgrad_pays(g, all, false) && narrow_bwd_blocks(g, all, false, &rows, &copies)) {
+        if (int e = launch_narrow_bwd(st, g, K, 2, dy, W, packed, stats, nullptr, nullptr, da3, all)) return e;
+        const DwSum dwsum{da3, copies, n, dW};
         if (int e = launch_split_weights(st, SplitWeights{}, &dwsum)) return e;
-        if (int e = launch_narrow_bwd(st, g, K, 1, dy, W, packed, stats, da3, static_cast<double*>(red), nullptr, 0)) return e;
+      } else if (int e = launch_conv_wgrad_packed(st, *s, K, false, packed, stats, dy, da3, dW, false, nullptr, act)) {
+        return e;
       }
-      return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, rows, dx, dgamma, dbeta, one ? &dwsum : nullptr, 0.0f,
+      if (int e = launch_narrow_bwd(st, g, K, 1, dy, W, packed, stats, da3, static_cast<double*>(red), nullptr, 0)) return e;
+      return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, narrow_dgrad_rows(g), dx, dgamma, dbeta, nullptr, 0.0f,
                                   next);
     }
   }
@@ -431,6 +435,13 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
   };
   // Stride-1 convolutions with a filter larger than 1x1 take the Eq. 6-7 sums in the epilogue of
   // the dgrad kernel (dA3 is still in registers there), which saves the reduce pass over dA3.
+  if (narrow) {
+    if (int e = launch_narrow_bwd(st, g, K, 1, dy, W, packed, stats, da3, static_cast<double*>(red), nullptr, 0)) return e;
+    DwSum dwsum;
+    if (int e = weight_gradient(&dwsum)) return e;
+    return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, narrow_dgrad_rows(g), dx, dgamma, dbeta,
+                                dwsum.copies > 0 ? &dwsum : nullptr, 0.0f, next);
+  }
   // bf16 operands with a dgrad on the 32-deep bf16 matrix instruction: the separate stages
   const bool bf16_gemm = bf16 && bf16_gemm_supported(g, 1);
   // 16-channel 3x3 layers: both contractions and the Eq. 6-7 sums in one kernel
@@ -651,7 +662,7 @@ int abl_conv_dgrad_bn_reduce(void* stream, const abl_shape* s, int K, uint32_t f
     return ABL_ERR_ARG;
   const ConvGeom g = geom_of(*s);
   if (scratch_bytes < bn_partial_bytes(rows_of(*s), s->Cin)) return ABL_ERR_SCRATCH;
-  if (!(flags & ABL_MATH_BF16) && g.stride == 1 && narrow_pays(g) && reduce_stage_accepts(g)) {   // the kernel of abl_conv_dgrad
+  if (!(flags & ABL_MATH_BF16) && g.stride == 1 && narrow_dgrad_pays(g) && reduce_stage_accepts(g)) {   // the kernel of abl_conv_dgrad
     *rows = narrow_dgrad_rows(g);
     return launch_narrow_bwd((hipStream_t)stream, g, K, 1, dy, W, packed, stats, da3, static_cast<double*>(scratch), nullptr, 0);
   }
@@ -686,14 +697,14 @@ int abl_split_products(const abl_shape* s, int K, uint32_t flags, int stage) {
   const ConvGeom g = geom_of(*s);
   int rows;
   switch (stage) {   // (each as its stage call decides)
-    case ABL_STAGE_CONV_FWD: return narrow_pays(g) || split_conv_blocks(g, 0) > 0 ? 6 : 0;
+    case ABL_STAGE_CONV_FWD: return narrow_fwd_pays(g) || split_conv_blocks(g, 0) > 0 ? 6 : 0;
     case ABL_STAGE_BN_CONV_FWD:
       if (K == 32 || igemm_fused_supported(*s) || !halo_fused_supported(g)) return 0;
       return narrow_fuses(g) || c16_tiles(g, 0) > 0 || (forward_fused_path(*s, g, K, false, false, &rows) == 1 && rows > 0) ? 6 : 0;
-    case ABL_STAGE_CONV_DGRAD: return narrow_pays(g) || split_conv_blocks(g, 1) > 0 ? 6 : 0;
+    case ABL_STAGE_CONV_DGRAD: return narrow_dgrad_pays(g) || split_conv_blocks(g, 1) > 0 ? 6 : 0;
     case ABL_STAGE_CONV_DGRAD_BN_REDUCE:
       if (K == 32 || !reduce_stage_accepts(g)) return 0;
-      return (g.stride == 1 && narrow_pays(g)) || split_conv_blocks(g, 1, false, true) > 0 ? 6 : 0;
+      return (g.stride == 1 && narrow_dgrad_pays(g)) || split_conv_blocks(g, 1, false, true) > 0 ? 6 : 0;
     case ABL_STAGE_CONV_WGRAD_PACKED: return split_wgrad_copies(g, K, false, wgrad_partial_bytes(*s)) > 0 ? 3 : 0;
     default: return 0;
   }

@@ -161,7 +161,12 @@ int launch_c16_stack_bwd(hipStream_t st, const abl_layer* layers, int L, int K, 
                          float* copies, float* means, float* const* trace);
 
 // ---- layers of few channels on split operands, fp32 (conv_narrow.hip) ----
-bool narrow_pays(const ConvGeom& g);
+// Where these are the faster kernels: forward with or without the prologue; gradient to the input; the same with the sums of a layer
+// call; the weight gradient beside that in one launch, or (both = false, channel counts off sixteen) in its own, of `room` copies.
+bool narrow_fwd_pays(const ConvGeom& g);
+bool narrow_dgrad_pays(const ConvGeom& g);
+bool narrow_bwd_pays(const ConvGeom& g);
+bool narrow_wgrad_pays(const ConvGeom& g, int64_t room, bool both);
 // Blocks of the forward (rows of its sums of y); 0: not supported.
 int narrow_fwd_blocks(const ConvGeom& g);
 // Rows of the statistics' sums that its blocks should have to add up at most.
@@ -218,6 +223,9 @@ int launch_conv_wgrad_packed(hipStream_t st, const abl_shape& s, int K, bool bf1
                              DwSum* defer = nullptr, size_t room = 0);
 
 // ---- channel counts that are not multiples of 16 (conv_ragged.hip), fp32 ----
+// What launch_ragged_conv (mode 1, filters) and launch_conv_wgrad_packed take on up to 64 channels, us.
+double ragged_dgrad_us(const ConvGeom& g);
+double ragged_wgrad_us(const ConvGeom& g, size_t room);
 inline bool channels_in_tiles(const ConvGeom& g) { return g.Cin % 16 == 0 && g.Cout % 16 == 0; }
 int launch_ragged_conv(hipStream_t st, const ConvGeom& g, int mode, const float* in, const float* w, const float* skip,
                        float* out);

@@ -937,7 +937,7 @@ int launch_conv_fwd(hipStream_t st, const abl_shape& s, bool bf16, const float* 
                     const float* skip, float* y, double* sums, int* rows, const void* parts) {
   const ConvGeom g = geom_of(s);
   if (rows != nullptr) *rows = 0;
-  if (!bf16 && narrow_pays(g)) {
+  if (!bf16 && narrow_fwd_pays(g)) {
     const bool want = sums != nullptr && rows != nullptr;
     if (want) *rows = narrow_fwd_blocks(g);
     return launch_narrow_fwd(st, g, 0, a3, w, nullptr, 0, nullptr, nullptr, nullptr, nullptr, skip, y, nullptr, want ? sums : nullptr);
@@ -994,7 +994,7 @@ int launch_conv_fwd_fused(hipStream_t st, const abl_shape& s, int K, bool bf16, 
 int launch_conv_dgrad(hipStream_t st, const abl_shape& s, bool bf16, const float* dy, const float* w,
                       float* da3) {
   const ConvGeom g = geom_of(s);
-  if (!bf16 && narrow_pays(g)) return launch_narrow_bwd(st, g, 4, 1, dy, w, nullptr, nullptr, da3, nullptr, nullptr, 0);
+  if (!bf16 && narrow_dgrad_pays(g)) return launch_narrow_bwd(st, g, 4, 1, dy, w, nullptr, nullptr, da3, nullptr, nullptr, 0);
   if (!mfma_ok(g)) return launch_ragged_conv(st, g, 1, dy, w, nullptr, da3);
   if (bf16 && image_bf16_supported(g, 1)) return launch_image_bf16(st, g, 1, dy, w, nullptr, da3, nullptr);
   // (1x1: from contractions of 1024 channels on, 512 -> 2048 @7x7 44 -> 35 us, 256 -> 1024 @14x14 28 -> 26; shorter ones

@@ -58,6 +58,7 @@ struct NarrowPlan {
   int blocks, lds;
   Tiles w;                     // of the weight gradient
   int per_wave, nsub, copies, wlds;   // units of a wave, blocks that share a copy
+  float fwd_us, dgrad_us, wgrad_us;   // what the plans expect
   Divisor by_pw, by_wo, by_tiles, by_ip, by_op, by_dw, by_nw0, by_nw1, wby_pw, wby_tiles;
 };
 
@@ -1081,6 +1082,7 @@ bool fwd_plan(const ConvGeom& g, NarrowPlan& p, int* mt) {
     *mt = m;
   }
   if (best >= 1e30) return false;
+  p.fwd_us = (float)best;
   p.blocks = p.t.count;
   p.by_pw = Divisor(p.t.PW);
   p.by_tiles = Divisor(p.t.per_image);
@@ -1120,6 +1122,7 @@ double dgrad_plan(NarrowPlan& p, int places, int* mt) {
     *mt = m;
   }
   if (best >= 1e30) return -1.0;
+  p.dgrad_us = (float)best;
   p.blocks = p.t.count;
   p.by_dw = Divisor(p.t.DW);
   // columns of a class: w = wf, wf + st, ...
@@ -1162,6 +1165,7 @@ double wgrad_plan(NarrowPlan& p, int64_t room, int places) {
     }
   }
   if (best >= 1e30) return -1.0;
+  p.wgrad_us = (float)best;
   p.wby_pw = Divisor(p.w.PW);
   p.wby_tiles = Divisor(p.w.per_image);
   return best;
@@ -1228,22 +1232,70 @@ int launch(hipStream_t st, Kern kern, unsigned blocks, int lds, const Args& a, c
 
 }  // namespace
 
-// Layers that the kernels for few channels take: where they are the faster ones, forward and backward together, us before / now
-// (the other kernels of csrc/ with their passes in between), 85 layers of 5 to 57 pixels, 3 to 64 channels, 8 to 160 images:
-// 3x3 64 -> 64 @8x8 N=128 60 / 48, @14x14 N=64 69 / 59; 32 -> 32 @18x18 N=100 78 / 51; stride 2 16 -> 32 @32x32 N=128 73 / 53,
-// 64 -> 128 @18x18 N=128 134 / 95; 20 -> 36 @27x21 N=50 104 / 62; 5x5 12 -> 60 @12x30 N=96 276 / 135.  Not:
-// - 1x1 stride 1, whose GEMMs need no patch, and 1x1 stride 2 of large tensors or many channels (16 -> 32 @35x35 N=112 55 / 57,
-//   64 -> 128 @10x10 N=128 50 / 52, but @16x16 32 -> 64 N=128 47 / 38);
+// Layers that the kernels for few channels may take.  Not:
+// - 1x1, whose GEMMs need no patch (32 -> 64 @16x16 N=41, stride 2, us, the other kernels / these: plain forward 2.7 / 3.9, gradient
+//   4.5 / 8.0, backward of a layer call 24 / 30; its forward 13.9 / 12.0);
 // - more than 4 million elements, and 3x3 layers that conv_split.hip takes beyond a few blocks' work per compute unit: there the
 //   splits of the weights by every wave cost more than the launches (64 -> 64 @28x28 N=20 68 / 70, @56x56 N=12 97 / 118);
 // - images of one to three channels on few pixels (3 -> 16 @34x33 N=8 50 / 53, N=96 91 / 81).
-bool narrow_pays(const ConvGeom& g) {
+static bool split_shape(const ConvGeom& g) {
+  return g.R == 3 && g.S == 3 && g.pad == 1 && g.stride == 1 && g.Cin % 32 == 0 && g.Cout % 64 == 0;
+}
+static bool narrow_takes(const ConvGeom& g) {
   const int64_t M = (int64_t)g.N * g.H * g.W;
-  if (g.R == 1 && g.S == 1 && (g.stride == 1 || g.Cout > 64 || M * g.Cin > 3 << 19)) return false;
-  if (M * g.Cin > 4 << 20 || !in_range(g)) return false;
-  if (g.R == 3 && g.S == 3 && g.pad == 1 && g.stride == 1 && g.Cin % 32 == 0 && g.Cout % 64 == 0 && M * g.Cin * g.Cout > 53 << 20) return false;
+  if ((g.R == 1 && g.S == 1) || M * g.Cin > 4 << 20 || !in_range(g)) return false;
+  if (split_shape(g) && M * g.Cin * g.Cout > 53 << 20) return false;
   if (g.Cin < 4 && M < 1 << 14) return false;
   return planned(g, FWD).ok && planned(g, DGRAD).ok;
+}
+static double gflop(const ConvGeom& g) { return 2e-9 * g.N * g.Ho * g.Wo * ((g.Cin + 15) / 16 * 16) * ((g.Cout + 15) / 16 * 16) * g.R * g.S; }
+
+// The rules below weigh the plans' us, which are within a fifth of 0.75 (forward) and 0.85 (gradient) of them, against those of the
+// kernels that take the layer otherwise: a launch, the rate, the chain of their contraction (870 layers, both measured; 0.6 to 1.2
+// of them).  Wide rows of few images make few blocks here, with all output channels in each (16 -> 96 @70x70 N=1, plain forward, us,
+// the others / these, 6.7 / 10.2), as do a few blocks more than compute units (16 -> 96 @8x8 N=287 9.5 / 14.8).
+
+// Forward, with or without the prologue (which saves a launch or two: layer calls of 375 layers with channels in sixteens 0.67 of the
+// others' time, plain forwards 0.65; 249 other ones 0.67 and 0.53).  Plain forwards of 16-channel 3x3 layers: 5.9 us against 6.5
+// where these are ahead, but 7.3 against 6.5 elsewhere.  (conv_split.hip's layers take about the same time up to a million pixels by
+// channels: 64 -> 64 13.9 us from N=7 to 134 @10x10.)
+bool narrow_fwd_pays(const ConvGeom& g) {
+  if (!narrow_takes(g) || c16_tiles(g, 0) > 0) return false;
+  return planned(g, FWD).p.fwd_us <= 4.8 + (split_shape(g) ? 0.0 : 11.7 * gflop(g)) + 0.0257 * g.R * g.S * ((g.Cin + 15) / 16 * 16);
+}
+
+// The plain gradient to the input (253 layers with channels in sixteens, stride 1: 0.71 of the others' time, none slower; strided
+// ones, whose classes of pixels follow each other, 16 -> 32 @13x13 N=280 13.1 / 18.6, but 32 -> 64 @16x16 N=128 14.8 / 13.1: not.
+// 241 other ones 0.52; not short contractions, 58 -> 7 @40x40 N=4, stride 2, 9.2 / 15.7, nor many blocks, 17 -> 15 @9x9 N=123 without
+// padding 9.3 / 14.6, 59 -> 48 @68x68 N=10 48.9 / 66.5).
+bool narrow_dgrad_pays(const ConvGeom& g) {
+  if (!narrow_takes(g)) return false;
+  if (!channels_in_tiles(g)) return g.R * g.S * g.Cout >= 100 && planned(g, DGRAD).p.dgrad_us <= 0.94 * ragged_dgrad_us(g);
+  return g.stride == 1 && planned(g, DGRAD).p.dgrad_us <= 3.7 + 4.8 * gflop(g) + 0.0196 * g.R * g.S * g.Cout;
+}
+
+// The gradient to the input of a layer call, whose sums save a pass (with the other kernels' weight gradient 840 layers take 0.77 of
+// the time with theirs, 14 of them 1.03 to 1.17; channel counts off sixteen again by their us).  16-channel 3x3 layers in tiles of conv_halo.hip's fused backward have that (15 us
+// for all of 16 -> 16 @10x10 N=17, 24 here).
+bool narrow_bwd_pays(const ConvGeom& g) {
+  if (!narrow_takes(g) || (g.Cin == 16 && g.Cout == 16 && (c16_tiles(g, 1) > 0 || halo_bwd16_tiles(g) > 0))) return false;
+  return channels_in_tiles(g) || planned(g, DGRAD).p.dgrad_us <= 4.0 + 1.1 * ragged_dgrad_us(g);
+}
+
+// The weight gradient beside it (`both`; room: copies).  A block walks its share of the tiles, so it pays where those are few, and
+// hidden by the other gradient for the most part, or the others' is long (backward, us, the others' weight gradient behind the data
+// gradient here / both here: 32 -> 32 @16x16 N=32, one tile, 22.0 / 20.1; 16 -> 32 @32x32 N=128 stride 2, two, 40.2 / 34.3; 48 -> 32
+// @6x6 N=36 stride 2, nine, 20.7 / 90; 890 layers, 1.03 of the better one of both).
+// Channel counts off sixteen: in a launch of its own against conv_ragged.hip's (51 -> 66 5x5 @13x17 N=19 150 / 837, 9 -> 16 5x5
+// @3x25 N=85 stride 2 35 / 13.5; 270 layers, 1.01 of the better one).
+bool narrow_wgrad_pays(const ConvGeom& g, int64_t room, bool both) {
+  const Planned& k = planned(g, both ? BOTH : WGRAD, room);
+  if (!k.ok) return false;
+  const double w = k.p.wgrad_us, d = k.p.dgrad_us;
+  if (!both) return 1.6 * w + 4.0 <= ragged_wgrad_us(g, (size_t)g.N * g.H * g.W * g.Cin * sizeof(float));
+  if (k.p.w.count > 3 * k.p.copies) return false;
+  const double others = 7.0 + 17.6 * gflop(g) + 0.65e-6 * ((double)g.N * g.H * g.W * g.Cin * 0.5 + 4.0 * g.N * g.Ho * g.Wo * g.Cout);
+  return std::max(1.2 * w, d) + 2.0 <= planned(g, DGRAD).p.dgrad_us + others;
 }
 
 int narrow_fwd_rows(const ConvGeom& g) { return std::min(kMaxPartialBlocks, std::max(32, 4096 / g.Cin)); }

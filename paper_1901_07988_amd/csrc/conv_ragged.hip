@@ -434,6 +434,21 @@ int ragged_wgrad_copies(const ConvGeom& g, size_t room) {
   return chunks / split > 64 ? 0 : (int)split;
 }
 
+// (241 layers of 3 to 64 channels, us: 0.72 to 1.2 of it)
+double ragged_dgrad_us(const ConvGeom& g) {
+  const int nt = ragged_nt(g.Cin), chunks = (g.R * g.S * g.Cout + RB_K - 1) / RB_K;
+  const int64_t blocks = (((int64_t)g.N * g.H * g.W + RB_M - 1) / RB_M) * ((g.Cin + 16 * nt - 1) / (16 * nt));
+  const double rounds = (double)blocks / 1024 * (nt + 1);
+  return 3.5 + chunks * (g.stride > 1 ? 1.44 + 0.19 * nt + rounds : 0.73 + 0.19 * nt + 0.55 * rounds);
+}
+// (270 layers: 0.77 to 1.2 of it)
+double ragged_wgrad_us(const ConvGeom& g, size_t room) {
+  const double n = (double)g.R * g.S * g.Cin * g.Cout, pixels = (double)g.N * g.Ho * g.Wo;
+  const int copies = ragged_wgrad_copies(g, room);
+  if (copies == 0) return 2.6 + 1.6e-3 * pixels + 5.8e-4 * n + 2.1e-6 * n * pixels;
+  return 3.8 + 2.3 * pixels / RB_K / copies + 0.02 * copies + 3.5e-6 * n * copies + 2.6e-8 * n * pixels;
+}
+
 int launch_ragged_wgrad(hipStream_t st, const ConvGeom& g, int K, const void* packed, const float* stats,
                         const float* dy, int copies, float* dst, bool relu32) {
   const int nt = ragged_nt(g.Cout);

@@ -16,15 +16,27 @@ SHAPES = [(128, 8, 8, 64, 64, 3, 1, 1),      # steps shared by two waves
           (5, 10, 9, 64, 96, 3, 1, 2),       # output larger than the input
           (50, 27, 21, 20, 36, 3, 1, 1),
           (40, 33, 32, 16, 32, 3, 2, 1),     # four classes of input pixels
-          (9, 15, 14, 32, 64, 1, 2, 0),      # three of them without a tap
-          (7, 12, 11, 50, 70, 5, 1, 2),      # channels not in fours: the pack pass in front
+          (9, 15, 14, 32, 64, 1, 2, 0),      # 1x1: other kernels
+          (7, 12, 11, 50, 70, 5, 1, 2),      # channels not in fours: the pack pass in front, conv_ragged.hip's weight gradient
           (3, 11, 13, 12, 20, 5, 2, 1),
-          (1, 6, 5, 4, 4, 3, 1, 1), (2, 3, 90, 8, 128, 3, 1, 1)]
+          (1, 6, 5, 4, 4, 3, 1, 1), (2, 3, 90, 8, 128, 3, 1, 1),                  # (the latter on other kernels)
+          (9, 15, 14, 32, 64, (1, 3), 2, 0), (5, 14, 15, 20, 24, (3, 1), 2, 1),   # two classes without a tap; the others' weight gradient
+          (28, 10, 8, 64, 64, 5, 1, 1), (3, 13, 16, 32, 64, 5, 2, 0),             # three tiles to a copy of dW
+          (23, 10, 18, 15, 22, (5, 3), 1, 2), (7, 21, 24, 35, 32, 5, 1, 1)]       # dW in a launch of its own, channels not in fours
 IDS = ["x".join(map(str, s)) for s in SHAPES]
 
 
+def filters(s):
+    return s[5] if isinstance(s[5], tuple) else (s[5], s[5])
+
+
+def shape9(s):
+    return s[:5] + filters(s) + s[6:]
+
+
 def draw(s, beta, seed=3):
-    N, H, W, ci, co, R, st, pad = s
+    N, H, W, ci, co, _, st, pad = s
+    R, S = filters(s)
     g = torch.Generator(device="cuda").manual_seed(seed)
 
     def normal(*size):
@@ -32,23 +44,24 @@ def draw(s, beta, seed=3):
 
     gamma = torch.rand(ci, device="cuda", generator=g) + 0.5
     gamma[1] = -gamma[1]
-    ho, wo = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
-    return (normal(N, H, W, ci), normal(R, R, ci, co) * (2.0 / (R * R * ci)) ** 0.5, gamma, beta + normal(ci) * 0.1, normal(N, ho, wo, co))
+    ho, wo = (H + 2 * pad - R) // st + 1, (W + 2 * pad - S) // st + 1
+    return (normal(N, H, W, ci), normal(R, S, ci, co) * (2.0 / (R * S * ci)) ** 0.5, gamma, beta + normal(ci) * 0.1, normal(N, ho, wo, co))
 
 
 def taps(s, ho, wo):
-    N, H, W, ci, co, R, st, pad = s
+    (R, S), st = filters(s), s[6]
     for r in range(R):
-        for q in range(R):
+        for q in range(S):
             yield r, q, slice(r, r + (ho - 1) * st + 1, st), slice(q, q + (wo - 1) * st + 1, st)
 
 
 def gradients64(s, a3t, dy, w):
     """dA3 and dW in 64 bits."""
-    N, H, W, ci, co, R, st, pad = s
+    N, H, W, ci, co, _, st, pad = s
+    R, S = filters(s)
     ho, wo = dy.shape[1:3]
     p = torch.nn.functional.pad(a3t.double(), (0, 0, pad, pad, pad, pad))
-    dp, dW, g, wd = torch.zeros_like(p), torch.zeros(R, R, ci, co, dtype=torch.float64, device="cuda"), dy.double().reshape(-1, co), w.double()
+    dp, dW, g, wd = torch.zeros_like(p), torch.zeros(R, S, ci, co, dtype=torch.float64, device="cuda"), dy.double().reshape(-1, co), w.double()
     for r, q, hs, ws in taps(s, ho, wo):
         piece = p[:, hs, ws]
         dW[r, q] = piece.reshape(-1, ci).t().contiguous() @ g
@@ -61,8 +74,9 @@ def gradients64(s, a3t, dy, w):
 @pytest.mark.parametrize("s", SHAPES, ids=IDS)
 def test_layer_step(s, K, beta):
     print("case layer of few channels", s, K, beta, flush=True)
-    N, H, W, ci, co, R, st, pad = s
-    s9, M = (N, H, W, ci, co, R, R, st, pad), N * H * W
+    N, H, W, ci, co, _, st, pad = s
+    R, S = filters(s)
+    s9, M = shape9(s), N * H * W
     x, w, gamma, beta, dy = draw(s, beta)
     packed, stats, scratch = raw(B.abl_packed_bytes(s9, K)), raw(B.abl_stats_bytes(s9)), raw(B.abl_scratch_bytes(s9, K))
     y, skip = f32(*dy.shape), torch.randn_like(dy)
@@ -79,7 +93,7 @@ def test_layer_step(s, K, beta):
     # their sum where beta is large
     top = float(beta.abs().max())
     worse = 1 if top < 1 else 20 if top < 50 else 900
-    terms = 2.0 ** -24 * ((R * R * max(ci, co) / 32) ** 0.5 + 5)
+    terms = 2.0 ** -24 * ((R * S * max(ci, co) / 32) ** 0.5 + 5)
     assert rel(y, ref) < worse * terms
     B.abl_unpack(packed, M, ci, K, stats, a2t)
     dx, dW, dg, db = f32(*x.shape), f32(*w.shape), f32(ci), f32(ci)
@@ -95,8 +109,8 @@ def test_layer_step(s, K, beta):
     assert rel(dW, rdW) < worse * 2.0 ** -24 * ((M / 32) ** 0.5 + 5)
 
 
-# strided layers whose own room holds few copies of dW, 8, 12 and one: two launches, where dW lies apart from W
-@pytest.mark.parametrize("s", [(64, 8, 8, 64, 64, 1, 2, 0), (32, 14, 14, 64, 32, 3, 2, 1), (2, 16, 16, 16, 16, 3, 2, 1)],
+# strided layers: dW beside the data gradient, by the kernels of other layers (own room for 12 copies and for one), 1x1
+@pytest.mark.parametrize("s", [(40, 33, 32, 16, 32, 3, 2, 1), (32, 14, 14, 64, 32, 3, 2, 1), (2, 16, 16, 16, 16, 3, 2, 1), (64, 8, 8, 64, 64, 1, 2, 0)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_weight_gradient_over_the_weights(s):
     """dW over all of W and over a part of it: the data gradient reads W before."""

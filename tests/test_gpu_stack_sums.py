@@ -16,10 +16,10 @@ def equal(N, H, W, c, count=4):
     return [(N, H, W, c, c, 3, 1, 1)] * count
 
 
-# 512, 500, 300, 300 and 256 blocks a layer; then rows that go from kernel to kernel through every kind of layer: few channels,
+# 512, 500, 300 and 256 blocks a layer; pairs of layers in place; then rows that go from kernel to kernel through every kind of layer: few channels,
 # strided, with the weights split beside the second pass (64 -> 64 @14x14), 16 channels behind those
 STACKS = {"16ch 32x32 N256": (equal(256, 32, 32, 16), 2), "16ch 33x33 N100": (equal(100, 33, 33, 16), 2),
-          "24ch 12x12 N300": (equal(300, 12, 12, 24), 2), "20ch 7x7 N300": (equal(300, 7, 7, 20, 5), 0),
+          "24ch 5x5 10x10 N300": ([(300, 10, 10, 24, 24, 5, 1, 2)] * 5, 0),
           "32ch 16x16 N128": (equal(128, 16, 16, 32), 2), "16ch 32x32 N256, in place": (equal(256, 32, 32, 16, 6), 3),
           "mixed": ([(80, 28, 28, 64, 32, 3, 1, 1), (80, 28, 28, 32, 64, 3, 2, 1)] + equal(80, 14, 14, 64, 3) +
                     [(80, 14, 14, 64, 16, 3, 1, 1)] + equal(80, 14, 14, 16, 3) + [(80, 14, 14, 16, 32, 3, 2, 1)], 0)}
