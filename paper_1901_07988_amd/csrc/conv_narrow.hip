@@ -1232,15 +1232,17 @@ int launch(hipStream_t st, Kern kern, unsigned blocks, int lds, const Args& a, c
 
 }  // namespace
 
-// Layers that the kernels for few channels may take.  Not:
-// - 1x1, whose GEMMs need no patch (32 -> 64 @16x16 N=41, stride 2, us, the other kernels / these: plain forward 2.7 / 3.9, gradient
-//   4.5 / 8.0, backward of a layer call 24 / 30; its forward 13.9 / 12.0);
-// - more than 4 million elements, and 3x3 layers that conv_split.hip takes beyond a few blocks' work per compute unit: there the
-//   splits of the weights by every wave cost more than the launches (64 -> 64 @28x28 N=20 68 / 70, @56x56 N=12 97 / 118);
-// - images of one to three channels on few pixels (3 -> 16 @34x33 N=8 50 / 53, N=96 91 / 81).
 static bool split_shape(const ConvGeom& g) {
   return g.R == 3 && g.S == 3 && g.pad == 1 && g.stride == 1 && g.Cin % 32 == 0 && g.Cout % 64 == 0;
 }
+static double gflop(const ConvGeom& g) { return 2e-9 * g.N * g.Ho * g.Wo * ((g.Cin + 15) / 16 * 16) * ((g.Cout + 15) / 16 * 16) * g.R * g.S; }
+
+// Layers that the kernels for few channels may take.  Not:
+// - 1x1, whose GEMMs need no patch (stride 2, us, the other kernels / these: 32 -> 32 @41x41 N=20 plain forward 3.3 / 4.7, gradient
+//   5.7 / 11.1; backward of 32 -> 64 @16x16 N=41 24 / 30; only the forward of layer calls takes 0.84 of the others' time);
+// - more than 4 million elements, and 3x3 layers that conv_split.hip takes beyond a few blocks' work per compute unit: there the
+//   splits of the weights by every wave cost more than the launches (64 -> 64 @28x28 N=20 68 / 70, @56x56 N=12 97 / 118);
+// - images of one to three channels on few pixels (3 -> 16 @34x33 N=8 50 / 53, N=96 91 / 81).
 static bool narrow_takes(const ConvGeom& g) {
   const int64_t M = (int64_t)g.N * g.H * g.W;
   if ((g.R == 1 && g.S == 1) || M * g.Cin > 4 << 20 || !in_range(g)) return false;
@@ -1248,7 +1250,6 @@ static bool narrow_takes(const ConvGeom& g) {
   if (g.Cin < 4 && M < 1 << 14) return false;
   return planned(g, FWD).ok && planned(g, DGRAD).ok;
 }
-static double gflop(const ConvGeom& g) { return 2e-9 * g.N * g.Ho * g.Wo * ((g.Cin + 15) / 16 * 16) * ((g.Cout + 15) / 16 * 16) * g.R * g.S; }
 
 // The rules below weigh the plans' us, which are within a fifth of 0.75 (forward) and 0.85 (gradient) of them, against those of the
 // kernels that take the layer otherwise: a launch, the rate, the chain of their contraction (870 layers, both measured; 0.6 to 1.2
@@ -1264,19 +1265,19 @@ bool narrow_fwd_pays(const ConvGeom& g) {
   return planned(g, FWD).p.fwd_us <= 4.8 + (split_shape(g) ? 0.0 : 11.7 * gflop(g)) + 0.0257 * g.R * g.S * ((g.Cin + 15) / 16 * 16);
 }
 
-// The plain gradient to the input (253 layers with channels in sixteens, stride 1: 0.71 of the others' time, none slower; strided
-// ones, whose classes of pixels follow each other, 16 -> 32 @13x13 N=280 13.1 / 18.6, but 32 -> 64 @16x16 N=128 14.8 / 13.1: not.
-// 241 other ones 0.52; not short contractions, 58 -> 7 @40x40 N=4, stride 2, 9.2 / 15.7, nor many blocks, 17 -> 15 @9x9 N=123 without
-// padding 9.3 / 14.6, 59 -> 48 @68x68 N=10 48.9 / 66.5).
+// The plain gradient to the input.  (Channels in sixteens, stride 1: 253 layers 0.71 of the others' time, none slower.  Not strided,
+// where the classes of pixels follow each other: 16 -> 32 @13x13 N=280 13.1 / 18.6, though 32 -> 64 @16x16 N=128 14.9 / 13.0.  Other
+// counts: 241 layers 0.52; not short contractions, 58 -> 7 @40x40 N=4, stride 2, 9.2 / 15.7, nor many blocks, 17 -> 15 @9x9 N=123
+// without padding 9.3 / 14.6, 59 -> 48 @68x68 N=10 48.9 / 66.5.)
 bool narrow_dgrad_pays(const ConvGeom& g) {
   if (!narrow_takes(g)) return false;
   if (!channels_in_tiles(g)) return g.R * g.S * g.Cout >= 100 && planned(g, DGRAD).p.dgrad_us <= 0.94 * ragged_dgrad_us(g);
   return g.stride == 1 && planned(g, DGRAD).p.dgrad_us <= 3.7 + 4.8 * gflop(g) + 0.0196 * g.R * g.S * g.Cout;
 }
 
-// The gradient to the input of a layer call, whose sums save a pass (with the other kernels' weight gradient 840 layers take 0.77 of
-// the time with theirs, 14 of them 1.03 to 1.17; channel counts off sixteen again by their us).  16-channel 3x3 layers in tiles of conv_halo.hip's fused backward have that (15 us
-// for all of 16 -> 16 @10x10 N=17, 24 here).
+// The gradient to the input of a layer call, whose sums save a pass (840 layers take 0.77 of the time with it, the other kernels'
+// weight gradient behind it, 14 of them 1.03 to 1.17).  16-channel 3x3 layers in conv_halo.hip's tiles have its fused backward (15 us
+// for all of 16 -> 16 @10x10 N=17, 24 with this).
 bool narrow_bwd_pays(const ConvGeom& g) {
   if (!narrow_takes(g) || (g.Cin == 16 && g.Cout == 16 && (c16_tiles(g, 1) > 0 || halo_bwd16_tiles(g) > 0))) return false;
   return channels_in_tiles(g) || planned(g, DGRAD).p.dgrad_us <= 4.0 + 1.1 * ragged_dgrad_us(g);
