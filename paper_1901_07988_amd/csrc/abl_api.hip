@@ -197,6 +197,9 @@ namespace {
 inline bool aliased(const void* a, const void* b) { return a == b; }
 // Layers of few channels whose forward has the prologue.
 bool narrow_fuses(const ConvGeom& g) { return g.Cin % 4 == 0 && g.Cout % 4 == 0 && narrow_fwd_pays(g); }
+// ... and whose stage with the prologue takes the same kernel.  (Where conv_split.hip carries the plain convolution that stage is the
+// halo kernel, on the fp32 instruction, as for the larger ones of these layers.)
+bool narrow_stage(const ConvGeom& g) { return halo_fused_supported(g) && narrow_fuses(g) && split_conv_blocks(g, 0) == 0; }
 // (*split_rows: path 1 on the split-operand kernel, rows of its sums of y; 0 = the halo kernel.)
 int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, bool naive, int* split_rows) {
   *split_rows = 0;
@@ -617,7 +620,7 @@ int abl_bn_conv_fwd(void* stream, const abl_shape* s, int K, uint32_t flags, con
   const bool bf16 = (flags & ABL_MATH_BF16) != 0;
   if (igemm_fused_supported(*s))
     return launch_conv_fwd_fused((hipStream_t)stream, *s, K, bf16, x, stats, W, skip, y, packed);
-  if (!bf16 && narrow_fuses(g) && halo_fused_supported(g))   // (as abl_forward does, here and below)
+  if (!bf16 && narrow_stage(g))   // (as abl_forward does, here and below)
     return launch_narrow_fwd((hipStream_t)stream, g, K, x, W, nullptr, 0, nullptr, nullptr, nullptr, const_cast<void*>(stats), skip, y,
                              packed, nullptr);
   int split_rows;
@@ -700,7 +703,7 @@ int abl_split_products(const abl_shape* s, int K, uint32_t flags, int stage) {
     case ABL_STAGE_CONV_FWD: return narrow_fwd_pays(g) || split_conv_blocks(g, 0) > 0 ? 6 : 0;
     case ABL_STAGE_BN_CONV_FWD:
       if (K == 32 || igemm_fused_supported(*s) || !halo_fused_supported(g)) return 0;
-      return narrow_fuses(g) || c16_tiles(g, 0) > 0 || (forward_fused_path(*s, g, K, false, false, &rows) == 1 && rows > 0) ? 6 : 0;
+      return narrow_stage(g) || c16_tiles(g, 0) > 0 || (forward_fused_path(*s, g, K, false, false, &rows) == 1 && rows > 0) ? 6 : 0;
     case ABL_STAGE_CONV_DGRAD: return narrow_dgrad_pays(g) || split_conv_blocks(g, 1) > 0 ? 6 : 0;
     case ABL_STAGE_CONV_DGRAD_BN_REDUCE:
       if (K == 32 || !reduce_stage_accepts(g)) return 0;

@@ -1265,14 +1265,16 @@ bool narrow_fwd_pays(const ConvGeom& g) {
   return planned(g, FWD).p.fwd_us <= 4.8 + (split_shape(g) ? 0.0 : 11.7 * gflop(g)) + 0.0257 * g.R * g.S * ((g.Cin + 15) / 16 * 16);
 }
 
-// The plain gradient to the input.  (Channels in sixteens, stride 1: 253 layers 0.71 of the others' time, none slower.  Not strided,
-// where the classes of pixels follow each other: 16 -> 32 @13x13 N=280 13.1 / 18.6, though 32 -> 64 @16x16 N=128 14.9 / 13.0.  Other
-// counts: 241 layers 0.52; not short contractions, 58 -> 7 @40x40 N=4, stride 2, 9.2 / 15.7, nor many blocks, 17 -> 15 @9x9 N=123
+// The plain gradient to the input.  (Channels in sixteens, stride 1: 253 layers 0.71 of the others' time, none slower.  Strided ones,
+// whose classes of pixels follow each other, where a block has few of them: 122 layers 0.85, six 1.03 to 1.31; 16 -> 32 @13x13 N=280,
+// two rounds, 13.1 / 18.6, 32 -> 64 @16x16 N=128 14.9 / 13.0.  Other counts: 241 layers 0.52; not short contractions, 58 -> 7 @40x40 N=4, stride 2, 9.2 / 15.7, nor many blocks, 17 -> 15 @9x9 N=123
 // without padding 9.3 / 14.6, 59 -> 48 @68x68 N=10 48.9 / 66.5.)
 bool narrow_dgrad_pays(const ConvGeom& g) {
   if (!narrow_takes(g)) return false;
   if (!channels_in_tiles(g)) return g.R * g.S * g.Cout >= 100 && planned(g, DGRAD).p.dgrad_us <= 0.94 * ragged_dgrad_us(g);
-  return g.stride == 1 && planned(g, DGRAD).p.dgrad_us <= 3.7 + 4.8 * gflop(g) + 0.0196 * g.R * g.S * g.Cout;
+  const NarrowPlan& p = planned(g, DGRAD).p;
+  if (g.stride > 1) return p.t.rows * g.W * (g.Cin / 16) * cdiv(p.blocks, 256) <= 300;
+  return p.dgrad_us <= 3.7 + 4.8 * gflop(g) + 0.0196 * g.R * g.S * g.Cout;
 }
 
 // The gradient to the input of a layer call, whose sums save a pass (840 layers take 0.77 of the time with it, the other kernels'
