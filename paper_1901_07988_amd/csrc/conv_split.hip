@@ -150,6 +150,10 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   // spilled without).  Elsewhere the free order of the loads is worth more (us: nine sets 33.4 / 44.5, opaque 36.8 / 50.6; fp32 256
   // -> 256 @14x14 70.2 / 76.3, opaque 73.2 / 79.1; bf16 1x1 1024 -> 256 22.0 / 23.0, opaque 22.6 / 24.0, four waves 33.3 / 32.1)
   constexpr bool OPAQUE = NP == 1 && NT == 2 && (TAPS == 9 || KS == 1);
+  // Remainders by dot products (split3): 1x1 layers (1024 -> 256 @14x14 in a layer call 217 -> 211 us, plain forwards 0.99 of the time,
+  // 0.95 to 1.04) and 3x3 gradients with the weights in parts.  Other 3x3 kernels depend on the grid: 0.92 to 1.05 of the time in stage
+  // calls, and 512 -> 128 @31x31 N=35 in a layer call 257 us without, 282 with.
+  constexpr bool DOT = TAPS != 9 || (PRE && FUSE == 0);
   static_assert(NF % SLOTS == 0, "a k-step starts in the slot of the one before");
   // the patch: bytes from a position, eight channels, a part and a chunk to the next
   constexpr int NPOS = SU * THREADS / C8;
@@ -248,7 +252,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
     if (TAPS == 9 || s_off[u] < 0)
 #pragma unroll
       for (int e = 0; e < 8; ++e) sv[u][e] = s_off[u] < 0 ? 0.0f : sv[u][e];
-    if constexpr (NP == 3) split3(sv[u], h, m, l);
+    if constexpr (NP == 3) split3<DOT>(sv[u], h, m, l);
     else h = to_bf16x8(sv[u]);
     const int it = tid + THREADS * u;
     const int pos = TAPS == 9 ? (it & 15) + 16 * (it / (16 * C8)) : it / C8;
@@ -412,7 +416,7 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
           float x[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(use[j][e]);
-          if constexpr (NP == 3) split3(x, bh[j], bm[j], bl[j]);
+          if constexpr (NP == 3) split3<DOT>(x, bh[j], bm[j], bl[j]);
           else bh[j] = to_bf16x8(x);
         }
       }
