@@ -1027,12 +1027,18 @@ bool split_beats_image(const ConvGeom& g, int mode) {
   return n >= 128 || Cg < 512 || (int64_t)g.N * (Ng / 64) > 256;
 }
 
-// ... and where the weights come in parts, which the image kernel does not read: with 512 channels and more to contract, on every
-// grid (us, layer, image kernel / here: 512 -> 512 @8x8 N=40 192 / 117, N=14 112 / 93, @7x7 N=28 115 / 100; 256 -> 256 about the
-// same on both, @14x14 N=40 105.7 / 106.4, @10x10 N=52 91.0 / 87.8).
+// ... and where the weights come in parts, which the image kernel does not read: with 512 channels and more to contract (us, layer,
+// image kernel / here: 512 -> 512 @8x8 N=40 192 / 117, N=14 112 / 93, @7x7 N=28 115 / 100; 256 -> 256 about the same on both, @14x14
+// N=40 105.7 / 106.4, @10x10 N=52 91.0 / 87.8).  Not on images of a tile or two where that kernel's grid is one round of the compute
+// units (forward of 512 -> 64 @3x3 N=108 28.9 / 34.6, 512 -> 128 @4x5 N=74 33.8 / 36.6; both equal below 60 blocks, and 512 -> 512
+// @3x5 N=58, two rounds, 44.1 / 37.8; gradients, with their sums, 0.81 to 1 of the time there too).
 bool split_parts_beat_image(const ConvGeom& g, int mode) {
+  if (split_beats_image(g, mode)) return true;
+  const int Cg = mode == 0 ? g.Cin : g.Cout, Ng = mode == 0 ? g.Cout : g.Cin;
+  const int64_t blocks = (int64_t)g.N * (Ng / 64);
+  if (Cg < 512 || (mode == 0 && g.H * g.W <= 20 && blocks > 60 && blocks <= 256)) return false;
   Plan p;
-  return split_beats_image(g, mode) || ((mode == 0 ? g.Cin : g.Cout) >= 512 && make_plan(g, mode, 1, mode == 1, p));
+  return make_plan(g, mode, 1, mode == 1, p);
 }
 
 // Four-wave grids that fill less than three quarters of their 512 places are not (512 -> 128 @28x28, step, us, with the

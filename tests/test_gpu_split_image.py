@@ -44,6 +44,20 @@ def test_layer_against_image_kernel(s, K):
         assert float((got - want).abs().max()) <= 2.0 ** -20 * float(want.abs().max())
 
 
+@pytest.mark.parametrize("s", [(108, 3, 3, 512, 64, 3), (74, 4, 5, 512, 128, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_one_round_of_small_images(s):
+    """Forward on images of a tile or two, one round of the compute units: the image kernel in layer calls too."""
+    print("case bf16 512 channels, small images", s, flush=True)
+    K, s9, C, M = 4, shape9(s), s[3], s[0] * s[1] * s[2]
+    x, w, gamma, beta, dy = draw(s, 18)
+    packed, stats, scratch = raw(B.abl_packed_bytes(s9, K)), raw(B.abl_stats_bytes(s9)), raw(B.abl_scratch_bytes(s9, K))
+    y, y2, a3 = f32(*dy.shape), f32(*dy.shape), f32(*x.shape)
+    B.abl_forward(s9, K, x, w, gamma, beta, None, scratch, y, packed, stats, flags=B.ABL_MATH_BF16)
+    B.abl_bn_relu_pack(x, M, C, K, stats, a3, raw(B.abl_packed_bytes(s9, K)))
+    B.abl_conv_fwd(s9, a3, w, None, y2, flags=B.ABL_MATH_BF16)
+    assert torch.equal(y, y2)
+
+
 def test_rule():
     """What the stage calls take is what it was."""
     assert not R.beats_image(SHAPES[0], 0) and not R.beats_image(SHAPES[0], 1)
