@@ -414,6 +414,22 @@ __device__ inline bf16x8_t to_bf16x8(const float (&v)[8]) {
   return bf16x8_t{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3],
                   (__bf16)v[4], (__bf16)v[5], (__bf16)v[6], (__bf16)v[7]};
 }
+// ---- 16-byte pieces of eight bf16 values in LDS (conv_c16.hip, conv_narrow.hip) ----
+typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) short4_t lds_short4;
+
+__device__ inline floatx4 mfma32(const bf16x8_t& a, const bf16x8_t& b, const floatx4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ inline bf16x8_t piece(const char* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
+__device__ inline void put(char* p, const bf16x8_t& v) { *reinterpret_cast<bf16x8_t*>(p) = v; }
+// Eight positions of one channel: 16 lanes fetch four positions' 16 channels each time and receive one channel's four.
+__device__ inline bf16x8_t transposed(const char* p, const char* q) {
+  struct two { short4_t a, b; };
+  const two t{__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)p), __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)q)};
+  return __builtin_bit_cast(bf16x8_t, t);
+}
+__device__ inline bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
 // ---- fp32 operands in three bf16 parts (conv_split.hip) ----
 constexpr float kUp = 0x1p23f, kDown = 0x1p-46f;   // both operands are split as 2^23 times their values
 // u holds two bf16 values: a minus the lower or the upper one in one instruction (fp32 result of exact products, here exact).  The

@@ -44,22 +44,6 @@ struct C16Plan {
   Divisor by_pw, by_w, by_tiles;
 };
 
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) short4_t lds_short4;
-
-__device__ inline floatx4 mfma32(const bf16x8_t& a, const bf16x8_t& b, const floatx4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-__device__ inline bf16x8_t piece(const char* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
-__device__ inline void put(char* p, const bf16x8_t& v) { *reinterpret_cast<bf16x8_t*>(p) = v; }
-// Eight positions of one channel: see the head of the file.
-__device__ inline bf16x8_t transposed(const char* p, const char* q) {
-  struct two { short4_t a, b; };
-  const two t{__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)p), __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)q)};
-  return __builtin_bit_cast(bf16x8_t, t);
-}
-__device__ inline bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
-
 // Six of the nine products of two split operands (the others are below 2^-24 of it): the large one, the rest.  (Two sums of the
 // rest in turn: an MFMA waits for the one before it on the same registers.)
 __device__ inline void six(const bf16x8_t (&a)[3], const bf16x8_t (&b)[3], floatx4& big, floatx4& r0, floatx4& r1) {

@@ -62,21 +62,6 @@ struct NarrowPlan {
   Divisor by_pw, by_wo, by_tiles, by_ip, by_op, by_dw, by_nw0, by_nw1, wby_pw, wby_tiles;
 };
 
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) short4_t lds_short4;
-
-__device__ inline floatx4 mfma32(const bf16x8_t& a, const bf16x8_t& b, const floatx4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-__device__ inline bf16x8_t piece(const char* p) { return *reinterpret_cast<const bf16x8_t*>(p); }
-__device__ inline void put(char* p, const bf16x8_t& v) { *reinterpret_cast<bf16x8_t*>(p) = v; }
-__device__ inline bf16x8_t transposed(const char* p, const char* q) {
-  struct two { short4_t a, b; };
-  const two t{__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)p), __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)q)};
-  return __builtin_bit_cast(bf16x8_t, t);
-}
-__device__ inline bool finite(float v) { return __builtin_fabsf(v) <= 3.402823466e38f; }
-
 // Channels c0 .. c0 + 7 of C as they are in memory (past the last: any; `below` clears them where they are used - a select next to
 // the load would wait for it).
 template <bool VEC>
