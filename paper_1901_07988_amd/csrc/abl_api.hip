@@ -197,9 +197,12 @@ namespace {
 inline bool aliased(const void* a, const void* b) { return a == b; }
 // Layers of few channels whose forward has the prologue.
 bool narrow_fuses(const ConvGeom& g) { return g.Cin % 4 == 0 && g.Cout % 4 == 0 && narrow_fwd_pays(g); }
-// ... and whose stage with the prologue takes the same kernel.  (Where conv_split.hip carries the plain convolution that stage is the
-// halo kernel, on the fp32 instruction, as for the larger ones of these layers.)
-bool narrow_stage(const ConvGeom& g) { return halo_fused_supported(g) && narrow_fuses(g) && split_conv_blocks(g, 0) == 0; }
+// ... and whose stage with the prologue takes the same kernel.  (Where conv_split.hip has the plain convolution but not the one with
+// the prologue, that stage is the halo kernel, on the fp32 instruction, as for the larger ones of these layers.)
+bool narrow_stage(const ConvGeom& g) {
+  int rows;
+  return halo_fused_supported(g) && narrow_fuses(g) && (split_conv_blocks(g, 0) == 0 || split_forward3(g, &rows) > 0);
+}
 // (*split_rows: path 1 on the split-operand kernel, rows of its sums of y; 0 = the halo kernel.)
 int forward_fused_path(const abl_shape& s, const ConvGeom& g, int K, bool bf16, bool naive, int* split_rows) {
   *split_rows = 0;

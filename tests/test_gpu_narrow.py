@@ -109,6 +109,23 @@ def test_layer_step(s, K, beta):
     assert rel(dW, rdW) < worse * 2.0 ** -24 * ((M / 32) ** 0.5 + 5)
 
 
+# layers whose convolution with the prologue conv_split.hip has too
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("s", [(64, 12, 12, 64, 64, 3, 1, 1), (27, 15, 15, 32, 128, 3, 1, 1), (68, 9, 9, 64, 128, 3, 1, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_stage_with_the_prologue_is_the_layers_kernel(s, K):
+    """Where abl_forward_is_fused answers 1, abl_bn_conv_fwd runs what abl_forward runs: the same bits."""
+    print("case layer of few channels, stage with the prologue", s, K, flush=True)
+    s9, ci = shape9(s), s[3]
+    x, w, gamma, beta, dy = draw(s, 0.1)
+    assert B.abl_forward_is_fused(s9, K) == 1
+    packed, stats, p2 = raw(B.abl_packed_bytes(s9, K)), raw(B.abl_stats_bytes(s9)), raw(B.abl_packed_bytes(s9, K))
+    y, y2, skip = f32(*dy.shape), f32(*dy.shape), torch.randn_like(dy)
+    B.abl_forward(s9, K, x, w, gamma, beta, skip, raw(B.abl_scratch_bytes(s9, K)), y, packed, stats)
+    B.abl_bn_conv_fwd(s9, K, x, stats, w, skip, y2, p2)
+    assert torch.equal(packed, p2) and torch.equal(y, y2)
+
+
 # strided layers: dW beside the data gradient, by the kernels of other layers (own room for 12 copies and for one), 1x1
 @pytest.mark.parametrize("s", [(40, 33, 32, 16, 32, 3, 2, 1), (32, 14, 14, 64, 32, 3, 2, 1), (2, 16, 16, 16, 16, 3, 2, 1), (64, 8, 8, 64, 64, 1, 2, 0)],
                          ids=lambda s: "x".join(map(str, s)))
