@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libabl.so")
 
-# every HIP translation unit: no packed-fp32 instructions (they have misbehaved on the test machines)
+# every HIP translation unit: no packed-fp32 instructions (some forms have given wrong results on this hardware)
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-variable",
           "-Wno-unused-but-set-variable",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

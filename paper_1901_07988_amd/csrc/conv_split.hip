@@ -151,8 +151,8 @@ __global__ __launch_bounds__(64 * WN * KS, 2) void split_conv_kernel(const float
   // -> 256 @14x14 70.2 / 76.3, opaque 73.2 / 79.1; bf16 1x1 1024 -> 256 22.0 / 23.0, opaque 22.6 / 24.0, four waves 33.3 / 32.1)
   constexpr bool OPAQUE = NP == 1 && NT == 2 && (TAPS == 9 || KS == 1);
   // Remainders by dot products (split3): 1x1 layers (1024 -> 256 @14x14 in a layer call 217 -> 211 us, plain forwards 0.99 of the time,
-  // 0.95 to 1.04) and 3x3 gradients with the weights in parts.  Other 3x3 kernels depend on the grid: 0.92 to 1.05 of the time in stage
-  // calls, and 512 -> 128 @31x31 N=35 in a layer call 257 us without, 282 with.
+  // 0.95 to 1.04) and 3x3 kernels with the weights in parts and no prologue.  Other 3x3 kernels depend on the grid: 0.92 to 1.05 of the
+  // time in stage calls, and with the prologue 512 -> 128 @31x31 N=35 in a layer call 257 us without, 282 with.
   constexpr bool DOT = TAPS != 9 || (PRE && FUSE == 0);
   static_assert(NF % SLOTS == 0, "a k-step starts in the slot of the one before");
   // the patch: bytes from a position, eight channels, a part and a chunk to the next
