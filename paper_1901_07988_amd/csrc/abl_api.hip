@@ -391,14 +391,14 @@ int backward_impl(hipStream_t st, const abl_shape* s, int K, uint32_t flags, con
     const int64_t own = (int64_t)(wgrad_partial_bytes(*s) / (n * sizeof(float))), all = M * s->Cin / n;
     int rows = 0, copies = 0;
     // both contractions in one launch, the copies of dW in their own place
-    if (channels_in_tiles(g) && narrow_wgrad_pays(g, own, true) && narrow_bwd_blocks(g, own, true, &rows, &copies)) {
+    if (channels_in_tiles(g) && narrow_wgrad_pays(g, K, own, true) && narrow_bwd_blocks(g, own, true, &rows, &copies)) {
       if (int e = launch_narrow_bwd(st, g, K, 3, dy, W, packed, stats, da3, static_cast<double*>(red), static_cast<float*>(wpart), own)) return e;
       const DwSum dwsum{static_cast<const float*>(wpart), copies, n, dW};
       return launch_bn_bwd_finish(st, packed, stats, da3, M, s->Cin, K, accum, red, rows, dx, dgamma, dbeta, &dwsum, 0.0f, next);
     }
     // channel counts off sixteen: the weight gradient goes first, its copies in the place of dA3
     if (!channels_in_tiles(g)) {
-      if (all >= 1 && narrow_wgrad_pays(g, all, false) && narrow_bwd_blocks(g, all, false, &rows, &copies)) {
+      if (all >= 1 && narrow_wgrad_pays(g, K, all, false) && narrow_bwd_blocks(g, all, false, &rows, &copies)) {
         if (int e = launch_narrow_bwd(st, g, K, 2, dy, W, packed, stats, nullptr, nullptr, da3, all)) return e;
         const DwSum dwsum{da3, copies, n, dW};
         if (int e = launch_split_weights(st, SplitWeights{}, &dwsum)) return e;

@@ -166,7 +166,7 @@ int launch_c16_stack_bwd(hipStream_t st, const abl_layer* layers, int L, int K, 
 bool narrow_fwd_pays(const ConvGeom& g);
 bool narrow_dgrad_pays(const ConvGeom& g);
 bool narrow_bwd_pays(const ConvGeom& g);
-bool narrow_wgrad_pays(const ConvGeom& g, int64_t room, bool both);
+bool narrow_wgrad_pays(const ConvGeom& g, int K, int64_t room, bool both);
 // Blocks of the forward (rows of its sums of y); 0: not supported.
 int narrow_fwd_blocks(const ConvGeom& g);
 // Rows of the statistics' sums that its blocks should have to add up at most.

@@ -1244,46 +1244,83 @@ static bool narrow_takes(const ConvGeom& g) {
 // Forward, with or without the prologue (which saves a launch or two: layer calls of 375 layers with channels in sixteens 0.67 of the
 // others' time, plain forwards 0.65; 249 other ones 0.67 and 0.53).  Plain forwards of 16-channel 3x3 layers: 5.9 us against 6.5
 // where these are ahead, but 7.3 against 6.5 elsewhere.  (conv_split.hip's layers take about the same time up to a million pixels by
-// channels: 64 -> 64 13.9 us from N=7 to 134 @10x10.)
+// channels: 64 -> 64 13.9 us from N=7 to 134 @10x10.)  Images of one to three channels: conv_ragged.hip's kernels contract 32 elements
+// at a time whatever tap they belong to, or have a thread per output (plain forward, us, those / here: 3 -> 64 @23x29 N=86 15.8 / 18.4,
+// 1 -> 38 5x5 stride 2 @24x17 N=43 5.0 / 6.8; 3 -> 16 @32x32 N=128 12.8 / 10.2, 3 -> 60 5x5 @16x24 N=55 13.3 / 10.6, 1 -> 63 @18x17
+// N=113, a thread per output, 17.0 / 11.5).
 bool narrow_fwd_pays(const ConvGeom& g) {
   if (!narrow_takes(g) || c16_tiles(g, 0) > 0) return false;
+  if (g.Cin < 4) {
+    const double outputs = 1e-6 * g.N * g.Ho * g.Wo * g.Cout, chunks = (g.R * g.S * g.Cin + 31) / 32;
+    const double others = 3.5 + (g.R * g.S * g.Cin <= 9 ? 6.2 * outputs : chunks + (2.4 + 0.7 * chunks) * outputs);
+    return 0.77 * planned(g, FWD).p.fwd_us + 1.7 * outputs <= others;
+  }
   return planned(g, FWD).p.fwd_us <= 4.8 + (split_shape(g) ? 0.0 : 11.7 * gflop(g)) + 0.0257 * g.R * g.S * ((g.Cin + 15) / 16 * 16);
 }
 
-// The plain gradient to the input.  (Channels in sixteens, stride 1: 253 layers 0.71 of the others' time, none slower.  Strided ones,
-// whose classes of pixels follow each other, where a block has few of them: 122 layers 0.85, six 1.03 to 1.31; 16 -> 32 @13x13 N=280,
-// two rounds, 13.1 / 18.6, 32 -> 64 @16x16 N=128 14.9 / 13.0.  Other counts: 241 layers 0.52; not short contractions, 58 -> 7 @40x40 N=4, stride 2, 9.2 / 15.7, nor many blocks, 17 -> 15 @9x9 N=123
-// without padding 9.3 / 14.6, 59 -> 48 @68x68 N=10 48.9 / 66.5.)
+// Channel counts off sixteen: us of the gradient to the input here.  Channels off fours are read and written one by one, which takes
+// 1.0 to 1.3 of what the plan expects, and 1.4 to 2.2 where rows of weights have 16, 32 ... of them (64 layers; 39 -> 64 @25x29 N=40
+// 67 us, other kernels 38; 36 -> 64 @26x17 N=39 19 and 37).
+static double ragged_us_here(const ConvGeom& g) {
+  return planned(g, DGRAD).p.dgrad_us * (g.Cin % 4 != 0 && g.Cout % 16 == 0 ? 2.0 : 1.0);
+}
+// Strided layers: us of the gradient to the input here and on the other kernels (igemm_kernel, with the pass of Eq. 6-7 behind it where
+// `sums`).  Here a unit of work is one class of pixels, short for its epilogue, which the plans leave out: 293 layers, both within a
+// fifth of these.
+static double strided_dgrad_us(const ConvGeom& g) {
+  const NarrowPlan& p = planned(g, DGRAD).p;
+  return 1.7 + 0.34 * p.dgrad_us + cdiv(p.blocks, 256) * (g.Cin / 16) * (0.0161 * p.t.rows * g.W + 1.09);
+}
+static double strided_igemm_us(const ConvGeom& g, bool sums) {
+  const double elements = (double)g.N * g.H * g.W * g.Cin, taps = g.R * g.S;
+  return sums ? 7.4 + 7.0 * gflop(g) + 0.0084 * taps * g.Cout + 3.8e-6 * elements + 0.33 * taps
+              : 2.85 + 8.7 * gflop(g) + 0.0078 * taps * g.Cout + 1.8e-6 * elements + 0.37 * taps;
+}
+
+// The plain gradient to the input.  (Channels in sixteens, stride 1: 253 layers 0.71 of the others' time, none slower.  Strided: 290
+// layers 0.90, six of them more than 1.03, with a margin for the longer ones, 13 without it; by the pixels of a block alone it was
+// 0.99, and 87: 16 -> 128 @5x98 N=28 without padding 14.2 / 23.8.  Other counts: 241 layers 0.52; not short contractions, 58 -> 7
+// @40x40 N=4, stride 2, 9.2 / 15.7, nor many blocks, 17 -> 15 @9x9 N=123 without padding 9.3 / 14.6, 59 -> 48 @68x68 N=10 48.9 / 66.5.)
 bool narrow_dgrad_pays(const ConvGeom& g) {
   if (!narrow_takes(g)) return false;
-  if (!channels_in_tiles(g)) return g.R * g.S * g.Cout >= 100 && planned(g, DGRAD).p.dgrad_us <= 0.94 * ragged_dgrad_us(g);
-  const NarrowPlan& p = planned(g, DGRAD).p;
-  if (g.stride > 1) return p.t.rows * g.W * (g.Cin / 16) * cdiv(p.blocks, 256) <= 300;
-  return p.dgrad_us <= 3.7 + 4.8 * gflop(g) + 0.0196 * g.R * g.S * g.Cout;
+  if (!channels_in_tiles(g)) return g.R * g.S * g.Cout >= 100 && ragged_us_here(g) <= 0.94 * ragged_dgrad_us(g);
+  if (g.stride > 1) {
+    const double others = strided_igemm_us(g, false);
+    return strided_dgrad_us(g) <= std::min(others, 3.0 + 0.7 * others);
+  }
+  return planned(g, DGRAD).p.dgrad_us <= 3.7 + 4.8 * gflop(g) + 0.0196 * g.R * g.S * g.Cout;
 }
 
 // The gradient to the input of a layer call, whose sums save a pass (840 layers take 0.77 of the time with it, the other kernels'
-// weight gradient behind it, 14 of them 1.03 to 1.17).  16-channel 3x3 layers in conv_halo.hip's tiles have its fused backward (15 us
-// for all of 16 -> 16 @10x10 N=17, 24 with this).
+// weight gradient behind it, 14 of them 1.03 to 1.17).  Not where that takes longer than theirs with the sums: conv_split.hip's (two
+// rounds of blocks, backward of 64 -> 64 @6x6 N=300 44.9 / 53.8; 198 layers of stride 1, 0.75 of the time), igemm_kernel where a class has
+// a tap or two on wide rows (64 -> 32 2x2 @51x51 N=1 23.2 / 30.6, 64 -> 64 @57x57 N=3 without padding 36.9 / 47.1).  16-channel 3x3 layers
+// in conv_halo.hip's tiles have its fused backward (15 us for all of 16 -> 16 @10x10 N=17, 24 with this).
 bool narrow_bwd_pays(const ConvGeom& g) {
   if (!narrow_takes(g) || (g.Cin == 16 && g.Cout == 16 && (c16_tiles(g, 1) > 0 || halo_bwd16_tiles(g) > 0))) return false;
-  return channels_in_tiles(g) || planned(g, DGRAD).p.dgrad_us <= 4.0 + 1.1 * ragged_dgrad_us(g);
+  if (!channels_in_tiles(g)) return ragged_us_here(g) <= 4.0 + 1.1 * ragged_dgrad_us(g);
+  if (g.stride > 1) return strided_dgrad_us(g) <= strided_igemm_us(g, true);
+  const double chain = g.R * g.S * g.Cout, us = planned(g, DGRAD).p.dgrad_us;
+  if (split_shape(g)) return us <= 6.2 + 0.0239 * chain;
+  return us <= 7.0 + 6.5 * gflop(g) + 0.0294 * chain + 4.2e-6 * g.N * g.H * g.W * g.Cin;
 }
 
 // The weight gradient beside it (`both`; room: copies).  A block walks its share of the tiles, so it pays where those are few, and
 // hidden by the other gradient for the most part, or the others' is long (backward, us, the others' weight gradient behind the data
 // gradient here / both here: 32 -> 32 @16x16 N=32, one tile, 22.0 / 20.1; 16 -> 32 @32x32 N=128 stride 2, two, 40.2 / 34.3; 48 -> 32
-// @6x6 N=36 stride 2, nine, 20.7 / 90; 890 layers, 1.03 of the better one of both).
+// @6x6 N=36 stride 2, nine, 20.7 / 90; 890 layers, 1.03 of the better one of both).  Codes of 8 bits have integers in two parts where
+// beta is not 0: a quarter more of its time at the median, twice at worst (48 -> 64 @58x81 N=6 68.8 / 107.4).  Nor where
+// the places that it takes cost the other gradient a second round of blocks (32 -> 32 @16x16 N=200, 8 bits, 45.2 / 60.6).
 // Channel counts off sixteen: in a launch of its own against conv_ragged.hip's (51 -> 66 5x5 @13x17 N=19 150 / 837, 9 -> 16 5x5
 // @3x25 N=85 stride 2 35 / 13.5; 270 layers, 1.01 of the better one).
-bool narrow_wgrad_pays(const ConvGeom& g, int64_t room, bool both) {
+bool narrow_wgrad_pays(const ConvGeom& g, int K, int64_t room, bool both) {
   const Planned& k = planned(g, both ? BOTH : WGRAD, room);
   if (!k.ok) return false;
   const double w = k.p.wgrad_us, d = k.p.dgrad_us;
   if (!both) return 1.6 * w + 4.0 <= ragged_wgrad_us(g, (size_t)g.N * g.H * g.W * g.Cin * sizeof(float));
-  if (k.p.w.count > 3 * k.p.copies) return false;
+  if (k.p.w.count > 3 * k.p.copies || d > 1.9 * planned(g, DGRAD).p.dgrad_us) return false;
   const double others = 7.0 + 17.6 * gflop(g) + 0.65e-6 * ((double)g.N * g.H * g.W * g.Cin * 0.5 + 4.0 * g.N * g.Ho * g.Wo * g.Cout);
-  return std::max(1.2 * w, d) + 2.0 <= planned(g, DGRAD).p.dgrad_us + others;
+  return std::max((K == 8 ? 1.45 : 1.2) * w, d) + 2.0 <= planned(g, DGRAD).p.dgrad_us + others;
 }
 
 int narrow_fwd_rows(const ConvGeom& g) { return std::min(kMaxPartialBlocks, std::max(32, 4096 / g.Cin)); }

@@ -189,3 +189,18 @@ def test_split_products_of_few_channels(B, shape, K, want):
     """The kernels for few channels split their operands too."""
     assert [B.abl_split_products(shape, K, n) for n in B.STAGES] == want
     assert [B.abl_split_products(shape, K, n, B.ABL_MATH_BF16) for n in B.STAGES] == [0] * 5
+
+
+# N, H, W, Cin, Cout, R, S, stride, pad; a stage; whether the kernels for few channels are the faster ones (us, the others / these)
+@pytest.mark.parametrize("shape,stage,want", [
+    ((3, 12, 12, 32, 48, 3, 3, 2, 1), "conv_dgrad", 6),      # 9.4 / 8.9
+    ((28, 5, 98, 16, 128, 3, 3, 2, 0), "conv_dgrad", 0),     # 14.2 / 23.8: long contractions of strided layers
+    ((91, 13, 13, 64, 128, 3, 3, 2, 1), "conv_dgrad", 0),    # 22.2 / 27.0
+    ((39, 26, 17, 36, 64, 3, 3, 1, 1), "conv_dgrad", 6),     # 37.1 / 18.8
+    ((40, 25, 29, 39, 64, 3, 3, 1, 1), "conv_dgrad", 0),     # 38.3 / 67.3: channels off fours, 64 to contract
+    ((128, 32, 32, 3, 16, 3, 3, 1, 1), "conv_fwd", 6),       # 12.8 / 10.2
+    ((113, 18, 17, 1, 63, 3, 3, 1, 1), "conv_fwd", 6),       # 17.0 / 11.5
+    ((86, 23, 29, 3, 64, 3, 3, 1, 1), "conv_fwd", 0),        # 15.8 / 18.4: images of three channels, many outputs
+    ((43, 24, 17, 1, 38, 5, 5, 2, 2), "conv_fwd", 0)])       # 5.0 / 6.8
+def test_few_channels_where_they_are_faster(B, shape, stage, want):
+    assert B.abl_split_products(shape, 4, stage) == want
