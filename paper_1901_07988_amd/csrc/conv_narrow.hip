@@ -1259,10 +1259,10 @@ bool narrow_fwd_pays(const ConvGeom& g) {
 }
 
 // Channel counts off sixteen: us of the gradient to the input here.  Channels off fours are read and written one by one, which takes
-// 1.0 to 1.3 of what the plan expects, and 1.4 to 2.2 where rows of weights have 16, 32 ... of them (64 layers; 39 -> 64 @25x29 N=40
+// 1.0 to 1.5 of what the plan expects, and 1.4 to 2.2 where rows of weights have 16, 32 ... of them (250 layers; 39 -> 64 @25x29 N=40
 // 67 us, other kernels 38; 36 -> 64 @26x17 N=39 19 and 37).
 static double ragged_us_here(const ConvGeom& g) {
-  return planned(g, DGRAD).p.dgrad_us * (g.Cin % 4 != 0 && g.Cout % 16 == 0 ? 2.0 : 1.0);
+  return planned(g, DGRAD).p.dgrad_us * (g.Cin % 4 == 0 || g.Cout % 16 != 0 ? 1.0 : g.Cout % 64 == 0 ? 2.0 : 1.65);
 }
 // Strided layers: us of the gradient to the input here and on the other kernels (igemm_kernel, with the pass of Eq. 6-7 behind it where
 // `sums`).  Here a unit of work is one class of pixels, short for its epilogue, which the plans leave out: 293 layers, both within a
@@ -1298,11 +1298,12 @@ bool narrow_dgrad_pays(const ConvGeom& g) {
 // in conv_halo.hip's tiles have its fused backward (15 us for all of 16 -> 16 @10x10 N=17, 24 with this).
 bool narrow_bwd_pays(const ConvGeom& g) {
   if (!narrow_takes(g) || (g.Cin == 16 && g.Cout == 16 && (c16_tiles(g, 1) > 0 || halo_bwd16_tiles(g) > 0))) return false;
-  if (!channels_in_tiles(g)) return ragged_us_here(g) <= 4.0 + 1.1 * ragged_dgrad_us(g);
+  const double elements = (double)g.N * g.H * g.W * g.Cin;
+  if (!channels_in_tiles(g)) return ragged_us_here(g) <= ragged_dgrad_us(g) + 5.0 + 4e-6 * elements;   // (and the pass that it saves)
   if (g.stride > 1) return strided_dgrad_us(g) <= strided_igemm_us(g, true);
   const double chain = g.R * g.S * g.Cout, us = planned(g, DGRAD).p.dgrad_us;
   if (split_shape(g)) return us <= 6.2 + 0.0239 * chain;
-  return us <= 7.0 + 6.5 * gflop(g) + 0.0294 * chain + 4.2e-6 * g.N * g.H * g.W * g.Cin;
+  return us <= 7.0 + 6.5 * gflop(g) + 0.0294 * chain + 4.2e-6 * elements;
 }
 
 // The weight gradient beside it (`both`; room: copies).  A block walks its share of the tiles, so it pays where those are few, and
@@ -1312,12 +1313,13 @@ bool narrow_bwd_pays(const ConvGeom& g) {
 // beta is not 0: a quarter more of its time at the median, twice at worst (48 -> 64 @58x81 N=6 68.8 / 107.4).  Nor where
 // the places that it takes cost the other gradient a second round of blocks (32 -> 32 @16x16 N=200, 8 bits, 45.2 / 60.6).
 // Channel counts off sixteen: in a launch of its own against conv_ragged.hip's (51 -> 66 5x5 @13x17 N=19 150 / 837, 9 -> 16 5x5
-// @3x25 N=85 stride 2 35 / 13.5; 270 layers, 1.01 of the better one).
+// @3x25 N=85 stride 2 35 / 13.5; 270 layers, 1.01 of the better one; of 250 with up to 50 -> 70 channels, which take 1.7 and, from 8
+// bits, 1.85 times what the plan expects, 1.02: backward of 45 -> 64 5x5 @23x26 N=23, 8 bits, 232 / 302).
 bool narrow_wgrad_pays(const ConvGeom& g, int K, int64_t room, bool both) {
   const Planned& k = planned(g, both ? BOTH : WGRAD, room);
   if (!k.ok) return false;
   const double w = k.p.wgrad_us, d = k.p.dgrad_us;
-  if (!both) return 1.6 * w + 4.0 <= ragged_wgrad_us(g, (size_t)g.N * g.H * g.W * g.Cin * sizeof(float));
+  if (!both) return (K == 8 ? 1.85 : 1.7) * w + 4.0 <= ragged_wgrad_us(g, (size_t)g.N * g.H * g.W * g.Cin * sizeof(float));
   if (k.p.w.count > 3 * k.p.copies || d > 1.9 * planned(g, DGRAD).p.dgrad_us) return false;
   const double others = 7.0 + 17.6 * gflop(g) + 0.65e-6 * ((double)g.N * g.H * g.W * g.Cin * 0.5 + 4.0 * g.N * g.Ho * g.Wo * g.Cout);
   return std::max((K == 8 ? 1.45 : 1.2) * w, d) + 2.0 <= planned(g, DGRAD).p.dgrad_us + others;
